@@ -16,6 +16,7 @@
 // K/V (one workgroup per query row and KV head); bf16 models use the MFMA kernel at the end of
 // this file.
 #include "common.h"
+#include <algorithm>
 #include "kernels.h"
 
 namespace rlhf {
@@ -159,7 +160,7 @@ __device__ __forceinline__ void attend_tile(const T* __restrict__ kt, const T* _
 //   sm[g], sl[g], sacc[g][HD] = block-wide max, sum, un-normalised accumulator.
 template <int HD, int G>
 __device__ __forceinline__ void block_merge(HeadState (&st)[G], int lane, int wave, float* s_m,
-                                            float* s_l, float* s_acc /*[4][G][HD]*/) {
+                                            float* s_l, float* s_acc /*[waves][G][HD]*/) {
     constexpr int CPT = HD / 8;
     const int dc = lane % CPT;
 #pragma unroll
@@ -182,20 +183,20 @@ __device__ __forceinline__ void block_merge(HeadState (&st)[G], int lane, int wa
 
 // After the waves' (max, sum, accumulator) sit in LDS: merge them and write either the output
 // row or this split's partial.
-template <typename T, int HD, int G>
+template <typename T, int HD, int G, int WV>
 __device__ __forceinline__ void decode_block_finish(const float* s_m, const float* s_l, const float* s_acc,
                                                     int r, int kh, int split, int nsplit, int Hq,
-                                                    T* __restrict__ out, float* __restrict__ part_acc,
-                                                    float* __restrict__ part_ml) {
-    for (int i = threadIdx.x; i < G * HD; i += 256) {
+                                                    T* __restrict__ out, const ActLayout& ol,
+                                                    float* __restrict__ part_acc, float* __restrict__ part_ml) {
+    for (int i = threadIdx.x; i < G * HD; i += WV * 64) {
         const int g = i / HD, e = i - g * HD;
         float mt = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) mt = fmaxf(mt, s_m[w * G + g]);
+        for (int w = 0; w < WV; ++w) mt = fmaxf(mt, s_m[w * G + g]);
         float lt = 0.f, at = 0.f;
         if (mt > -INFINITY) {
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
+            for (int w = 0; w < WV; ++w) {
                 const float f = __expf(s_m[w * G + g] - mt);
                 lt += s_l[w * G + g] * f;
                 at += s_acc[(w * G + g) * HD + e] * f;
@@ -203,7 +204,7 @@ __device__ __forceinline__ void decode_block_finish(const float* s_m, const floa
         }
         const int h = kh * G + g;
         if (nsplit == 1) {
-            out[((size_t)r * Hq + h) * HD + e] = from_f32<T>(at / lt);
+            out[act_index(ol, r, h * HD + e)] = from_f32<T>(at / lt);
         } else {
             const size_t slot = ((size_t)r * Hq + h) * nsplit + split;
             part_acc[slot * HD + e] = at;
@@ -212,8 +213,8 @@ __device__ __forceinline__ void decode_block_finish(const float* s_m, const floa
     }
 }
 
-template <typename T, int HD, int G>
-__global__ __launch_bounds__(256) void k_decode_attn(const T* __restrict__ q,
+template <typename T, int HD, int G, int WV>
+__global__ __launch_bounds__(WV * 64) void k_decode_attn(const T* __restrict__ q,
                                                      const T* __restrict__ pool,
                                                      const int* __restrict__ page_table,
                                                      int pt_stride,
@@ -221,9 +222,9 @@ __global__ __launch_bounds__(256) void k_decode_attn(const T* __restrict__ q,
                                                      const int* __restrict__ ctx_len,
                                                      T* __restrict__ out, float* __restrict__ part_acc,
                                                      float* __restrict__ part_ml, int layer,
-                                                     int nsplit, int n_layers, int Hkv) {
-    __shared__ float s_m[4 * G], s_l[4 * G];
-    __shared__ float s_acc[4 * G * HD];
+                                                     int nsplit, int n_layers, int Hkv, ActLayout ol) {
+    __shared__ float s_m[WV * G], s_l[WV * G];
+    __shared__ float s_acc[WV * G * HD];
     const int r = blockIdx.x, kh = blockIdx.y, split = blockIdx.z;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int Hq = Hkv * G;
@@ -253,20 +254,20 @@ __global__ __launch_bounds__(256) void k_decode_attn(const T* __restrict__ q,
     const size_t page_elems = (size_t)n_layers * 2 * Hkv * kPT * HD;
     const size_t head_off = ((size_t)layer * 2 * Hkv + kh) * kPT * HD;
     const size_t v_off = (size_t)Hkv * kPT * HD;
-    // A wave walks pages pb + wave, + 4, ...  The page index of the next tile is fetched before
+    // A wave walks pages pb + wave, + WV, ...  The page index of the next tile is fetched before
     // this tile's K and V, so that a tile costs one memory round trip instead of two dependent
     // ones.  (Fetching K and V a tile ahead as well was measured: 120 registers instead of 73, the
     // kernel no longer fits beside a scoring workgroup on a compute unit, and the stage is slower.)
     int pi = pb + wave;
     int page = pi < pe ? pt[pi] : 0;
-    for (; pi < pe; pi += 4) {
-        const int page_next = pi + 4 < pe ? pt[pi + 4] : 0;
+    for (; pi < pe; pi += WV) {
+        const int page_next = pi + WV < pe ? pt[pi + WV] : 0;
         const T* kt = pool + (size_t)page * page_elems + head_off;
         attend_tile<T, HD, G>(kt, kt + v_off, (size_t)HD, min(kPT, ctx - pi * kPT), qf, st, lane);
         page = page_next;
     }
     block_merge<HD, G>(st, lane, wave, s_m, s_l, s_acc);
-    decode_block_finish<T, HD, G>(s_m, s_l, s_acc, r, kh, split, nsplit, Hq, out, part_acc, part_ml);
+    decode_block_finish<T, HD, G, WV>(s_m, s_l, s_acc, r, kh, split, nsplit, Hq, out, ol, part_acc, part_ml);
 }
 
 // ------------------------------------------------- decode attention for grouped KV heads, MFMA
@@ -285,20 +286,20 @@ __global__ __launch_bounds__(256) void k_decode_attn(const T* __restrict__ q,
 // splits, by (max, sum, accumulator).
 typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
 
-template <int HD, int G>
-__global__ __launch_bounds__(256) void k_decode_attn_gqa(const f16_t* __restrict__ q,
+template <int HD, int G, int WV>
+__global__ __launch_bounds__(WV * 64) void k_decode_attn_gqa(const f16_t* __restrict__ q,
                                                          const f16_t* __restrict__ pool,
                                                          const int* __restrict__ page_table, int pt_stride,
                                                          const int* __restrict__ row_sample,
                                                          const int* __restrict__ ctx_len,
                                                          f16_t* __restrict__ out, float* __restrict__ part_acc,
                                                          float* __restrict__ part_ml, int layer, int nsplit,
-                                                         int n_layers, int Hkv) {
+                                                         int n_layers, int Hkv, ActLayout ol) {
     static_assert(HD == 128 && G <= 16, "one 16-wide head block, eight 16-dim blocks");
     constexpr int VROW = HD + 4;                       // halves per staged V row (264 bytes)
     constexpr int kStage = 16 * VROW / 2;              // floats per wave of staging
-    constexpr int kBuf = 4 * G * HD > 4 * kStage ? 4 * G * HD : 4 * kStage;
-    __shared__ float s_m[4 * G], s_l[4 * G];
+    constexpr int kBuf = WV * (G * HD > kStage ? G * HD : kStage);
+    __shared__ float s_m[WV * G], s_l[WV * G];
     __shared__ __attribute__((aligned(16))) float s_buf[kBuf];   // V staging, then the waves' accumulators
     const int r = blockIdx.x, kh = blockIdx.y, split = blockIdx.z;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -328,10 +329,10 @@ __global__ __launch_bounds__(256) void k_decode_attn_gqa(const f16_t* __restrict
     f16_t* vs = reinterpret_cast<f16_t*>(s_buf) + wave * 16 * VROW;
 
     int page = pb + wave < pe ? pt[pb + wave] : 0;      // page indices are fetched one tile ahead
-    for (int pi = pb + wave; pi < pe; pi += 4) {
+    for (int pi = pb + wave; pi < pe; pi += WV) {
         const f16_t* kt = pool + (size_t)page * page_elems + head_off;
         const f16_t* vt = kt + v_off;
-        page = pi + 4 < pe ? pt[pi + 4] : 0;
+        page = pi + WV < pe ? pt[pi + WV] : 0;
         const int n_valid = min(kPT, ctx - pi * kPT);
         // tokens past the context are read from token 0 (finite data) and masked below
         const int tk = head < n_valid ? head : 0;
@@ -401,13 +402,13 @@ __global__ __launch_bounds__(256) void k_decode_attn_gqa(const f16_t* __restrict
             for (int e = 0; e < 4; ++e) s_acc[(wave * G + head) * HD + b * 16 + tg * 4 + e] = o[b][e];
     }
     __syncthreads();
-    decode_block_finish<f16_t, HD, G>(s_m, s_l, s_acc, r, kh, split, nsplit, Hq, out, part_acc, part_ml);
+    decode_block_finish<f16_t, HD, G, WV>(s_m, s_l, s_acc, r, kh, split, nsplit, Hq, out, ol, part_acc, part_ml);
 }
 
 // LSE merge of the split partials: one block per (row, head), HD threads.
 template <typename T>
 __global__ void k_attn_merge(const float* __restrict__ part_acc, const float* __restrict__ part_ml,
-                             T* __restrict__ out, int nsplit, int HD) {
+                             T* __restrict__ out, ActLayout ol, int Hq, int nsplit, int HD) {
     const size_t rh = blockIdx.x;
     const int e = threadIdx.x;
     float mt = -INFINITY;
@@ -420,57 +421,79 @@ __global__ void k_attn_merge(const float* __restrict__ part_acc, const float* __
         lt += part_ml[(rh * nsplit + s) * 2 + 1] * f;
         at += part_acc[(rh * nsplit + s) * HD + e] * f;
     }
-    out[rh * HD + e] = from_f32<T>(at / lt);
+    const int r = (int)(rh / Hq), h = (int)(rh % Hq);
+    out[act_index(ol, r, h * HD + e)] = from_f32<T>(at / lt);
 }
 
-template <typename T, int HD, int G>
-static hipError_t decode_launch(hipStream_t st, const void* q, const void* pool,
-                                const int* page_table, int pt_stride, const int* row_sample,
-                                const int* ctx_len, void* out, float* part_acc, float* part_ml,
-                                int rows, int layer, int nsplit, const Dims& dm) {
-    dim3 grid(rows, dm.n_kv_heads, nsplit);
-    k_decode_attn<T, HD, G><<<grid, 256, 0, st>>>((const T*)q, (const T*)pool, page_table, pt_stride,
-                                                  row_sample, ctx_len, (T*)out, part_acc, part_ml,
-                                                  layer, nsplit, dm.n_layers, dm.n_kv_heads);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || nsplit == 1) return e;
-    k_attn_merge<T><<<rows * dm.n_q_heads, HD, 0, st>>>(part_acc, part_ml, (T*)out, nsplit, HD);
-    return hipGetLastError();
+// Waves per workgroup: a workgroup holds one (row, KV head, split), its waves take the pages in turn.
+// With few workgroups the pages of one are spread over 8 or 16 waves, which costs a merge in LDS where
+// more splits would cost a merge kernel (about 5 us).
+static int decode_attn_waves(long blocks, int group) { return 4; }
+
+// As many splits as give the chip about sixteen waves per compute unit, unless that leaves a wave with
+// fewer than four pages.
+int decode_attn_nsplit(int rows, int max_pages, const Dims& dm, int max_split) {
+    const long blocks = (long)rows * dm.n_kv_heads;
+    const int wv = decode_attn_waves(blocks, dm.n_q_heads / dm.n_kv_heads);
+    long ns = 1024 * 4 / (blocks * wv > 0 ? blocks * wv : 1);
+    const int by_pages = std::max(1, max_pages / 8);
+    if (ns > by_pages) ns = by_pages;
+    if (ns > max_split) ns = max_split;
+    return ns < 1 ? 1 : (int)ns;
 }
 
 hipError_t launch_decode_attn(hipStream_t st, int dtype, const void* q, const void* pool,
                               const int* page_table, int pt_stride, const int* row_sample,
                               const int* ctx_len, void* out, float* part_acc, float* part_ml,
-                              int rows, int layer, int nsplit, const Dims& dm) {
+                              int rows, int layer, int nsplit, const Dims& dm, const ActLayout& out_layout) {
     if (rows <= 0) return hipSuccess;
     if (dm.page_tokens != kPT || nsplit < 1) return hipErrorInvalidValue;
     const int G = dm.n_q_heads / dm.n_kv_heads, hd = dm.head_dim;
-#define RLHF_DEC(TT, HD_, G_)                                                                     \
-    return decode_launch<TT, HD_, G_>(st, q, pool, page_table, pt_stride, row_sample, ctx_len, out, \
-                                      part_acc, part_ml, rows, layer, nsplit, dm)
+    ActLayout ol = out_layout;
+    if (ol.row == 0) ol = ActLayout{dm.n_q_heads * hd, 8};
+    const dim3 grid(rows, dm.n_kv_heads, nsplit);
+    const int wv = decode_attn_waves((long)rows * dm.n_kv_heads, G);
+#define RLHF_DEC_WV(KERNEL, TT, ...)                                                                             \
+    KERNEL<__VA_ARGS__><<<grid, WV_ * 64, 0, st>>>((const TT*)q, (const TT*)pool, page_table, pt_stride, row_sample, \
+                                                   ctx_len, (TT*)out, part_acc, part_ml, layer, nsplit, dm.n_layers, \
+                                                   dm.n_kv_heads, ol)
+#define RLHF_DEC(TT, HD_, G_)                                                                                    \
+    do {                                                                                                         \
+        if (wv == 16) { constexpr int WV_ = 16; RLHF_DEC_WV(k_decode_attn, TT, TT, HD_, G_, 16); }               \
+        else if (wv == 8) { constexpr int WV_ = 8; RLHF_DEC_WV(k_decode_attn, TT, TT, HD_, G_, 8); }             \
+        else { constexpr int WV_ = 4; RLHF_DEC_WV(k_decode_attn, TT, TT, HD_, G_, 4); }                          \
+    } while (0)
+#define RLHF_MERGE(TT)                                                                                           \
+    do {                                                                                                         \
+        hipError_t e_ = hipGetLastError();                                                                       \
+        if (e_ != hipSuccess || nsplit == 1) return e_;                                                          \
+        k_attn_merge<TT><<<rows * dm.n_q_heads, hd, 0, st>>>(part_acc, part_ml, (TT*)out, ol, dm.n_q_heads, nsplit, hd); \
+        return hipGetLastError();                                                                                \
+    } while (0)
     if (dtype == kBF16) {
         if (hd == 128 && G == 1) RLHF_DEC(bf16_t, 128, 1);
-        if (hd == 128 && G == 8) RLHF_DEC(bf16_t, 128, 8);
-        if (hd == 64 && G == 1) RLHF_DEC(bf16_t, 64, 1);
-    } else if (dtype == kF16) {
-        if (hd == 128 && G == 1) RLHF_DEC(f16_t, 128, 1);
-        if (hd == 128 && G == 8) {
-            dim3 grid(rows, dm.n_kv_heads, nsplit);
-            k_decode_attn_gqa<128, 8><<<grid, 256, 0, st>>>((const f16_t*)q, (const f16_t*)pool, page_table, pt_stride,
-                                                            row_sample, ctx_len, (f16_t*)out, part_acc, part_ml, layer,
-                                                            nsplit, dm.n_layers, dm.n_kv_heads);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess || nsplit == 1) return e;
-            k_attn_merge<f16_t><<<rows * dm.n_q_heads, 128, 0, st>>>(part_acc, part_ml, (f16_t*)out, nsplit, 128);
-            return hipGetLastError();
-        }
-        if (hd == 64 && G == 1) RLHF_DEC(f16_t, 64, 1);
-    } else {
-        if (hd == 128 && G == 1) RLHF_DEC(float, 128, 1);
-        if (hd == 64 && G == 1) RLHF_DEC(float, 64, 1);
+        else if (hd == 128 && G == 8) { constexpr int WV_ = 4; RLHF_DEC_WV(k_decode_attn, bf16_t, bf16_t, 128, 8, 4); }
+        else if (hd == 64 && G == 1) RLHF_DEC(bf16_t, 64, 1);
+        else return hipErrorInvalidValue;
+        RLHF_MERGE(bf16_t);
     }
+    if (dtype == kF16) {
+        if (hd == 128 && G == 1) RLHF_DEC(f16_t, 128, 1);
+        else if (hd == 128 && G == 8) {
+            if (wv >= 8) { constexpr int WV_ = 8; RLHF_DEC_WV(k_decode_attn_gqa, f16_t, 128, 8, 8); }
+            else { constexpr int WV_ = 4; RLHF_DEC_WV(k_decode_attn_gqa, f16_t, 128, 8, 4); }
+        }
+        else if (hd == 64 && G == 1) RLHF_DEC(f16_t, 64, 1);
+        else return hipErrorInvalidValue;
+        RLHF_MERGE(f16_t);
+    }
+    if (hd == 128 && G == 1) RLHF_DEC(float, 128, 1);
+    else if (hd == 64 && G == 1) RLHF_DEC(float, 64, 1);
+    else return hipErrorInvalidValue;
+    RLHF_MERGE(float);
 #undef RLHF_DEC
-    return hipErrorInvalidValue;
+#undef RLHF_DEC_WV
+#undef RLHF_MERGE
 }
 
 // ------------------------------------------------------------- prefill / scoring (v1)

@@ -97,6 +97,9 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// Largest power of two not above x (x positive and normal).
+__device__ __forceinline__ float pow2_below(float x) { return __uint_as_float(__float_as_uint(x) & 0x7F800000u); }
+
 // Block-wide sum over blockDim.x (multiple of 64, <= 1024) threads; red holds >= 16 floats.
 __device__ __forceinline__ float block_sum(float v, float* red) {
     v = wave_sum(v);

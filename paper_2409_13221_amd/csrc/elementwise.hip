@@ -39,6 +39,56 @@ hipError_t launch_embed(hipStream_t st, int dtype, const int* tokens, const int*
     return hipGetLastError();
 }
 
+// With the first norm (see gemm_stream.hip): one block per row, the row in registers between the passes.
+constexpr int kEmbedIter = 4;
+template <typename T>
+__global__ __launch_bounds__(256) void k_embed_norm(const int* __restrict__ tokens, const int* __restrict__ tok_idx,
+                                                    const T* __restrict__ table, float* __restrict__ h,
+                                                    const float* __restrict__ g, f16_t* __restrict__ x, ActLayout xl,
+                                                    float* __restrict__ s_out, float* __restrict__ ssq_out, int d,
+                                                    int vocab, float eps) {
+    __shared__ float red[16];
+    const int r = blockIdx.x;
+    const int tok = min(max(tokens[tok_idx[r]], 0), vocab - 1);
+    const T* src = table + (size_t)tok * d;
+    float v[kEmbedIter][8], ss = 0.f;
+#pragma unroll
+    for (int it = 0; it < kEmbedIter; ++it) {
+        const int i = (it * 256 + threadIdx.x) * 8;
+        if (i < d) {
+            load8<T>(src + i, v[it]);
+            store8<float>(h + (size_t)r * d + i, v[it]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ss += v[it][e] * v[it][e];
+        }
+    }
+    const float tot = block_sum(ss, red);
+    const float sc = pow2_below(rsqrtf(tot / (float)d + eps));
+#pragma unroll
+    for (int it = 0; it < kEmbedIter; ++it) {
+        const int i = (it * 256 + threadIdx.x) * 8;
+        if (i < d) {
+            float gg[8];
+            load8<float>(g + i, gg);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) gg[e] *= v[it][e] * sc;
+            store8<f16_t>(x + act_index(xl, r, i), gg);
+        }
+    }
+    for (int i = threadIdx.x; i < kSsqStride; i += 256) ssq_out[(size_t)r * kSsqStride + i] = i == 0 ? tot : 0.f;
+    if (threadIdx.x == 0) s_out[r] = sc;
+}
+
+hipError_t launch_embed_norm(hipStream_t st, int dtype, const int* tokens, const int* tok_idx, const void* table,
+                             float* h, const float* g, void* x, const ActLayout& x_layout, float* s, float* ssq,
+                             int rows, int d, int vocab, float eps) {
+    if (rows <= 0) return hipSuccess;
+    if (dtype != kBF16 || d % 8 || d > 256 * 8 * kEmbedIter) return hipErrorInvalidValue;
+    k_embed_norm<bf16_t><<<rows, 256, 0, st>>>(tokens, tok_idx, (const bf16_t*)table, h, g, (f16_t*)x, x_layout, s, ssq,
+                                               d, vocab, eps);
+    return hipGetLastError();
+}
+
 // --------------------------------------------------------------------------------- RMSNorm
 // One block per output row, one float4 of the row per thread and iteration (up to
 // kRmsMaxIter iterations).  The residual add of the split-K partial planes is fused in: all
@@ -69,7 +119,7 @@ __global__ __launch_bounds__(1024) void k_rmsnorm(float* __restrict__ h, const f
                                                   int nsplit, size_t sstride,
                                                   const int* __restrict__ row_idx,
                                                   const float* __restrict__ g, T* __restrict__ xn,
-                                                  int d, float eps) {
+                                                  ActLayout xl, int d, float eps) {
     __shared__ float red[16];
     const int r = blockIdx.x;
     const int src = row_idx ? row_idx[r] : r;
@@ -108,7 +158,7 @@ __global__ __launch_bounds__(1024) void k_rmsnorm(float* __restrict__ h, const f
     for (int it = 0; it < kRmsMaxIter; ++it) {
         const int i = (it * blockDim.x + threadIdx.x) * 4;
         if (i < d)
-            store4<T>(xn + (size_t)r * d + i,
+            store4<T>(xn + act_index(xl, r, i),
                       make_float4(v[it].x * inv * gg[it].x, v[it].y * inv * gg[it].y, v[it].z * inv * gg[it].z,
                                   v[it].w * inv * gg[it].w));
     }
@@ -116,8 +166,9 @@ __global__ __launch_bounds__(1024) void k_rmsnorm(float* __restrict__ h, const f
 
 template <typename T>
 static hipError_t rmsnorm_launch(hipStream_t st, float* h, const float* part, int nsplit, size_t sstride,
-                                 const int* row_idx, const float* g, T* xn, int rows, int threads, int d, float eps) {
-#define RLHF_RMS(NS) k_rmsnorm<T, NS><<<rows, threads, 0, st>>>(h, part, nsplit, sstride, row_idx, g, xn, d, eps)
+                                 const int* row_idx, const float* g, T* xn, const ActLayout& xl, int rows, int threads, int d,
+                                 float eps) {
+#define RLHF_RMS(NS) k_rmsnorm<T, NS><<<rows, threads, 0, st>>>(h, part, nsplit, sstride, row_idx, g, xn, xl, d, eps)
     switch (nsplit) {
         case 0: RLHF_RMS(0); break;
         case 1: RLHF_RMS(1); break;
@@ -135,15 +186,17 @@ static hipError_t rmsnorm_launch(hipStream_t st, float* h, const float* part, in
 
 hipError_t launch_rmsnorm(hipStream_t st, int adt, float* h, const float* part, int nsplit,
                           size_t sstride, const int* row_idx, const float* g, void* xn, int rows,
-                          int d, float eps) {
+                          int d, float eps, const ActLayout& xn_layout) {
     if (rows <= 0) return hipSuccess;
     if (d > 1024 * 4 * kRmsMaxIter || d % 8 || nsplit < 0 || nsplit > kMaxPlanes) return hipErrorInvalidValue;
+    ActLayout xl = xn_layout;
+    if (xl.row == 0) xl = ActLayout{d, 8};
     const int quads = d / 4;
     const int iters = (quads + 1023) / 1024;
     const int threads = ((quads + iters - 1) / iters + 63) / 64 * 64;
-    if (adt == kBF16) return rmsnorm_launch<bf16_t>(st, h, part, nsplit, sstride, row_idx, g, (bf16_t*)xn, rows, threads, d, eps);
-    if (adt == kF16) return rmsnorm_launch<f16_t>(st, h, part, nsplit, sstride, row_idx, g, (f16_t*)xn, rows, threads, d, eps);
-    return rmsnorm_launch<float>(st, h, part, nsplit, sstride, row_idx, g, (float*)xn, rows, threads, d, eps);
+    if (adt == kBF16) return rmsnorm_launch<bf16_t>(st, h, part, nsplit, sstride, row_idx, g, (bf16_t*)xn, xl, rows, threads, d, eps);
+    if (adt == kF16) return rmsnorm_launch<f16_t>(st, h, part, nsplit, sstride, row_idx, g, (f16_t*)xn, xl, rows, threads, d, eps);
+    return rmsnorm_launch<float>(st, h, part, nsplit, sstride, row_idx, g, (float*)xn, xl, rows, threads, d, eps);
 }
 
 // ---------------------------------------------------------------- rotary + KV-cache append

@@ -98,6 +98,8 @@ struct Workspace {
     float* logits = nullptr;  // [logit_rows, vocab] (batch passes; decode uses `part`)
     int logit_rows = 0;
     float* pick_scratch = nullptr;  // per-chunk partial results of the greedy pick
+    float* ssq = nullptr;       // few-row passes: partial sums of h^2 of the rows in flight
+    float* scale = nullptr;     // [2][kStreamResidRows]: scales of the normed rows, ping and pong
     float* attn_acc = nullptr;  // decode split-KV partials
     float* attn_ml = nullptr;
     size_t attn_slots = 0;
@@ -297,6 +299,8 @@ int alloc_workspace(rlhf_ctx* c, Workspace& ws, int rows, bool decode) {
     HIPCK(c, dev_alloc(&ws, (char**)&ws.act, rows * f * es));
     HIPCK(c, dev_alloc(&ws, (char**)&ws.xsel, rows * d * 4));    // float rows for the value / reward head
     HIPCK(c, dev_alloc(&ws, &ws.pick_scratch, pick_scratch_floats(rows) * 4));
+    HIPCK(c, dev_alloc(&ws, &ws.ssq, (size_t)kStreamResidRows * kSsqStride * 4));
+    HIPCK(c, dev_alloc(&ws, &ws.scale, (size_t)2 * kStreamResidRows * 4));
     if (decode) {
         HIPCK(c, dev_alloc(&ws, &ws.attn_acc, ws.attn_slots * m.head_dim * 4));
         HIPCK(c, dev_alloc(&ws, &ws.attn_ml, ws.attn_slots * 2 * 4));
@@ -340,6 +344,118 @@ struct PassMeta {         // device pointers into a MetaRing arena
     double attn_bytes = 0, attn_flops = 0;   // algorithmic, per layer (for the profiler)
 };
 
+// Few rows of a bf16 model: every layer runs on the projections of gemm_stream.hip.
+bool stream_pass(const rlhf_ctx* c, int rows) {
+    const rlhf_model_cfg& m = c->mc;
+    return c->dtype == kBF16 && rows <= kStreamMaxRows && m.d_model % 64 == 0 && (m.n_q_heads * m.head_dim) % 64 == 0 &&
+           m.ffn % 64 == 0;
+}
+
+// Norm input of a few-row projection over the residual stream: how ws.xn was scaled, and the sums of
+// squares its producer left.
+NormIn stream_norm(const rlhf_ctx* c, const Workspace& ws, int n_ssq, float* s_in, float* s_out) {
+    NormIn ni;
+    ni.ssq = ws.ssq;
+    ni.n_ssq = n_ssq;
+    ni.s_in = s_in;
+    ni.s_out = s_out;
+    ni.eps = c->mc.rms_eps;
+    return ni;
+}
+
+// The layers of such a pass, their activations in the packed layout.  Up to kStreamResidRows rows: five
+// kernels a layer (six when the contexts are split), the residual stream in ws.h is complete after every
+// O and down projection, and ws.xn holds the next norm's input as gemm_stream.hip describes it, at the
+// end that of the final norm (scale in ws.scale, sums in ws.ssq: *n_ssq per row; *pend_ns = 0).  More
+// rows: seven kernels, O and down leave planes that RMSNorm adds, at the end *pend_ns of them.
+int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights& rw, int rows,
+                          const PassMeta& pm, AttnMode mode, int attn_nsplit, int* pend_ns, int* n_ssq) {
+    const rlhf_weights& w = rw.w;
+    const rlhf_model_cfg& m = c->mc;
+    const int d = m.d_model, qd = m.n_q_heads * m.head_dim, kvd = m.n_kv_heads * m.head_dim;
+    const int qkv_w = qd + 2 * kvd, f = m.ffn, es = c->esz, dt = c->dtype;
+    const int gcls = mode == kModeDecode ? kGemmDecode : kGemmBatch;
+    const bool resid = rows <= kStreamResidRows;
+    const size_t plane = (size_t)rows * d;
+    const int cap = (int)std::min<size_t>(16, ws.part_cap / plane);
+    const ActLayout packed{8, 8 * rows}, attn_layout = mode == kModeDecode ? packed : ActLayout{qd, 8};
+    float* sc[2] = {ws.scale, ws.scale + kStreamResidRows};
+    auto gain_after = [&](int l) { return l + 1 < m.n_layers ? w.g_attn + (size_t)(l + 1) * d : w.g_final; };
+    if (resid)
+        HIPCK(c, launch_embed_norm(st, dt, c->d_tokens, pm.tok_idx, w.embed, ws.h, m.n_layers > 0 ? w.g_attn : w.g_final,
+                                   ws.xn, packed, sc[0], ws.ssq, rows, d, m.vocab, m.rms_eps));
+    else
+        HIPCK(c, launch_embed(st, dt, c->d_tokens, pm.tok_idx, w.embed, ws.h, rows, d, m.vocab));
+    *n_ssq = 1;
+    int ns = 0;
+    auto project = [&](int md, const void* A, const void* W, int N, int K, const RowsEpi& ep, int nsplit = 1) {
+        const double bytes = ((double)N * K + (double)rows * K) * es + (double)rows * N * (md == 0 ? 4 : es);
+        return profiled(c, st, gcls, bytes, 2.0 * rows * N * K,
+                        [&] { return launch_gemm_stream(st, dt, kF16, md, A, W, ws.part, rows, N, K, ep, nsplit); });
+    };
+    // O and down projections: finish the residual stream, or leave planes and let RMSNorm do it
+    auto into_stream = [&](const void* A, const ActLayout& la, const void* W, int K, const float* g_next, float* s) -> int {
+        RowsEpi ep;
+        ep.a = la;
+        if (resid) {
+            ep.out = packed;
+            ep.res.h = ws.h; ep.res.g = g_next; ep.res.x = ws.xn; ep.res.s = s; ep.res.ssq = ws.ssq;
+            HIPCK(c, project(3, A, W, d, K, ep));
+            *n_ssq = d / 16;
+        } else {
+            ns = gemm_stream_nsplit(rows, d, K, cap);
+            HIPCK(c, project(0, A, W, d, K, ep, ns));
+        }
+        return RLHF_OK;
+    };
+    for (int l = 0; l < m.n_layers; ++l) {
+        if (!resid)
+            HIPCK(c, launch_rmsnorm(st, kF16, ws.h, ws.part, ns, plane, nullptr, w.g_attn + (size_t)l * d, ws.xn, rows, d,
+                                    m.rms_eps, packed));
+        RowsEpi ep;
+        ep.a = packed;
+        if (resid) ep.nrm = stream_norm(c, ws, *n_ssq, sc[0], sc[1]);
+        ep.ro.pos = pm.pos;
+        ep.ro.kv_dst = pm.kv_dst;
+        ep.ro.table = c->d_rope;
+        ep.ro.q = ws.q;
+        ep.ro.k = mode == kModeBatch ? ws.k : nullptr;
+        ep.ro.v = mode == kModeBatch ? ws.v : nullptr;
+        ep.ro.pool = pm.kv_dst ? c->pool : nullptr;
+        ep.ro.layer = l; ep.ro.n_layers = m.n_layers;
+        ep.ro.n_q_heads = m.n_q_heads; ep.ro.n_kv_heads = m.n_kv_heads; ep.ro.head_dim = m.head_dim;
+        ep.ro.page_tokens = c->ec.page_tokens;
+        HIPCK(c, project(2, ws.xn, layer_ptr(w.wqkv, l, qkv_w, d, es), qkv_w, d, ep));
+        if (mode == kModeDecode) {
+            HIPCK(c, profiled(c, st, kAttnDecode, pm.attn_bytes, pm.attn_flops, [&] {
+                return launch_decode_attn(st, kF16, ws.q, c->pool, c->d_page_table, c->max_pages, pm.row_sample,
+                                          pm.ctx_len, ws.attn, ws.attn_acc, ws.attn_ml, rows, l, attn_nsplit, c->dm,
+                                          attn_layout);
+            }));
+        } else {
+            HIPCK(c, profiled(c, st, kAttnBatch, pm.attn_bytes, pm.attn_flops, [&] {
+                return launch_flash_attn(st, ws.q, ws.k, ws.v, pm.tile_start, pm.tile_q0, pm.tile_len, ws.attn,
+                                         pm.n_tiles, rows, c->dm);
+            }));
+        }
+        int rc = into_stream(ws.attn, attn_layout, layer_ptr(w.wo, l, d, qd, es), qd, w.g_mlp + (size_t)l * d, sc[1]);
+        if (rc) return rc;
+        if (!resid)
+            HIPCK(c, launch_rmsnorm(st, kF16, ws.h, ws.part, ns, plane, nullptr, w.g_mlp + (size_t)l * d, ws.xn, rows, d,
+                                    m.rms_eps, packed));
+        RowsEpi eg;
+        eg.a = eg.out = packed;
+        if (resid) eg.nrm = stream_norm(c, ws, *n_ssq, sc[1], sc[0]);
+        eg.act = ws.act;
+        eg.ffn = f;
+        HIPCK(c, project(1, ws.xn, layer_ptr(w.w_gate_up, l, 2 * (size_t)f, d, es), 2 * f, d, eg));
+        rc = into_stream(ws.act, packed, layer_ptr(w.w_down, l, d, f, es), f, gain_after(l), sc[0]);
+        if (rc) return rc;
+    }
+    *pend_ns = ns;
+    return RLHF_OK;
+}
+
 // Embedding and all decoder layers over `rows` rows.  On return ws.h holds the residual
 // stream except for the last down-projection, whose split-K partials are still in ws.part:
 // (*pend_ns, *pend_stride) describe them for the final norm.
@@ -354,6 +470,11 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
     const int gcls = mode == kModeDecode ? kGemmDecode : kGemmBatch;
     const int adt = act_type(c, mode == kModeBatch);
     const int qdt = adt;               // q/k/v of a pass share the activation type
+    if (mode == kModeBatch && stream_pass(c, rows)) {
+        int n_ssq;
+        *pend_stride = (size_t)rows * d;
+        return forward_layers_stream(c, st, ws, rw, rows, pm, mode, 1, pend_ns, &n_ssq);
+    }
     HIPCK(c, launch_embed(st, dt, c->d_tokens, pm.tok_idx, w.embed, ws.h, rows, d, m.vocab));
     int pns = 0;
     size_t pstride = 0;
@@ -361,26 +482,7 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, pns, pstride, nullptr, w.g_attn + (size_t)l * d,
                                 ws.xn, rows, d, m.rms_eps));
         int ns = 0;
-        const bool few = gemm_rows16_supported(dt, adt, rows, d) && (m.head_dim == 64 || m.head_dim == 128);
-        if (few) {
-            // up to 16 rows: the projection walks the whole K range, rotary + KV append ride in its epilogue
-            RowsEpi ep;
-            ep.ro.pos = pm.pos;
-            ep.ro.kv_dst = pm.kv_dst;
-            ep.ro.table = c->d_rope;
-            ep.ro.q = ws.q;
-            ep.ro.k = mode == kModeBatch ? ws.k : nullptr;
-            ep.ro.v = mode == kModeBatch ? ws.v : nullptr;
-            ep.ro.pool = pm.kv_dst ? c->pool : nullptr;
-            ep.ro.layer = l; ep.ro.n_layers = m.n_layers;
-            ep.ro.n_q_heads = m.n_q_heads; ep.ro.n_kv_heads = m.n_kv_heads; ep.ro.head_dim = m.head_dim;
-            ep.ro.page_tokens = c->ec.page_tokens;
-            const double bytes = ((double)qkv_w * d + (double)rows * d) * es + (double)rows * qkv_w * es;
-            const void* wq = layer_ptr(w.wqkv, l, qkv_w, d, es);
-            HIPCK(c, profiled(c, st, gcls, bytes, 2.0 * rows * qkv_w * d, [&] {
-                return launch_gemm_rows16(st, dt, adt, 2, ws.xn, wq, nullptr, rows, qkv_w, d, ep);
-            }));
-        } else if (mode == kModeBatch && gemm_rope_supported(dt, adt, rows, d, c->dm)) {
+        if (mode == kModeBatch && gemm_rope_supported(dt, adt, rows, d, c->dm)) {
             // tall pass: rotary, rounding and the q / k / v / pool scatter ride in the GEMM's epilogue
             RopeOut ro;
             ro.pos = pm.pos;
@@ -427,16 +529,7 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         }
         HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, ns, (size_t)rows * d, nullptr,
                                 w.g_mlp + (size_t)l * d, ws.xn, rows, d, m.rms_eps));
-        if (few && f % 8 == 0) {
-            RowsEpi ep;
-            ep.act = ws.act;
-            ep.ffn = f;
-            const void* wgu = layer_ptr(w.w_gate_up, l, 2 * (size_t)f, d, es);
-            const double bytes = (2.0 * f * d + (double)rows * d) * es + (double)rows * f * es;
-            HIPCK(c, profiled(c, st, gcls, bytes, 4.0 * rows * f * d, [&] {
-                return launch_gemm_rows16(st, dt, adt, 1, ws.xn, wgu, nullptr, rows, 2 * f, d, ep);
-            }));
-        } else if (gemm_swiglu_supported(dt, adt, rows, f, d)) {
+        if (gemm_swiglu_supported(dt, adt, rows, f, d)) {
             const bool hw = wh.w_gate_up && adt == kF16 && d % 64 == 0;
             const void* wgu = layer_ptr(hw ? wh.w_gate_up : w.w_gate_up, l, 2 * (size_t)f, d, es);
             const double bytes = (2.0 * f * d + (double)rows * d) * es + (double)rows * f * es;
@@ -816,7 +909,14 @@ int lm_head_chunks(rlhf_ctx* c, hipStream_t st, Workspace& ws, const rlhf_weight
     for (int r0 = 0; r0 < hp.n_sel; r0 += ws.logit_rows) {
         const int nr = std::min(ws.logit_rows, hp.n_sel - r0);
         const char* x = (const char*)ws.xsel + (size_t)r0 * d * c->esz;
-        HIPCK(c, gemm_profiled(c, st, kGemmBatch, act_type(c, true), x, w.head, ws.logits, nr, V, d, 1));
+        if (gemm_stream_supported(c->dtype, act_type(c, true), nr, d)) {
+            const double bytes = ((double)V * d + (double)nr * d) * c->esz + (double)nr * V * 4;
+            HIPCK(c, profiled(c, st, kGemmBatch, bytes, 2.0 * nr * V * d, [&] {
+                return launch_gemm_stream(st, c->dtype, kF16, 0, x, w.head, ws.logits, nr, V, d, RowsEpi{});
+            }));
+        } else {
+            HIPCK(c, gemm_profiled(c, st, kGemmBatch, act_type(c, true), x, w.head, ws.logits, nr, V, d, 1));
+        }
         if (pick)
             HIPCK(c, launch_pick(st, ws.logits, 1, 0, nr, V, hp.forced + r0, c->d_tokens, hp.tok_dst + r0,
                                  c->d_lp_actor, hp.lp_dst + r0, nullptr, ws.pick_scratch, c->d_nonfinite));
@@ -1041,23 +1141,37 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
     }
     // split long contexts so that a handful of samples still fills the chip
     Workspace& ws = c->ws_dec;
-    const int blocks = R * c->mc.n_kv_heads;
-    int asplit = std::max(1, 1024 / std::max(blocks, 1));
-    asplit = std::min(asplit, std::max(1, ceil_div(max_ctx_len, pt) / 8));
-    asplit = std::min<int>(asplit, 32);
-    asplit = (int)std::min<size_t>(asplit, ws.attn_slots / ((size_t)R * c->mc.n_q_heads));
-    if (asplit < 1) asplit = 1;
+    const int max_split = (int)std::min<size_t>(32, ws.attn_slots / ((size_t)R * c->mc.n_q_heads));
+    const int asplit = decode_attn_nsplit(R, ceil_div(max_ctx_len, pt), c->dm, std::max(1, max_split));
 
     const rlhf_weights& w = c->roles[RLHF_ACTOR].w;
-    int pns;
-    size_t pstride;
-    int rc = forward_layers(c, c->sd, ws, c->roles[RLHF_ACTOR], R, pm, kModeDecode, asplit, &pns, &pstride);
-    if (rc) return rc;
     const int d = c->mc.d_model, V = c->mc.vocab;
-    HIPCK(c, launch_rmsnorm(c->sd, act_type(c, false), ws.h, ws.part, pns, pstride, nullptr, w.g_final, ws.xsel, R, d,
-                            c->mc.rms_eps));
-    const int ns = nsplit_for(c, ws, R, V, d);
-    HIPCK(c, gemm_profiled(c, c->sd, kGemmDecode, act_type(c, false), ws.xsel, w.head, ws.part, R, V, d, ns));
+    int ns = 1;
+    if (stream_pass(c, R)) {
+        int n_ssq, pns;
+        int rc = forward_layers_stream(c, c->sd, ws, c->roles[RLHF_ACTOR], R, pm, kModeDecode, asplit, &pns, &n_ssq);
+        if (rc) return rc;
+        RowsEpi ep;
+        ep.a = ActLayout{8, 8 * R};
+        if (R <= kStreamResidRows)
+            ep.nrm = stream_norm(c, ws, n_ssq, ws.scale, nullptr);
+        else
+            HIPCK(c, launch_rmsnorm(c->sd, kF16, ws.h, ws.part, pns, (size_t)R * d, nullptr, w.g_final, ws.xn, R, d,
+                                    c->mc.rms_eps, ep.a));
+        const double bytes = ((double)V * d + (double)R * d) * c->esz + (double)R * V * 4;
+        HIPCK(c, profiled(c, c->sd, kGemmDecode, bytes, 2.0 * R * V * d, [&] {
+            return launch_gemm_stream(c->sd, c->dtype, kF16, 0, ws.xn, w.head, ws.part, R, V, d, ep);
+        }));
+    } else {
+        int pns;
+        size_t pstride;
+        int rc = forward_layers(c, c->sd, ws, c->roles[RLHF_ACTOR], R, pm, kModeDecode, asplit, &pns, &pstride);
+        if (rc) return rc;
+        HIPCK(c, launch_rmsnorm(c->sd, act_type(c, false), ws.h, ws.part, pns, pstride, nullptr, w.g_final, ws.xsel, R, d,
+                                c->mc.rms_eps));
+        ns = nsplit_for(c, ws, R, V, d);
+        HIPCK(c, gemm_profiled(c, c->sd, kGemmDecode, act_type(c, false), ws.xsel, w.head, ws.part, R, V, d, ns));
+    }
     HIPCK(c, launch_pick(c->sd, ws.part, ns, (size_t)R * V, R, V, dmeta + 7 * R, c->d_tokens, dmeta + 5 * R,
                          c->d_lp_actor, dmeta + 6 * R, c->d_picked, ws.pick_scratch, c->d_nonfinite));
     // algorithmic bytes of this step

@@ -1,0 +1,443 @@
+// Projections of decode steps (and of very short passes): up to 64 activation rows against a bf16
+// weight matrix that is read once, with everything the decoder block does to the result in the
+// epilogue.
+//
+// What bounds it is how fast the weights come in.  A workgroup owns 16 * NB weight rows and the WHOLE
+// K range, its waves a contiguous share of K each, so that nothing is left to a consumer to sum (no
+// split-K planes) and the waves never wait for one another before the epilogue.  Weights go global ->
+// LDS directly into a ring that belongs to one wave (no barrier, no registers), D steps of 64 k ahead,
+// as buffer loads of 8 rows x 128 bytes: whole cache lines per instruction, which the matrix-operand
+// layout itself (16 rows x 64 bytes per load) would not give.  Measured on the 7B shapes, weights
+// cold, loads alone: 16.9 / 6.7 / 30.2 / 16.9 us (QKV, O, gate||up, down) this way, 17.9 / 7.3 / 32.8
+// / 21.3 us with loads in operand layout straight to registers; a linear read of the same bytes takes
+// 15.4 / 6.0 / 27.6 / 14.1 us.  A deeper ring (128 KB in flight per workgroup) is slower: 19.6 us QKV.
+// Activations are a few KB per step, shared by all workgroups, and come from the L2 straight into
+// matrix-operand registers.
+//
+// Up to 16 rows RMSNorm costs no kernel of its own.  The projection that finishes the residual stream (O, down)
+// adds its result to h, and writes x = h * g * s (half; g the next norm's gain, s the power of two below
+// the row's previous 1/rms, which keeps x near unit scale and rounds nothing by itself) and the partial sums of h^2 of its 16 * NB columns; the
+// projection that consumes the normed row multiplies x by W as it is and scales the result of row m by
+// (1/rms_m) / s_m in its epilogue.
+#include "common.h"
+#include "kernels.h"
+#include <type_traits>
+
+namespace rlhf {
+
+namespace {
+
+template <bool AF16> struct StreamMfma;
+template <> struct StreamMfma<false> {
+    typedef bf16x8_t frag;
+    static __device__ __forceinline__ f32x4_t run(frag a, frag b, f32x4_t c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+};
+template <> struct StreamMfma<true> {
+    typedef f16x8_t frag;
+    static __device__ __forceinline__ f32x4_t run(frag a, frag b, f32x4_t c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+    }
+};
+
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+typedef uint32_t u32x4s_t __attribute__((ext_vector_type(4)));
+
+template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
+
+}  // namespace
+
+// MB: 16-row blocks of activations; NB: 16-row blocks of weights per workgroup; WAVES share K.
+// Row blocks of weights: 8 rows "low", 8 rows "high" each.  MODE 0 plain, 3 residual: 16 consecutive
+// rows.  MODE 1 (SwiGLU): 8 gate rows and the matching 8 up rows.  MODE 2 (rotary): dims c .. c+7 and
+// c + hd/2 .. of one head.  So the members of every pair meet in one workgroup.
+template <int MB, int NB, int WAVES, int D, int MODE, bool AF16>
+__global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
+                                                            float* __restrict__ C, int M, int N, int K,
+                                                            const RowsEpi ep) {
+#if defined(__HIP_DEVICE_COMPILE__)                        // buffer resources exist in the device pass only
+    constexpr int OPS = 2 * NB + 2 * MB;                   // vector memory operations per step
+    constexpr int kRing = WAVES * D * NB * 1024;           // halves (2 KB per step and weight block)
+    constexpr int MP = MB * 16 + 1;
+    constexpr int kRed = WAVES * NB * 16 * MP;             // floats
+    __shared__ __attribute__((aligned(16))) uint8_t smem[kRing * 2 > kRed * 4 ? kRing * 2 : kRed * 4];
+    __shared__ float s_scale[MB * 16];
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int fr = lane & 15, fq = lane >> 4;
+    const int blk = blockIdx.x;
+    if (MODE == 0) C += (size_t)blockIdx.y * M * N;        // K range blockIdx.y of gridDim.y: a plane of its own
+
+    // weight row of (block nb, half hi, row r of 8); clamped rows are computed and never stored
+    auto wrow = [&](int nb, int hi) -> int {
+        const int b = blk * NB + nb;
+        if (MODE == 1) return hi * ep.ffn + min(b * 8, ep.ffn - 1);
+        if (MODE == 2) {
+            const int hd = ep.ro.head_dim, half = hd >> 1, per_head = half / 8;
+            const int head = min(b / per_head, N / hd - 1), c = (b % per_head) * 8;
+            return head * hd + hi * half + c;
+        }
+        return min(b * 16 + hi * 8, N - 1);
+    };
+    const int row_end = MODE == 1 ? ep.ffn : N;            // first row that does not exist, counted from a half's base
+
+    // this wave's steps; the count is rounded up to whole rings, surplus steps re-read the last one against zeros
+    const int steps = K >> 6, parts = WAVES * (MODE == 0 ? gridDim.y : 1);
+    const int per = (steps + parts - 1) / parts;
+    const int s0 = min(((MODE == 0 ? (int)blockIdx.y * WAVES : 0) + w) * per, steps), n_real = min(steps - s0, per);
+    const int n = (per + D - 1) / D * D;
+
+    __amdgpu_buffer_rsrc_t rs[NB][2];
+    uint32_t vo[NB][2];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int hi = 0; hi < 2; ++hi) {
+            const int base = __builtin_amdgcn_readfirstlane(wrow(nb, hi));
+            rs[nb][hi] = __builtin_amdgcn_make_buffer_rsrc((void*)(W + (size_t)base * K), 0, -1, 0x00020000);
+            const int r = lane >> 3;
+            const int lim = (MODE == 1 && hi ? 2 * row_end : row_end) - 1 - base;      // last row that exists
+            // LDS position p of row r holds chunk p ^ r: the fragment reads below then spread over the banks
+            vo[nb][hi] = (uint32_t)(min(r, max(lim, 0)) * K * 2 + ((lane & 7) ^ r) * 16);
+        }
+    bf16_t* ring = reinterpret_cast<bf16_t*>(smem) + w * (D * NB * 1024);
+    typedef typename StreamMfma<AF16>::frag frag_t;
+    const bf16_t* pa[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) pa[mb] = A + act_index(ep.a, min(mb * 16 + fr, M - 1), fq * 8);
+    const size_t a_half = (size_t)4 * ep.a.chunk;          // elements from one 32-k half of a step to the next
+
+    // partial sums of squares of the normed rows, requested before everything else: RPW rows per wave,
+    // kSsqStride floats each (unused ones are zero), a float4 per lane and 256 floats
+    constexpr int RPW = MB * 16 / WAVES;
+    // (up to 16 rows only: at 64 rows the registers it takes halve the occupancy, 40 against 31 us for QKV)
+    const bool normed = MODE != 3 && MB == 1 && ep.nrm.ssq != nullptr, two = ep.nrm.n_ssq > 256;
+    float4 q0[RPW], q1[RPW];
+    if (normed) {
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+            const float* src = ep.nrm.ssq + (size_t)min(w * RPW + i, M - 1) * kSsqStride + lane * 4;
+            q0[i] = *reinterpret_cast<const float4*>(src);
+            q1[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (two) q1[i] = *reinterpret_cast<const float4*>(src + 256);
+        }
+    }
+
+    // what the epilogue needs of this thread's outputs, requested now so that it does not wait at the end
+    constexpr int NT = WAVES * 64, R16 = NB * 16, R8 = NB * 8;
+    constexpr int OUT_IT = ((MODE == 1 || MODE == 2 ? R8 : R16) * MB * 16 + NT - 1) / NT;
+    float pre_a[OUT_IT], pre_b[OUT_IT];                    // MODE 3: h, g * s;  MODE 2: cos, sin
+    int pre_i[OUT_IT];                                     // MODE 2: position, then pool slot
+    if (MODE == 2) {
+#pragma unroll
+        for (int i = 0; i < OUT_IT; ++i) pre_i[i] = ep.ro.pos[min((t + i * NT) / R8, M - 1)];
+    }
+    if (MODE == 3) {
+#pragma unroll
+        for (int i = 0; i < OUT_IT; ++i) {
+            const int o = t + i * NT, m = min(o / R16, M - 1), nn = min(blk * R16 + o % R16, N - 1);
+            pre_a[i] = ep.res.h[(size_t)m * N + nn];
+            pre_b[i] = ep.res.g[nn] * ep.res.s[m];
+        }
+    }
+
+    frag_t fa[D][2 * MB];
+#define RLHF_ST_ISSUE(STEP, J)                                                                                     \
+    do {                                                                                                           \
+        const int st_ = s0 + max(min((STEP), n_real - 1), 0);                                                      \
+        const int sc_ = min(st_, steps - 1);                                                                       \
+        _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) {                                                        \
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[nb][0], (lds_ptr_t)(ring + ((J) * NB + nb) * 1024), 16,    \
+                                                     vo[nb][0], sc_ * 128, 0, 2);                                  \
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[nb][1], (lds_ptr_t)(ring + ((J) * NB + nb) * 1024 + 512), 16, \
+                                                     vo[nb][1], sc_ * 128, 0, 2);                                  \
+        }                                                                                                          \
+        __builtin_amdgcn_sched_barrier(0);                                                                         \
+        _Pragma("unroll") for (int mb = 0; mb < MB; ++mb) {                                                        \
+            fa[J][2 * mb] = *reinterpret_cast<const frag_t*>(pa[mb] + (size_t)sc_ * 2 * a_half);                           \
+            fa[J][2 * mb + 1] = *reinterpret_cast<const frag_t*>(pa[mb] + (size_t)sc_ * 2 * a_half + a_half);                  \
+        }                                                                                                          \
+        __builtin_amdgcn_sched_barrier(0);                                                                         \
+    } while (0)
+    f32x4_t acc[NB][MB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // fragment reads: row fr of the block, chunk s * 4 + fq; rows 8.. of a block sit 1 KB further (128 bytes a row)
+    const uint32_t lb = (uint32_t)(size_t)(lds_ptr_t)ring + fr * 128;
+    const uint32_t l0 = lb + ((uint32_t)fq ^ (fr & 7)) * 16, l1 = lb + ((uint32_t)(4 + fq) ^ (fr & 7)) * 16;
+#define RLHF_ST_CONSUME(STEP, J)                                                                                   \
+    do {                                                                                                           \
+        u32x4s_t wr_[NB][2];                                                                                       \
+        _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) {                                                        \
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(wr_[nb][0]) : "v"(l0), "n"(((J) * NB + nb) * 2048) : "memory"); \
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(wr_[nb][1]) : "v"(l1), "n"(((J) * NB + nb) * 2048) : "memory"); \
+        }                                                                                                          \
+        _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)   /* the first one waits, the others only tie their registers to it */ \
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(wr_[nb][0]), "+v"(wr_[nb][1]) : : "memory");                \
+        const bool live_ = (STEP) < n_real;                                                                        \
+        _Pragma("unroll") for (int s = 0; s < 2; ++s)                                                              \
+        _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) {                                                        \
+            u32x4s_t x_ = wr_[nb][s];                                                                              \
+            if (AF16) {                                                                                            \
+                x_[0] = bf16x2_to_f16x2(x_[0]); x_[1] = bf16x2_to_f16x2(x_[1]);                                    \
+                x_[2] = bf16x2_to_f16x2(x_[2]); x_[3] = bf16x2_to_f16x2(x_[3]);                                    \
+            }                                                                                                      \
+            if (!live_) x_ = u32x4s_t{0, 0, 0, 0};                                                                 \
+            const frag_t wf_ = *reinterpret_cast<const frag_t*>(&x_);                                              \
+            _Pragma("unroll") for (int mb = 0; mb < MB; ++mb)                                                      \
+                acc[nb][mb] = StreamMfma<AF16>::run(wf_, fa[J][2 * mb + s], acc[nb][mb]);                          \
+        }                                                                                                          \
+        __builtin_amdgcn_sched_barrier(0);                                                                         \
+    } while (0)
+
+#pragma unroll
+    for (int j = 0; j < D; ++j) RLHF_ST_ISSUE(j, j);
+    if (MODE == 2) {
+        const int half = ep.ro.head_dim >> 1, per_head = half / 8;
+#pragma unroll
+        for (int i = 0; i < OUT_IT; ++i) {
+            const int o = t + i * NT, r = o % R8, d0 = ((blk * NB + (r >> 3)) % per_head) * 8 + (r & 7);
+            const float2 cs = *reinterpret_cast<const float2*>(ep.ro.table + ((size_t)pre_i[i] * half + d0) * 2);
+            pre_a[i] = cs.x;
+            pre_b[i] = cs.y;
+            pre_i[i] = ep.ro.kv_dst ? ep.ro.kv_dst[min(o / R8, M - 1)] : 0;
+        }
+    }
+    if (normed) {
+        float v[RPW];
+#pragma unroll
+        for (int i = 0; i < RPW; ++i)
+            v[i] = ((q0[i].x + q1[i].x) + (q0[i].y + q1[i].y)) + ((q0[i].z + q1[i].z) + (q0[i].w + q1[i].w));
+        // all rows at once: every exchange halves the rows a lane still carries, row lane / (64 / RPW) in the end
+        int o = 32;
+#pragma unroll
+        for (int nn = RPW; nn > 1; nn >>= 1, o >>= 1)
+#pragma unroll
+            for (int i = 0; i < nn / 2; ++i) {
+                const bool up = lane & o;
+                const float give = up ? v[i] : v[i + nn / 2], keep = up ? v[i + nn / 2] : v[i];
+                v[i] = keep + __shfl_xor(give, o, kWave);
+            }
+#pragma unroll
+        for (; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, kWave);
+        constexpr int LPR = 64 / RPW;
+        const int m = w * RPW + lane / LPR;
+        if (m < M && lane % LPR == 0) {
+            const float inv = rsqrtf(v[0] / (float)K + ep.nrm.eps);
+            s_scale[m] = inv / ep.nrm.s_in[m];
+            if (blk == 0 && ep.nrm.s_out) ep.nrm.s_out[m] = pow2_below(inv);
+        }
+    }
+    int k = 0;
+    for (; k + D < n; k += D) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            wait_vmem<(D - 1) * OPS>();
+            RLHF_ST_CONSUME(k + j, j);
+            RLHF_ST_ISSUE(k + j + D, j);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < D; ++j) {                          // the last ring: nothing left to request
+        if (j == D - 1) wait_vmem<0>();
+        else if (j == D - 2) wait_vmem<OPS>();
+        else if (j == D - 3) wait_vmem<2 * OPS>();
+        else wait_vmem<3 * OPS>();
+        RLHF_ST_CONSUME(k + j, j);
+    }
+    static_assert(D >= 2 && D <= 4 && (D - 1) * OPS < 64, "waits written out for up to four steps; vmcnt has six bits");
+#undef RLHF_ST_ISSUE
+#undef RLHF_ST_CONSUME
+
+    // ---- the waves' shares of K meet in LDS: red[wave][weight row][activation row]
+    __syncthreads();
+    float* red = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                red[(w * NB * 16 + nb * 16 + fq * 4 + e) * MP + mb * 16 + fr] = acc[nb][mb][e];
+    __syncthreads();
+    auto total = [&](int row, int m) {
+        float v = 0.f;
+#pragma unroll
+        for (int x = 0; x < WAVES; ++x) v += red[(x * NB * 16 + row) * MP + m];
+        return v;
+    };
+    typedef typename std::conditional<AF16, f16_t, bf16_t>::type TO;
+    if (MODE == 0) {
+        for (int i = t; i < R16 * M; i += NT) {
+            const int m = i / R16, r = i % R16, nn = blk * R16 + r;
+            if (nn < N) C[(size_t)m * N + nn] = total(r, m) * (normed ? s_scale[m] : 1.f);
+        }
+        return;
+    }
+    if (MODE == 1) {
+        TO* act = reinterpret_cast<TO*>(ep.act);
+        for (int i = t; i < R8 * M; i += NT) {
+            const int m = i / R8, r = i % R8, oc = blk * R8 + r, lr = (r >> 3) * 16 + (r & 7);
+            if (oc < ep.ffn) {
+                const float sc = normed ? s_scale[m] : 1.f;
+                const float g = total(lr, m) * sc, u = total(lr + 8, m) * sc;
+                act[act_index(ep.out, m, oc)] = from_f32<TO>(g / (1.f + __expf(-g)) * u);
+            }
+        }
+        return;
+    }
+    if (MODE == 2) {
+        const RopeOut& ro = ep.ro;
+        const int hd = ro.head_dim, half = hd >> 1, per_head = half / 8;
+        const int Hq = ro.n_q_heads, Hkv = ro.n_kv_heads;
+        TO* q_out = reinterpret_cast<TO*>(ro.q);
+        TO* k_out = reinterpret_cast<TO*>(ro.k);
+        TO* v_out = reinterpret_cast<TO*>(ro.v);
+        TO* pool = reinterpret_cast<TO*>(ro.pool);
+#pragma unroll
+        for (int it = 0; it < OUT_IT; ++it) {
+            const int i = t + it * NT, m = i / R8, r = i % R8, lr = (r >> 3) * 16 + (r & 7);
+            const int b = blk * NB + (r >> 3), head = b / per_head;
+            if (m >= M || head >= Hq + 2 * Hkv) continue;
+            const int d0 = (b % per_head) * 8 + (r & 7), d1 = d0 + half;
+            const float sc = normed ? s_scale[m] : 1.f;
+            float a = total(lr, m) * sc, c = total(lr + 8, m) * sc;
+            if (head < Hq + Hkv) {
+                const float ra = a * pre_a[it] - c * pre_b[it], rc = a * pre_b[it] + c * pre_a[it];
+                a = ra; c = rc;
+            }
+            if (head < Hq) {
+                TO* dst = q_out + ((size_t)m * Hq + head) * hd;
+                dst[d0] = from_f32<TO>(a);
+                dst[d1] = from_f32<TO>(c);
+            } else {
+                const bool is_k = head < Hq + Hkv;
+                const int kh = is_k ? head - Hq : head - Hq - Hkv;
+                TO* lin = is_k ? k_out : v_out;
+                if (lin) {
+                    lin[((size_t)m * Hkv + kh) * hd + d0] = from_f32<TO>(a);
+                    lin[((size_t)m * Hkv + kh) * hd + d1] = from_f32<TO>(c);
+                }
+                if (pool) {
+                    const int slot = pre_i[it], pt = ro.page_tokens;
+                    TO* dst = pool + ((size_t)(slot / pt) * ro.n_layers + ro.layer) * 2 * (size_t)Hkv * pt * hd +
+                              (size_t)(is_k ? 0 : Hkv) * pt * hd + (size_t)kh * pt * hd + (size_t)(slot % pt) * hd;
+                    dst[d0] = from_f32<TO>(a);
+                    dst[d1] = from_f32<TO>(c);
+                }
+            }
+        }
+        return;
+    }
+    if (MODE == 3) {
+        const ResidOut& rz = ep.res;
+        f16_t* x = reinterpret_cast<f16_t*>(rz.x);
+#pragma unroll
+        for (int it = 0; it < OUT_IT; ++it) {              // whole waves take part: the sums below are lane shuffles
+            const int i = t + it * NT, m = i / R16, r = i % R16, nn = blk * R16 + r;
+            float v = 0.f;
+            if (m < M && nn < N) {
+                v = pre_a[it] + total(r, m);
+                rz.h[(size_t)m * N + nn] = v;
+                x[act_index(ep.out, m, nn)] = (f16_t)(v * pre_b[it]);
+            }
+            float q = v * v;
+#pragma unroll
+            for (int o = 1; o < R16; o <<= 1) q += __shfl_xor(q, o, kWave);
+            if (m < M && r == 0) rz.ssq[(size_t)m * kSsqStride + blk] = q;
+        }
+    }
+#endif
+}
+
+namespace {
+
+template <int MB, int NB, int WAVES, int D, bool AF16>
+hipError_t stream_launch(hipStream_t st, int mode, int blocks, int nsplit, const bf16_t* a, const bf16_t* w, float* C,
+                         int M, int N, int K, const RowsEpi& ep) {
+    const dim3 grid(blocks, nsplit);
+    switch (mode) {
+        case 0: k_gemm_stream<MB, NB, WAVES, D, 0, AF16><<<grid, WAVES * 64, 0, st>>>(a, w, C, M, N, K, ep); break;
+        case 1: k_gemm_stream<MB, NB, WAVES, D, 1, AF16><<<grid, WAVES * 64, 0, st>>>(a, w, C, M, N, K, ep); break;
+        case 2: k_gemm_stream<MB, NB, WAVES, D, 2, AF16><<<grid, WAVES * 64, 0, st>>>(a, w, C, M, N, K, ep); break;
+        default:
+            if constexpr (MB == 1 && NB == 1 && AF16)
+                k_gemm_stream<MB, NB, WAVES, D, 3, AF16><<<grid, WAVES * 64, 0, st>>>(a, w, C, M, N, K, ep);
+            else
+                return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool gemm_stream_supported(int wdt, int adt, int M, int K) {
+    return wdt == kBF16 && (adt == kF16 || (adt == kBF16 && M <= 16)) && M >= 1 && M <= kStreamMaxRows && K > 0 && K % 64 == 0;
+}
+
+// Shape of a launch: 16-row blocks of activations, of weights per workgroup, ring depth (four waves
+// throughout).  Every workgroup reads all activation rows of its K range, from the L2, and the loads of
+// a compute unit share one queue: time goes with weight bytes times the latency of HBM plus activation
+// bytes times that of the L2 (about 0.4 of it).  So more weight blocks per workgroup help as rows grow
+// (7B gate||up, us: 16 rows 34.5 / 30.5 with one / two; 32 rows 33.8 / 31.8 with two / three; 64 rows
+// 47.1 / 41.2), as long as about one workgroup per compute unit is left (QKV at 64 rows: 32.0 / 23.0 /
+// 25.5 with two / three / four, the last one 192 workgroups).  N = 4096 falls short of that: with more
+// than 16 rows O and down split K instead and leave planes to the norm that follows (64 rows: O 11.0
+// and down 22.8 as four planes of four blocks, 13.5 and 32.0 unsplit with one block).
+struct StreamShape { int mb, nb, depth; };
+static StreamShape stream_shape(int M, int N, bool planes) {
+    if (M <= 16) return N >= 19200 ? StreamShape{1, 2, 4} : StreamShape{1, 1, 4};
+    const int mb = M <= 32 ? 2 : 4;
+    if (N < 4096) return {mb, 1, 4};                       // small matrices: workgroups before traffic
+    if (planes) return mb == 2 ? StreamShape{2, 2, 4} : StreamShape{4, 4, 2};
+    return {mb, 3, 2};
+}
+int gemm_stream_nsplit(int M, int N, int K, int max_split) {
+    const StreamShape sh = stream_shape(M, N, true);
+    const int blocks = (N + 16 * sh.nb - 1) / (16 * sh.nb);
+    int ns = (256 + blocks - 1) / blocks;
+    ns = ns < (K >> 6) / 8 ? ns : (K >> 6) / 8;            // at least two steps of 64 per wave
+    ns = ns < max_split ? ns : max_split;
+    return ns < 1 ? 1 : ns;
+}
+
+hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const void* A, const void* W, float* C, int M,
+                              int N, int K, const RowsEpi& ep_in, int nsplit) {
+    RowsEpi ep = ep_in;
+    if (ep.a.row == 0) ep.a = ActLayout{K, 8};             // row-major unless the caller says otherwise
+    if (ep.out.row == 0) ep.out = ActLayout{mode == 1 ? ep.ffn : N, 8};
+    if (!gemm_stream_supported(wdt, adt, M, K) || N <= 0 || mode < 0 || mode > 3) return hipErrorInvalidValue;
+    if ((long)8 * K * 2 >= (1L << 31)) return hipErrorInvalidValue;
+    if (nsplit < 1 || (mode == 0 ? !C : nsplit != 1) || (nsplit > 1 && ep.nrm.ssq)) return hipErrorInvalidValue;
+    if (mode == 1 && (!ep.act || ep.ffn <= 0 || N != 2 * ep.ffn || ep.ffn % 8)) return hipErrorInvalidValue;
+    if (mode == 2) {
+        const RopeOut& ro = ep.ro;
+        if ((ro.head_dim != 64 && ro.head_dim != 128) || !ro.pos || !ro.table || !ro.q || (ro.pool && !ro.kv_dst) ||
+            N != (ro.n_q_heads + 2 * ro.n_kv_heads) * ro.head_dim)
+            return hipErrorInvalidValue;
+    }
+    if (mode == 3 && (adt != kF16 || M > 16 || N % 16 || N > 16 * kSsqStride || !ep.res.h || !ep.res.g || !ep.res.x || !ep.res.s || !ep.res.ssq))
+        return hipErrorInvalidValue;
+    const bf16_t* a = (const bf16_t*)A;
+    const bf16_t* w = (const bf16_t*)W;
+    const StreamShape sh = mode == 3 ? StreamShape{1, 1, 4} : stream_shape(M, N, nsplit > 1);
+    const int blocks = (N + 16 * sh.nb - 1) / (16 * sh.nb);
+    if (adt == kBF16) return stream_launch<1, 1, 4, 4, false>(st, mode, (N + 15) / 16, nsplit, a, w, C, M, N, K, ep);
+#define RLHF_STREAM(MB, NB, D)              \
+    if (sh.mb == MB && sh.nb == NB && sh.depth == D) \
+        return stream_launch<MB, NB, 4, D, true>(st, mode, blocks, nsplit, a, w, C, M, N, K, ep)
+    RLHF_STREAM(1, 1, 4);
+    RLHF_STREAM(1, 2, 4);
+    RLHF_STREAM(2, 1, 4);
+    RLHF_STREAM(2, 2, 4);
+    RLHF_STREAM(2, 3, 2);
+    RLHF_STREAM(4, 1, 4);
+    RLHF_STREAM(4, 3, 2);
+    RLHF_STREAM(4, 4, 2);
+#undef RLHF_STREAM
+    return hipErrorInvalidValue;
+}
+
+}  // namespace rlhf

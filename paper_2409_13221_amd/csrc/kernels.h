@@ -20,6 +20,15 @@ struct Dims {
     int page_tokens;
 };
 
+// Where element (m, k) of a 16-bit activation matrix lies: m * row + (k / 8) * chunk + k % 8.  Row-major
+// is {K, 8}.  Between the kernels of a decode step it is {8, 8 M}: the same 16-byte chunk of all rows is
+// contiguous, which is how a matrix operand is read (M = 16, 7B gate||up + QKV: 52.5 us against 56.3 with
+// row-major activations; M = 64: 76 against 95).  row == 0 stands for row-major.
+struct ActLayout { int row = 0, chunk = 8; };
+__host__ __device__ inline size_t act_index(const ActLayout& l, int m, int k) {
+    return (size_t)m * l.row + (size_t)(k >> 3) * l.chunk + (k & 7);
+}
+
 // ---- GEMM: C[s][m][n] = sum over k in split s of A[m][k] * W[n][k];  C float, split stride M*N
 // (wdt, adt) in {(kF32,kF32), (kBF16,kBF16), (kBF16,kF16)}
 int gemm_choose_nsplit(int wdt, int M, int N, int K, int max_split);
@@ -57,19 +66,42 @@ bool gemm_rope_supported(int wdt, int adt, int M, int K, const Dims& dm);
 hipError_t launch_gemm_rope(hipStream_t st, int wdt, int adt, const void* A, const void* Wqkv, int M, int K,
                             const RopeOut& ro);
 
-// Few rows (1..16), bf16 weights: a kernel whose workgroups walk the whole K range (no split), so that
-// the step that consumes the projection rides in its epilogue and needs no launch of its own.
+// Few rows, bf16 weights (gemm_stream.hip): workgroups walk the whole K range, so that the step that
+// consumes the projection rides in its epilogue and needs no launch of its own.
 // mode 0: C float [M, N]; mode 1: gate||up with SwiGLU, act [M, ffn] of type adt (N = 2 ffn);
-// mode 2: QKV with rotary embedding and the q / k / v / paged-pool scatter (ep.ro as in launch_gemm_rope).
-// K must be a multiple of 256.  Mode 0 may also split K (nsplit float planes, (K / 64) a multiple of
-// 4 * nsplit).
+// mode 2: QKV with rotary embedding and the q / k / v / paged-pool scatter (ep.ro as in launch_gemm_rope);
+// mode 3: residual: h += result, and the unscaled input of the next norm (ep.res).
+// Half activations: 1..kStreamMaxRows rows; bf16 activations: 1..16.  K a multiple of 64.
+constexpr int kStreamMaxRows = 64;
+constexpr int kSsqStride = 512; // floats per row of the partial sums of squares (d_model <= 8192, 16 columns each)
+struct NormIn {                 // modes 0..2: A holds x = h * gain * s_in; result of row m times (1/rms) / s_in[m]
+    const float* ssq = nullptr;     // [M, kSsqStride] partial sums of h^2 (n_ssq used, the others zero), or NULL: A is used as it is
+    int n_ssq = 0;
+    const float* s_in = nullptr;    // [M]
+    float* s_out = nullptr;         // [M] receives the power of two below 1/rms (may be NULL)
+    float eps = 0.f;
+};
+struct ResidOut {               // mode 3
+    float* h = nullptr;             // [M, N] residual stream, updated
+    const float* g = nullptr;       // [N] gain of the norm that follows
+    void* x = nullptr;              // [M, N] half: h * g * s
+    const float* s = nullptr;       // [M] scale that keeps x in half's range (power of two below the row's previous 1/rms)
+    float* ssq = nullptr;           // [M, kSsqStride] partial sums of h^2, one per 16 columns
+};
 struct RowsEpi {
+    ActLayout a, out;          // layout of A; of act (mode 1) or x (mode 3)
     void* act = nullptr;       // mode 1
     int ffn = 0;
     RopeOut ro;                // mode 2
+    NormIn nrm;
+    ResidOut res;
 };
-bool gemm_rows16_supported(int wdt, int adt, int M, int K);
-hipError_t launch_gemm_rows16(hipStream_t st, int wdt, int adt, int mode, const void* A, const void* W, float* C,
+bool gemm_stream_supported(int wdt, int adt, int M, int K);
+constexpr int kStreamResidRows = 16;         // mode 3 and NormIn: up to this many rows
+// Mode 0 may split K into nsplit planes C [nsplit][M][N]; the split for O and down projections of more
+// than kStreamResidRows rows:
+int gemm_stream_nsplit(int M, int N, int K, int max_split);
+hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const void* A, const void* W, float* C,
                               int M, int N, int K, const RowsEpi& ep, int nsplit = 1);
 
 // LM head of a scoring pass fused with the log-softmax gather: the logits stay in registers.  Per
@@ -95,11 +127,16 @@ hipError_t launch_lse_merge(hipStream_t st, const float* part_max, const float* 
 // ---- elementwise / row kernels
 hipError_t launch_embed(hipStream_t st, int dtype, const int* tokens, const int* tok_idx,
                         const void* table, float* h, int rows, int d, int vocab);
+// The embedding row with the first norm applied, for the few-row projections of gemm_stream.hip: h, and
+// x = h * s * g (half, layout x_layout), s[r] the power of two below 1/rms, ssq [rows, kSsqStride]: the sum of h^2, then zeros.
+hipError_t launch_embed_norm(hipStream_t st, int dtype, const int* tokens, const int* tok_idx, const void* table,
+                             float* h, const float* g, void* x, const ActLayout& x_layout, float* s, float* ssq,
+                             int rows, int d, int vocab, float eps);
 // v = h[src] + sum partials[src];  (row_idx == NULL: src = r and h[src] = v is written back)
 // xn[r] = v * rsqrt(mean(v^2) + eps) * g
 hipError_t launch_rmsnorm(hipStream_t st, int adt, float* h, const float* part, int nsplit,
                           size_t sstride, const int* row_idx, const float* g, void* xn, int rows,
-                          int d, float eps);
+                          int d, float eps, const ActLayout& xn_layout = ActLayout{});
 // Rotary on Q and K heads of qkv rows.  q_out [rows, Hq*hd] and, if non-NULL, k_out/v_out
 // [rows, Hkv*hd] have type qdt; if pool != NULL and kv_dst[r] >= 0, K/V of row r also go (as
 // type pdt) to token slot kv_dst[r] (= page * page_tokens + offset) of `layer` in the paged pool.
@@ -141,10 +178,13 @@ hipError_t launch_gae_returns(hipStream_t st, const float* A, const float* value
 // Decode: one query row per active sample against its paged K/V.  q [rows, Hq*hd]; out the same.
 // row_sample[r] selects the page-table row; ctx_len[r] keys are visible.  part_* hold split
 // partials when nsplit > 1 (sizes rows*Hq*nsplit*(hd or 1)).
+// out_layout: row-major by default.
 hipError_t launch_decode_attn(hipStream_t st, int dtype, const void* q, const void* pool,
                               const int* page_table, int pt_stride, const int* row_sample,
                               const int* ctx_len, void* out, float* part_acc, float* part_ml,
-                              int rows, int layer, int nsplit, const Dims& dm);
+                              int rows, int layer, int nsplit, const Dims& dm, const ActLayout& out_layout = ActLayout{});
+// Splits of the contexts for a decode step of `rows` rows whose longest context has max_pages pages.
+int decode_attn_nsplit(int rows, int max_pages, const Dims& dm, int max_split);
 // Prefill / scoring: packed varlen causal attention over contiguous float q [T,Hq*hd], k, v
 // [T,Hkv*hd]; out has type odt; row r belongs to the sequence starting at row_start[r] and sits at position
 // row_pos[r] in it (sees keys row_start[r] .. row_start[r] + row_pos[r]).

@@ -141,11 +141,11 @@ extern "C" int rlhf_op_gemm_swiglu(int act_half, const void* A, const void* W_ga
     if (!A || !W_gate_up || !act) return RLHF_EINVAL;
     const int adt = act_half ? kF16 : kBF16, wdt = act_half == 2 ? kF16 : kBF16;
     if (M >= 1 && M <= 16) {            // the few-row kernel of decode steps (no K split, SwiGLU in its epilogue)
-        if (!gemm_rows16_supported(wdt, adt, M, K) || ffn <= 0 || ffn % 8) return RLHF_EINVAL;
+        if (!gemm_stream_supported(wdt, adt, M, K) || K % 256 || ffn <= 0 || ffn % 8) return RLHF_EINVAL;
         RowsEpi ep;
         ep.act = act;
         ep.ffn = ffn;
-        return status_of(launch_gemm_rows16((hipStream_t)stream, wdt, adt, 1, A, W_gate_up, nullptr, M, 2 * ffn, K, ep));
+        return status_of(launch_gemm_stream((hipStream_t)stream, wdt, adt, 1, A, W_gate_up, nullptr, M, 2 * ffn, K, ep));
     }
     if (!gemm_swiglu_supported(wdt, adt, M, ffn, K)) return RLHF_EINVAL;
     return status_of(launch_gemm_swiglu((hipStream_t)stream, wdt, adt, A, W_gate_up, act, M, ffn, K));
@@ -166,10 +166,10 @@ extern "C" int rlhf_op_gemm_rope(int act_half, const void* A, const void* W_qkv,
     ro.layer = layer; ro.n_layers = n_layers;
     ro.n_q_heads = n_q_heads; ro.n_kv_heads = n_kv_heads; ro.head_dim = head_dim;
     if (M >= 1 && M <= 16) {            // the few-row kernel of decode steps (no K split, rotary in its epilogue)
-        if (!gemm_rows16_supported(wdt, adt, M, K) || (head_dim != 64 && head_dim != 128)) return RLHF_EINVAL;
+        if (!gemm_stream_supported(wdt, adt, M, K) || K % 256 || (head_dim != 64 && head_dim != 128)) return RLHF_EINVAL;
         RowsEpi ep;
         ep.ro = ro;
-        return status_of(launch_gemm_rows16((hipStream_t)stream, wdt, adt, 2, A, W_qkv, nullptr, M,
+        return status_of(launch_gemm_stream((hipStream_t)stream, wdt, adt, 2, A, W_qkv, nullptr, M,
                                             (n_q_heads + 2 * n_kv_heads) * head_dim, K, ep));
     }
     if (!gemm_rope_supported(wdt, adt, M, K, dm)) return RLHF_EINVAL;

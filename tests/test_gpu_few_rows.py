@@ -1,0 +1,28 @@
+"""Decode steps (and short prefills) of 1..64 rows run on the weight-streaming projections: batch sizes
+at the edges of their row blocks, a model whose sizes leave remainders in every projection, and one
+wide enough for several weight blocks per workgroup and for K splits.  The oracle generates; log-probs,
+values and rewards are held to the tolerances of the other stage tests."""
+from dataclasses import replace
+
+import pytest
+
+from tests import stage_harness as H
+from workload import CONFIGS
+
+pytestmark = pytest.mark.gpu
+
+_GPT2S = CONFIGS["gpt2s"]
+# 5 steps of 64 along d and 7 along ffn: waves with no step of their own; a ragged vocabulary
+_SMALL = replace(_GPT2S.model, n_layers=2, d_model=320, n_q_heads=5, n_kv_heads=5, head_dim=64, ffn=448, vocab=1003)
+# N >= 4096 everywhere but in the KV heads' share, K = 4096 and 704
+_WIDE = replace(_GPT2S.model, n_layers=1, d_model=4096, n_q_heads=32, n_kv_heads=4, head_dim=128, ffn=704, vocab=4100)
+_GROUPED = replace(_SMALL, d_model=1024, n_q_heads=8, n_kv_heads=1, head_dim=128)
+
+
+@pytest.mark.parametrize("model,n", [(_SMALL, n) for n in (1, 16, 17, 32, 33, 64, 65)]
+                         + [(_WIDE, n) for n in (3, 16, 31, 64)] + [(_GROUPED, n) for n in (2, 19)])
+def test_decode_batches_of_few_rows(model, n):
+    cfg = _GPT2S.with_(name="few_rows", model=model, n_samples=n, prompt_len=(3, 5), gain_jitter=0.05)
+    ref = H.oracle_stage(cfg, n=n, max_len=4)
+    got = H.run_gpu_stage(cfg, ref, fused=False, R_t=0, chunk_tokens=64)
+    H.compare_stage(cfg, ref, got)
