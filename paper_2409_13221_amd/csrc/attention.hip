@@ -16,7 +16,6 @@
 // K/V (one workgroup per query row and KV head); bf16 models use the MFMA kernel at the end of
 // this file.
 #include "common.h"
-#include <algorithm>
 #include "kernels.h"
 
 namespace rlhf {
@@ -426,17 +425,20 @@ __global__ void k_attn_merge(const float* __restrict__ part_acc, const float* __
 }
 
 // Waves per workgroup: a workgroup holds one (row, KV head, split), its waves take the pages in turn.
-// With few workgroups the pages of one are spread over 8 or 16 waves, which costs a merge in LDS where
-// more splits would cost a merge kernel (about 5 us).
-static int decode_attn_waves(long blocks, int group) { return 4; }
+// With few workgroups the pages of one are spread over 8 or 16 waves, merged in LDS, where more splits
+// would cost a merge kernel (about 4 us).  32 heads of 128, half, us with 4 waves / with this rule, best
+// split each: 1 row at context 500 12.2 / 9.3, 13 rows at 500 21.4 / 20.0, at 2500 89.9 / 83.4; grouped
+// heads (64 over 8), 32 rows at 1100 33.4 / 27.9.  From 512 workgroups on four waves fill the chip.
+static int decode_attn_waves(long blocks, int group) { return blocks >= 512 ? 4 : blocks >= 256 || group > 1 ? 8 : 16; }
 
-// As many splits as give the chip about sixteen waves per compute unit, unless that leaves a wave with
-// fewer than four pages.
+// As many splits as give the chip about sixteen waves per compute unit (twelve of the grouped kernel,
+// which keeps more in flight: 32 rows at 1100 27.9 us unsplit, 30.3 with two), unless that leaves a wave
+// with fewer than four pages.
 int decode_attn_nsplit(int rows, int max_pages, const Dims& dm, int max_split) {
     const long blocks = (long)rows * dm.n_kv_heads;
-    const int wv = decode_attn_waves(blocks, dm.n_q_heads / dm.n_kv_heads);
-    long ns = 1024 * 4 / (blocks * wv > 0 ? blocks * wv : 1);
-    const int by_pages = std::max(1, max_pages / 8);
+    const int group = dm.n_q_heads / dm.n_kv_heads, wv = decode_attn_waves(blocks, group);
+    long ns = (group > 1 ? 3072 : 4096) / (blocks * wv > 0 ? blocks * wv : 1);
+    const int by_pages = (max_pages + wv * 4 - 1) / (wv * 4);
     if (ns > by_pages) ns = by_pages;
     if (ns > max_split) ns = max_split;
     return ns < 1 ? 1 : (int)ns;
