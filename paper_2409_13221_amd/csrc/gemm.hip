@@ -14,7 +14,7 @@
 // fp32: a plain LDS-tiled kernel for the float configuration (small model; not tuned).
 #include "common.h"
 #include "kernels.h"
-#include <type_traits>
+#include "tile_walk.h"
 
 namespace rlhf {
 
@@ -41,46 +41,13 @@ template <> struct Mfma<true> {
 };
 
 // Tile index of a workgroup.  Few-row launches (XCD == false) walk the N tiles in order, the
-// row tiles of a column tile next to each other so that its weights are fetched once.
-// Compute-bound launches (XCD == true): the tile grid is cut into panels of kGroupM tile rows.
-// Inside a panel the tile columns are dealt to the 8 XCDs (workgroup id modulo 8, the order in
-// which the dispatcher deals workgroups to XCDs) in contiguous groups, and an XCD walks its
-// group column by column.  Two things follow.  The workgroups resident on one XCD at a time
-// cover a compact block of kGroupM x 4 tiles, so its L2 re-serves the A rows and W rows they
-// share.  And all XCDs work on the SAME panel of A rows at the same time, each on W columns of
-// its own: an A panel is requested by the eight L2s within a short time of each other (one
-// fetch from HBM, the others from the memory-side cache even while a decode stream sweeps its
-// weights through that cache) and every W column is fetched by one XCD only, once per panel.
-// (Before, each XCD walked its own contiguous eighth of the panel-ordered tile list; the
-// eight of them then sat on up to four different A panels and up to eight W ranges, and with the
-// memory-side cache swept by the decode stream the scoring GEMMs pulled several times their
-// operands from HBM.)
-constexpr int kGroupM = 8;
-__host__ __device__ inline int xcd_cols(int tiles_n) { return (tiles_n + 7) >> 3; }   // tile columns per XCD
-inline int xcd_grid(int tiles_m, int tiles_n) { return 8 * tiles_m * xcd_cols(tiles_n); }
+// row tiles of a column tile next to each other so that its weights are fetched once; the others as
+// tile_walk.h says.
 template <bool XCD>
-__host__ __device__ __forceinline__ bool tile_of(int bid, int tiles_m, int tiles_n, int& tm, int& tn) {
-    if (!XCD) {           // the (at most two) row tiles of one column tile run side by side
-        tn = bid / tiles_m;
-        tm = bid - tn * tiles_m;
-        return true;
-    }
-    const int xcd = bid & 7, slot = bid >> 3;
-    const int cx = xcd_cols(tiles_n);
-    const int c_lo = xcd * cx;
-    const int c_n = min(tiles_n, c_lo + cx) - c_lo;          // this XCD's columns (may be <= 0 at the end)
-    if (c_n <= 0) return false;
-    const int per_panel = kGroupM * c_n;
-    const int full = tiles_m / kGroupM;
-    int panel = slot / per_panel, r = slot - panel * per_panel, rows = kGroupM;
-    if (panel >= full) {                                     // the last, shorter panel
-        panel = full;
-        r = slot - full * per_panel;
-        rows = tiles_m - full * kGroupM;
-        if (rows <= 0 || r >= rows * c_n) return false;
-    }
-    tm = panel * kGroupM + r % rows;
-    tn = c_lo + r / rows;
+__device__ __forceinline__ bool tile_of(int bid, int tiles_m, int tiles_n, int& tm, int& tn) {
+    if (XCD) return xcd_tile_of(bid, tiles_m, tiles_n, tm, tn);
+    tn = bid / tiles_m;
+    tm = bid - tn * tiles_m;
     return true;
 }
 
@@ -93,43 +60,11 @@ __host__ __device__ __forceinline__ bool tile_of(int bid, int tiles_m, int tiles
 // lane ends up with gate and up of the same output column in neighbouring fragments; the
 // epilogue writes act = silu(gate) * up as 16-bit [M, f] (of the activation type) to C and the
 // float [M, 2f] intermediate never exists.
-//
-// ADMA: the activation tile, which never needs converting, goes from global memory straight
-// into LDS (global_load_lds, 16 bytes per lane, 1 KB per wave and instruction: the lane picks
-// the global chunk whose swizzled place it fills).  That frees its staging registers, which
-// is what lets a decode workgroup sit beside one of these on a compute unit.  Needs whole K
-// tiles (K a multiple of TK, no split); rows past M are clamped (computed, never stored).
-//
-// ROPE (= head_dim, 64 or 128; 0 = off): W is a layer's QKV matrix and the epilogue finishes the
-// projection: query and key heads are rotated (pair (k, k + head_dim/2); a wave tile of 128
-// columns holds whole heads, so both halves of a pair sit in one lane, in fragments head_dim/32
-// apart), everything is rounded to the activation type and written where attention reads it:
-// q, k, v row-major, and k, v also into the paged pool when the pass fills the cache.  The
-// float [M, (Hq + 2 Hkv) head_dim] intermediate and the separate rotary kernel disappear.
-//
-// LSE: W is an LM head [vocab, K] and the logits never leave the registers: the epilogue reduces
-// each wave's 128 columns of a row to (max, sum of exp(z - max)), writes that pair as one of the
-// row's 2 * tiles_n partials, and the lane that holds the row's target column stores that logit.
-// A small merge kernel turns the partials into log_softmax(z)[target] (k_lse_merge).
-//
-// BDMA: W is IEEE half in memory (a copy of the bf16 matrix made when the weights were bound) and
-// goes global -> LDS directly like the activations: no staging registers, no conversion, no LDS
-// stores in the loop.  Both operands then come in as buffer loads (buffer_load_dwordx4 ... lds):
-// a lane's 32-bit byte offset is fixed for the whole K walk, which is the instruction's scalar
-// offset, so issuing a load costs one scalar add for M0 and no vector work (operands < 4 GiB).
-// Needs ADMA's conditions and half activations.
-//
-// RING (> 1, register-staged tiles only): that many K tiles are kept in flight in registers, so that a
-// workgroup which streams its weights over the whole K range (no split) still has enough bytes on
-// their way to keep HBM busy.
-template <int TM, int TN, int TK, int WM, int WN, bool AF16, bool XCD, bool SWIGLU, bool ADMA = false, int ROPE = 0,
-          bool LSE = false, bool BDMA = false, int RING = 1>
+template <int TM, int TN, int TK, int WM, int WN, bool AF16, bool XCD, bool SWIGLU>
 __global__ __launch_bounds__(WM * WN * 64) void k_gemm_bf16(const bf16_t* __restrict__ A,
                                                            const bf16_t* __restrict__ W,
                                                            float* __restrict__ C, int M, int N, int K,
-                                                           int kchunk, int tiles_m, int tiles_n,
-                                                           const RopeOut ro = RopeOut{},
-                                                           const LseOut lo = LseOut{}) {
+                                                           int kchunk, int tiles_m, int tiles_n) {
     constexpr int NT = WM * WN * 64;
     constexpr int FM = TM / WM / 16, FN = TN / WN / 16;
     constexpr int CH = TK / 8;                            // 16-byte chunks per tile row
@@ -146,82 +81,14 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_bf16(const bf16_t* __rest
     const int kend = min(K, kbeg + kchunk);
     const int nk = (kend - kbeg + TK - 1) / TK;
 
-    // the wave index as a scalar: the wave's tile origin and the LDS destinations of its direct loads
-    // then live in scalar registers
-    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int wm = w / WN, wn = w - wm * WN;
 
-    // direct path: wave w fills the 1 KB blocks w * D_IT .. of the A tile (1024 / (2 TK) rows each)
-    constexpr int D_RPB = 512 / TK, D_IT = ADMA ? TM / D_RPB / (NT / 64) : 1;
-    static_assert(!ADMA || (TM / D_RPB) % (NT / 64) == 0, "A tile blocks must divide among the waves");
-    size_t da[D_IT];
-    if (ADMA) {
-#pragma unroll
-        for (int i = 0; i < D_IT; ++i) {
-            const int row = (w * D_IT + i) * D_RPB + lane / CH, p = lane % CH;
-            // LDS chunk p of this row holds global chunk c with swz(row, c) == p; the swizzle is an XOR
-            const int c = swz<TK>(row, p);
-            da[i] = (size_t)min(m0 + row, M - 1) * K + c * 8;
-        }
-    }
-    static_assert(!BDMA || (ADMA && AF16), "half weights go with half activations on the direct path");
-    constexpr int DB_IT = BDMA ? TN / D_RPB / (NT / 64) : 1;
-    static_assert(!BDMA || (TN / D_RPB) % (NT / 64) == 0, "W tile blocks must divide among the waves");
-    size_t db[DB_IT];
-    if (BDMA) {
-#pragma unroll
-        for (int i = 0; i < DB_IT; ++i) {
-            const int row = (w * DB_IT + i) * D_RPB + lane / CH, p = lane % CH;
-            const int c = swz<TK>(row, p);
-            int gn = min(n0 + row, N - 1);        // rows past N are clamped (computed, never stored)
-            if (SWIGLU) {
-                const int oc = min((n0 >> 1) + (row >> 5) * 16 + (row & 15), (N >> 1) - 1);
-                gn = ((row >> 4) & 1) * (N >> 1) + oc;
-            }
-            db[i] = (size_t)gn * K + c * 8;
-        }
-    }
-    typedef __attribute__((address_space(3))) void* lds_ptr_t;
-    typedef const __attribute__((address_space(1))) void* glb_ptr_t;
-    // BDMA: both operands come in through buffer loads (buffer_load_dwordx4 ... lds): the lane's 32-bit byte
-    // offset never changes, the walk along K is a scalar offset, so a direct load costs no vector ALU work
-    // and half the address traffic of a 64-bit global load.
-    uint32_t oa[D_IT], ob[DB_IT];
-#if defined(__HIP_DEVICE_COMPILE__)          // the buffer resource type exists in the device pass only
-    __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, BDMA ? -1 : 0, 0x00020000);
-    __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void*)W, 0, BDMA ? -1 : 0, 0x00020000);
-#endif
-    if (BDMA) {
-#pragma unroll
-        for (int i = 0; i < D_IT; ++i) oa[i] = (uint32_t)(da[i] * 2);
-#pragma unroll
-        for (int i = 0; i < DB_IT; ++i) ob[i] = (uint32_t)(db[i] * 2);
-    }
-
-    uint4 ra[ADMA ? 1 : A_IT], rb[BDMA ? 1 : B_IT];
-    auto gload = [&](int kt, uint4* ra, uint4* rb) {
+    uint4 ra[A_IT], rb[B_IT];
+    auto gload = [&](int kt) {
         const int k0 = kbeg + kt * TK;
-        if (BDMA) {
-#if defined(__HIP_DEVICE_COMPILE__)
 #pragma unroll
-            for (int i = 0; i < D_IT; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_a, (lds_ptr_t)&sA[kt & 1][(w * D_IT + i) * 512], 16, oa[i],
-                                                         k0 * 2, 0, 0);
-#pragma unroll
-            for (int i = 0; i < DB_IT; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w, (lds_ptr_t)&sB[kt & 1][(w * DB_IT + i) * 512], 16, ob[i],
-                                                         k0 * 2, 0, 0);
-#endif
-        } else if (ADMA) {
-            // issued first: the wait the compiler places before the next LDS reads then covers
-            // these and leaves the weight loads below in flight
-#pragma unroll
-            for (int i = 0; i < D_IT; ++i)
-                __builtin_amdgcn_global_load_lds((glb_ptr_t)(A + da[i] + k0),
-                                                 (lds_ptr_t)&sA[kt & 1][(w * D_IT + i) * 512], 16, 0, 0);
-        }
-#pragma unroll
-        for (int i = 0; i < (ADMA ? 0 : A_IT); ++i) {
+        for (int i = 0; i < A_IT; ++i) {
             const int idx = t + i * NT;
             const int row = idx / CH, c = idx % CH;
             const int gm = m0 + row, gk = k0 + c * 8;
@@ -230,7 +97,7 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_bf16(const bf16_t* __rest
                 ra[i] = *reinterpret_cast<const uint4*>(A + (size_t)gm * K + gk);
         }
 #pragma unroll
-        for (int i = 0; i < (BDMA ? 0 : B_IT); ++i) {
+        for (int i = 0; i < B_IT; ++i) {
             const int idx = t + i * NT;
             const int row = idx / CH, c = idx % CH;
             int gn = n0 + row;
@@ -255,16 +122,16 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_bf16(const bf16_t* __rest
             }
         }
     };
-    auto sstore = [&](int buf, uint4* ra, uint4* rb) {
+    auto sstore = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < (ADMA ? 0 : A_IT); ++i) {
+        for (int i = 0; i < A_IT; ++i) {
             const int idx = t + i * NT;
             const int row = idx / CH, c = idx % CH;
             if (idx < A_CH)
                 *reinterpret_cast<uint4*>(&sA[buf][row * TK + swz<TK>(row, c) * 8]) = ra[i];
         }
 #pragma unroll
-        for (int i = 0; i < (BDMA ? 0 : B_IT); ++i) {
+        for (int i = 0; i < B_IT; ++i) {
             const int idx = t + i * NT;
             const int row = idx / CH, c = idx % CH;
             if (AF16) {   // bf16 -> half once per element per workgroup (exact in half's normal range)
@@ -284,48 +151,6 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_bf16(const bf16_t* __rest
 
     const int fr = lane & 15, fq = lane >> 4;
     auto compute = [&](int buf) {
-        if constexpr (ADMA) {
-            // The fragment reads and their waits are written out by hand.  If the compiler saw LDS
-            // reads here it would first wait for the global -> LDS loads of the NEXT tile issued just
-            // above (it cannot tell the two buffers apart), and the prefetch would overlap nothing.
-            // As it is, those loads are waited for where the loop needs them: by the weight tile's
-            // LDS stores and by the fence of the barrier at the end of the step.
-            static_assert(!ADMA || (FM == 4 && FN == 8 && TK == 64), "hand-placed reads are for the 64 x 128 wave tile");
-            typedef typename Mfma<AF16>::frag frag;
-            const uint32_t xr = (fr >> 1) & 7;       // row part of the swizzle: row bases are multiples of 16
-            const uint32_t pa0 = (uint32_t)(size_t)(lds_ptr_t)&sA[buf][0] + (wm * (TM / WM) + fr) * (TK * 2);
-            const uint32_t pb0 = (uint32_t)(size_t)(lds_ptr_t)&sB[buf][0] + (wn * (TN / WN) + fr) * (TK * 2);
-#define RLHF_DS_READ(dst, addr, off) asm volatile("ds_read_b128 %0, %1 offset:" #off : "=v"(dst) : "v"(addr) : "memory")
-#define RLHF_LGKM0(...) asm volatile("s_waitcnt lgkmcnt(0)" : __VA_ARGS__ : : "memory")
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                frag fa[4], fb[8];
-                const uint32_t co = ((uint32_t)(s * 4 + fq) ^ xr) * 16;
-                const uint32_t pa = pa0 + co, pb = pb0 + co;
-                RLHF_DS_READ(fa[0], pa, 0); RLHF_DS_READ(fa[1], pa, 2048);
-                RLHF_DS_READ(fa[2], pa, 4096); RLHF_DS_READ(fa[3], pa, 6144);
-                RLHF_DS_READ(fb[0], pb, 0); RLHF_DS_READ(fb[1], pb, 2048);
-                RLHF_DS_READ(fb[2], pb, 4096); RLHF_DS_READ(fb[3], pb, 6144);
-                RLHF_LGKM0("+v"(fa[0]), "+v"(fa[1]), "+v"(fa[2]), "+v"(fa[3]), "+v"(fb[0]), "+v"(fb[1]), "+v"(fb[2]),
-                           "+v"(fb[3]));
-                RLHF_DS_READ(fb[4], pb, 8192); RLHF_DS_READ(fb[5], pb, 10240);
-                RLHF_DS_READ(fb[6], pb, 12288); RLHF_DS_READ(fb[7], pb, 14336);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = Mfma<AF16>::run(fb[j], fa[i], acc[i][j]);
-                __builtin_amdgcn_sched_barrier(0);
-                RLHF_LGKM0("+v"(fb[4]), "+v"(fb[5]), "+v"(fb[6]), "+v"(fb[7]));
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 4; j < 8; ++j) acc[i][j] = Mfma<AF16>::run(fb[j], fa[i], acc[i][j]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#undef RLHF_DS_READ
-#undef RLHF_LGKM0
-            return;
-        }
 #pragma unroll
         for (int s = 0; s < TK / 32; ++s) {
             typename Mfma<AF16>::frag fa[FM], fb[FN];
@@ -349,41 +174,17 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_bf16(const bf16_t* __rest
                     acc[i][j] = Mfma<AF16>::run(fb[j], fa[i], acc[i][j]);
         }
     };
-    if constexpr (RING > 1) {
-        static_assert(RING == 1 || (!ADMA && !BDMA && RING % 2 == 0), "the register ring holds register-staged tiles");
-        // ring slot j holds tile kt with kt % RING == j; the slot of the tile that has just gone to LDS
-        // is refilled with the tile RING steps ahead (the waits for a slot's loads follow from its use)
-        uint4 qa[RING][A_IT], qb[RING][B_IT];
-#pragma unroll
-        for (int j = 0; j < RING; ++j)
-            if (j < nk) gload(j, qa[j], qb[j]);
-        if (nk > 0) sstore(0, qa[0], qb[0]);
+    if (nk > 0) {
+        gload(0);
+        sstore(0);
+    }
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+        const int buf = kt & 1;
+        if (kt + 1 < nk) gload(kt + 1);
+        compute(buf);
+        if (kt + 1 < nk) sstore(buf ^ 1);
         __syncthreads();
-        for (int kt0 = 0; kt0 < nk; kt0 += RING) {
-#pragma unroll
-            for (int j = 0; j < RING; ++j) {
-                const int kt = kt0 + j;
-                if (kt < nk) {
-                    gload(kt + RING, qa[j], qb[j]);      // past the range every lane's guard is off: nothing is loaded
-                    compute(j & 1);
-                    if (kt + 1 < nk) sstore((j + 1) & 1, qa[(j + 1) % RING], qb[(j + 1) % RING]);
-                    __syncthreads();
-                }
-            }
-        }
-    } else {
-        if (nk > 0) {
-            gload(0, ra, rb);
-            sstore(0, ra, rb);
-        }
-        __syncthreads();
-        for (int kt = 0; kt < nk; ++kt) {
-            const int buf = kt & 1;
-            if (kt + 1 < nk) gload(kt + 1, ra, rb);
-            compute(buf);
-            if (kt + 1 < nk) sstore(buf ^ 1, ra, rb);
-            __syncthreads();
-        }
     }
 
     if (SWIGLU) {
@@ -426,128 +227,6 @@ __global__ __launch_bounds__(WM * WN * 64) void k_gemm_bf16(const bf16_t* __rest
                 const int oc = (n0 >> 1) + ((wn * (TN / WN) + (odd ? j + 2 : j) * 16) >> 1) + (fq & 2) * 4;
                 if (m >= M || oc >= f) continue;       // f is a multiple of 8: a group of 8 is in or out
                 *reinterpret_cast<uint4*>(act + (size_t)m * f + oc) = pk;
-            }
-        }
-        return;
-    }
-    if constexpr (ROPE > 0) {
-        static_assert(ROPE == 0 || ((TN / WN) % ROPE == 0 && TN % ROPE == 0), "a wave tile holds whole heads");
-        constexpr int HD = ROPE > 0 ? ROPE : 64, HALF = HD / 2, PF = HD / 32;   // PF: fragments between pair halves
-        typedef typename std::conditional<AF16, f16_t, bf16_t>::type TO;
-        TO* q_out = reinterpret_cast<TO*>(ro.q);
-        TO* k_out = reinterpret_cast<TO*>(ro.k);
-        TO* v_out = reinterpret_cast<TO*>(ro.v);
-        TO* pool = reinterpret_cast<TO*>(ro.pool);
-        const int Hq = ro.n_q_heads, Hkv = ro.n_kv_heads;
-        static_assert(ROPE == 0 || FN % 2 == 0, "fragments are stored in pairs");
-#pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            const int m = m0 + wm * (TM / WM) + i * 16 + fr;
-            const bool row_ok = m < M;
-            const int mc = row_ok ? m : M - 1;
-            const float* tab = ro.table + (size_t)ro.pos[mc] * HD;
-            TO* prow = nullptr;                 // this token's K row of head 0 in the pool
-            if (pool) {
-                const int slot = ro.kv_dst[mc];
-                prow = pool + ((size_t)(slot / ro.page_tokens) * ro.n_layers + ro.layer) * 2 * (size_t)Hkv * ro.page_tokens * HD +
-                       (size_t)(slot % ro.page_tokens) * HD;
-            }
-            const size_t head_stride = (size_t)ro.page_tokens * HD;
-            // rotated, rounded and packed fragment j of this row: four consecutive columns in 8 bytes
-            auto packed = [&](int j) {
-                const int c = (wn * (TN / WN) + j * 16 + fq * 4) % HD;
-                const bool rot = n0 + wn * (TN / WN) + j * 16 < (Hq + Hkv) * HD;
-                const bool first = ((j % (2 * PF)) < PF);
-                float o[4];
-                if (rot) {
-                    const int jp = first ? j + PF : j - PF;
-                    const int k = first ? c : c - HALF;
-                    const float4 t0 = *reinterpret_cast<const float4*>(tab + 2 * k);
-                    const float4 t1 = *reinterpret_cast<const float4*>(tab + 2 * k + 4);
-                    const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float a = first ? acc[i][j][e] : acc[i][jp][e];
-                        const float b = first ? acc[i][jp][e] : acc[i][j][e];
-                        o[e] = first ? a * cs[e] - b * sn[e] : a * sn[e] + b * cs[e];
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = acc[i][j][e];
-                }
-                uint2 pk;
-                if (AF16) {
-                    fp16x2_t a = {(__fp16)o[0], (__fp16)o[1]}, b = {(__fp16)o[2], (__fp16)o[3]};
-                    pk.x = *reinterpret_cast<uint32_t*>(&a);
-                    pk.y = *reinterpret_cast<uint32_t*>(&b);
-                } else {
-                    pk.x = (uint32_t)f32_to_bf16(o[0]) | ((uint32_t)f32_to_bf16(o[1]) << 16);
-                    pk.y = (uint32_t)f32_to_bf16(o[2]) | ((uint32_t)f32_to_bf16(o[3]) << 16);
-                }
-                return pk;
-            };
-            // Fragments j and j + 1 cover 32 consecutive columns, four at a time per quarter wave.
-            // Neighbouring quarter waves swap one fragment each, after which a lane holds eight
-            // consecutive columns (16 bytes) and a row's 64 bytes are written by four lanes.
-            const bool odd = fq & 1;
-#pragma unroll
-            for (int j = 0; j < FN; j += 2) {
-                const uint2 p0 = packed(j), p1 = packed(j + 1);
-                const uint2 give = odd ? p0 : p1;
-                uint2 got;
-                got.x = (uint32_t)__shfl_xor((int)give.x, 16, kWave);
-                got.y = (uint32_t)__shfl_xor((int)give.y, 16, kWave);
-                const uint4 pk = odd ? make_uint4(got.x, got.y, p1.x, p1.y) : make_uint4(p0.x, p0.y, got.x, got.y);
-                const int n = n0 + wn * (TN / WN) + (odd ? j + 1 : j) * 16 + (fq & 2) * 4;
-                if (!row_ok || n >= N) continue;     // N is a multiple of head_dim: a group of 8 is in or out
-                const int head = n / HD, c = n - head * HD;
-                if (head < Hq) {
-                    *reinterpret_cast<uint4*>(q_out + ((size_t)m * Hq + head) * HD + c) = pk;
-                } else {
-                    const bool is_k = head < Hq + Hkv;
-                    const int kh = is_k ? head - Hq : head - Hq - Hkv;
-                    TO* dst = is_k ? k_out : v_out;
-                    if (dst) *reinterpret_cast<uint4*>(dst + ((size_t)m * Hkv + kh) * HD + c) = pk;
-                    if (prow)
-                        *reinterpret_cast<uint4*>(prow + (is_k ? 0 : (size_t)Hkv * head_stride) + kh * head_stride + c) = pk;
-                }
-            }
-        }
-        return;
-    }
-    if constexpr (LSE) {
-        const int pcol = tn * WN + wn;                       // this wave's partial of the row
-        const int ncol0 = n0 + wn * (TN / WN) + fq * 4;
-#pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            const int m = m0 + wm * (TM / WM) + i * 16 + fr;
-            const bool row_ok = m < M;
-            int t = -1;
-            if (row_ok) t = min(max(lo.tokens[lo.target_idx[m]], 0), N - 1);
-            float mx = -INFINITY;
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int n = ncol0 + j * 16 + e;
-                    if (n < N) mx = fmaxf(mx, acc[i][j][e]);
-                    if (n == t) lo.tgt[m] = acc[i][j][e];
-                }
-            mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
-            mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-            float se = 0.f;
-            if (mx > -INFINITY) {
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (ncol0 + j * 16 + e < N) se += __expf(acc[i][j][e] - mx);
-            }
-            se += __shfl_xor(se, 16, kWave);
-            se += __shfl_xor(se, 32, kWave);
-            if (row_ok && fq == 0) {
-                lo.part_max[(size_t)m * lo.n_part + pcol] = mx;
-                lo.part_sum[(size_t)m * lo.n_part + pcol] = se;
             }
         }
         return;
@@ -684,12 +363,6 @@ constexpr int kTargetBlocks = 1024;      // about four workgroups per compute un
 
 // True when launch_gemm would run the 256 x 256 tiling for this shape and split (the shapes for
 // which a half copy of the weights, if there is one, is the better operand).
-// The tile a workgroup of a compute-bound launch takes (host copy of the device mapping, for tests).
-int gemm_tall_grid(int tiles_m, int tiles_n) { return xcd_grid(tiles_m, tiles_n); }
-bool gemm_tall_tile(int bid, int tiles_m, int tiles_n, int* tm, int* tn) {
-    return tile_of<true>(bid, tiles_m, tiles_n, *tm, *tn);
-}
-
 bool gemm_is_tall(int M, int N, int K, int nsplit) { return K % 64 == 0 && kCfgs[pick_variant(M, N, K, nsplit)].xcd; }
 
 // bf16 -> IEEE half, element by element (round toward zero; exact in half's normal range, values
@@ -767,12 +440,9 @@ static hipError_t launch_bf16(hipStream_t st, int variant, const bf16_t* a, cons
         }
         case 5: RLHF_GEMM(128, 128, 64, 2, 2, true); break;
         case 6: RLHF_GEMM(256, 128, 32, 2, 2, true); break;
-        case 7:                                                  // eight waves, wave tile 64 x 128
-            if (K % 64 == 0)
-                k_gemm_bf16<256, 256, 64, 4, 2, AF16, true, false, true><<<grid, 512, 0, st>>>(a, w, C, M, N, K, kchunk,
-                                                                                             tiles_m, tiles_n);
-            else
-                RLHF_GEMM(256, 256, 64, 4, 2, true);
+        case 7:                                                  // gemm_tall.hip, unless K leaves a remainder
+            if (K % 64 == 0) return launch_gemm_tall(st, kBF16, AF16 ? kF16 : kBF16, a, w, C, M, N, K, nsplit);
+            RLHF_GEMM(256, 256, 64, 4, 2, true);
             break;
         default: return hipErrorInvalidValue;
     }
@@ -795,82 +465,17 @@ bool gemm_swiglu_supported(int wdt, int adt, int M, int ffn, int K) {
 hipError_t launch_gemm_swiglu(hipStream_t st, int wdt, int adt, const void* A, const void* W_gate_up,
                               void* act, int M, int ffn, int K) {
     if (!gemm_swiglu_supported(wdt, adt, M, ffn, K) || !half_offsets_ok(wdt, M, 2L * ffn, K)) return hipErrorInvalidValue;
+    if (K % 64 == 0) return launch_gemm_tall_swiglu(st, wdt, adt, A, W_gate_up, act, M, ffn, K);
     constexpr int TM = 256, TN = 256;
     const int N = 2 * ffn;
     const int tiles_m = (M + TM - 1) / TM, tiles_n = (N + TN - 1) / TN;
     dim3 grid(xcd_grid(tiles_m, tiles_n), 1);
     const int kchunk = (K + 63) / 64 * 64;
-#define RLHF_SWIGLU(AF, DMA)                                               \
-    k_gemm_bf16<TM, TN, 64, 4, 2, AF, true, true, DMA><<<grid, 512, 0, st>>>( \
+#define RLHF_SWIGLU(AF)                                               \
+    k_gemm_bf16<TM, TN, 64, 4, 2, AF, true, true><<<grid, 512, 0, st>>>( \
         (const bf16_t*)A, (const bf16_t*)W_gate_up, (float*)act, M, N, K, kchunk, tiles_m, tiles_n)
-    const bool dma = K % 64 == 0;
-    if (wdt == kF16)
-        k_gemm_bf16<TM, TN, 64, 4, 2, true, true, true, true, 0, false, true><<<grid, 512, 0, st>>>(
-            (const bf16_t*)A, (const bf16_t*)W_gate_up, (float*)act, M, N, K, kchunk, tiles_m, tiles_n);
-    else if (adt == kF16) { if (dma) RLHF_SWIGLU(true, true); else RLHF_SWIGLU(true, false); }
-    else { if (dma) RLHF_SWIGLU(false, true); else RLHF_SWIGLU(false, false); }
+    if (adt == kF16) RLHF_SWIGLU(true); else RLHF_SWIGLU(false);
 #undef RLHF_SWIGLU
-    return hipGetLastError();
-}
-
-bool gemm_rope_supported(int wdt, int adt, int M, int K, const Dims& dm) {
-    return (wdt == kBF16 || wdt == kF16) && half_weights_ok(wdt, adt, K) && (adt == kF16 || adt == kBF16) && M >= 512 &&
-           K % 64 == 0 && (dm.head_dim == 64 || dm.head_dim == 128);
-}
-
-hipError_t launch_gemm_rope(hipStream_t st, int wdt, int adt, const void* A, const void* Wqkv, int M, int K,
-                            const RopeOut& ro) {
-    Dims dm{};
-    dm.head_dim = ro.head_dim;
-    if (!gemm_rope_supported(wdt, adt, M, K, dm) || !ro.pos || !ro.table || !ro.q || (ro.pool && !ro.kv_dst))
-        return hipErrorInvalidValue;
-    constexpr int TM = 256, TN = 256;
-    const int N = (ro.n_q_heads + 2 * ro.n_kv_heads) * ro.head_dim;
-    if (!half_offsets_ok(wdt, M, N, K)) return hipErrorInvalidValue;
-    const int tiles_m = (M + TM - 1) / TM, tiles_n = (N + TN - 1) / TN;
-    dim3 grid(xcd_grid(tiles_m, tiles_n), 1);
-    const bf16_t* a = (const bf16_t*)A;
-    const bf16_t* w = (const bf16_t*)Wqkv;
-#define RLHF_ROPE(AF, HD)                                                                             \
-    k_gemm_bf16<TM, TN, 64, 4, 2, AF, true, false, true, HD><<<grid, 512, 0, st>>>(a, w, nullptr, M, N, K, K, \
-                                                                                   tiles_m, tiles_n, ro)
-#define RLHF_ROPE_HALF_W(HD)                                                                                    \
-    k_gemm_bf16<TM, TN, 64, 4, 2, true, true, false, true, HD, false, true><<<grid, 512, 0, st>>>(a, w, nullptr, M, N, \
-                                                                                                  K, K, tiles_m, tiles_n, ro)
-    if (wdt == kF16) { if (ro.head_dim == 128) RLHF_ROPE_HALF_W(128); else RLHF_ROPE_HALF_W(64); }
-    else if (adt == kF16) { if (ro.head_dim == 128) RLHF_ROPE(true, 128); else RLHF_ROPE(true, 64); }
-    else { if (ro.head_dim == 128) RLHF_ROPE(false, 128); else RLHF_ROPE(false, 64); }
-#undef RLHF_ROPE
-#undef RLHF_ROPE_HALF_W
-    return hipGetLastError();
-}
-
-bool gemm_lse_supported(int wdt, int adt, int K) {
-    return (wdt == kBF16 || wdt == kF16) && half_weights_ok(wdt, adt, K) && (adt == kF16 || adt == kBF16) && K % 64 == 0;
-}
-
-int gemm_lse_partials(int N) { return (N + 255) / 256 * 2; }
-
-hipError_t launch_gemm_lse(hipStream_t st, int wdt, int adt, const void* A, const void* W_head, int M, int N, int K,
-                           const LseOut& lo) {
-    if (M <= 0) return hipSuccess;
-    if (!gemm_lse_supported(wdt, adt, K) || N <= 0 || !lo.tokens || !lo.target_idx || !lo.part_max || !lo.part_sum ||
-        !lo.tgt || lo.n_part != gemm_lse_partials(N) || !half_offsets_ok(wdt, M, N, K))
-        return hipErrorInvalidValue;
-    constexpr int TM = 256, TN = 256;
-    const int tiles_m = (M + TM - 1) / TM, tiles_n = (N + TN - 1) / TN;
-    dim3 grid(xcd_grid(tiles_m, tiles_n), 1);
-    const bf16_t* a = (const bf16_t*)A;
-    const bf16_t* w = (const bf16_t*)W_head;
-    if (wdt == kF16)
-        k_gemm_bf16<TM, TN, 64, 4, 2, true, true, false, true, 0, true, true><<<grid, 512, 0, st>>>(
-            a, w, nullptr, M, N, K, K, tiles_m, tiles_n, RopeOut{}, lo);
-    else if (adt == kF16)
-        k_gemm_bf16<TM, TN, 64, 4, 2, true, true, false, true, 0, true><<<grid, 512, 0, st>>>(
-            a, w, nullptr, M, N, K, K, tiles_m, tiles_n, RopeOut{}, lo);
-    else
-        k_gemm_bf16<TM, TN, 64, 4, 2, false, true, false, true, 0, true><<<grid, 512, 0, st>>>(
-            a, w, nullptr, M, N, K, K, tiles_m, tiles_n, RopeOut{}, lo);
     return hipGetLastError();
 }
 
@@ -882,13 +487,7 @@ hipError_t launch_gemm(hipStream_t st, int wdt, int adt, const void* A, const vo
         // half copy of a bf16 matrix: the tall tiling with both operands global -> LDS directly
         if (adt != kF16 || K % 64 || (variant != 0 && variant != 7) || !half_offsets_ok(wdt, M, N, K))
             return hipErrorInvalidValue;
-        const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256;
-        const int kchunk = ((K + nsplit - 1) / nsplit + 63) / 64 * 64;
-        if ((long)(nsplit - 1) * kchunk >= K) return hipErrorInvalidValue;
-        dim3 grid(xcd_grid(tiles_m, tiles_n), nsplit);
-        k_gemm_bf16<256, 256, 64, 4, 2, true, true, false, true, 0, false, true><<<grid, 512, 0, st>>>(
-            (const bf16_t*)A, (const bf16_t*)W, C, M, N, K, kchunk, tiles_m, tiles_n);
-        return hipGetLastError();
+        return launch_gemm_tall(st, wdt, adt, A, W, C, M, N, K, nsplit);
     }
     if (wdt == kBF16) {
         if (adt != kBF16 && adt != kF16) return hipErrorInvalidValue;

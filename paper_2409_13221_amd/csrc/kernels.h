@@ -43,6 +43,13 @@ hipError_t launch_bf16_to_half(hipStream_t st, const void* src, void* dst, size_
 hipError_t launch_gemm(hipStream_t st, int wdt, int adt, const void* A, const void* W, float* C,
                        int M, int N, int K, int nsplit, int variant = 0);
 
+// The compute-bound kernel behind them (gemm_tall.hip), K a multiple of 64.
+bool gemm_tall_supported(int wdt, int adt, int K);
+hipError_t launch_gemm_tall(hipStream_t st, int wdt, int adt, const void* A, const void* W, float* C, int M, int N, int K,
+                            int nsplit);
+hipError_t launch_gemm_tall_swiglu(hipStream_t st, int wdt, int adt, const void* A, const void* W, void* act, int M, int ffn,
+                                   int K);
+
 // Gate||up projection with SwiGLU fused into the epilogue (tall passes of bf16 models):
 // act[m][c] = silu(<A[m], W[c]>) * <A[m], W[ffn + c]>, written as adt [M, ffn].
 bool gemm_swiglu_supported(int wdt, int adt, int M, int ffn, int K);
