@@ -175,7 +175,9 @@ static hipError_t rmsnorm_launch(hipStream_t st, float* h, const float* part, in
         case 2: RLHF_RMS(2); break;
         case 3: RLHF_RMS(3); break;
         case 4: RLHF_RMS(4); break;
+        case 5: RLHF_RMS(5); break;
         case 6: RLHF_RMS(6); break;
+        case 7: RLHF_RMS(7); break;
         case 8: RLHF_RMS(8); break;
         case 16: RLHF_RMS(16); break;
         default: RLHF_RMS(-1); break;

@@ -500,7 +500,9 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
                               [&] { return launch_gemm_rope(st, hw ? kF16 : dt, adt, ws.xn, wq, rows, d, ro); }));
         } else {
             ns = nsplit_for(c, ws, rows, qkv_w, d);
-            HIPCK(c, gemm_profiled(c, st, gcls, adt, ws.xn, layer_ptr(w.wqkv, l, qkv_w, d, es), ws.part, rows, qkv_w, d, ns));
+            const bool hw = wh.wqkv && adt == kF16 && gemm_is_tall(rows, qkv_w, d, ns);
+            HIPCK(c, gemm_profiled(c, st, gcls, adt, ws.xn, layer_ptr(hw ? wh.wqkv : w.wqkv, l, qkv_w, d, es), ws.part, rows,
+                                   qkv_w, d, ns, hw));
             HIPCK(c, launch_rope_kv(st, qdt, adt, ws.part, ns, (size_t)rows * qkv_w, pm.pos, pm.kv_dst, c->d_rope,
                                     ws.q, mode == kModeBatch ? ws.k : nullptr,
                                     mode == kModeBatch ? ws.v : nullptr, pm.kv_dst ? c->pool : nullptr, l,
@@ -523,7 +525,7 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         }
         ns = nsplit_for(c, ws, rows, d, qd);
         {
-            const bool hw = wh.wo && adt == kF16 && mode == kModeBatch && gemm_is_tall(rows, d, qd, ns);
+            const bool hw = wh.wo && adt == kF16 && gemm_is_tall(rows, d, qd, ns);
             HIPCK(c, gemm_profiled(c, st, gcls, adt, ws.attn, layer_ptr(hw ? wh.wo : w.wo, l, d, qd, es), ws.part, rows,
                                    d, qd, ns, hw));
         }
@@ -537,14 +539,15 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
                               [&] { return launch_gemm_swiglu(st, hw ? kF16 : dt, adt, ws.xn, wgu, ws.act, rows, f, d); }));
         } else {
             ns = nsplit_for(c, ws, rows, 2 * f, d);
-            HIPCK(c, gemm_profiled(c, st, gcls, adt, ws.xn, layer_ptr(w.w_gate_up, l, 2 * (size_t)f, d, es), ws.part,
-                                   rows, 2 * f, d, ns));
+            const bool hw = wh.w_gate_up && adt == kF16 && gemm_is_tall(rows, 2 * f, d, ns);
+            HIPCK(c, gemm_profiled(c, st, gcls, adt, ws.xn, layer_ptr(hw ? wh.w_gate_up : w.w_gate_up, l, 2 * (size_t)f, d, es),
+                                   ws.part, rows, 2 * f, d, ns, hw));
             HIPCK(c, launch_swiglu(st, adt, ws.part, ns, (size_t)rows * 2 * f, ws.act, rows, f));
         }
         pns = nsplit_for(c, ws, rows, d, f);
         pstride = (size_t)rows * d;
         {
-            const bool hw = wh.w_down && adt == kF16 && mode == kModeBatch && gemm_is_tall(rows, d, f, pns);
+            const bool hw = wh.w_down && adt == kF16 && gemm_is_tall(rows, d, f, pns);
             HIPCK(c, gemm_profiled(c, st, gcls, adt, ws.act, layer_ptr(hw ? wh.w_down : w.w_down, l, d, f, es), ws.part,
                                    rows, d, f, pns, hw));
         }

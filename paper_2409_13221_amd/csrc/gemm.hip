@@ -324,24 +324,40 @@ constexpr TileCfg kCfgs[] = {
 };
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 
-// Few rows: the smallest row tile that holds them, weights streamed once, K split.  Many rows:
-// the 256 x 256 tiling, unless its tiles would leave much of the chip idle (a prefill of a few
-// hundred tokens, a narrow N): then 128 x 128 tiles with K split, which trades some efficiency
-// per workgroup for having all compute units busy.
-// 129..256 rows of a large matrix: one row of 256 x 256 tiles, K split so that the tiles times the
-// splits come close to, and never exceed, one workgroup per compute unit (a second round of such
-// workgroups costs more than it adds: at M = 256 the 7B-shape QKV takes 42.8 us with 4 splits = 192
-// workgroups, 60 us with 6 = 288; gate||up 71 us with 2 = 172, 96 us with 3 = 258; against 54 and
-// 97 us for 128 x 128 tiles).  Returns 0 when the tall tiling is not the better one.
-int tall_split_for_mid_rows(int M, int N, int K, int max_split) {
-    if (M <= 128 || M > 256 || K % 64 || (long)N * K < 40L * 1000 * 1000) return 0;
-    const int tiles = (N + 255) / 256;
-    int ns = 256 / tiles;
-    if (ns > K / 256) ns = K / 256;          // at least four K tiles per split
-    if (ns > 16) ns = 16;
-    if (ns > max_split) ns = max_split;
-    if (ns < 1 || tiles * ns < 160) return 0;
-    while (ns > 1) {                          // every split gets a K range
+// Few rows: the smallest row tile that holds them, weights streamed once, K split.  Many rows: the tall
+// kernel.  In between, and for narrow matrices, 128 x 128 tiles with K split.
+// K split of the tall kernel (gemm_tall.hip), 0 where another tiling is the better one.
+// 129..256 rows of a large matrix: one row of tiles, K split so that the tiles times the splits come
+// close to, and never exceed, one workgroup per compute unit (a second round costs more than it adds:
+// 7B QKV at 256 rows 36 us with 4 splits, 62 with 6), eight at most (down 41 us with 8, 37 with 12 and
+// 47 with 16, but every plane costs its reader 1 us).
+// More rows, N >= 1536: a workgroup takes about 1.15 us per K tile and 4 us besides, one per compute
+// unit at a time, and a plane is written and read once at about 5 TB/s; the split with the least sum.
+// N = 4096: 320 rows 27 us with 8 splits (128 x 128 tiles: 32), 1024 rows 47 with 2 (65), 2048 rows 58 with
+// 2 (77 unsplit), 4160 rows 156 unsplit, though its second round is nearly empty (128 x 128 tiles: 270).
+// Narrower matrices have too few tiles of this size (N = 768, 2048 rows: 29 us against 20).
+int tall_nsplit(int M, int N, int K, int max_split) {
+    if (K % 64 || M <= 128) return 0;
+    const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
+    const int steps = K / 64;
+    int ns = 1;
+    if (M <= 256) {
+        if ((long)N * K < 40L * 1000 * 1000) return 0;
+        ns = (int)(256 / tiles);
+        if (ns > steps / 4) ns = steps / 4;      // at least four K tiles per split
+        if (ns > 8) ns = 8;
+        if (ns > max_split) ns = max_split;
+        if (ns < 1 || tiles * ns < 120) return 0;
+    } else {
+        if (N < 1536) return 0;
+        double best = 0;
+        for (int c = 1; c <= 8 && c <= max_split && c <= (steps + 3) / 4; ++c) {
+            const double rounds = (double)((tiles * c + 255) / 256);
+            const double us = rounds * (((steps + c - 1) / c) * 1.15 + 4.0) + 8.0 * M * N * c / 5e6;
+            if (c == 1 || us < best) { best = us; ns = c; }
+        }
+    }
+    while (ns > 1) {                             // every split gets a K range
         const int kchunk = ((K + ns - 1) / ns + 63) / 64 * 64;
         if ((long)(ns - 1) * kchunk < K) break;
         --ns;
@@ -349,11 +365,12 @@ int tall_split_for_mid_rows(int M, int N, int K, int max_split) {
     return ns;
 }
 
-int pick_variant(int M, int N, int K = 0, int nsplit = 0) {
+int pick_variant(int M, int N, int K, int nsplit = 0) {
     if (M <= 16) return 1;
     if (M <= 32) return 2;
     if (M <= 64) return 3;
-    if (M <= 256) return (K > 0 && nsplit > 0 && tall_split_for_mid_rows(M, N, K, nsplit) == nsplit) ? 7 : 4;
+    if (M <= 256) return nsplit > 0 && tall_nsplit(M, N, K, nsplit) == nsplit ? 7 : 4;
+    if (K % 64 == 0) return N >= 1536 ? 7 : 4;
     const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
     const long rounds = (tiles + 255) / 256;            // one 256 x 256 tile per compute unit at a time
     return tiles * 10 >= rounds * 256 * 6 ? 7 : 4;      // at least 60 % of the tile slots filled
@@ -381,9 +398,9 @@ hipError_t launch_bf16_to_half(hipStream_t st, const void* src, void* dst, size_
 int gemm_choose_nsplit(int wdt, int M, int N, int K, int max_split) {
     int tm, tn, kgran;
     if (wdt == kBF16) {
-        const int tall = tall_split_for_mid_rows(M, N, K, max_split);
+        const int tall = tall_nsplit(M, N, K, max_split);
         if (tall > 0) return tall;
-        const TileCfg& c = kCfgs[pick_variant(M, N)];
+        const TileCfg& c = kCfgs[pick_variant(M, N, K)];
         if (c.xcd) return 1;
         tm = c.tm; tn = c.tn; kgran = c.tk;
     } else { tm = 64; tn = 64; kgran = 16; }
@@ -458,7 +475,7 @@ static bool half_offsets_ok(int wdt, long M, long N, long K) {
 }
 
 bool gemm_swiglu_supported(int wdt, int adt, int M, int ffn, int K) {
-    return (wdt == kBF16 || wdt == kF16) && half_weights_ok(wdt, adt, K) && (adt == kF16 || adt == kBF16) && M >= 512 &&
+    return (wdt == kBF16 || wdt == kF16) && half_weights_ok(wdt, adt, K) && (adt == kF16 || adt == kBF16) && M > 256 &&
            ffn % 8 == 0 && K % 8 == 0;
 }
 
@@ -494,7 +511,7 @@ hipError_t launch_gemm(hipStream_t st, int wdt, int adt, const void* A, const vo
         if (K % 8 || variant < 0 || variant >= kNumCfgs) return hipErrorInvalidValue;
         if (variant == 0) {
             variant = pick_variant(M, N, K, nsplit);
-            if (kCfgs[variant].xcd && nsplit != 1 && M > 256) variant = 4;   // a caller-imposed split of a tall GEMM
+            if (kCfgs[variant].xcd && nsplit != 1 && K % 64) variant = 4;   // only the kernel for whole K tiles splits
         }
         const bf16_t* a = (const bf16_t*)A;
         const bf16_t* w = (const bf16_t*)W;

@@ -391,7 +391,8 @@ static StreamShape stream_shape(int M, int N, bool planes) {
     if (M <= 16) return N >= 19200 ? StreamShape{1, 2, 4} : StreamShape{1, 1, 4};
     const int mb = M <= 32 ? 2 : 4;
     if (N < 4096) return {mb, 1, 4};                       // small matrices: workgroups before traffic
-    if (planes) return mb == 2 ? StreamShape{2, 2, 4} : StreamShape{4, 4, 2};
+    if (planes && N < 48 * 240) return mb == 2 ? StreamShape{2, 2, 4} : StreamShape{4, 4, 2};
+    if (mb == 2 && N < 48 * 240) return {2, 2, 4};
     return {mb, 3, 2};
 }
 int gemm_stream_nsplit(int M, int N, int K, int max_split) {
@@ -422,7 +423,7 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
         return hipErrorInvalidValue;
     const bf16_t* a = (const bf16_t*)A;
     const bf16_t* w = (const bf16_t*)W;
-    const StreamShape sh = mode == 3 ? StreamShape{1, 1, 4} : stream_shape(M, N, nsplit > 1);
+    const StreamShape sh = mode == 3 ? StreamShape{1, 1, 4} : stream_shape(M, N, mode == 0);
     const int blocks = (N + 16 * sh.nb - 1) / (16 * sh.nb);
     if (adt == kBF16) return stream_launch<1, 1, 4, 4, false>(st, mode, (N + 15) / 16, nsplit, a, w, C, M, N, K, ep);
 #define RLHF_STREAM(MB, NB, D)              \

@@ -493,7 +493,7 @@ static bool half_offsets_ok(int wdt, long M, long N, long K) {
 }
 
 bool gemm_rope_supported(int wdt, int adt, int M, int K, const Dims& dm) {
-    return (wdt == kBF16 || wdt == kF16) && half_weights_ok(wdt, adt, K) && (adt == kF16 || adt == kBF16) && M >= 512 &&
+    return (wdt == kBF16 || wdt == kF16) && half_weights_ok(wdt, adt, K) && (adt == kF16 || adt == kBF16) && M > 256 &&
            K % 64 == 0 && (dm.head_dim == 64 || dm.head_dim == 128);
 }
 

@@ -147,7 +147,7 @@ extern "C" int rlhf_op_gemm_swiglu(int act_half, const void* A, const void* W_ga
         ep.ffn = ffn;
         return status_of(launch_gemm_stream((hipStream_t)stream, wdt, adt, 1, A, W_gate_up, nullptr, M, 2 * ffn, K, ep));
     }
-    if (!gemm_swiglu_supported(wdt, adt, M, ffn, K)) return RLHF_EINVAL;
+    if (M < 512 || !gemm_swiglu_supported(wdt, adt, M, ffn, K)) return RLHF_EINVAL;
     return status_of(launch_gemm_swiglu((hipStream_t)stream, wdt, adt, A, W_gate_up, act, M, ffn, K));
 }
 
@@ -172,7 +172,7 @@ extern "C" int rlhf_op_gemm_rope(int act_half, const void* A, const void* W_qkv,
         return status_of(launch_gemm_stream((hipStream_t)stream, wdt, adt, 2, A, W_qkv, nullptr, M,
                                             (n_q_heads + 2 * n_kv_heads) * head_dim, K, ep));
     }
-    if (!gemm_rope_supported(wdt, adt, M, K, dm)) return RLHF_EINVAL;
+    if (M < 512 || !gemm_rope_supported(wdt, adt, M, K, dm)) return RLHF_EINVAL;
     return status_of(launch_gemm_rope((hipStream_t)stream, wdt, adt, A, W_qkv, M, K, ro));
 }
 
