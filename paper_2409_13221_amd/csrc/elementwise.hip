@@ -579,58 +579,106 @@ hipError_t launch_noop(hipStream_t st) {
     return hipGetLastError();
 }
 
+// ------------------------------------------------- results on their way to the host
+// Ragged rows of the stage's result buffers, packed back to back into pinned host memory: one kernel and
+// one wait instead of a copy of the whole padded buffer per array (8 samples: 5 copies of about 12 us each).
+__global__ __launch_bounds__(256) void k_pack_results(PackArgs a) {
+    const int i = blockIdx.x, k = blockIdx.y;
+    if (i == a.n) {                                        // the scalars: rewards, the non-finite flag
+        if (k > 0) return;
+        for (int j = threadIdx.x; j < a.n_reward; j += 256) a.scalars[j] = a.reward[j];
+        if (threadIdx.x == 0) a.scalars[a.n_reward] = (uint32_t)*a.flag;
+        return;
+    }
+    const PackRow r = a.rows[i];
+    const uint32_t* src = a.src[k] + (size_t)r.row * a.stride + (a.after_prompt[k] ? r.prompt : 0);
+    uint32_t* dst = a.out + (size_t)k * a.total + r.offset;
+    for (int t = threadIdx.x; t < r.len; t += 256) dst[t] = src[t];
+}
+
+hipError_t launch_pack_results(hipStream_t st, const PackArgs& a) {
+    if (a.n_arrays <= 0 && !a.scalars) return hipSuccess;
+    k_pack_results<<<dim3(a.n + (a.scalars ? 1 : 0), a.n_arrays > 0 ? a.n_arrays : 1), 256, 0, st>>>(a);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------- Generalized Advantage Estimation
-// The recursion A_t = delta_t + gamma*lam*A_{t+1} unrolled along the output length: with
-// delta as a zero-padded matrix D [n, Lp] and U[t][s] = (gamma*lam)^(s-t) for s >= t (else 0),
-// A = D U^T is one matrix multiply.  These kernels build D and U and finish the returns.
+// The recursion A_t = delta_t + gamma*lam*A_{t+1}, unrolled: A_t = sum over s >= t of (gamma*lam)^(s-t) delta_s,
 //   delta_t = r_t + gamma*V_{t+1} - V_t,  V_{L+1} = 0,
 //   r_t = -kl_coef*(lp_actor_t - lp_ref_t) + [t == L] * reward
-// Inputs are the stage's result buffers, row stride `stride`, entry j-1 of row i for token j.
-__global__ void k_gae_delta(const float* __restrict__ lp_actor, const float* __restrict__ lp_ref,
-                            const float* __restrict__ values, const float* __restrict__ reward,
-                            const int* __restrict__ gen_len, int stride, float gamma, float kl_coef,
-                            float* __restrict__ D, int Lp) {
-    const int i = blockIdx.x, L = gen_len[i];
-    for (int t = threadIdx.x; t < Lp; t += blockDim.x) {
-        float d = 0.f;
-        if (t < L) {
-            const size_t o = (size_t)i * stride + t;
-            float r = -kl_coef * (lp_actor[o] - lp_ref[o]);
-            if (t == L - 1) r += reward[i];
-            const float vnext = t + 1 < L ? values[o + 1] : 0.f;
-            d = r + gamma * vnext - values[o];
+// As a matrix product (D times the triangular matrix of the powers) this is 2 n L^2 flops and an L x L matrix
+// for L outputs of 2 flops each; a workgroup per sample evaluates the same sums as a suffix scan instead,
+// in tiles of 2048 tokens from the end: a thread sums 8 tokens, six lane exchanges weighted by
+// (gamma*lam)^(8 * 2^k) cover a wave, LDS the four waves and the carry between tiles.  What is left is
+// latency: 256 samples with up to 2048 tokens take about 25 us, most of it stores to host memory.
+constexpr int kGaeE = 8, kGaeTile = 256 * kGaeE;
+
+__global__ __launch_bounds__(256) void k_gae(const float* __restrict__ lp_actor, const float* __restrict__ lp_ref,
+                                             const float* __restrict__ values, const float* __restrict__ reward,
+                                             const PackRow* __restrict__ rows, int stride, float gamma, float kl_coef,
+                                             GaePowers pw, float* __restrict__ adv, float* __restrict__ ret) {
+    // token i of a tile sits at i + i / 32: the 8-token stride of the scan then spreads over the banks
+    __shared__ float sd[kGaeTile + kGaeTile / 32], sv[kGaeTile + kGaeTile / 32];
+    __shared__ float s_tot[4], s_carry;
+    const PackRow r = rows[blockIdx.x];
+    const int L = r.len, t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const size_t base = (size_t)r.row * stride;
+    auto at = [](int i) { return i + (i >> 5); };
+    if (t == 0) s_carry = 0.f;
+    for (int tile = (L - 1) / kGaeTile; tile >= 0; --tile) {
+        const int t0 = tile * kGaeTile;
+#pragma unroll
+        for (int e = 0; e < kGaeE; ++e) {
+            const int i = e * 256 + t, k = t0 + i;
+            float d = 0.f, v = 0.f;
+            if (k < L) {
+                v = values[base + k];
+                d = -kl_coef * (lp_actor[base + k] - lp_ref[base + k]);
+                if (k == L - 1) d += reward[r.row];
+                else d += gamma * values[base + k + 1];
+                d -= v;
+            }
+            sd[at(i)] = d;
+            sv[at(i)] = v;
         }
-        D[(size_t)i * Lp + t] = d;
+        __syncthreads();
+        float a = 0.f;
+#pragma unroll
+        for (int e = kGaeE - 1; e >= 0; --e) a = sd[at(t * kGaeE + e)] + pw.gl * a;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {                      // suffix sums over the wave's lanes
+            const float x = __shfl_down(a, 1 << k, kWave);
+            if (lane + (1 << k) < 64) a += pw.lanes[1 << k] * x;
+        }
+        if (lane == 0) s_tot[w] = a;
+        __syncthreads();
+        float c = s_carry;                                 // the advantage right after this wave's tokens
+        for (int x = 3; x > w; --x) c = s_tot[x] + pw.lanes[64] * c;
+        float x = __shfl_down(a, 1, kWave);
+        if (lane == 63) x = 0.f;
+        a = x + pw.lanes[63 - lane] * c;
+        float o[kGaeE];
+#pragma unroll
+        for (int e = kGaeE - 1; e >= 0; --e) { a = sd[at(t * kGaeE + e)] + pw.gl * a; o[e] = a; }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kGaeE; ++e) sd[at(t * kGaeE + e)] = o[e];
+        if (t == 0) s_carry = o[0];
+        __syncthreads();
+        for (int i = t; i < kGaeTile && t0 + i < L; i += 256) {
+            const float x = sd[at(i)];
+            if (adv) adv[r.offset + t0 + i] = x;
+            if (ret) ret[r.offset + t0 + i] = x + sv[at(i)];
+        }
+        __syncthreads();
     }
 }
 
-__global__ void k_gae_matrix(float* __restrict__ U, int Lp, double gl) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x, t = blockIdx.y;
-    if (s < Lp) U[(size_t)t * Lp + s] = s >= t ? (float)pow(gl, (double)(s - t)) : 0.f;
-}
-
-__global__ void k_gae_returns(const float* __restrict__ A, const float* __restrict__ values,
-                              const int* __restrict__ gen_len, int stride, float* __restrict__ R, int Lp) {
-    const int i = blockIdx.x, L = gen_len[i];
-    for (int t = threadIdx.x; t < Lp; t += blockDim.x)
-        R[(size_t)i * Lp + t] = t < L ? A[(size_t)i * Lp + t] + values[(size_t)i * stride + t] : 0.f;
-}
-
-hipError_t launch_gae_delta(hipStream_t st, const float* lp_actor, const float* lp_ref, const float* values,
-                            const float* reward, const int* gen_len, int stride, float gamma, float kl_coef,
-                            float* D, int n, int Lp) {
+hipError_t launch_gae(hipStream_t st, const float* lp_actor, const float* lp_ref, const float* values,
+                      const float* reward, const PackRow* rows, int n, int stride, float gamma, float kl_coef,
+                      const GaePowers& pw, float* adv, float* ret) {
     if (n <= 0) return hipSuccess;
-    k_gae_delta<<<n, 256, 0, st>>>(lp_actor, lp_ref, values, reward, gen_len, stride, gamma, kl_coef, D, Lp);
-    return hipGetLastError();
-}
-hipError_t launch_gae_matrix(hipStream_t st, float* U, int Lp, double gamma_lam) {
-    k_gae_matrix<<<dim3((Lp + 255) / 256, Lp), 256, 0, st>>>(U, Lp, gamma_lam);
-    return hipGetLastError();
-}
-hipError_t launch_gae_returns(hipStream_t st, const float* A, const float* values, const int* gen_len,
-                              int stride, float* R, int n, int Lp) {
-    if (n <= 0) return hipSuccess;
-    k_gae_returns<<<n, 256, 0, st>>>(A, values, gen_len, stride, R, Lp);
+    k_gae<<<n, 256, 0, st>>>(lp_actor, lp_ref, values, reward, rows, stride, gamma, kl_coef, pw, adv, ret);
     return hipGetLastError();
 }
 

@@ -167,6 +167,8 @@ struct rlhf_ctx {
     int* d_nonfinite = nullptr;    // set by the kernels that write results when one is not finite
     int* d_picked = nullptr;       // [max_active] tokens of the last pick (stop_on_eos)
     int* h_picked = nullptr;       // pinned
+    uint32_t* h_stage = nullptr;   // pinned: results on their way to the caller's arrays
+    size_t stage_words = 0;
 
     Workspace ws_dec, ws_pre, ws_score;
     MetaRing meta_dec, meta_pre, meta_score;
@@ -586,6 +588,7 @@ extern "C" void rlhf_destroy(rlhf_ctx* c) {
     for (void* p : bufs)
         if (p) (void)hipFree(p);
     if (c->h_picked) (void)hipHostFree(c->h_picked);
+    if (c->h_stage) (void)hipHostFree(c->h_stage);
     hipEvent_t evs[] = {c->ev_dep, c->ev_d0, c->ev_d1, c->ev_s0, c->ev_s1, c->ev_sw_d, c->ev_sw_s, c->ev_score_last};
     for (hipEvent_t e : evs)
         if (e) (void)hipEventDestroy(e);
@@ -677,6 +680,9 @@ static int create_impl(rlhf_ctx* c) {
     HIPCK(c, hipMalloc((void**)&c->d_nonfinite, sizeof(int)));
     HIPCK(c, hipMemset(c->d_nonfinite, 0, sizeof(int)));
     HIPCK(c, hipHostMalloc((void**)&c->h_picked, (size_t)e.max_active * sizeof(int), hipHostMallocDefault));
+    // one sample's five result arrays at least, normally a whole stage's
+    c->stage_words = std::max<size_t>((size_t)1 << 20, 5 * mc + ns + 64);
+    HIPCK(c, hipHostMalloc((void**)&c->h_stage, c->stage_words * 4, hipHostMallocDefault));
     HIPCK(c, hipMemset(c->d_page_table, 0, ns * c->max_pages * sizeof(int)));
 
     {   // rotary table in double, stored as float (cos, sin) per (position, pair)
@@ -1653,6 +1659,25 @@ extern "C" int rlhf_run_stage(rlhf_ctx* c, const rlhf_stage_opts* opts, rlhf_sta
 
 // ======================================================================== results / snapshot
 
+namespace {
+// Rows of the samples i0 .. *i1 - 1 at the head of the staging area: as many as leave room for n_arrays
+// packed arrays and n_scalars words behind them (one sample always fits).  *words: packed entries.
+void stage_rows(rlhf_ctx* c, int i0, int n_arrays, size_t n_scalars, int* i1, int64_t* words) {
+    PackRow* rows = (PackRow*)c->h_stage;
+    int i = i0;
+    int64_t w = 0;
+    for (; i < c->N; ++i) {
+        const Sample& s = c->smp[i];
+        const size_t need = 4 * (size_t)(i - i0 + 1) + n_scalars + (size_t)n_arrays * (w + s.gen_len);
+        if (i > i0 && need > c->stage_words) break;
+        rows[i - i0] = PackRow{i, s.P, s.gen_len, (int)w};
+        w += s.gen_len;
+    }
+    *i1 = i;
+    *words = w;
+}
+}  // namespace
+
 extern "C" int rlhf_get_results(rlhf_ctx* c, rlhf_results* out) {
     if (!c) return RLHF_EINVAL;
     if (!out) return c->fail(RLHF_EINVAL, "rlhf_get_results: NULL");
@@ -1670,38 +1695,52 @@ extern "C" int rlhf_get_results(rlhf_ctx* c, rlhf_results* out) {
         out->resp_offsets[0] = 0;
         for (int i = 0; i < n; ++i) out->resp_offsets[i + 1] = out->resp_offsets[i] + c->smp[i].gen_len;
     }
-    std::vector<float> buf;
-    auto fetch_packed = [&](const float* dsrc, float* dst) -> int {
-        if (!dst || n == 0) return RLHF_OK;
-        buf.resize((size_t)n * mc);
-        HIPCK(c, hipMemcpy(buf.data(), dsrc, buf.size() * 4, hipMemcpyDeviceToHost));
-        int64_t o = 0;
-        for (int i = 0; i < n; ++i) {
-            std::copy(buf.begin() + (size_t)i * mc, buf.begin() + (size_t)i * mc + c->smp[i].gen_len, dst + o);
-            o += c->smp[i].gen_len;
+    // packed on the device into the pinned staging area, as many samples at a time as fit it
+    struct Array { const void* src; void* dst; int after_prompt; };
+    std::vector<Array> arrays;
+    for (const Array& x : {Array{c->d_tokens, out->tokens, 1}, Array{c->d_lp_actor, out->lp_actor, 0},
+                           Array{c->d_lp_rescored, out->lp_actor_rescored, 0}, Array{c->d_lp_ref, out->lp_ref, 0},
+                           Array{c->d_values, out->values, 0}})
+        if (x.dst) arrays.push_back(x);
+    int bad = 0;
+    int64_t done = 0;
+    for (int i0 = 0, first = 1; i0 < n || first; first = 0) {
+        int i1;
+        int64_t words;
+        const size_t n_scalars = first ? (size_t)n + 1 : 0;
+        stage_rows(c, i0, (int)arrays.size(), n_scalars, &i1, &words);
+        PackArgs pa;
+        pa.n_arrays = (int)arrays.size();
+        pa.n = i1 - i0;
+        pa.stride = mc;
+        pa.total = (int)words;
+        pa.rows = (const PackRow*)c->h_stage;
+        uint32_t* body = c->h_stage + 4 * (size_t)(i1 - i0);
+        if (first) {
+            pa.scalars = body;
+            pa.reward = (const uint32_t*)c->d_reward;
+            pa.flag = c->d_nonfinite;
+            pa.n_reward = n;
         }
-        return RLHF_OK;
-    };
-    if ((rc = fetch_packed(c->d_lp_actor, out->lp_actor))) return rc;
-    if ((rc = fetch_packed(c->d_lp_rescored, out->lp_actor_rescored))) return rc;
-    if ((rc = fetch_packed(c->d_lp_ref, out->lp_ref))) return rc;
-    if ((rc = fetch_packed(c->d_values, out->values))) return rc;
-    if (out->tokens && n) {
-        std::vector<int> tb((size_t)n * mc);
-        HIPCK(c, hipMemcpy(tb.data(), c->d_tokens, tb.size() * sizeof(int), hipMemcpyDeviceToHost));
-        int64_t o = 0;
-        for (int i = 0; i < n; ++i) {
-            const Sample& s = c->smp[i];
-            std::copy(tb.begin() + (size_t)i * mc + s.P, tb.begin() + (size_t)i * mc + s.P + s.gen_len, out->tokens + o);
-            o += s.gen_len;
+        pa.out = body + n_scalars;
+        for (size_t k = 0; k < arrays.size(); ++k) {
+            pa.src[k] = (const uint32_t*)arrays[k].src;
+            pa.after_prompt[k] = arrays[k].after_prompt;
         }
+        HIPCK(c, launch_pack_results(c->sd, pa));
+        HIPCK(c, hipStreamSynchronize(c->sd));
+        if (first) {
+            if (out->reward && n) memcpy(out->reward, body, (size_t)n * 4);
+            bad = (int)body[n];
+        }
+        for (size_t k = 0; k < arrays.size(); ++k)
+            memcpy((uint32_t*)arrays[k].dst + done, pa.out + k * (size_t)words, (size_t)words * 4);
+        done += words;
+        i0 = i1;
     }
-    if (out->reward && n) HIPCK(c, hipMemcpy(out->reward, c->d_reward, (size_t)n * 4, hipMemcpyDeviceToHost));
     // The 16-bit activation path has no scaling: a model whose activations leave IEEE half's range
     // (|x| > 65504) produces infinities and then NaNs.  Every kernel that writes a result raises
     // this flag when the value is not finite; the outputs above are still delivered.
-    int bad = 0;
-    HIPCK(c, hipMemcpy(&bad, c->d_nonfinite, sizeof(int), hipMemcpyDeviceToHost));
     if (bad)
         return c->fail(RLHF_ENONFINITE, "rlhf_get_results: a log-prob, value or reward of this stage is not finite "
                                         "(activations outside the range of the 16-bit path?)");
@@ -1756,48 +1795,29 @@ extern "C" int rlhf_compute_gae(rlhf_ctx* c, float gamma, float lam, float kl_co
     if (rc) return rc;
     const int n = c->N, mc = c->ec.max_ctx;
     int64_t total = 0;
-    int Lmax = 0;
-    std::vector<int> gl(n);
     for (int i = 0; i < n; ++i) {
         const Sample& s = c->smp[i];
         if (!sample_done(s) || s.gen_len < 1) return c->fail(RLHF_ESTATE, "rlhf_compute_gae: sample %d is not finished", i);
-        gl[i] = s.gen_len;
         total += s.gen_len;
-        Lmax = std::max(Lmax, s.gen_len);
     }
     if ((advantages || returns) && packed_capacity < total)
         return c->fail(RLHF_EINVAL, "rlhf_compute_gae: packed_capacity %lld < %lld", (long long)packed_capacity, (long long)total);
-    if (n == 0) return RLHF_OK;
-    const int Lp = (Lmax + 15) / 16 * 16;
-    float *D = nullptr, *U = nullptr, *A = nullptr, *R = nullptr;
-    int* d_gl = nullptr;
-    auto cleanup = [&] { for (void* p : {(void*)D, (void*)U, (void*)A, (void*)R, (void*)d_gl}) if (p) (void)hipFree(p); };
-#define GAECK(call)                                                                              \
-    do {                                                                                         \
-        hipError_t e_ = (call);                                                                  \
-        if (e_ != hipSuccess) { cleanup(); return c->fail(RLHF_EDEVICE, "%s failed: %s", #call, hipGetErrorString(e_)); } \
-    } while (0)
-    GAECK(hipMalloc((void**)&D, (size_t)n * Lp * 4));
-    GAECK(hipMalloc((void**)&A, (size_t)n * Lp * 4));
-    GAECK(hipMalloc((void**)&R, (size_t)n * Lp * 4));
-    GAECK(hipMalloc((void**)&U, (size_t)Lp * Lp * 4));
-    GAECK(hipMalloc((void**)&d_gl, (size_t)n * sizeof(int)));
-    GAECK(hipMemcpyAsync(d_gl, gl.data(), (size_t)n * sizeof(int), hipMemcpyHostToDevice, c->sd));
-    GAECK(launch_gae_delta(c->sd, c->d_lp_actor, c->d_lp_ref, c->d_values, c->d_reward, d_gl, mc, gamma, kl_coef, D, n, Lp));
-    GAECK(launch_gae_matrix(c->sd, U, Lp, (double)gamma * (double)lam));
-    GAECK(launch_gemm(c->sd, kF32, kF32, D, U, A, n, Lp, Lp, 1));          // A = D U^T, one matrix multiply
-    GAECK(launch_gae_returns(c->sd, A, c->d_values, d_gl, mc, R, n, Lp));
-    std::vector<float> ha((size_t)n * Lp), hr((size_t)n * Lp);
-    GAECK(hipMemcpyAsync(ha.data(), A, ha.size() * 4, hipMemcpyDeviceToHost, c->sd));
-    GAECK(hipMemcpyAsync(hr.data(), R, hr.size() * 4, hipMemcpyDeviceToHost, c->sd));
-    GAECK(hipStreamSynchronize(c->sd));
-#undef GAECK
-    cleanup();
-    int64_t o = 0;
-    for (int i = 0; i < n; ++i) {
-        if (advantages) std::copy(ha.begin() + (size_t)i * Lp, ha.begin() + (size_t)i * Lp + gl[i], advantages + o);
-        if (returns) std::copy(hr.begin() + (size_t)i * Lp, hr.begin() + (size_t)i * Lp + gl[i], returns + o);
-        o += gl[i];
+    GaePowers pw;
+    pw.gl = (float)((double)gamma * (double)lam);
+    for (int k = 0; k <= 64; ++k) pw.lanes[k] = (float)std::pow((double)gamma * (double)lam, 8.0 * k);
+    int64_t done = 0;
+    for (int i0 = 0; i0 < n;) {
+        int i1;
+        int64_t words;
+        stage_rows(c, i0, 2, 0, &i1, &words);
+        float* body = (float*)(c->h_stage + 4 * (size_t)(i1 - i0));
+        HIPCK(c, launch_gae(c->sd, c->d_lp_actor, c->d_lp_ref, c->d_values, c->d_reward, (const PackRow*)c->h_stage, i1 - i0,
+                            mc, gamma, kl_coef, pw, advantages ? body : nullptr, returns ? body + words : nullptr));
+        HIPCK(c, hipStreamSynchronize(c->sd));
+        if (advantages) memcpy(advantages + done, body, (size_t)words * 4);
+        if (returns) memcpy(returns + done, body + words, (size_t)words * 4);
+        done += words;
+        i0 = i1;
     }
     return RLHF_OK;
 }

@@ -173,13 +173,26 @@ hipError_t launch_noop(hipStream_t st);   // empty kernel (calibrates event brac
 // page_table[upd_idx[i]] = upd_val[i]
 hipError_t launch_scatter_int(hipStream_t st, int* dst, const int* idx, const int* val, int n);
 
-// ---- GAE as one matrix multiply: D = delta (zero-padded [n, Lp]), U[t][s] = (gamma lam)^(s-t)
-hipError_t launch_gae_delta(hipStream_t st, const float* lp_actor, const float* lp_ref, const float* values,
-                            const float* reward, const int* gen_len, int stride, float gamma, float kl_coef,
-                            float* D, int n, int Lp);
-hipError_t launch_gae_matrix(hipStream_t st, float* U, int Lp, double gamma_lam);
-hipError_t launch_gae_returns(hipStream_t st, const float* A, const float* values, const int* gen_len,
-                              int stride, float* R, int n, int Lp);
+// ---- results to pinned host memory (pointers the device can write)
+struct PackRow { int row, prompt, len, offset; };   // buffer row, prompt length, entries, place in the packed output
+struct PackArgs {
+    const uint32_t* src[5] = {};      // [max_samples][stride] buffers of 32-bit entries
+    int after_prompt[5] = {};         // entries start behind the row's prompt (token buffer)
+    int n_arrays = 0, n = 0, stride = 0, total = 0;
+    const PackRow* rows = nullptr;    // [n]
+    uint32_t* out = nullptr;          // [n_arrays][total]
+    uint32_t* scalars = nullptr;      // [n_reward] rewards, then the flag; or NULL
+    const uint32_t* reward = nullptr;
+    const int* flag = nullptr;
+    int n_reward = 0;
+};
+hipError_t launch_pack_results(hipStream_t st, const PackArgs& a);
+
+// ---- GAE: advantages and returns of n samples (either may be NULL), packed by PackRow::offset
+struct GaePowers { float gl, lanes[65]; };          // gamma*lam and its powers 8 * k, k = 0..64
+hipError_t launch_gae(hipStream_t st, const float* lp_actor, const float* lp_ref, const float* values,
+                      const float* reward, const PackRow* rows, int n, int stride, float gamma, float kl_coef,
+                      const GaePowers& pw, float* adv, float* ret);
 
 // ---- attention
 // Decode: one query row per active sample against its paged K/V.  q [rows, Hq*hd]; out the same.
