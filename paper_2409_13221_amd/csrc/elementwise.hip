@@ -41,10 +41,10 @@ hipError_t launch_embed(hipStream_t st, int dtype, const int* tokens, const int*
 
 // With the first norm (see gemm_stream.hip): one block per row, the row in registers between the passes.
 constexpr int kEmbedIter = 4;
-template <typename T>
+template <typename T, typename TX>
 __global__ __launch_bounds__(256) void k_embed_norm(const int* __restrict__ tokens, const int* __restrict__ tok_idx,
                                                     const T* __restrict__ table, float* __restrict__ h,
-                                                    const float* __restrict__ g, f16_t* __restrict__ x, ActLayout xl,
+                                                    const float* __restrict__ g, TX* __restrict__ x, ActLayout xl,
                                                     float* __restrict__ s_out, float* __restrict__ ssq_out, int d,
                                                     int vocab, float eps) {
     __shared__ float red[16];
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) void k_embed_norm(const int* __restrict__ toke
             load8<float>(g + i, gg);
 #pragma unroll
             for (int e = 0; e < 8; ++e) gg[e] *= v[it][e] * sc;
-            store8<f16_t>(x + act_index(xl, r, i), gg);
+            store8<TX>(x + act_index(xl, r, i), gg);
         }
     }
     for (int i = threadIdx.x; i < kSsqStride; i += 256) ssq_out[(size_t)r * kSsqStride + i] = i == 0 ? tot : 0.f;
@@ -83,9 +83,15 @@ hipError_t launch_embed_norm(hipStream_t st, int dtype, const int* tokens, const
                              float* h, const float* g, void* x, const ActLayout& x_layout, float* s, float* ssq,
                              int rows, int d, int vocab, float eps) {
     if (rows <= 0) return hipSuccess;
-    if (dtype != kBF16 || d % 8 || d > 256 * 8 * kEmbedIter) return hipErrorInvalidValue;
-    k_embed_norm<bf16_t><<<rows, 256, 0, st>>>(tokens, tok_idx, (const bf16_t*)table, h, g, (f16_t*)x, x_layout, s, ssq,
-                                               d, vocab, eps);
+    if (d % 8 || d > 256 * 8 * kEmbedIter) return hipErrorInvalidValue;
+    ActLayout xl = x_layout;
+    if (xl.row == 0) xl = ActLayout{d, 8};
+    if (dtype == kBF16)
+        k_embed_norm<bf16_t, f16_t><<<rows, 256, 0, st>>>(tokens, tok_idx, (const bf16_t*)table, h, g, (f16_t*)x, xl, s,
+                                                          ssq, d, vocab, eps);
+    else
+        k_embed_norm<float, float><<<rows, 256, 0, st>>>(tokens, tok_idx, (const float*)table, h, g, (float*)x, xl, s, ssq,
+                                                        d, vocab, eps);
     return hipGetLastError();
 }
 

@@ -346,9 +346,10 @@ struct PassMeta {         // device pointers into a MetaRing arena
     double attn_bytes = 0, attn_flops = 0;   // algorithmic, per layer (for the profiler)
 };
 
-// Few rows of a bf16 model: every layer runs on the projections of gemm_stream.hip.
+// Few rows: every layer runs on the projections of gemm_stream.hip.
 bool stream_pass(const rlhf_ctx* c, int rows) {
     const rlhf_model_cfg& m = c->mc;
+    if (c->dtype == kF32) return rows <= kStreamResidRows && m.d_model % 16 == 0;
     return c->dtype == kBF16 && rows <= kStreamMaxRows && m.d_model % 64 == 0 && (m.n_q_heads * m.head_dim) % 64 == 0 &&
            m.ffn % 64 == 0;
 }
@@ -365,7 +366,7 @@ NormIn stream_norm(const rlhf_ctx* c, const Workspace& ws, int n_ssq, float* s_i
     return ni;
 }
 
-// The layers of such a pass, their activations in the packed layout.  Up to kStreamResidRows rows: five
+// The layers of such a pass, 16-bit activations in the packed layout.  Up to kStreamResidRows rows: five
 // kernels a layer (six when the contexts are split), the residual stream in ws.h is complete after every
 // O and down projection, and ws.xn holds the next norm's input as gemm_stream.hip describes it, at the
 // end that of the final norm (scale in ws.scale, sums in ws.ssq: *n_ssq per row; *pend_ns = 0).  More
@@ -380,7 +381,9 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
     const bool resid = rows <= kStreamResidRows;
     const size_t plane = (size_t)rows * d;
     const int cap = (int)std::min<size_t>(16, ws.part_cap / plane);
-    const ActLayout packed{8, 8 * rows}, attn_layout = mode == kModeDecode ? packed : ActLayout{qd, 8};
+    const int adt = act_type(c, mode == kModeBatch);
+    // row 0: row-major, whatever the width
+    const ActLayout packed = adt == kF16 ? ActLayout{8, 8 * rows} : ActLayout{}, attn_layout = mode == kModeDecode ? packed : ActLayout{};
     float* sc[2] = {ws.scale, ws.scale + kStreamResidRows};
     auto gain_after = [&](int l) { return l + 1 < m.n_layers ? w.g_attn + (size_t)(l + 1) * d : w.g_final; };
     if (resid)
@@ -393,7 +396,7 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
     auto project = [&](int md, const void* A, const void* W, int N, int K, const RowsEpi& ep, int nsplit = 1) {
         const double bytes = ((double)N * K + (double)rows * K) * es + (double)rows * N * (md == 0 ? 4 : es);
         return profiled(c, st, gcls, bytes, 2.0 * rows * N * K,
-                        [&] { return launch_gemm_stream(st, dt, kF16, md, A, W, ws.part, rows, N, K, ep, nsplit); });
+                        [&] { return launch_gemm_stream(st, dt, adt, md, A, W, ws.part, rows, N, K, ep, nsplit); });
     };
     // O and down projections: finish the residual stream, or leave planes and let RMSNorm do it
     auto into_stream = [&](const void* A, const ActLayout& la, const void* W, int K, const float* g_next, float* s) -> int {
@@ -412,7 +415,7 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
     };
     for (int l = 0; l < m.n_layers; ++l) {
         if (!resid)
-            HIPCK(c, launch_rmsnorm(st, kF16, ws.h, ws.part, ns, plane, nullptr, w.g_attn + (size_t)l * d, ws.xn, rows, d,
+            HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, ns, plane, nullptr, w.g_attn + (size_t)l * d, ws.xn, rows, d,
                                     m.rms_eps, packed));
         RowsEpi ep;
         ep.a = packed;
@@ -430,20 +433,23 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
         HIPCK(c, project(2, ws.xn, layer_ptr(w.wqkv, l, qkv_w, d, es), qkv_w, d, ep));
         if (mode == kModeDecode) {
             HIPCK(c, profiled(c, st, kAttnDecode, pm.attn_bytes, pm.attn_flops, [&] {
-                return launch_decode_attn(st, kF16, ws.q, c->pool, c->d_page_table, c->max_pages, pm.row_sample,
+                return launch_decode_attn(st, adt, ws.q, c->pool, c->d_page_table, c->max_pages, pm.row_sample,
                                           pm.ctx_len, ws.attn, ws.attn_acc, ws.attn_ml, rows, l, attn_nsplit, c->dm,
                                           attn_layout);
             }));
         } else {
             HIPCK(c, profiled(c, st, kAttnBatch, pm.attn_bytes, pm.attn_flops, [&] {
-                return launch_flash_attn(st, ws.q, ws.k, ws.v, pm.tile_start, pm.tile_q0, pm.tile_len, ws.attn,
-                                         pm.n_tiles, rows, c->dm);
+                if (adt == kF16)
+                    return launch_flash_attn(st, ws.q, ws.k, ws.v, pm.tile_start, pm.tile_q0, pm.tile_len, ws.attn,
+                                             pm.n_tiles, rows, c->dm);
+                return launch_prefill_attn(st, adt, (const float*)ws.q, (const float*)ws.k, (const float*)ws.v,
+                                           pm.row_start, pm.pos, ws.attn, rows, c->dm);
             }));
         }
         int rc = into_stream(ws.attn, attn_layout, layer_ptr(w.wo, l, d, qd, es), qd, w.g_mlp + (size_t)l * d, sc[1]);
         if (rc) return rc;
         if (!resid)
-            HIPCK(c, launch_rmsnorm(st, kF16, ws.h, ws.part, ns, plane, nullptr, w.g_mlp + (size_t)l * d, ws.xn, rows, d,
+            HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, ns, plane, nullptr, w.g_mlp + (size_t)l * d, ws.xn, rows, d,
                                     m.rms_eps, packed));
         RowsEpi eg;
         eg.a = eg.out = packed;
@@ -921,7 +927,7 @@ int lm_head_chunks(rlhf_ctx* c, hipStream_t st, Workspace& ws, const rlhf_weight
         if (gemm_stream_supported(c->dtype, act_type(c, true), nr, d)) {
             const double bytes = ((double)V * d + (double)nr * d) * c->esz + (double)nr * V * 4;
             HIPCK(c, profiled(c, st, kGemmBatch, bytes, 2.0 * nr * V * d, [&] {
-                return launch_gemm_stream(st, c->dtype, kF16, 0, x, w.head, ws.logits, nr, V, d, RowsEpi{});
+                return launch_gemm_stream(st, c->dtype, act_type(c, true), 0, x, w.head, ws.logits, nr, V, d, RowsEpi{});
             }));
         } else {
             HIPCK(c, gemm_profiled(c, st, kGemmBatch, act_type(c, true), x, w.head, ws.logits, nr, V, d, 1));
@@ -1161,15 +1167,16 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
         int rc = forward_layers_stream(c, c->sd, ws, c->roles[RLHF_ACTOR], R, pm, kModeDecode, asplit, &pns, &n_ssq);
         if (rc) return rc;
         RowsEpi ep;
-        ep.a = ActLayout{8, 8 * R};
+        const int adt = act_type(c, false);
+        if (adt == kF16) ep.a = ActLayout{8, 8 * R};
         if (R <= kStreamResidRows)
             ep.nrm = stream_norm(c, ws, n_ssq, ws.scale, nullptr);
         else
-            HIPCK(c, launch_rmsnorm(c->sd, kF16, ws.h, ws.part, pns, (size_t)R * d, nullptr, w.g_final, ws.xn, R, d,
+            HIPCK(c, launch_rmsnorm(c->sd, adt, ws.h, ws.part, pns, (size_t)R * d, nullptr, w.g_final, ws.xn, R, d,
                                     c->mc.rms_eps, ep.a));
         const double bytes = ((double)V * d + (double)R * d) * c->esz + (double)R * V * 4;
         HIPCK(c, profiled(c, c->sd, kGemmDecode, bytes, 2.0 * R * V * d, [&] {
-            return launch_gemm_stream(c->sd, c->dtype, kF16, 0, ws.xn, w.head, ws.part, R, V, d, ep);
+            return launch_gemm_stream(c->sd, c->dtype, adt, 0, ws.xn, w.head, ws.part, R, V, d, ep);
         }));
     } else {
         int pns;

@@ -48,10 +48,191 @@ template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_w
 
 }  // namespace
 
-// MB: 16-row blocks of activations; NB: 16-row blocks of weights per workgroup; WAVES share K.
-// Row blocks of weights: 8 rows "low", 8 rows "high" each.  MODE 0 plain, 3 residual: 16 consecutive
-// rows.  MODE 1 (SwiGLU): 8 gate rows and the matching 8 up rows.  MODE 2 (rotary): dims c .. c+7 and
-// c + hd/2 .. of one head.  So the members of every pair meet in one workgroup.
+// First weight row of half `hi` (8 rows) of row block b; rows past the end are clamped, computed and never
+// stored.  MODE 0 plain, 3 residual: 16 consecutive rows.  MODE 1 (SwiGLU): 8 gate rows and the matching 8
+// up rows.  MODE 2 (rotary): dims c .. c+7 and c + hd/2 .. of one head.  So the members of every pair meet
+// in one workgroup.
+template <int MODE> __device__ __forceinline__ int stream_wrow(const RowsEpi& ep, int N, int b, int hi) {
+    if (MODE == 1) return hi * ep.ffn + min(b * 8, ep.ffn - 1);
+    if (MODE == 2) {
+        const int hd = ep.ro.head_dim, half = hd >> 1, per_head = half / 8;
+        const int head = min(b / per_head, N / hd - 1), c = (b % per_head) * 8;
+        return head * hd + hi * half + c;
+    }
+    return min(b * 16 + hi * 8, N - 1);
+}
+// last row of that half that exists
+template <int MODE> __device__ __forceinline__ int stream_last_row(const RowsEpi& ep, int N, int hi) {
+    return (MODE == 1 ? (hi + 1) * ep.ffn : N) - 1;
+}
+
+// 1/rms of the rows of an unscaled norm input, RPW rows per wave: kSsqStride partial sums of squares each
+// (unused ones are zero), a float4 per lane and 256 of them.
+template <int RPW> struct StreamNorm {
+    float4 q0[RPW], q1[RPW];
+    __device__ __forceinline__ void request(const NormIn& ni, int M, int w, int lane) {
+        const bool two = ni.n_ssq > 256;
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+            const float* src = ni.ssq + (size_t)min(w * RPW + i, M - 1) * kSsqStride + lane * 4;
+            q0[i] = *reinterpret_cast<const float4*>(src);
+            q1[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (two) q1[i] = *reinterpret_cast<const float4*>(src + 256);
+        }
+    }
+    __device__ __forceinline__ void reduce(const NormIn& ni, int M, int K, int w, int lane, bool first_block, float* s_scale) {
+        float v[RPW];
+#pragma unroll
+        for (int i = 0; i < RPW; ++i)
+            v[i] = ((q0[i].x + q1[i].x) + (q0[i].y + q1[i].y)) + ((q0[i].z + q1[i].z) + (q0[i].w + q1[i].w));
+        // all rows at once: every exchange halves the rows a lane still carries, row lane / (64 / RPW) in the end
+        int o = 32;
+#pragma unroll
+        for (int nn = RPW; nn > 1; nn >>= 1, o >>= 1)
+#pragma unroll
+            for (int i = 0; i < nn / 2; ++i) {
+                const bool up = lane & o;
+                const float give = up ? v[i] : v[i + nn / 2], keep = up ? v[i + nn / 2] : v[i];
+                v[i] = keep + __shfl_xor(give, o, kWave);
+            }
+#pragma unroll
+        for (; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, kWave);
+        constexpr int LPR = 64 / RPW;
+        const int m = w * RPW + lane / LPR;
+        if (m < M && lane % LPR == 0) {
+            const float inv = rsqrtf(v[0] / (float)K + ni.eps);
+            s_scale[m] = inv / ni.s_in[m];
+            if (first_block && ni.s_out) ni.s_out[m] = pow2_below(inv);
+        }
+    }
+};
+
+// What becomes of the result.  The waves' shares of K lie in red[wave][weight row][activation row] (row pitch
+// MB * 16 + 1); a thread owns OUT_IT outputs (pairs, in MODE 1 and 2) and asks for what it needs of other
+// arrays before the weights come, so that it does not wait at the end.  TO: type of activations and pool.
+template <int MB, int NB, int WAVES, int MODE, typename TO> struct StreamEpilogue {
+    static constexpr int NT = WAVES * 64, R16 = NB * 16, R8 = NB * 8, MP = MB * 16 + 1;
+    static constexpr int OUT_IT = ((MODE == 1 || MODE == 2 ? R8 : R16) * MB * 16 + NT - 1) / NT;
+    float pre_a[OUT_IT], pre_b[OUT_IT];                    // MODE 3: h, g * s;  MODE 2: cos, sin
+    int pre_i[OUT_IT];                                     // MODE 2: position, then pool slot
+
+    __device__ __forceinline__ void request(const RowsEpi& ep, int M, int N, int blk, int t) {
+        if (MODE == 2) {
+#pragma unroll
+            for (int i = 0; i < OUT_IT; ++i) pre_i[i] = ep.ro.pos[min((t + i * NT) / R8, M - 1)];
+        }
+        if (MODE == 3) {
+#pragma unroll
+            for (int i = 0; i < OUT_IT; ++i) {
+                const int o = t + i * NT, m = min(o / R16, M - 1), nn = min(blk * R16 + o % R16, N - 1);
+                pre_a[i] = ep.res.h[(size_t)m * N + nn];
+                pre_b[i] = ep.res.g[nn] * ep.res.s[m];
+            }
+        }
+    }
+    __device__ __forceinline__ void request_table(const RowsEpi& ep, int M, int blk, int t) {     // after the first weights
+        if (MODE == 2) {
+            const int half = ep.ro.head_dim >> 1, per_head = half / 8;
+#pragma unroll
+            for (int i = 0; i < OUT_IT; ++i) {
+                const int o = t + i * NT, r = o % R8, d0 = ((blk * NB + (r >> 3)) % per_head) * 8 + (r & 7);
+                const float2 cs = *reinterpret_cast<const float2*>(ep.ro.table + ((size_t)pre_i[i] * half + d0) * 2);
+                pre_a[i] = cs.x;
+                pre_b[i] = cs.y;
+                pre_i[i] = ep.ro.kv_dst ? ep.ro.kv_dst[min(o / R8, M - 1)] : 0;
+            }
+        }
+    }
+    __device__ __forceinline__ void finish(const RowsEpi& ep, const float* red, const float* s_scale, bool normed, float* C,
+                                           int M, int N, int blk, int t) {
+        auto total = [&](int row, int m) {
+            float v = 0.f;
+#pragma unroll
+            for (int x = 0; x < WAVES; ++x) v += red[(x * NB * 16 + row) * MP + m];
+            return v;
+        };
+        if (MODE == 0) {
+            for (int i = t; i < R16 * M; i += NT) {
+                const int m = i / R16, r = i % R16, nn = blk * R16 + r;
+                if (nn < N) C[(size_t)m * N + nn] = total(r, m) * (normed ? s_scale[m] : 1.f);
+            }
+        }
+        if (MODE == 1) {
+            TO* act = reinterpret_cast<TO*>(ep.act);
+            for (int i = t; i < R8 * M; i += NT) {
+                const int m = i / R8, r = i % R8, oc = blk * R8 + r, lr = (r >> 3) * 16 + (r & 7);
+                if (oc < ep.ffn) {
+                    const float sc = normed ? s_scale[m] : 1.f;
+                    const float g = total(lr, m) * sc, u = total(lr + 8, m) * sc;
+                    act[act_index(ep.out, m, oc)] = from_f32<TO>(g / (1.f + __expf(-g)) * u);
+                }
+            }
+        }
+        if (MODE == 2) {
+            const RopeOut& ro = ep.ro;
+            const int hd = ro.head_dim, half = hd >> 1, per_head = half / 8;
+            const int Hq = ro.n_q_heads, Hkv = ro.n_kv_heads;
+            TO* q_out = reinterpret_cast<TO*>(ro.q);
+            TO* k_out = reinterpret_cast<TO*>(ro.k);
+            TO* v_out = reinterpret_cast<TO*>(ro.v);
+            TO* pool = reinterpret_cast<TO*>(ro.pool);
+#pragma unroll
+            for (int it = 0; it < OUT_IT; ++it) {
+                const int i = t + it * NT, m = i / R8, r = i % R8, lr = (r >> 3) * 16 + (r & 7);
+                const int b = blk * NB + (r >> 3), head = b / per_head;
+                if (m >= M || head >= Hq + 2 * Hkv) continue;
+                const int d0 = (b % per_head) * 8 + (r & 7), d1 = d0 + half;
+                const float sc = normed ? s_scale[m] : 1.f;
+                float a = total(lr, m) * sc, c = total(lr + 8, m) * sc;
+                if (head < Hq + Hkv) {
+                    const float ra = a * pre_a[it] - c * pre_b[it], rc = a * pre_b[it] + c * pre_a[it];
+                    a = ra; c = rc;
+                }
+                if (head < Hq) {
+                    TO* dst = q_out + ((size_t)m * Hq + head) * hd;
+                    dst[d0] = from_f32<TO>(a);
+                    dst[d1] = from_f32<TO>(c);
+                } else {
+                    const bool is_k = head < Hq + Hkv;
+                    const int kh = is_k ? head - Hq : head - Hq - Hkv;
+                    TO* lin = is_k ? k_out : v_out;
+                    if (lin) {
+                        lin[((size_t)m * Hkv + kh) * hd + d0] = from_f32<TO>(a);
+                        lin[((size_t)m * Hkv + kh) * hd + d1] = from_f32<TO>(c);
+                    }
+                    if (pool) {
+                        const int slot = pre_i[it], pt = ro.page_tokens;
+                        TO* dst = pool + ((size_t)(slot / pt) * ro.n_layers + ro.layer) * 2 * (size_t)Hkv * pt * hd +
+                                  (size_t)(is_k ? 0 : Hkv) * pt * hd + (size_t)kh * pt * hd + (size_t)(slot % pt) * hd;
+                        dst[d0] = from_f32<TO>(a);
+                        dst[d1] = from_f32<TO>(c);
+                    }
+                }
+            }
+        }
+        if (MODE == 3) {
+            const ResidOut& rz = ep.res;
+            TO* x = reinterpret_cast<TO*>(rz.x);
+#pragma unroll
+            for (int it = 0; it < OUT_IT; ++it) {          // whole waves take part: the sums below are lane shuffles
+                const int i = t + it * NT, m = i / R16, r = i % R16, nn = blk * R16 + r;
+                float v = 0.f;
+                if (m < M && nn < N) {
+                    v = pre_a[it] + total(r, m);
+                    rz.h[(size_t)m * N + nn] = v;
+                    x[act_index(ep.out, m, nn)] = from_f32<TO>(v * pre_b[it]);
+                }
+                float q = v * v;
+#pragma unroll
+                for (int o = 1; o < R16; o <<= 1) q += __shfl_xor(q, o, kWave);
+                if (m < M && r == 0) rz.ssq[(size_t)m * kSsqStride + blk] = q;
+            }
+        }
+    }
+};
+
+// MB: 16-row blocks of activations; NB: 16-row blocks of weights per workgroup; WAVES share K; D: ring depth
+// in steps of 64 k.
 template <int MB, int NB, int WAVES, int D, int MODE, bool AF16>
 __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                                             float* __restrict__ C, int M, int N, int K,
@@ -68,19 +249,6 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
     const int blk = blockIdx.x;
     if (MODE == 0) C += (size_t)blockIdx.y * M * N;        // K range blockIdx.y of gridDim.y: a plane of its own
 
-    // weight row of (block nb, half hi, row r of 8); clamped rows are computed and never stored
-    auto wrow = [&](int nb, int hi) -> int {
-        const int b = blk * NB + nb;
-        if (MODE == 1) return hi * ep.ffn + min(b * 8, ep.ffn - 1);
-        if (MODE == 2) {
-            const int hd = ep.ro.head_dim, half = hd >> 1, per_head = half / 8;
-            const int head = min(b / per_head, N / hd - 1), c = (b % per_head) * 8;
-            return head * hd + hi * half + c;
-        }
-        return min(b * 16 + hi * 8, N - 1);
-    };
-    const int row_end = MODE == 1 ? ep.ffn : N;            // first row that does not exist, counted from a half's base
-
     // this wave's steps; the count is rounded up to whole rings, surplus steps re-read the last one against zeros
     const int steps = K >> 6, parts = WAVES * (MODE == 0 ? gridDim.y : 1);
     const int per = (steps + parts - 1) / parts;
@@ -93,10 +261,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int hi = 0; hi < 2; ++hi) {
-            const int base = __builtin_amdgcn_readfirstlane(wrow(nb, hi));
+            const int base = __builtin_amdgcn_readfirstlane(stream_wrow<MODE>(ep, N, blk * NB + nb, hi));
             rs[nb][hi] = __builtin_amdgcn_make_buffer_rsrc((void*)(W + (size_t)base * K), 0, -1, 0x00020000);
             const int r = lane >> 3;
-            const int lim = (MODE == 1 && hi ? 2 * row_end : row_end) - 1 - base;      // last row that exists
+            const int lim = stream_last_row<MODE>(ep, N, hi) - base;
             // LDS position p of row r holds chunk p ^ r: the fragment reads below then spread over the banks
             vo[nb][hi] = (uint32_t)(min(r, max(lim, 0)) * K * 2 + ((lane & 7) ^ r) * 16);
         }
@@ -107,39 +275,14 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
     for (int mb = 0; mb < MB; ++mb) pa[mb] = A + act_index(ep.a, min(mb * 16 + fr, M - 1), fq * 8);
     const size_t a_half = (size_t)4 * ep.a.chunk;          // elements from one 32-k half of a step to the next
 
-    // partial sums of squares of the normed rows, requested before everything else: RPW rows per wave,
-    // kSsqStride floats each (unused ones are zero), a float4 per lane and 256 floats
-    constexpr int RPW = MB * 16 / WAVES;
-    // (up to 16 rows only: at 64 rows the registers it takes halve the occupancy, 40 against 31 us for QKV)
-    const bool normed = MODE != 3 && MB == 1 && ep.nrm.ssq != nullptr, two = ep.nrm.n_ssq > 256;
-    float4 q0[RPW], q1[RPW];
-    if (normed) {
-#pragma unroll
-        for (int i = 0; i < RPW; ++i) {
-            const float* src = ep.nrm.ssq + (size_t)min(w * RPW + i, M - 1) * kSsqStride + lane * 4;
-            q0[i] = *reinterpret_cast<const float4*>(src);
-            q1[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (two) q1[i] = *reinterpret_cast<const float4*>(src + 256);
-        }
-    }
-
-    // what the epilogue needs of this thread's outputs, requested now so that it does not wait at the end
-    constexpr int NT = WAVES * 64, R16 = NB * 16, R8 = NB * 8;
-    constexpr int OUT_IT = ((MODE == 1 || MODE == 2 ? R8 : R16) * MB * 16 + NT - 1) / NT;
-    float pre_a[OUT_IT], pre_b[OUT_IT];                    // MODE 3: h, g * s;  MODE 2: cos, sin
-    int pre_i[OUT_IT];                                     // MODE 2: position, then pool slot
-    if (MODE == 2) {
-#pragma unroll
-        for (int i = 0; i < OUT_IT; ++i) pre_i[i] = ep.ro.pos[min((t + i * NT) / R8, M - 1)];
-    }
-    if (MODE == 3) {
-#pragma unroll
-        for (int i = 0; i < OUT_IT; ++i) {
-            const int o = t + i * NT, m = min(o / R16, M - 1), nn = min(blk * R16 + o % R16, N - 1);
-            pre_a[i] = ep.res.h[(size_t)m * N + nn];
-            pre_b[i] = ep.res.g[nn] * ep.res.s[m];
-        }
-    }
+    // requested before everything else.  (Norms up to 16 rows only: at 64 rows the registers they take halve the
+    // occupancy, 40 against 31 us for QKV.)
+    typedef typename std::conditional<AF16, f16_t, bf16_t>::type TO;
+    const bool normed = MODE != 3 && MB == 1 && ep.nrm.ssq != nullptr;
+    StreamNorm<MB * 16 / WAVES> norm;
+    if (normed) norm.request(ep.nrm, M, w, lane);
+    StreamEpilogue<MB, NB, WAVES, MODE, TO> epi;
+    epi.request(ep, M, N, blk, t);
 
     frag_t fa[D][2 * MB];
 #define RLHF_ST_ISSUE(STEP, J)                                                                                     \
@@ -194,42 +337,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
 
 #pragma unroll
     for (int j = 0; j < D; ++j) RLHF_ST_ISSUE(j, j);
-    if (MODE == 2) {
-        const int half = ep.ro.head_dim >> 1, per_head = half / 8;
-#pragma unroll
-        for (int i = 0; i < OUT_IT; ++i) {
-            const int o = t + i * NT, r = o % R8, d0 = ((blk * NB + (r >> 3)) % per_head) * 8 + (r & 7);
-            const float2 cs = *reinterpret_cast<const float2*>(ep.ro.table + ((size_t)pre_i[i] * half + d0) * 2);
-            pre_a[i] = cs.x;
-            pre_b[i] = cs.y;
-            pre_i[i] = ep.ro.kv_dst ? ep.ro.kv_dst[min(o / R8, M - 1)] : 0;
-        }
-    }
-    if (normed) {
-        float v[RPW];
-#pragma unroll
-        for (int i = 0; i < RPW; ++i)
-            v[i] = ((q0[i].x + q1[i].x) + (q0[i].y + q1[i].y)) + ((q0[i].z + q1[i].z) + (q0[i].w + q1[i].w));
-        // all rows at once: every exchange halves the rows a lane still carries, row lane / (64 / RPW) in the end
-        int o = 32;
-#pragma unroll
-        for (int nn = RPW; nn > 1; nn >>= 1, o >>= 1)
-#pragma unroll
-            for (int i = 0; i < nn / 2; ++i) {
-                const bool up = lane & o;
-                const float give = up ? v[i] : v[i + nn / 2], keep = up ? v[i + nn / 2] : v[i];
-                v[i] = keep + __shfl_xor(give, o, kWave);
-            }
-#pragma unroll
-        for (; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, kWave);
-        constexpr int LPR = 64 / RPW;
-        const int m = w * RPW + lane / LPR;
-        if (m < M && lane % LPR == 0) {
-            const float inv = rsqrtf(v[0] / (float)K + ep.nrm.eps);
-            s_scale[m] = inv / ep.nrm.s_in[m];
-            if (blk == 0 && ep.nrm.s_out) ep.nrm.s_out[m] = pow2_below(inv);
-        }
-    }
+    epi.request_table(ep, M, blk, t);
+    if (normed) norm.reduce(ep.nrm, M, K, w, lane, blk == 0, s_scale);
     int k = 0;
     for (; k + D < n; k += D) {
 #pragma unroll
@@ -262,94 +371,57 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
             for (int e = 0; e < 4; ++e)
                 red[(w * NB * 16 + nb * 16 + fq * 4 + e) * MP + mb * 16 + fr] = acc[nb][mb][e];
     __syncthreads();
-    auto total = [&](int row, int m) {
-        float v = 0.f;
-#pragma unroll
-        for (int x = 0; x < WAVES; ++x) v += red[(x * NB * 16 + row) * MP + m];
-        return v;
-    };
-    typedef typename std::conditional<AF16, f16_t, bf16_t>::type TO;
-    if (MODE == 0) {
-        for (int i = t; i < R16 * M; i += NT) {
-            const int m = i / R16, r = i % R16, nn = blk * R16 + r;
-            if (nn < N) C[(size_t)m * N + nn] = total(r, m) * (normed ? s_scale[m] : 1.f);
-        }
-        return;
-    }
-    if (MODE == 1) {
-        TO* act = reinterpret_cast<TO*>(ep.act);
-        for (int i = t; i < R8 * M; i += NT) {
-            const int m = i / R8, r = i % R8, oc = blk * R8 + r, lr = (r >> 3) * 16 + (r & 7);
-            if (oc < ep.ffn) {
-                const float sc = normed ? s_scale[m] : 1.f;
-                const float g = total(lr, m) * sc, u = total(lr + 8, m) * sc;
-                act[act_index(ep.out, m, oc)] = from_f32<TO>(g / (1.f + __expf(-g)) * u);
-            }
-        }
-        return;
-    }
-    if (MODE == 2) {
-        const RopeOut& ro = ep.ro;
-        const int hd = ro.head_dim, half = hd >> 1, per_head = half / 8;
-        const int Hq = ro.n_q_heads, Hkv = ro.n_kv_heads;
-        TO* q_out = reinterpret_cast<TO*>(ro.q);
-        TO* k_out = reinterpret_cast<TO*>(ro.k);
-        TO* v_out = reinterpret_cast<TO*>(ro.v);
-        TO* pool = reinterpret_cast<TO*>(ro.pool);
-#pragma unroll
-        for (int it = 0; it < OUT_IT; ++it) {
-            const int i = t + it * NT, m = i / R8, r = i % R8, lr = (r >> 3) * 16 + (r & 7);
-            const int b = blk * NB + (r >> 3), head = b / per_head;
-            if (m >= M || head >= Hq + 2 * Hkv) continue;
-            const int d0 = (b % per_head) * 8 + (r & 7), d1 = d0 + half;
-            const float sc = normed ? s_scale[m] : 1.f;
-            float a = total(lr, m) * sc, c = total(lr + 8, m) * sc;
-            if (head < Hq + Hkv) {
-                const float ra = a * pre_a[it] - c * pre_b[it], rc = a * pre_b[it] + c * pre_a[it];
-                a = ra; c = rc;
-            }
-            if (head < Hq) {
-                TO* dst = q_out + ((size_t)m * Hq + head) * hd;
-                dst[d0] = from_f32<TO>(a);
-                dst[d1] = from_f32<TO>(c);
-            } else {
-                const bool is_k = head < Hq + Hkv;
-                const int kh = is_k ? head - Hq : head - Hq - Hkv;
-                TO* lin = is_k ? k_out : v_out;
-                if (lin) {
-                    lin[((size_t)m * Hkv + kh) * hd + d0] = from_f32<TO>(a);
-                    lin[((size_t)m * Hkv + kh) * hd + d1] = from_f32<TO>(c);
-                }
-                if (pool) {
-                    const int slot = pre_i[it], pt = ro.page_tokens;
-                    TO* dst = pool + ((size_t)(slot / pt) * ro.n_layers + ro.layer) * 2 * (size_t)Hkv * pt * hd +
-                              (size_t)(is_k ? 0 : Hkv) * pt * hd + (size_t)kh * pt * hd + (size_t)(slot % pt) * hd;
-                    dst[d0] = from_f32<TO>(a);
-                    dst[d1] = from_f32<TO>(c);
-                }
-            }
-        }
-        return;
-    }
-    if (MODE == 3) {
-        const ResidOut& rz = ep.res;
-        f16_t* x = reinterpret_cast<f16_t*>(rz.x);
-#pragma unroll
-        for (int it = 0; it < OUT_IT; ++it) {              // whole waves take part: the sums below are lane shuffles
-            const int i = t + it * NT, m = i / R16, r = i % R16, nn = blk * R16 + r;
-            float v = 0.f;
-            if (m < M && nn < N) {
-                v = pre_a[it] + total(r, m);
-                rz.h[(size_t)m * N + nn] = v;
-                x[act_index(ep.out, m, nn)] = (f16_t)(v * pre_b[it]);
-            }
-            float q = v * v;
-#pragma unroll
-            for (int o = 1; o < R16; o <<= 1) q += __shfl_xor(q, o, kWave);
-            if (m < M && r == 0) rz.ssq[(size_t)m * kSsqStride + blk] = q;
-        }
-    }
+    epi.finish(ep, red, s_scale, normed, C, M, N, blk, t);
 #endif
+}
+
+// Float models, up to 16 rows: the same split and epilogues on float matrix instructions (16x16x4: products
+// and sums in float).  These matrices fit the caches, so the time is that of one dependent chain: eight
+// waves share K, a lane takes four consecutive k of its row and of its activation row per 16 k, four such
+// loads ahead.  (8 rows of 256 x 256 .. 1376 weights: 2.5-3 us a launch, where 64 x 64 tiles took 6.9 us and
+// left planes to rotary, SwiGLU and norm kernels of 3 us each.)
+template <int MODE>
+__global__ __launch_bounds__(512) void k_gemm_stream_f32(const float* __restrict__ A, const float* __restrict__ W,
+                                                         float* __restrict__ C, int M, int N, int K, const RowsEpi ep) {
+    constexpr int WAVES = 8, U = 4, MP = 17;
+    __shared__ float red[WAVES * 16 * MP];
+    __shared__ float s_scale[16];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, fr = lane & 15, fq = lane >> 4, blk = blockIdx.x;
+    const bool normed = MODE != 3 && ep.nrm.ssq != nullptr;
+    StreamNorm<2> norm;
+    if (normed) norm.request(ep.nrm, M, w, lane);
+    StreamEpilogue<1, 1, WAVES, MODE, float> epi;
+    epi.request(ep, M, N, blk, t);
+    const int hi = fr >> 3;
+    const float* pw = W + (size_t)min(stream_wrow<MODE>(ep, N, blk, hi) + (fr & 7), stream_last_row<MODE>(ep, N, hi)) * K;
+    const float* pa = A + (size_t)min(fr, M - 1) * K;
+    const int chunks = (K + 15) / 16, per = (chunks + WAVES - 1) / WAVES;
+    const int c0 = w * per, c1 = min(chunks, c0 + per);
+    f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int c = c0; c < c1; c += U) {
+        float4 fw[U], fa[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {                      // past the share or past K: read in bounds, count as zero
+            const int k = (c + u) * 16 + fq * 4, kc = min(k, K - 4);
+            const float z = c + u < c1 && k < K ? 1.f : 0.f;
+            fw[u] = *reinterpret_cast<const float4*>(pw + kc);
+            fa[u] = *reinterpret_cast<const float4*>(pa + kc);
+            if (z == 0.f) { fw[u] = make_float4(0.f, 0.f, 0.f, 0.f); fa[u] = fw[u]; }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[u].x, fa[u].x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[u].y, fa[u].y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[u].z, fa[u].z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[u].w, fa[u].w, acc, 0, 0, 0);
+        }
+    }
+    epi.request_table(ep, M, blk, t);
+    if (normed) norm.reduce(ep.nrm, M, K, w, lane, blk == 0, s_scale);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[(w * 16 + fq * 4 + e) * MP + fr] = acc[e];
+    __syncthreads();
+    epi.finish(ep, red, s_scale, normed, C, M, N, blk, t);
 }
 
 namespace {
@@ -374,6 +446,7 @@ hipError_t stream_launch(hipStream_t st, int mode, int blocks, int nsplit, const
 }  // namespace
 
 bool gemm_stream_supported(int wdt, int adt, int M, int K) {
+    if (wdt == kF32) return adt == kF32 && M >= 1 && M <= kStreamResidRows && K >= 4 && K % 4 == 0;
     return wdt == kBF16 && (adt == kF16 || (adt == kBF16 && M <= 16)) && M >= 1 && M <= kStreamMaxRows && K > 0 && K % 64 == 0;
 }
 
@@ -419,8 +492,21 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
             N != (ro.n_q_heads + 2 * ro.n_kv_heads) * ro.head_dim)
             return hipErrorInvalidValue;
     }
-    if (mode == 3 && (adt != kF16 || M > 16 || N % 16 || N > 16 * kSsqStride || !ep.res.h || !ep.res.g || !ep.res.x || !ep.res.s || !ep.res.ssq))
+    if (mode == 3 && (adt == kBF16 || M > 16 || N % 16 || N > 16 * kSsqStride || !ep.res.h || !ep.res.g || !ep.res.x || !ep.res.s || !ep.res.ssq))
         return hipErrorInvalidValue;
+    if (wdt == kF32) {
+        if (nsplit != 1 || ep.a.row != K || (mode == 1 && ep.out.row != ep.ffn) || (mode == 3 && ep.out.row != N))
+            return hipErrorInvalidValue;                   // row-major only
+        const float *af = (const float*)A, *wf = (const float*)W;
+        const int nb = (N + 15) / 16;
+        switch (mode) {
+            case 0: k_gemm_stream_f32<0><<<nb, 512, 0, st>>>(af, wf, C, M, N, K, ep); break;
+            case 1: k_gemm_stream_f32<1><<<nb, 512, 0, st>>>(af, wf, C, M, N, K, ep); break;
+            case 2: k_gemm_stream_f32<2><<<nb, 512, 0, st>>>(af, wf, C, M, N, K, ep); break;
+            default: k_gemm_stream_f32<3><<<nb, 512, 0, st>>>(af, wf, C, M, N, K, ep); break;
+        }
+        return hipGetLastError();
+    }
     const bf16_t* a = (const bf16_t*)A;
     const bf16_t* w = (const bf16_t*)W;
     const StreamShape sh = mode == 3 ? StreamShape{1, 1, 4} : stream_shape(M, N, mode == 0);

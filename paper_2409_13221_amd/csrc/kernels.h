@@ -73,12 +73,13 @@ bool gemm_rope_supported(int wdt, int adt, int M, int K, const Dims& dm);
 hipError_t launch_gemm_rope(hipStream_t st, int wdt, int adt, const void* A, const void* Wqkv, int M, int K,
                             const RopeOut& ro);
 
-// Few rows, bf16 weights (gemm_stream.hip): workgroups walk the whole K range, so that the step that
+// Few rows (gemm_stream.hip): workgroups walk the whole K range, so that the step that
 // consumes the projection rides in its epilogue and needs no launch of its own.
 // mode 0: C float [M, N]; mode 1: gate||up with SwiGLU, act [M, ffn] of type adt (N = 2 ffn);
 // mode 2: QKV with rotary embedding and the q / k / v / paged-pool scatter (ep.ro as in launch_gemm_rope);
 // mode 3: residual: h += result, and the unscaled input of the next norm (ep.res).
-// Half activations: 1..kStreamMaxRows rows; bf16 activations: 1..16.  K a multiple of 64.
+// Half activations: 1..kStreamMaxRows rows; bf16 activations: 1..16; K a multiple of 64.  Float weights and
+// activations (row-major): 1..16 rows, K a multiple of 4.
 constexpr int kStreamMaxRows = 64;
 constexpr int kSsqStride = 512; // floats per row of the partial sums of squares (d_model <= 8192, 16 columns each)
 struct NormIn {                 // modes 0..2: A holds x = h * gain * s_in; result of row m times (1/rms) / s_in[m]
@@ -91,7 +92,7 @@ struct NormIn {                 // modes 0..2: A holds x = h * gain * s_in; resu
 struct ResidOut {               // mode 3
     float* h = nullptr;             // [M, N] residual stream, updated
     const float* g = nullptr;       // [N] gain of the norm that follows
-    void* x = nullptr;              // [M, N] half: h * g * s
+    void* x = nullptr;              // [M, N] in the activation type: h * g * s
     const float* s = nullptr;       // [M] scale that keeps x in half's range (power of two below the row's previous 1/rms)
     float* ssq = nullptr;           // [M, kSsqStride] partial sums of h^2, one per 16 columns
 };
@@ -135,7 +136,7 @@ hipError_t launch_lse_merge(hipStream_t st, const float* part_max, const float* 
 hipError_t launch_embed(hipStream_t st, int dtype, const int* tokens, const int* tok_idx,
                         const void* table, float* h, int rows, int d, int vocab);
 // The embedding row with the first norm applied, for the few-row projections of gemm_stream.hip: h, and
-// x = h * s * g (half, layout x_layout), s[r] the power of two below 1/rms, ssq [rows, kSsqStride]: the sum of h^2, then zeros.
+// x = h * s * g (activation type, layout x_layout), s[r] the power of two below 1/rms, ssq [rows, kSsqStride]: the sum of h^2, then zeros.
 hipError_t launch_embed_norm(hipStream_t st, int dtype, const int* tokens, const int* tok_idx, const void* table,
                              float* h, const float* g, void* x, const ActLayout& x_layout, float* s, float* ssq,
                              int rows, int d, int vocab, float eps);

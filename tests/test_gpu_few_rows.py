@@ -16,11 +16,13 @@ _GPT2S = CONFIGS["gpt2s"]
 _SMALL = replace(_GPT2S.model, n_layers=2, d_model=320, n_q_heads=5, n_kv_heads=5, head_dim=64, ffn=448, vocab=1003)
 # N >= 4096 everywhere but in the KV heads' share, K = 4096 and 704
 _WIDE = replace(_GPT2S.model, n_layers=1, d_model=4096, n_q_heads=32, n_kv_heads=4, head_dim=128, ffn=704, vocab=4100)
+# the float model's own kernel: K with half a chunk of 16 left over, a ragged vocabulary
+_FLOAT = replace(_SMALL, d_model=208, n_q_heads=2, n_kv_heads=2, ffn=120, vocab=203, dtype="fp32")
 _GROUPED = replace(_SMALL, d_model=1024, n_q_heads=8, n_kv_heads=1, head_dim=128)
 
 
 @pytest.mark.parametrize("model,n", [(_SMALL, n) for n in (1, 16, 17, 32, 33, 64, 65)]
-                         + [(_WIDE, n) for n in (3, 16, 31, 64)] + [(_GROUPED, n) for n in (2, 19)])
+                         + [(_WIDE, n) for n in (3, 16, 31, 64)] + [(_GROUPED, n) for n in (2, 19)] + [(_FLOAT, n) for n in (1, 9, 16, 17)])
 def test_decode_batches_of_few_rows(model, n):
     cfg = _GPT2S.with_(name="few_rows", model=model, n_samples=n, prompt_len=(3, 5), gain_jitter=0.05)
     ref = H.oracle_stage(cfg, n=n, max_len=4)
