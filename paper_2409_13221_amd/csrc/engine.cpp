@@ -99,7 +99,7 @@ struct Workspace {
     int logit_rows = 0;
     float* pick_scratch = nullptr;  // per-chunk partial results of the greedy pick
     float* ssq = nullptr;       // few-row passes: partial sums of h^2 of the rows in flight
-    float* scale = nullptr;     // [2][kStreamResidRows]: scales of the normed rows, ping and pong
+    float* scale = nullptr;     // [2][kStreamMaxRows]: scales of the normed rows, ping and pong
     float* attn_acc = nullptr;  // decode split-KV partials
     float* attn_ml = nullptr;
     size_t attn_slots = 0;
@@ -301,8 +301,8 @@ int alloc_workspace(rlhf_ctx* c, Workspace& ws, int rows, bool decode) {
     HIPCK(c, dev_alloc(&ws, (char**)&ws.act, rows * f * es));
     HIPCK(c, dev_alloc(&ws, (char**)&ws.xsel, rows * d * 4));    // float rows for the value / reward head
     HIPCK(c, dev_alloc(&ws, &ws.pick_scratch, pick_scratch_floats(rows) * 4));
-    HIPCK(c, dev_alloc(&ws, &ws.ssq, (size_t)kStreamResidRows * kSsqStride * 4));
-    HIPCK(c, dev_alloc(&ws, &ws.scale, (size_t)2 * kStreamResidRows * 4));
+    HIPCK(c, dev_alloc(&ws, &ws.ssq, (size_t)kStreamMaxRows * kSsqStride * 4));
+    HIPCK(c, dev_alloc(&ws, &ws.scale, (size_t)2 * kStreamMaxRows * 4));
     if (decode) {
         HIPCK(c, dev_alloc(&ws, &ws.attn_acc, ws.attn_slots * m.head_dim * 4));
         HIPCK(c, dev_alloc(&ws, &ws.attn_ml, ws.attn_slots * 2 * 4));
@@ -366,11 +366,11 @@ NormIn stream_norm(const rlhf_ctx* c, const Workspace& ws, int n_ssq, float* s_i
     return ni;
 }
 
-// The layers of such a pass, 16-bit activations in the packed layout.  Up to kStreamResidRows rows: five
+// The layers of such a pass, 16-bit activations in the packed layout.  Where stream_resid says so: five
 // kernels a layer (six when the contexts are split), the residual stream in ws.h is complete after every
 // O and down projection, and ws.xn holds the next norm's input as gemm_stream.hip describes it, at the
-// end that of the final norm (scale in ws.scale, sums in ws.ssq: *n_ssq per row; *pend_ns = 0).  More
-// rows: seven kernels, O and down leave planes that RMSNorm adds, at the end *pend_ns of them.
+// end that of the final norm (scale in ws.scale, sums in ws.ssq: *n_ssq per row; *pend_ns = 0).  Otherwise:
+// seven kernels, O and down leave planes that RMSNorm adds, at the end *pend_ns of them.
 int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights& rw, int rows,
                           const PassMeta& pm, AttnMode mode, int attn_nsplit, int* pend_ns, int* n_ssq) {
     const rlhf_weights& w = rw.w;
@@ -378,13 +378,13 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
     const int d = m.d_model, qd = m.n_q_heads * m.head_dim, kvd = m.n_kv_heads * m.head_dim;
     const int qkv_w = qd + 2 * kvd, f = m.ffn, es = c->esz, dt = c->dtype;
     const int gcls = mode == kModeDecode ? kGemmDecode : kGemmBatch;
-    const bool resid = rows <= kStreamResidRows;
+    const bool resid = stream_resid(rows, m.d_model);
     const size_t plane = (size_t)rows * d;
     const int cap = (int)std::min<size_t>(16, ws.part_cap / plane);
     const int adt = act_type(c, mode == kModeBatch);
     // row 0: row-major, whatever the width
     const ActLayout packed = adt == kF16 ? ActLayout{8, 8 * rows} : ActLayout{}, attn_layout = mode == kModeDecode ? packed : ActLayout{};
-    float* sc[2] = {ws.scale, ws.scale + kStreamResidRows};
+    float* sc[2] = {ws.scale, ws.scale + kStreamMaxRows};
     auto gain_after = [&](int l) { return l + 1 < m.n_layers ? w.g_attn + (size_t)(l + 1) * d : w.g_final; };
     if (resid)
         HIPCK(c, launch_embed_norm(st, dt, c->d_tokens, pm.tok_idx, w.embed, ws.h, m.n_layers > 0 ? w.g_attn : w.g_final,

@@ -67,13 +67,20 @@ template <int MODE> __device__ __forceinline__ int stream_last_row(const RowsEpi
 }
 
 // 1/rms of the rows of an unscaled norm input, RPW rows per wave: kSsqStride partial sums of squares each
-// (unused ones are zero), a float4 per lane and 256 of them.
-template <int RPW> struct StreamNorm {
-    float4 q0[RPW], q1[RPW];
+// (unused ones are zero), a float4 per lane and 256 of them.  FEW: at most 64 are used, one per lane; with 64
+// rows the float4 form would take 128 registers.
+template <int RPW, bool FEW> struct StreamNorm {
+    float4 q0[FEW ? 1 : RPW], q1[FEW ? 1 : RPW];
+    float q[RPW];
     __device__ __forceinline__ void request(const NormIn& ni, int M, int w, int lane) {
+        if constexpr (FEW) {
+#pragma unroll
+            for (int i = 0; i < RPW; ++i) q[i] = ni.ssq[(size_t)min(w * RPW + i, M - 1) * kSsqStride + lane];
+            return;
+        }
         const bool two = ni.n_ssq > 256;
 #pragma unroll
-        for (int i = 0; i < RPW; ++i) {
+        for (int i = 0; i < (FEW ? 1 : RPW); ++i) {
             const float* src = ni.ssq + (size_t)min(w * RPW + i, M - 1) * kSsqStride + lane * 4;
             q0[i] = *reinterpret_cast<const float4*>(src);
             q1[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -84,7 +91,8 @@ template <int RPW> struct StreamNorm {
         float v[RPW];
 #pragma unroll
         for (int i = 0; i < RPW; ++i)
-            v[i] = ((q0[i].x + q1[i].x) + (q0[i].y + q1[i].y)) + ((q0[i].z + q1[i].z) + (q0[i].w + q1[i].w));
+            if constexpr (FEW) v[i] = q[i];
+            else v[i] = ((q0[i].x + q1[i].x) + (q0[i].y + q1[i].y)) + ((q0[i].z + q1[i].z) + (q0[i].w + q1[i].w));
         // all rows at once: every exchange halves the rows a lane still carries, row lane / (64 / RPW) in the end
         int o = 32;
 #pragma unroll
@@ -232,11 +240,11 @@ template <int MB, int NB, int WAVES, int MODE, typename TO> struct StreamEpilogu
 };
 
 // MB: 16-row blocks of activations; NB: 16-row blocks of weights per workgroup; WAVES share K; D: ring depth
-// in steps of 64 k.
-template <int MB, int NB, int WAVES, int D, int MODE, bool AF16>
+// in steps of 64 k; NORM: A may be an unscaled norm input (above 16 rows of at most 64 partial sums).
+template <int MB, int NB, int WAVES, int D, int MODE, bool AF16, bool NORM>
 __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                                             float* __restrict__ C, int M, int N, int K,
-                                                            const RowsEpi ep) {
+                                                            const RowsEpi ep_in) {
 #if defined(__HIP_DEVICE_COMPILE__)                        // buffer resources exist in the device pass only
     constexpr int OPS = 2 * NB + 2 * MB;                   // vector memory operations per step
     constexpr int kRing = WAVES * D * NB * 1024;           // halves (2 KB per step and weight block)
@@ -247,7 +255,19 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
     const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int fr = lane & 15, fq = lane >> 4;
     const int blk = blockIdx.x;
+    RowsEpi ep = ep_in;
+    typedef typename std::conditional<AF16, f16_t, bf16_t>::type TO;
     if (MODE == 0) C += (size_t)blockIdx.y * M * N;        // K range blockIdx.y of gridDim.y: a plane of its own
+
+    if (MODE == 3) {                                       // row group blockIdx.z: everything that goes by rows moves along
+        const int m0 = blockIdx.z * (MB * 16);
+        M = min(M - m0, MB * 16);
+        A += act_index(ep.a, m0, 0);
+        ep.res.h += (size_t)m0 * N;
+        ep.res.x = (TO*)ep.res.x + act_index(ep.out, m0, 0);
+        ep.res.s += m0;
+        ep.res.ssq += (size_t)m0 * kSsqStride;
+    }
 
     // this wave's steps; the count is rounded up to whole rings, surplus steps re-read the last one against zeros
     const int steps = K >> 6, parts = WAVES * (MODE == 0 ? gridDim.y : 1);
@@ -275,11 +295,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
     for (int mb = 0; mb < MB; ++mb) pa[mb] = A + act_index(ep.a, min(mb * 16 + fr, M - 1), fq * 8);
     const size_t a_half = (size_t)4 * ep.a.chunk;          // elements from one 32-k half of a step to the next
 
-    // requested before everything else.  (Norms up to 16 rows only: at 64 rows the registers they take halve the
-    // occupancy, 40 against 31 us for QKV.)
-    typedef typename std::conditional<AF16, f16_t, bf16_t>::type TO;
-    const bool normed = MODE != 3 && MB == 1 && ep.nrm.ssq != nullptr;
-    StreamNorm<MB * 16 / WAVES> norm;
+    // requested before everything else
+    const bool normed = NORM && ep.nrm.ssq != nullptr;
+    StreamNorm<MB * 16 / WAVES, (MB > 1)> norm;
     if (normed) norm.request(ep.nrm, M, w, lane);
     StreamEpilogue<MB, NB, WAVES, MODE, TO> epi;
     epi.request(ep, M, N, blk, t);
@@ -388,7 +406,7 @@ __global__ __launch_bounds__(512) void k_gemm_stream_f32(const float* __restrict
     __shared__ float s_scale[16];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, fr = lane & 15, fq = lane >> 4, blk = blockIdx.x;
     const bool normed = MODE != 3 && ep.nrm.ssq != nullptr;
-    StreamNorm<2> norm;
+    StreamNorm<2, false> norm;
     if (normed) norm.request(ep.nrm, M, w, lane);
     StreamEpilogue<1, 1, WAVES, MODE, float> epi;
     epi.request(ep, M, N, blk, t);
@@ -426,20 +444,30 @@ __global__ __launch_bounds__(512) void k_gemm_stream_f32(const float* __restrict
 
 namespace {
 
-template <int MB, int NB, int WAVES, int D, bool AF16>
+template <int MB, int NB, int WAVES, int D, bool AF16, bool NORM>
 hipError_t stream_launch(hipStream_t st, int mode, int blocks, int nsplit, const bf16_t* a, const bf16_t* w, float* C,
                          int M, int N, int K, const RowsEpi& ep) {
     const dim3 grid(blocks, nsplit);
     switch (mode) {
-        case 0: k_gemm_stream<MB, NB, WAVES, D, 0, AF16><<<grid, WAVES * 64, 0, st>>>(a, w, C, M, N, K, ep); break;
-        case 1: k_gemm_stream<MB, NB, WAVES, D, 1, AF16><<<grid, WAVES * 64, 0, st>>>(a, w, C, M, N, K, ep); break;
-        case 2: k_gemm_stream<MB, NB, WAVES, D, 2, AF16><<<grid, WAVES * 64, 0, st>>>(a, w, C, M, N, K, ep); break;
-        default:
-            if constexpr (MB == 1 && NB == 1 && AF16)
-                k_gemm_stream<MB, NB, WAVES, D, 3, AF16><<<grid, WAVES * 64, 0, st>>>(a, w, C, M, N, K, ep);
-            else
-                return hipErrorInvalidValue;
+        case 0: k_gemm_stream<MB, NB, WAVES, D, 0, AF16, NORM><<<grid, WAVES * 64, 0, st>>>(a, w, C, M, N, K, ep); break;
+        case 1: k_gemm_stream<MB, NB, WAVES, D, 1, AF16, NORM><<<grid, WAVES * 64, 0, st>>>(a, w, C, M, N, K, ep); break;
+        case 2: k_gemm_stream<MB, NB, WAVES, D, 2, AF16, NORM><<<grid, WAVES * 64, 0, st>>>(a, w, C, M, N, K, ep); break;
+        default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+// mode 3: groups of 16 rows, each against the whole matrix
+template <int WAVES, int D>
+hipError_t stream_resid_launch(hipStream_t st, const bf16_t* a, const bf16_t* w, int M, int N, int K, const RowsEpi& ep) {
+    k_gemm_stream<1, 1, WAVES, D, 3, true, false><<<dim3(N / 16, 1, (M + 15) / 16), WAVES * 64, 0, st>>>(a, w, nullptr, M, N, K, ep);
+    return hipGetLastError();
+}
+// modes 1 and 2 with the norm of 17..64 rows: one weight block per workgroup, eight waves share K
+template <int MB>
+hipError_t stream_norm_launch(hipStream_t st, int mode, const bf16_t* a, const bf16_t* w, int M, int N, int K, const RowsEpi& ep) {
+    const int blocks = (N + 15) / 16;
+    if (mode == 1) k_gemm_stream<MB, 1, 8, 2, 1, true, true><<<blocks, 512, 0, st>>>(a, w, nullptr, M, N, K, ep);
+    else k_gemm_stream<MB, 1, 8, 2, 2, true, true><<<blocks, 512, 0, st>>>(a, w, nullptr, M, N, K, ep);
     return hipGetLastError();
 }
 
@@ -459,6 +487,14 @@ bool gemm_stream_supported(int wdt, int adt, int M, int K) {
 // 25.5 with two / three / four, the last one 192 workgroups).  N = 4096 falls short of that: with more
 // than 16 rows O and down split K instead and leave planes to the norm that follows (64 rows: O 11.0
 // and down 22.8 as four planes of four blocks, 13.5 and 32.0 unsplit with one block).
+//
+// 17..64 rows of a narrow residual stream (stream_resid: d_model <= 1024): the matrices come from the
+// caches and a kernel's time is mostly its start and its chain of loads, so the five kernels of the norm
+// form win over seven, with one weight block per workgroup and O and down in groups of 16 rows (d = 768,
+// ffn = 2048, 64 rows, us: QKV 6.3 -> 6.7, O 4.5 -> 3.8, gate||up 7.9 -> 6.4, down 5.1 -> 4.9, two RMSNorms of
+// 4.3 gone; O and down as one group of 64 rows 5.1 and 8.0).  Wider streams keep planes and RMSNorm: their
+// time is weight traffic, which groups of 16 rows would repeat.  The head stays with the norm kernel (32000
+// columns: 25 us against 19.6 + 4.3, and more registers).
 struct StreamShape { int mb, nb, depth; };
 static StreamShape stream_shape(int M, int N, bool planes) {
     if (M <= 16) return N >= 19200 ? StreamShape{1, 2, 4} : StreamShape{1, 1, 4};
@@ -468,6 +504,7 @@ static StreamShape stream_shape(int M, int N, bool planes) {
     if (mb == 2 && N < 48 * 240) return {2, 2, 4};
     return {mb, 3, 2};
 }
+bool stream_resid(int M, int d) { return M <= kStreamResidRows || (M <= kStreamMaxRows && d <= 1024); }
 int gemm_stream_nsplit(int M, int N, int K, int max_split) {
     const StreamShape sh = stream_shape(M, N, true);
     const int blocks = (N + 16 * sh.nb - 1) / (16 * sh.nb);
@@ -492,7 +529,8 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
             N != (ro.n_q_heads + 2 * ro.n_kv_heads) * ro.head_dim)
             return hipErrorInvalidValue;
     }
-    if (mode == 3 && (adt == kBF16 || M > 16 || N % 16 || N > 16 * kSsqStride || !ep.res.h || !ep.res.g || !ep.res.x || !ep.res.s || !ep.res.ssq))
+    if (ep.nrm.ssq && M > 16 && (ep.nrm.n_ssq > 64 || wdt == kF32 || mode == 0)) return hipErrorInvalidValue;
+    if (mode == 3 && (adt == kBF16 || N % 16 || N > 16 * kSsqStride || !ep.res.h || !ep.res.g || !ep.res.x || !ep.res.s || !ep.res.ssq))
         return hipErrorInvalidValue;
     if (wdt == kF32) {
         if (nsplit != 1 || ep.a.row != K || (mode == 1 && ep.out.row != ep.ffn) || (mode == 3 && ep.out.row != N))
@@ -509,12 +547,15 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
     }
     const bf16_t* a = (const bf16_t*)A;
     const bf16_t* w = (const bf16_t*)W;
-    const StreamShape sh = mode == 3 ? StreamShape{1, 1, 4} : stream_shape(M, N, mode == 0);
+    if (adt == kBF16) return stream_launch<1, 1, 4, 4, false, true>(st, mode, (N + 15) / 16, nsplit, a, w, C, M, N, K, ep);
+    if (mode == 3) return M <= 16 ? stream_resid_launch<4, 4>(st, a, w, M, N, K, ep) : stream_resid_launch<8, 2>(st, a, w, M, N, K, ep);
+    if (ep.nrm.ssq && M > 16)
+        return M <= 32 ? stream_norm_launch<2>(st, mode, a, w, M, N, K, ep) : stream_norm_launch<4>(st, mode, a, w, M, N, K, ep);
+    const StreamShape sh = stream_shape(M, N, mode == 0);
     const int blocks = (N + 16 * sh.nb - 1) / (16 * sh.nb);
-    if (adt == kBF16) return stream_launch<1, 1, 4, 4, false>(st, mode, (N + 15) / 16, nsplit, a, w, C, M, N, K, ep);
-#define RLHF_STREAM(MB, NB, D)              \
+#define RLHF_STREAM(MB, NB, D)                       \
     if (sh.mb == MB && sh.nb == NB && sh.depth == D) \
-        return stream_launch<MB, NB, 4, D, true>(st, mode, blocks, nsplit, a, w, C, M, N, K, ep)
+        return stream_launch<MB, NB, 4, D, true, MB == 1>(st, mode, blocks, nsplit, a, w, C, M, N, K, ep)
     RLHF_STREAM(1, 1, 4);
     RLHF_STREAM(1, 2, 4);
     RLHF_STREAM(2, 1, 4);

@@ -105,9 +105,12 @@ struct RowsEpi {
     ResidOut res;
 };
 bool gemm_stream_supported(int wdt, int adt, int M, int K);
-constexpr int kStreamResidRows = 16;         // mode 3 and NormIn: up to this many rows
-// Mode 0 may split K into nsplit planes C [nsplit][M][N]; the split for O and down projections of more
-// than kStreamResidRows rows:
+constexpr int kStreamResidRows = 16;
+// Whether a pass over a residual stream of d columns runs on mode 3 and NormIn: any up to kStreamResidRows
+// rows; half activations of up to 64 partial sums (n_ssq, a column block of 16 each) at any row count here,
+// but not into mode 0.
+bool stream_resid(int M, int d);
+// Mode 0 may split K into nsplit planes C [nsplit][M][N]; the split for O and down projections otherwise:
 int gemm_stream_nsplit(int M, int N, int K, int max_split);
 hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const void* A, const void* W, float* C,
                               int M, int N, int K, const RowsEpi& ep, int nsplit = 1);
