@@ -6,7 +6,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librlhf.so")
-SOURCES = ["engine.cpp", "gemm.hip", "gemm_stream.hip", "gemm_tall.hip", "attention.hip", "elementwise.hip", "ops_api.cpp"]
+SOURCES = ["engine.cpp", "gemm.hip", "gemm_stream.hip", "gemm_rows.hip", "gemm_tall.hip", "attention.hip", "elementwise.hip", "ops_api.cpp"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-result",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

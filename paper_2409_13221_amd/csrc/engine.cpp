@@ -350,7 +350,7 @@ struct PassMeta {         // device pointers into a MetaRing arena
 bool stream_pass(const rlhf_ctx* c, int rows) {
     const rlhf_model_cfg& m = c->mc;
     if (c->dtype == kF32) return rows <= kStreamResidRows && m.d_model % 16 == 0;
-    return c->dtype == kBF16 && rows <= kStreamMaxRows && m.d_model % 64 == 0 && (m.n_q_heads * m.head_dim) % 64 == 0 &&
+    return c->dtype == kBF16 && rows <= kRowsMaxRows && m.d_model % 64 == 0 && (m.n_q_heads * m.head_dim) % 64 == 0 &&
            m.ffn % 64 == 0;
 }
 
@@ -374,6 +374,7 @@ NormIn stream_norm(const rlhf_ctx* c, const Workspace& ws, int n_ssq, float* s_i
 int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights& rw, int rows,
                           const PassMeta& pm, AttnMode mode, int attn_nsplit, int* pend_ns, int* n_ssq) {
     const rlhf_weights& w = rw.w;
+    const rlhf_weights& wh = rw.h16;              // half copies (members may be NULL)
     const rlhf_model_cfg& m = c->mc;
     const int d = m.d_model, qd = m.n_q_heads * m.head_dim, kvd = m.n_kv_heads * m.head_dim;
     const int qkv_w = qd + 2 * kvd, f = m.ffn, es = c->esz, dt = c->dtype;
@@ -393,23 +394,29 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
         HIPCK(c, launch_embed(st, dt, c->d_tokens, pm.tok_idx, w.embed, ws.h, rows, d, m.vocab));
     *n_ssq = 1;
     int ns = 0;
-    auto project = [&](int md, const void* A, const void* W, int N, int K, const RowsEpi& ep, int nsplit = 1) {
+    // the weights of layer l: the half copy where the kernel of this row count gains by it
+    const bool half = !resid && rows >= kRowsHalfFrom;
+    auto project = [&](int md, const void* A, const void* w_bf16, const void* w_half, int l, int N, int K, const RowsEpi& ep,
+                       int nsplit = 1) {
+        const bool hw = half && w_half;
+        const void* W = layer_ptr(hw ? w_half : w_bf16, l, N, K, es);
         const double bytes = ((double)N * K + (double)rows * K) * es + (double)rows * N * (md == 0 ? 4 : es);
         return profiled(c, st, gcls, bytes, 2.0 * rows * N * K,
-                        [&] { return launch_gemm_stream(st, dt, adt, md, A, W, ws.part, rows, N, K, ep, nsplit); });
+                        [&] { return launch_gemm_stream(st, hw ? kF16 : dt, adt, md, A, W, ws.part, rows, N, K, ep, nsplit); });
     };
     // O and down projections: finish the residual stream, or leave planes and let RMSNorm do it
-    auto into_stream = [&](const void* A, const ActLayout& la, const void* W, int K, const float* g_next, float* s) -> int {
+    auto into_stream = [&](const void* A, const ActLayout& la, const void* w_bf16, const void* w_half, int l, int K,
+                           const float* g_next, float* s) -> int {
         RowsEpi ep;
         ep.a = la;
         if (resid) {
             ep.out = packed;
             ep.res.h = ws.h; ep.res.g = g_next; ep.res.x = ws.xn; ep.res.s = s; ep.res.ssq = ws.ssq;
-            HIPCK(c, project(3, A, W, d, K, ep));
+            HIPCK(c, project(3, A, w_bf16, w_half, l, d, K, ep));
             *n_ssq = d / 16;
         } else {
-            ns = gemm_stream_nsplit(rows, d, K, cap);
-            HIPCK(c, project(0, A, W, d, K, ep, ns));
+            ns = half && w_half ? gemm_rows_nsplit(d, K, cap) : gemm_stream_nsplit(rows, d, K, cap);
+            HIPCK(c, project(0, A, w_bf16, w_half, l, d, K, ep, ns));
         }
         return RLHF_OK;
     };
@@ -430,7 +437,7 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
         ep.ro.layer = l; ep.ro.n_layers = m.n_layers;
         ep.ro.n_q_heads = m.n_q_heads; ep.ro.n_kv_heads = m.n_kv_heads; ep.ro.head_dim = m.head_dim;
         ep.ro.page_tokens = c->ec.page_tokens;
-        HIPCK(c, project(2, ws.xn, layer_ptr(w.wqkv, l, qkv_w, d, es), qkv_w, d, ep));
+        HIPCK(c, project(2, ws.xn, w.wqkv, wh.wqkv, l, qkv_w, d, ep));
         if (mode == kModeDecode) {
             HIPCK(c, profiled(c, st, kAttnDecode, pm.attn_bytes, pm.attn_flops, [&] {
                 return launch_decode_attn(st, adt, ws.q, c->pool, c->d_page_table, c->max_pages, pm.row_sample,
@@ -446,7 +453,7 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
                                            pm.row_start, pm.pos, ws.attn, rows, c->dm);
             }));
         }
-        int rc = into_stream(ws.attn, attn_layout, layer_ptr(w.wo, l, d, qd, es), qd, w.g_mlp + (size_t)l * d, sc[1]);
+        int rc = into_stream(ws.attn, attn_layout, w.wo, wh.wo, l, qd, w.g_mlp + (size_t)l * d, sc[1]);
         if (rc) return rc;
         if (!resid)
             HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, ns, plane, nullptr, w.g_mlp + (size_t)l * d, ws.xn, rows, d,
@@ -456,8 +463,8 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
         if (resid) eg.nrm = stream_norm(c, ws, *n_ssq, sc[1], sc[0]);
         eg.act = ws.act;
         eg.ffn = f;
-        HIPCK(c, project(1, ws.xn, layer_ptr(w.w_gate_up, l, 2 * (size_t)f, d, es), 2 * f, d, eg));
-        rc = into_stream(ws.act, packed, layer_ptr(w.w_down, l, d, f, es), f, gain_after(l), sc[0]);
+        HIPCK(c, project(1, ws.xn, w.w_gate_up, wh.w_gate_up, l, 2 * f, d, eg));
+        rc = into_stream(ws.act, packed, w.w_down, wh.w_down, l, f, gain_after(l), sc[0]);
         if (rc) return rc;
     }
     *pend_ns = ns;
@@ -1169,6 +1176,7 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
         RowsEpi ep;
         const int adt = act_type(c, false);
         if (adt == kF16) ep.a = ActLayout{8, 8 * R};
+        const bool hw = R >= kRowsHalfFrom && c->roles[RLHF_ACTOR].h16.head && !stream_resid(R, d);
         if (R <= kStreamResidRows)
             ep.nrm = stream_norm(c, ws, n_ssq, ws.scale, nullptr);
         else
@@ -1176,7 +1184,8 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
                                     c->mc.rms_eps, ep.a));
         const double bytes = ((double)V * d + (double)R * d) * c->esz + (double)R * V * 4;
         HIPCK(c, profiled(c, c->sd, kGemmDecode, bytes, 2.0 * R * V * d, [&] {
-            return launch_gemm_stream(c->sd, c->dtype, adt, 0, ws.xn, w.head, ws.part, R, V, d, ep);
+            return launch_gemm_stream(c->sd, hw ? kF16 : c->dtype, adt, 0, ws.xn, hw ? c->roles[RLHF_ACTOR].h16.head : w.head, ws.part, R,
+                                      V, d, ep);
         }));
     } else {
         int pns;

@@ -506,6 +506,7 @@ static StreamShape stream_shape(int M, int N, bool planes) {
 }
 bool stream_resid(int M, int d) { return M <= kStreamResidRows || (M <= kStreamMaxRows && d <= 1024); }
 int gemm_stream_nsplit(int M, int N, int K, int max_split) {
+    if (M > kStreamMaxRows) return gemm_rows_nsplit(N, K, max_split);
     const StreamShape sh = stream_shape(M, N, true);
     const int blocks = (N + 16 * sh.nb - 1) / (16 * sh.nb);
     int ns = (256 + blocks - 1) / blocks;
@@ -519,7 +520,10 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
     RowsEpi ep = ep_in;
     if (ep.a.row == 0) ep.a = ActLayout{K, 8};             // row-major unless the caller says otherwise
     if (ep.out.row == 0) ep.out = ActLayout{mode == 1 ? ep.ffn : N, 8};
-    if (!gemm_stream_supported(wdt, adt, M, K) || N <= 0 || mode < 0 || mode > 3) return hipErrorInvalidValue;
+    // more rows than this kernel holds, or a half copy to read
+    const bool rows = M > kStreamMaxRows || wdt == kF16;
+    if (!(rows ? gemm_rows_supported(wdt, adt, M, K) : gemm_stream_supported(wdt, adt, M, K)) || N <= 0 || mode < 0 || mode > 3) return hipErrorInvalidValue;
+    if (rows && (mode == 3 || ep.nrm.ssq)) return hipErrorInvalidValue;
     if ((long)8 * K * 2 >= (1L << 31)) return hipErrorInvalidValue;
     if (nsplit < 1 || (mode == 0 ? !C : nsplit != 1) || (nsplit > 1 && ep.nrm.ssq)) return hipErrorInvalidValue;
     if (mode == 1 && (!ep.act || ep.ffn <= 0 || N != 2 * ep.ffn || ep.ffn % 8)) return hipErrorInvalidValue;
@@ -530,6 +534,7 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
             return hipErrorInvalidValue;
     }
     if (ep.nrm.ssq && M > 16 && (ep.nrm.n_ssq > 64 || wdt == kF32 || mode == 0)) return hipErrorInvalidValue;
+    if (rows) return mode == 1 && ep.ffn % 16 ? hipErrorInvalidValue : launch_gemm_rows(st, wdt, mode, A, W, C, M, N, K, ep, nsplit);
     if (mode == 3 && (adt == kBF16 || N % 16 || N > 16 * kSsqStride || !ep.res.h || !ep.res.g || !ep.res.x || !ep.res.s || !ep.res.ssq))
         return hipErrorInvalidValue;
     if (wdt == kF32) {

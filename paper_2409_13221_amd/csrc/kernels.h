@@ -114,6 +114,16 @@ bool stream_resid(int M, int d);
 int gemm_stream_nsplit(int M, int N, int K, int max_split);
 hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const void* A, const void* W, float* C,
                               int M, int N, int K, const RowsEpi& ep, int nsplit = 1);
+// The same for more rows (gemm_rows.hip; launch_gemm_stream hands such calls over): modes 0..2 without
+// norms, up to kRowsMaxRows rows, half activations, bf16 weights or their half copy (wdt == kF16).
+constexpr int kRowsMaxRows = 256;
+bool gemm_rows_supported(int wdt, int adt, int M, int K);
+int gemm_rows_nsplit(int N, int K, int max_split);
+// 33..64 rows: the half copy, where there is one, and this kernel.  (Converting bf16 weights in every compute wave costs
+// it 5 us of 25-40 there, and up to 32 rows k_gemm_stream is the faster one: QKV 19 against 31.)
+constexpr int kRowsHalfFrom = 33;
+hipError_t launch_gemm_rows(hipStream_t st, int wdt, int mode, const void* A, const void* W, float* C, int M, int N, int K,
+                            const RowsEpi& ep, int nsplit);
 
 // LM head of a scoring pass fused with the log-softmax gather: the logits stay in registers.  Per
 // row m the GEMM leaves n_part = gemm_lse_partials(N) pairs (max, sum of exp(z - max)), one per 128

@@ -1,4 +1,4 @@
-"""Decode steps (and short prefills) of 1..64 rows run on the weight-streaming projections: batch sizes
+"""Decode steps (and short prefills) of 1..256 rows run on the weight-streaming projections: batch sizes
 at the edges of their row blocks, a model whose sizes leave remainders in every projection, and one
 wide enough for several weight blocks per workgroup and for K splits.  The oracle generates; log-probs,
 values and rewards are held to the tolerances of the other stage tests."""
@@ -18,13 +18,23 @@ _SMALL = replace(_GPT2S.model, n_layers=2, d_model=320, n_q_heads=5, n_kv_heads=
 _WIDE = replace(_GPT2S.model, n_layers=1, d_model=4096, n_q_heads=32, n_kv_heads=4, head_dim=128, ffn=704, vocab=4100)
 # the float model's own kernel: K with half a chunk of 16 left over, a ragged vocabulary
 _FLOAT = replace(_SMALL, d_model=208, n_q_heads=2, n_kv_heads=2, ffn=120, vocab=203, dtype="fp32")
+# fewer K steps than the ring of the kernel for many rows is deep, ragged blocks of every projection
+_SHORT = replace(_SMALL, d_model=192, n_q_heads=3, n_kv_heads=3, ffn=320, vocab=515)
 _GROUPED = replace(_SMALL, d_model=1024, n_q_heads=8, n_kv_heads=1, head_dim=128)
 
 
-@pytest.mark.parametrize("model,n", [(_SMALL, n) for n in (1, 16, 17, 32, 33, 64, 65)]
-                         + [(_WIDE, n) for n in (3, 16, 31, 64)] + [(_GROUPED, n) for n in (2, 19)] + [(_FLOAT, n) for n in (1, 9, 16, 17)])
+@pytest.mark.parametrize("model,n", [(_SMALL, n) for n in (1, 16, 17, 32, 33, 64, 65, 128, 145, 256)]
+                         + [(_WIDE, n) for n in (3, 16, 31, 64, 130)] + [(_GROUPED, n) for n in (2, 19, 70)] + [(_SHORT, n) for n in (65, 129)] + [(_FLOAT, n) for n in (1, 9, 16, 17)])
 def test_decode_batches_of_few_rows(model, n):
     cfg = _GPT2S.with_(name="few_rows", model=model, n_samples=n, prompt_len=(3, 5), gain_jitter=0.05)
     ref = H.oracle_stage(cfg, n=n, max_len=4)
     got = H.run_gpu_stage(cfg, ref, fused=False, R_t=0, chunk_tokens=64)
+    H.compare_stage(cfg, ref, got)
+
+
+@pytest.mark.parametrize("model,n", [(_WIDE, 33), (_WIDE, 130), (_SMALL, 145), (_SHORT, 66)])
+def test_decode_batches_read_half_copies(model, n):
+    cfg = _GPT2S.with_(name="few_rows_half", model=model, n_samples=n, prompt_len=(3, 5), gain_jitter=0.05)
+    ref = H.oracle_stage(cfg, n=n, max_len=4)
+    got = H.run_gpu_stage(cfg, ref, fused=False, R_t=0, chunk_tokens=64, half_weight_copies=True)
     H.compare_stage(cfg, ref, got)
