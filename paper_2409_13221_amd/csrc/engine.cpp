@@ -491,8 +491,24 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         return forward_layers_stream(c, st, ws, rw, rows, pm, mode, 1, pend_ns, &n_ssq);
     }
     HIPCK(c, launch_embed(st, dt, c->d_tokens, pm.tok_idx, w.embed, ws.h, rows, d, m.vocab));
-    int pns = 0;
-    size_t pstride = 0;
+    int pns = 0, rc_proj;
+    const size_t pstride = (size_t)rows * d;
+    // O and down projections: an unsplit tall one finishes the residual stream, the others leave pns planes that
+    // RMSNorm adds
+    auto into_stream = [&](const void* A, const void* w_bf16, const void* w_half, int l, int K) -> int {
+        pns = nsplit_for(c, ws, rows, d, K);
+        const bool tall = gemm_is_tall(rows, d, K, pns), hw = w_half && adt == kF16 && tall;
+        const void* W = layer_ptr(hw ? w_half : w_bf16, l, d, K, es);
+        if (tall && rows > 256 && pns == 1 && dt == kBF16 && d % 4 == 0) {
+            pns = 0;
+            const double bytes = ((double)d * K + (double)rows * K) * es + (double)rows * d * 8;
+            HIPCK(c, profiled(c, st, gcls, bytes, 2.0 * rows * d * K,
+                              [&] { return launch_gemm_tall_add(st, hw ? kF16 : dt, adt, A, W, ws.h, rows, d, K); }));
+        } else {
+            HIPCK(c, gemm_profiled(c, st, gcls, adt, A, W, ws.part, rows, d, K, pns, hw));
+        }
+        return RLHF_OK;
+    };
     for (int l = 0; l < m.n_layers; ++l) {
         HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, pns, pstride, nullptr, w.g_attn + (size_t)l * d,
                                 ws.xn, rows, d, m.rms_eps));
@@ -538,14 +554,10 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
                                            pm.row_start, pm.pos, ws.attn, rows, c->dm);
             }));
         }
-        ns = nsplit_for(c, ws, rows, d, qd);
-        {
-            const bool hw = wh.wo && adt == kF16 && gemm_is_tall(rows, d, qd, ns);
-            HIPCK(c, gemm_profiled(c, st, gcls, adt, ws.attn, layer_ptr(hw ? wh.wo : w.wo, l, d, qd, es), ws.part, rows,
-                                   d, qd, ns, hw));
-        }
-        HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, ns, (size_t)rows * d, nullptr,
-                                w.g_mlp + (size_t)l * d, ws.xn, rows, d, m.rms_eps));
+        rc_proj = into_stream(ws.attn, w.wo, wh.wo, l, qd);
+        if (rc_proj) return rc_proj;
+        HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, pns, pstride, nullptr, w.g_mlp + (size_t)l * d, ws.xn, rows, d,
+                                m.rms_eps));
         if (gemm_swiglu_supported(dt, adt, rows, f, d)) {
             const bool hw = wh.w_gate_up && adt == kF16 && d % 64 == 0;
             const void* wgu = layer_ptr(hw ? wh.w_gate_up : w.w_gate_up, l, 2 * (size_t)f, d, es);
@@ -559,13 +571,8 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
                                    ws.part, rows, 2 * f, d, ns, hw));
             HIPCK(c, launch_swiglu(st, adt, ws.part, ns, (size_t)rows * 2 * f, ws.act, rows, f));
         }
-        pns = nsplit_for(c, ws, rows, d, f);
-        pstride = (size_t)rows * d;
-        {
-            const bool hw = wh.w_down && adt == kF16 && gemm_is_tall(rows, d, f, pns);
-            HIPCK(c, gemm_profiled(c, st, gcls, adt, ws.act, layer_ptr(hw ? wh.w_down : w.w_down, l, d, f, es), ws.part,
-                                   rows, d, f, pns, hw));
-        }
+        rc_proj = into_stream(ws.act, w.w_down, wh.w_down, l, f);
+        if (rc_proj) return rc_proj;
     }
     *pend_ns = pns;
     *pend_stride = pstride;

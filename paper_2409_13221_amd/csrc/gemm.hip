@@ -332,7 +332,8 @@ constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 // 7B QKV at 256 rows 36 us with 4 splits, 62 with 6), eight at most (down 41 us with 8, 37 with 12 and
 // 47 with 16, but every plane costs its reader 1 us).
 // More rows, N >= 1536: a workgroup takes about 1.15 us per K tile and 4 us besides, one per compute
-// unit at a time, and a plane is written and read once at about 5 TB/s; the split with the least sum.
+// unit at a time, and a plane is written and read once at about 5 TB/s; the split with the least sum, if that is
+// a tenth below the unsplit launch (which finishes the residual stream itself and leaves no planes).
 // N = 4096: 320 rows 27 us with 8 splits (128 x 128 tiles: 32), 1024 rows 47 with 2 (65), 2048 rows 58 with
 // 2 (77 unsplit), 4160 rows 156 unsplit, though its second round is nearly empty (128 x 128 tiles: 270).
 // Narrower matrices have too few tiles of this size (N = 768, 2048 rows: 29 us against 20).
@@ -353,8 +354,8 @@ int tall_nsplit(int M, int N, int K, int max_split) {
         double best = 0;
         for (int c = 1; c <= 8 && c <= max_split && c <= (steps + 3) / 4; ++c) {
             const double rounds = (double)((tiles * c + 255) / 256);
-            const double us = rounds * (((steps + c - 1) / c) * 1.15 + 4.0) + 8.0 * M * N * c / 5e6;
-            if (c == 1 || us < best) { best = us; ns = c; }
+            const double us = rounds * (((steps + c - 1) / c) * 1.15 + 4.0) + (c == 1 ? 0.0 : 8.0 * M * N * c / 5e6);
+            if (c == 1 || us < best) { best = c == 1 ? 0.9 * us : us; ns = c; }
         }
     }
     while (ns > 1) {                             // every split gets a K range

@@ -47,6 +47,8 @@ hipError_t launch_gemm(hipStream_t st, int wdt, int adt, const void* A, const vo
 bool gemm_tall_supported(int wdt, int adt, int K);
 hipError_t launch_gemm_tall(hipStream_t st, int wdt, int adt, const void* A, const void* W, float* C, int M, int N, int K,
                             int nsplit);
+// h [M, N] += A W^T, N a multiple of 4
+hipError_t launch_gemm_tall_add(hipStream_t st, int wdt, int adt, const void* A, const void* W, float* h, int M, int N, int K);
 hipError_t launch_gemm_tall_swiglu(hipStream_t st, int wdt, int adt, const void* A, const void* W, void* act, int M, int ffn,
                                    int K);
 
