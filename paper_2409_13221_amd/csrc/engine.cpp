@@ -354,11 +354,13 @@ bool stream_pass(const rlhf_ctx* c, int rows) {
            m.ffn % 64 == 0;
 }
 
-// Norm input of a few-row projection over the residual stream: how ws.xn was scaled, and the sums of
-// squares its producer left.
-NormIn stream_norm(const rlhf_ctx* c, const Workspace& ws, int n_ssq, float* s_in, float* s_out) {
+// Norm input of a few-row projection over the residual stream: how ws.xn was scaled, the sums of squares
+// its producer left, and the stream and gain themselves.
+NormIn stream_norm(const rlhf_ctx* c, const Workspace& ws, const float* g, int n_ssq, float* s_in, float* s_out) {
     NormIn ni;
     ni.ssq = ws.ssq;
+    ni.h = ws.h;
+    ni.g = g;
     ni.n_ssq = n_ssq;
     ni.s_in = s_in;
     ni.s_out = s_out;
@@ -426,7 +428,7 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
                                     m.rms_eps, packed));
         RowsEpi ep;
         ep.a = packed;
-        if (resid) ep.nrm = stream_norm(c, ws, *n_ssq, sc[0], sc[1]);
+        if (resid) ep.nrm = stream_norm(c, ws, w.g_attn + (size_t)l * d, *n_ssq, sc[0], sc[1]);
         ep.ro.pos = pm.pos;
         ep.ro.kv_dst = pm.kv_dst;
         ep.ro.table = c->d_rope;
@@ -460,7 +462,7 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
                                     m.rms_eps, packed));
         RowsEpi eg;
         eg.a = eg.out = packed;
-        if (resid) eg.nrm = stream_norm(c, ws, *n_ssq, sc[1], sc[0]);
+        if (resid) eg.nrm = stream_norm(c, ws, w.g_mlp + (size_t)l * d, *n_ssq, sc[1], sc[0]);
         eg.act = ws.act;
         eg.ffn = f;
         HIPCK(c, project(1, ws.xn, w.w_gate_up, wh.w_gate_up, l, 2 * f, d, eg));
@@ -1185,7 +1187,7 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
         if (adt == kF16) ep.a = ActLayout{8, 8 * R};
         const bool hw = R >= kRowsHalfFrom && c->roles[RLHF_ACTOR].h16.head && !stream_resid(R, d);
         if (R <= kStreamResidRows)
-            ep.nrm = stream_norm(c, ws, n_ssq, ws.scale, nullptr);
+            ep.nrm = stream_norm(c, ws, w.g_final, n_ssq, ws.scale, nullptr);
         else
             HIPCK(c, launch_rmsnorm(c->sd, adt, ws.h, ws.part, pns, (size_t)R * d, nullptr, w.g_final, ws.xn, R, d,
                                     c->mc.rms_eps, ep.a));

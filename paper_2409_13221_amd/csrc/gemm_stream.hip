@@ -16,9 +16,14 @@
 //
 // Up to 16 rows RMSNorm costs no kernel of its own.  The projection that finishes the residual stream (O, down)
 // adds its result to h, and writes x = h * g * s (half; g the next norm's gain, s the power of two below
-// the row's previous 1/rms, which keeps x near unit scale and rounds nothing by itself) and the partial sums of h^2 of its 16 * NB columns; the
+// the row's previous 1/rms, which rounds nothing by itself) and the partial sums of h^2 of its 16 * NB columns; the
 // projection that consumes the normed row multiplies x by W as it is and scales the result of row m by
 // (1/rms_m) / s_m in its epilogue.
+// x has the size of a normed row as long as one projection does not change the row's rms much.  A row that
+// grows may leave half's range (the producer marks it in the sign of its partial sum), one that shrinks sinks
+// into half's subnormals ((1/rms) / s > kMaxShrink shows it).  Then the consuming workgroups drop what they
+// have summed and take their share of K again from h itself, normalised before the rounding to half: any
+// stream that RMSNorm as a kernel can take is taken here, and ordinary rows pay one test.
 #include "common.h"
 #include "kernels.h"
 #include <type_traits>
@@ -43,6 +48,10 @@ template <> struct StreamMfma<true> {
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef uint32_t u32x4s_t __attribute__((ext_vector_type(4)));
+
+// Largest (1/rms) / s at which x is used: an entry of x is then at least 1/64 of the normed one, and half's
+// subnormal grid (2^-24) still 256 times finer than the rounding of an entry of average size.
+constexpr float kMaxShrink = 64.f;
 
 template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
 
@@ -71,8 +80,9 @@ template <int MODE> __device__ __forceinline__ int stream_last_row(const RowsEpi
 // rows the float4 form would take 128 registers.
 template <int RPW, bool FEW> struct StreamNorm {
     float4 q0[FEW ? 1 : RPW], q1[FEW ? 1 : RPW];
-    float q[RPW];
+    float q[RPW], s_in;
     __device__ __forceinline__ void request(const NormIn& ni, int M, int w, int lane) {
+        s_in = ni.s_in[min(w * RPW + lane / (64 / RPW), M - 1)];
         if constexpr (FEW) {
 #pragma unroll
             for (int i = 0; i < RPW; ++i) q[i] = ni.ssq[(size_t)min(w * RPW + i, M - 1) * kSsqStride + lane];
@@ -87,12 +97,20 @@ template <int RPW, bool FEW> struct StreamNorm {
             if (two) q1[i] = *reinterpret_cast<const float4*>(src + 256);
         }
     }
-    __device__ __forceinline__ void reduce(const NormIn& ni, int M, int K, int w, int lane, bool first_block, float* s_scale) {
+    // s_scale[m]: factor of row m's result; s_inv[m]: 1/rms.  Returns whether a row of this wave asks for h itself.
+    __device__ __forceinline__ bool reduce(const NormIn& ni, int M, int K, int w, int lane, bool first_block, float* s_scale,
+                                           float* s_inv) {
         float v[RPW];
+        uint32_t sign = 0;
+        auto sum = [&](const float4& a, const float4& b) {
+            sign |= (__float_as_uint(a.x) | __float_as_uint(a.y)) | (__float_as_uint(a.z) | __float_as_uint(a.w)) |
+                    (__float_as_uint(b.x) | __float_as_uint(b.y)) | (__float_as_uint(b.z) | __float_as_uint(b.w));
+            return ((fabsf(a.x) + fabsf(b.x)) + (fabsf(a.y) + fabsf(b.y))) + ((fabsf(a.z) + fabsf(b.z)) + (fabsf(a.w) + fabsf(b.w)));
+        };
 #pragma unroll
         for (int i = 0; i < RPW; ++i)
-            if constexpr (FEW) v[i] = q[i];
-            else v[i] = ((q0[i].x + q1[i].x) + (q0[i].y + q1[i].y)) + ((q0[i].z + q1[i].z) + (q0[i].w + q1[i].w));
+            if constexpr (FEW) { v[i] = fabsf(q[i]); sign |= __float_as_uint(q[i]); }
+            else v[i] = sum(q0[i], q1[i]);
         // all rows at once: every exchange halves the rows a lane still carries, row lane / (64 / RPW) in the end
         int o = 32;
 #pragma unroll
@@ -107,11 +125,15 @@ template <int RPW, bool FEW> struct StreamNorm {
         for (; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, kWave);
         constexpr int LPR = 64 / RPW;
         const int m = w * RPW + lane / LPR;
+        bool redo = sign >> 31;
         if (m < M && lane % LPR == 0) {
-            const float inv = rsqrtf(v[0] / (float)K + ni.eps);
-            s_scale[m] = inv / ni.s_in[m];
+            const float inv = rsqrtf(v[0] / (float)K + ni.eps), sc = inv / s_in;
+            s_scale[m] = sc;
+            s_inv[m] = inv;
+            redo |= !(sc <= kMaxShrink);                   // NaN too
             if (first_block && ni.s_out) ni.s_out[m] = pow2_below(inv);
         }
+        return __any(redo);
     }
 };
 
@@ -225,14 +247,19 @@ template <int MB, int NB, int WAVES, int MODE, typename TO> struct StreamEpilogu
             for (int it = 0; it < OUT_IT; ++it) {          // whole waves take part: the sums below are lane shuffles
                 const int i = t + it * NT, m = i / R16, r = i % R16, nn = blk * R16 + r;
                 float v = 0.f;
+                bool over = false;
                 if (m < M && nn < N) {
                     v = pre_a[it] + total(r, m);
+                    const float xv = v * pre_b[it];
+                    over = sizeof(TO) == 2 && fabsf(xv) > 65504.f;
                     rz.h[(size_t)m * N + nn] = v;
-                    x[act_index(ep.out, m, nn)] = from_f32<TO>(v * pre_b[it]);
+                    x[act_index(ep.out, m, nn)] = from_f32<TO>(xv);
                 }
                 float q = v * v;
 #pragma unroll
                 for (int o = 1; o < R16; o <<= 1) q += __shfl_xor(q, o, kWave);
+                static_assert(MODE != 3 || R16 == 16, "the lanes of a row are 16 neighbours");
+                if (__ballot(over) >> (t & 48) & 0xFFFF) q = -q;
                 if (m < M && r == 0) rz.ssq[(size_t)m * kSsqStride + blk] = q;
             }
         }
@@ -251,7 +278,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
     constexpr int MP = MB * 16 + 1;
     constexpr int kRed = WAVES * NB * 16 * MP;             // floats
     __shared__ __attribute__((aligned(16))) uint8_t smem[kRing * 2 > kRed * 4 ? kRing * 2 : kRed * 4];
-    __shared__ float s_scale[MB * 16];
+    __shared__ float s_scale[MB * 16], s_inv[MB * 16];
+    __shared__ int s_redo[WAVES];
     const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int fr = lane & 15, fq = lane >> 4;
     const int blk = blockIdx.x;
@@ -296,7 +324,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
     const size_t a_half = (size_t)4 * ep.a.chunk;          // elements from one 32-k half of a step to the next
 
     // requested before everything else
-    const bool normed = NORM && ep.nrm.ssq != nullptr;
+    bool normed = NORM && ep.nrm.ssq != nullptr;
     StreamNorm<MB * 16 / WAVES, (MB > 1)> norm;
     if (normed) norm.request(ep.nrm, M, w, lane);
     StreamEpilogue<MB, NB, WAVES, MODE, TO> epi;
@@ -356,7 +384,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
 #pragma unroll
     for (int j = 0; j < D; ++j) RLHF_ST_ISSUE(j, j);
     epi.request_table(ep, M, blk, t);
-    if (normed) norm.reduce(ep.nrm, M, K, w, lane, blk == 0, s_scale);
+    if (normed) {
+        const bool redo = norm.reduce(ep.nrm, M, K, w, lane, blk == 0, s_scale, s_inv);
+        if (lane == 0) s_redo[w] = redo;
+    }
     int k = 0;
     for (; k + D < n; k += D) {
 #pragma unroll
@@ -379,15 +410,54 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
 #undef RLHF_ST_CONSUME
 
     // ---- the waves' shares of K meet in LDS: red[wave][weight row][activation row]
-    __syncthreads();
     float* red = reinterpret_cast<float*>(smem);
+    auto put = [&] {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                red[(w * NB * 16 + nb * 16 + fq * 4 + e) * MP + mb * 16 + fr] = acc[nb][mb][e];
+                for (int e = 0; e < 4; ++e)
+                    red[(w * NB * 16 + nb * 16 + fq * 4 + e) * MP + mb * 16 + fr] = acc[nb][mb][e];
+    };
+    __syncthreads();
+    [[maybe_unused]] const bool redo = NORM && AF16 && normed && lane < WAVES && s_redo[lane];
+    put();
+    if constexpr (NORM && AF16) {
+        if (__builtin_expect(__any(redo), 0)) {            // all rows of the workgroup, from the residual stream
+            normed = false;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int k32 = 0; k32 < 2 * n_real; ++k32) {
+                const int kk = s0 * 64 + k32 * 32 + fq * 8;
+                frag_t fx[MB];
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    const int m = min(mb * 16 + fr, M - 1);
+                    float hv[8], gv[8];
+                    load8<float>(ep.nrm.h + (size_t)m * K + kk, hv);
+                    load8<float>(ep.nrm.g + kk, gv);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) fx[mb][e] = (f16_t)(hv[e] * s_inv[m] * gv[e]);
+                }
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    const int base = stream_wrow<MODE>(ep, N, blk * NB + nb, fr >> 3);
+                    const int row = base + min(fr & 7, max(stream_last_row<MODE>(ep, N, fr >> 3) - base, 0));
+                    u32x4s_t x = *reinterpret_cast<const u32x4s_t*>(W + (size_t)row * K + kk);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = bf16x2_to_f16x2(x[e]);
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+                        acc[nb][mb] = StreamMfma<AF16>::run(*reinterpret_cast<const frag_t*>(&x), fx[mb], acc[nb][mb]);
+                }
+            }
+            put();
+        }
+    }
     __syncthreads();
     epi.finish(ep, red, s_scale, normed, C, M, N, blk, t);
 #endif
@@ -403,7 +473,7 @@ __global__ __launch_bounds__(512) void k_gemm_stream_f32(const float* __restrict
                                                          float* __restrict__ C, int M, int N, int K, const RowsEpi ep) {
     constexpr int WAVES = 8, U = 4, MP = 17;
     __shared__ float red[WAVES * 16 * MP];
-    __shared__ float s_scale[16];
+    __shared__ float s_scale[16], s_inv[16];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, fr = lane & 15, fq = lane >> 4, blk = blockIdx.x;
     const bool normed = MODE != 3 && ep.nrm.ssq != nullptr;
     StreamNorm<2, false> norm;
@@ -435,7 +505,7 @@ __global__ __launch_bounds__(512) void k_gemm_stream_f32(const float* __restrict
         }
     }
     epi.request_table(ep, M, blk, t);
-    if (normed) norm.reduce(ep.nrm, M, K, w, lane, blk == 0, s_scale);
+    if (normed) norm.reduce(ep.nrm, M, K, w, lane, blk == 0, s_scale, s_inv);     // float x: any jump fits
 #pragma unroll
     for (int e = 0; e < 4; ++e) red[(w * 16 + fq * 4 + e) * MP + fr] = acc[e];
     __syncthreads();
@@ -533,6 +603,7 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
             N != (ro.n_q_heads + 2 * ro.n_kv_heads) * ro.head_dim)
             return hipErrorInvalidValue;
     }
+    if (ep.nrm.ssq && wdt == kBF16 && (!ep.nrm.h || !ep.nrm.g)) return hipErrorInvalidValue;
     if (ep.nrm.ssq && M > 16 && (ep.nrm.n_ssq > 64 || wdt == kF32 || mode == 0)) return hipErrorInvalidValue;
     if (rows) return mode == 1 && ep.ffn % 16 ? hipErrorInvalidValue : launch_gemm_rows(st, wdt, mode, A, W, C, M, N, K, ep, nsplit);
     if (mode == 3 && (adt == kBF16 || N % 16 || N > 16 * kSsqStride || !ep.res.h || !ep.res.g || !ep.res.x || !ep.res.s || !ep.res.ssq))

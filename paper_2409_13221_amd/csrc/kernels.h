@@ -86,6 +86,9 @@ constexpr int kStreamMaxRows = 64;
 constexpr int kSsqStride = 512; // floats per row of the partial sums of squares (d_model <= 8192, 16 columns each)
 struct NormIn {                 // modes 0..2: A holds x = h * gain * s_in; result of row m times (1/rms) / s_in[m]
     const float* ssq = nullptr;     // [M, kSsqStride] partial sums of h^2 (n_ssq used, the others zero), or NULL: A is used as it is
+                                    // sign bit set: an x among those columns left half's range
+    const float* h = nullptr;       // [M, K] residual stream and
+    const float* g = nullptr;       // [K] gain: half models take the norm from these where x will not do
     int n_ssq = 0;
     const float* s_in = nullptr;    // [M]
     float* s_out = nullptr;         // [M] receives the power of two below 1/rms (may be NULL)
@@ -96,7 +99,7 @@ struct ResidOut {               // mode 3
     const float* g = nullptr;       // [N] gain of the norm that follows
     void* x = nullptr;              // [M, N] in the activation type: h * g * s
     const float* s = nullptr;       // [M] scale that keeps x in half's range (power of two below the row's previous 1/rms)
-    float* ssq = nullptr;           // [M, kSsqStride] partial sums of h^2, one per 16 columns
+    float* ssq = nullptr;           // [M, kSsqStride] partial sums of h^2, one per 16 columns (sign as in NormIn)
 };
 struct RowsEpi {
     ActLayout a, out;          // layout of A; of act (mode 1) or x (mode 3)
