@@ -417,7 +417,7 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
             HIPCK(c, project(3, A, w_bf16, w_half, l, d, K, ep));
             *n_ssq = d / 16;
         } else {
-            ns = half && w_half ? gemm_rows_nsplit(d, K, cap) : gemm_stream_nsplit(rows, d, K, cap);
+            ns = gemm_stream_nsplit(rows, d, K, cap);
             HIPCK(c, project(0, A, w_bf16, w_half, l, d, K, ep, ns));
         }
         return RLHF_OK;

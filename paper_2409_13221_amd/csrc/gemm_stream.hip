@@ -194,7 +194,7 @@ template <int MB, int NB, int WAVES, int MODE, typename TO> struct StreamEpilogu
                 if (oc < ep.ffn) {
                     const float sc = normed ? s_scale[m] : 1.f;
                     const float g = total(lr, m) * sc, u = total(lr + 8, m) * sc;
-                    act[act_index(ep.out, m, oc)] = from_f32<TO>(g / (1.f + __expf(-g)) * u);
+                    act[act_index(ep.out, m, oc)] = mul_to<TO>(g / (1.f + __expf(-g)), u);
                 }
             }
         }
@@ -582,7 +582,9 @@ int gemm_stream_nsplit(int M, int N, int K, int max_split) {
     int ns = (256 + blocks - 1) / blocks;
     ns = ns < (K >> 6) / 8 ? ns : (K >> 6) / 8;            // at least two steps of 64 per wave
     ns = ns < max_split ? ns : max_split;
-    return ns < 1 ? 1 : ns;
+    if (ns < 1) ns = 1;
+    while (ns > 1 && (ns - 1) * 4 * (((K >> 6) + 4 * ns - 1) / (4 * ns)) >= K >> 6) --ns;      // every plane gets a K range
+    return ns;
 }
 
 hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const void* A, const void* W, float* C, int M,

@@ -123,9 +123,10 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
 // norms, up to kRowsMaxRows rows, half activations, bf16 weights or their half copy (wdt == kF16).
 constexpr int kRowsMaxRows = 256;
 bool gemm_rows_supported(int wdt, int adt, int M, int K);
-int gemm_rows_nsplit(int N, int K, int max_split);
-// 33..64 rows: the half copy, where there is one, and this kernel.  (Converting bf16 weights in every compute wave costs
-// it 5 us of 25-40 there, and up to 32 rows k_gemm_stream is the faster one: QKV 19 against 31.)
+int gemm_rows_nsplit(int N, int K, int max_split);          // beyond 64 rows
+// 33..64 rows: the half copy, where there is one, and this kernel, which then gives the bits of k_gemm_stream over the
+// bf16 weights.  (Converting them in every compute wave costs it 5 us of 25-40 there, and up to 32 rows k_gemm_stream
+// is the faster one: QKV 19 against 31.)
 constexpr int kRowsHalfFrom = 33;
 hipError_t launch_gemm_rows(hipStream_t st, int wdt, int mode, const void* A, const void* W, float* C, int M, int N, int K,
                             const RowsEpi& ep, int nsplit);
