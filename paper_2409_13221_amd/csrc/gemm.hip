@@ -458,8 +458,8 @@ static hipError_t launch_bf16(hipStream_t st, int variant, const bf16_t* a, cons
         }
         case 5: RLHF_GEMM(128, 128, 64, 2, 2, true); break;
         case 6: RLHF_GEMM(256, 128, 32, 2, 2, true); break;
-        case 7:                                                  // gemm_tall.hip, unless K leaves a remainder
-            if (K % 64 == 0) return launch_gemm_tall(st, kBF16, AF16 ? kF16 : kBF16, a, w, C, M, N, K, nsplit);
+        case 7:                                                  // gemm_tall.hip, unless K leaves a remainder or a split without a range
+            if (K % 64 == 0 && (long)(nsplit - 1) * kchunk < K) return launch_gemm_tall(st, kBF16, AF16 ? kF16 : kBF16, a, w, C, M, N, K, nsplit);
             RLHF_GEMM(256, 256, 64, 4, 2, true);
             break;
         default: return hipErrorInvalidValue;
