@@ -324,6 +324,23 @@ constexpr TileCfg kCfgs[] = {
 };
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 
+// K split of the 128 x 128 tiles.  Every split writes a float plane of M x N that the consumer reads back, which at
+// these M is no longer small beside the weights: the split that minimises (weight bytes + plane bytes) / (share of
+// the chip in use), 384 workgroups filling it.
+int split_128(int M, int N, int K, int max_split) {
+    const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
+    const int kmax = K / 256 > 0 ? K / 256 : 1;                   // keep >= 4 K tiles per split
+    const double wbytes = 2.0 * N * K, plane = 8.0 * M * N;
+    double best = 0;
+    int ns = 1;
+    for (int c = 1; c <= kmax && c <= max_split; c *= 2) {
+        const double fill = (double)(tiles * c) / 384.0;
+        const double cost = (wbytes + plane * c) / (fill < 1.0 ? fill : 1.0);
+        if (c == 1 || cost < best) { best = cost; ns = c; }
+    }
+    return ns;
+}
+
 // Few rows: the smallest row tile that holds them, weights streamed once, K split.  Many rows: the tall
 // kernel.  In between, and for narrow matrices, 128 x 128 tiles with K split.
 // K split of the tall kernel (gemm_tall.hip), 0 where another tiling is the better one.
@@ -331,12 +348,22 @@ constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 // close to, and never exceed, one workgroup per compute unit (a second round costs more than it adds:
 // 7B QKV at 256 rows 36 us with 4 splits, 62 with 6), eight at most (down 41 us with 8, 37 with 12 and
 // 47 with 16, but every plane costs its reader 1 us).
-// More rows, N >= 1536: a workgroup takes about 1.15 us per K tile and 4 us besides, one per compute
+// More rows: the kernel and split with the least cost.  Up to 511 rows, or N below 4096:
+//   tall        rounds * (1.1 us a K tile + 11) and 8 bytes of plane at 6.5 TB/s an output; unsplit it finishes the
+//               residual stream: 16 instead of 11, 4 bytes.  A round is 32 workgroups on the XCD that has most: tile
+//               columns are dealt to the XCDs (tile_walk.h), so that N = 1280 has 160 compute units, N = 1024 128.
+//   128 x 128   512 workgroups a round, two a compute unit: 1.3 us a K tile and 5.5, 1.15 in a last round of at
+//               most 256; planes as above.  Taken where it is 5 % cheaper (it reads bf16 weights only).
+// (Fitted to 257..16384 rows of N = 512..2048, O and down with the RMSNorm behind them, to 6 %; over those and
+// 257..511 rows of QKV and gate||up at N = 1536..57344 the choice is 2 % above the best measured on average and at
+// most 1 % above 128 x 128 with its split.  300 rows of N = K = 1536: 20.7 us with 128 x 128 and 4 splits, 26.5
+// tall; 8192 rows of N = 1280, K = 3456: 170 against 120 tall, 109 with half weights.)  Up to N = 1024 the tall
+// kernel, with half the compute units or fewer, never wins (16384 rows of N = 1024: 117 against 103).
+// From 512 rows and N = 4096 on: a workgroup takes about 1.15 us per K tile and 4 us besides, one per compute
 // unit at a time, and a plane is written and read once at about 5 TB/s; the split with the least sum, if that is
 // a tenth below the unsplit launch (which finishes the residual stream itself and leaves no planes).
-// N = 4096: 320 rows 27 us with 8 splits (128 x 128 tiles: 32), 1024 rows 47 with 2 (65), 2048 rows 58 with
-// 2 (77 unsplit), 4160 rows 156 unsplit, though its second round is nearly empty (128 x 128 tiles: 270).
-// Narrower matrices have too few tiles of this size (N = 768, 2048 rows: 29 us against 20).
+// N = 4096: 1024 rows 47 us with 2 splits (128 x 128 tiles: 65), 2048 rows 58 with 2 (77 unsplit), 4160 rows 156
+// unsplit, though its second round is nearly empty (128 x 128 tiles: 270).
 int tall_nsplit(int M, int N, int K, int max_split) {
     if (K % 64 || M <= 128) return 0;
     const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
@@ -349,8 +376,23 @@ int tall_nsplit(int M, int N, int K, int max_split) {
         if (ns > 8) ns = 8;
         if (ns > max_split) ns = max_split;
         if (ns < 1 || tiles * ns < 120) return 0;
+    } else if (N < 4096 || M < 512) {
+        if (N <= 1024) return 0;
+        const double plane = 8.0 * M * N / 6.5e6;
+        const long per_xcd = (long)((M + 255) / 256) * xcd_cols((N + 255) / 256);
+        double best = 0;
+        for (int c : {1, 2, 3, 4, 6, 8}) {
+            if (c > max_split || c > (steps + 3) / 4 || (c - 1) * ((steps + c - 1) / c) >= steps) continue;
+            const double rounds = (double)((per_xcd * c + 31) / 32);
+            const double us = c == 1 ? rounds * (steps * 1.1 + 16.0) + plane / 2
+                                     : rounds * (((steps + c - 1) / c) * 1.1 + 11.0) + plane * c;
+            if (c == 1 || us < best) { best = us; ns = c; }
+        }
+        const int n4 = split_128(M, N, K, max_split), s4 = (steps + n4 - 1) / n4;
+        const long wgs = (long)((M + 127) / 128) * ((N + 127) / 128) * n4, full = wgs / 512, rest = wgs % 512;
+        const double us4 = full * (s4 * 1.3 + 5.5) + (rest ? s4 * (rest <= 256 ? 1.15 : 1.3) + 5.5 : 0.0) + plane * n4;
+        if (us4 * 1.05 < best) return 0;
     } else {
-        if (N < 1536) return 0;
         double best = 0;
         for (int c = 1; c <= 8 && c <= max_split && c <= (steps + 3) / 4; ++c) {
             const double rounds = (double)((tiles * c + 255) / 256);
@@ -370,8 +412,8 @@ int pick_variant(int M, int N, int K, int nsplit = 0) {
     if (M <= 16) return 1;
     if (M <= 32) return 2;
     if (M <= 64) return 3;
-    if (M <= 256) return nsplit > 0 && tall_nsplit(M, N, K, nsplit) == nsplit ? 7 : 4;
-    if (K % 64 == 0) return N >= 1536 ? 7 : 4;
+    if (K % 64 == 0 && M >= 512 && N >= 4096) return 7;
+    if (K % 64 == 0 || M <= 256) return nsplit > 0 && tall_nsplit(M, N, K, nsplit) == nsplit ? 7 : 4;
     const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
     const long rounds = (tiles + 255) / 256;            // one 256 x 256 tile per compute unit at a time
     return tiles * 10 >= rounds * 256 * 6 ? 7 : 4;      // at least 60 % of the tile slots filled
@@ -409,17 +451,7 @@ int gemm_choose_nsplit(int wdt, int M, int N, int K, int max_split) {
     const int kmax = K / (4 * kgran) > 0 ? K / (4 * kgran) : 1;   // keep >= 4 K tiles per split
     int ns;
     if (tm >= 128) {
-        // 128-row tiles: every split writes a float plane of M x N that the consumer reads back,
-        // which at these M is no longer small beside the weights.  Take the split that minimises
-        // (weight bytes + plane bytes) / (share of the chip in use), 384 workgroups filling it.
-        const double wbytes = 2.0 * N * K, plane = 8.0 * M * N;
-        double best = 0;
-        ns = 1;
-        for (int c = 1; c <= kmax && c <= max_split; c *= 2) {
-            const double fill = (double)(tiles * c) / 384.0;
-            const double cost = (wbytes + plane * c) / (fill < 1.0 ? fill : 1.0);
-            if (c == 1 || cost < best) { best = cost; ns = c; }
-        }
+        ns = split_128(M, N, K, max_split);
     } else {
         ns = (int)((kTargetBlocks + tiles - 1) / tiles);
     }
