@@ -507,14 +507,23 @@ static bool half_offsets_ok(int wdt, long M, long N, long K) {
     return wdt != kF16 || ((M > N ? M : N) * K * 2 < (1L << 32));
 }
 
-bool gemm_swiglu_supported(int wdt, int adt, int M, int ffn, int K) {
+static bool swiglu_shape_ok(int wdt, int adt, int M, int ffn, int K) {
     return (wdt == kBF16 || wdt == kF16) && half_weights_ok(wdt, adt, K) && (adt == kF16 || adt == kBF16) && M > 256 &&
            ffn % 8 == 0 && K % 8 == 0;
 }
 
+// Below 448 rows the fused launch has to have more than half a round of tiles, as in gemm_rope_supported; its epilogue is
+// the lighter one, so that from 448 on it is level with the others at few tiles too.  us, bf16 weights, 300 / 511 rows,
+// fused and best other: N = 4096 24 and 20 / 24 and 25, 8192 39 and 31 / 39 and 35, 16384 69 and 59 / 71 and 65;
+// N = 22016 (172 tiles) 95 and 104 / 94 and 109.
+bool gemm_swiglu_supported(int wdt, int adt, int M, int ffn, int K) {
+    return swiglu_shape_ok(wdt, adt, M, ffn, K) &&
+           (M >= 512 || (K % 64 == 0 && (M >= 448 || (M + 255) / 256 * ((2L * ffn + 255) / 256) > 128)));
+}
+
 hipError_t launch_gemm_swiglu(hipStream_t st, int wdt, int adt, const void* A, const void* W_gate_up,
                               void* act, int M, int ffn, int K) {
-    if (!gemm_swiglu_supported(wdt, adt, M, ffn, K) || !half_offsets_ok(wdt, M, 2L * ffn, K)) return hipErrorInvalidValue;
+    if (!swiglu_shape_ok(wdt, adt, M, ffn, K) || !half_offsets_ok(wdt, M, 2L * ffn, K)) return hipErrorInvalidValue;
     if (K % 64 == 0) return launch_gemm_tall_swiglu(st, wdt, adt, A, W_gate_up, act, M, ffn, K);
     constexpr int TM = 256, TN = 256;
     const int N = 2 * ffn;
