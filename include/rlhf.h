@@ -142,11 +142,11 @@ typedef struct rlhf_stage_opts {
     int32_t fused;                 /* 1: score retired samples on the score stream while
                                       decoding goes on (Section 4); 0: generate everything,
                                       then score (the serial plan of Figure 4, top); 2: the
-                                      library chooses: the serial plan when a decode step of this
-                                      model is bound by kernel launches rather than by streaming
-                                      its weights (small models, where a second stream has nothing
-                                      idle to fill), else the fused one; rlhf_stage_stats.fused_used
-                                      tells which                                               */
+                                      library chooses: the serial plan when the samples have about
+                                      one scoring pass of tokens or less, so that nothing would run
+                                      beside anything, and a decode step of this model is bound by
+                                      kernel launches rather than by streaming its weights; else the
+                                      fused one; rlhf_stage_stats.fused_used tells which        */
     int32_t R_t;                   /* Section 4.2 trigger: scoring is enabled once the number
                                       of samples still in generation is below R_t.  R_t >
                                       n_samples enables it from the first retirement          */

@@ -1567,18 +1567,24 @@ extern "C" int rlhf_score(rlhf_ctx* c, int32_t n, const int32_t* sample_ids, uin
 // ================================================================================ run stage
 
 namespace {
-// A decode step is launch-bound when its chain of dependent kernels (about ten per layer, each
-// at least ~5 us however small) takes longer than streaming the step's weights at ~5 TB/s.  Then
-// a second stream has no idle bandwidth or matrix time to fill and only adds event traffic: the
-// serial plan is the faster one (measured: 0.81x and 0.93x for the fused plan on the two small
-// shapes, 1.03-1.05x on the three large ones).
-bool decode_is_launch_bound(const rlhf_ctx* c) {
+// Whether the serial plan is the faster one for the submitted samples.  Scoring passes gain by running beside
+// decode steps whatever bounds these, as soon as there is more than one pass of them: with passes of 8192 tokens,
+// serial / fused time 1.03-1.12 for the 2-layer float model from 9.7 k prompt + response tokens on, 1.01-1.05 for
+// d_model 512 to 1536 from 11 k, 1.03 at 2048 and 3072, 1.02 at 4096, 1.01 at 5120 and 8192.  With one pass nothing
+// runs beside anything and the second stream only adds its events: 0.96 and 0.98 for the float model (0.6 k and
+// 5 k tokens), 0.995-0.998 for d_model 512 to 2048 (6-9.5 k), 0.999 at 4096 (smaller passes may overlap there).
+// So: few tokens, and a decode step whose chain of dependent kernels (five a layer where the few-row kernels
+// finish the residual stream, else seven; at least ~4 us each) takes longer than streaming its weights at ~5 TB/s.
+bool serial_is_faster(const rlhf_ctx* c) {
+    int64_t tokens = 0;
+    for (const Sample& s : c->smp) tokens += s.P + s.target;
+    if (tokens >= 10000) return false;
     const rlhf_model_cfg& m = c->mc;
     const double qd = (double)m.n_q_heads * m.head_dim, kvd = (double)m.n_kv_heads * m.head_dim;
     const double per_layer = (qd + 2 * kvd) * m.d_model + m.d_model * qd + 3.0 * m.d_model * m.ffn;
     const double stream_us = (m.n_layers * per_layer + (double)m.vocab * m.d_model) * c->esz / 5.0e6;
-    const double launch_us = (10.0 * m.n_layers + 4) * 5.0;
-    return stream_us < launch_us;
+    const int launches = stream_resid(std::min(c->N, c->ec.max_active), m.d_model) ? 5 : 7;
+    return stream_us < (launches * m.n_layers + 6) * 4.0;
 }
 }  // namespace
 
@@ -1587,7 +1593,7 @@ extern "C" int rlhf_run_stage(rlhf_ctx* c, const rlhf_stage_opts* opts, rlhf_sta
     if (!opts) return c->fail(RLHF_EINVAL, "rlhf_run_stage: NULL options");
     if (opts->fused < 0 || opts->fused > 2) return c->fail(RLHF_EINVAL, "rlhf_run_stage: fused must be 0, 1 or 2");
     rlhf_stage_opts resolved = *opts;
-    if (resolved.fused == 2) resolved.fused = decode_is_launch_bound(c) ? 0 : 1;
+    if (resolved.fused == 2) resolved.fused = serial_is_faster(c) ? 0 : 1;
     const rlhf_stage_opts* o = &resolved;
     if (c->step != 0 || !c->retired.empty()) return c->fail(RLHF_ESTATE, "rlhf_run_stage: call rlhf_submit first");
     if (o->role_mask & ~0xFu) return c->fail(RLHF_EINVAL, "rlhf_run_stage: unknown role bits");
