@@ -780,8 +780,8 @@ extern "C" int rlhf_load_weights(rlhf_ctx* c, int role, const rlhf_weights* w) {
             {w->w_down, &rw.h16.w_down, L * d * f, d * f},
             {w->head, &rw.h16.head, (role == RLHF_ACTOR || role == RLHF_REF) ? (size_t)m.vocab * d : 0, (size_t)m.vocab * d},
         };
-        // the kernels that take the copies address an operand with 32-bit byte offsets: a matrix, or a pass's
-        // activations, of 4 GiB or more stays on the bf16-weight path
+        // launches with copies are for operands below 4 GiB: a matrix, or a pass's activations, beyond that stays on
+        // the bf16-weight path
         const size_t lim = (size_t)1 << 32;
         const bool acts_fit = (size_t)c->ec.max_batch_tokens * std::max(d, f) * 2 < lim;
         for (const Item& it : items) {

@@ -307,7 +307,8 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A,
 namespace {
 // Tilings.  Variants 1-4 stream the weights for few rows (split along K); 5-7 are the
 // compute-bound tilings of prefill / scoring passes.  Measured at M = 8192 on the 7B layer
-// shapes (half activations): 5: 650-820, 6: 800-900, 7: 950-1050 TFLOP/s.  Tried and dropped:
+// shapes (half activations): 5: 650-820, 6: 800-900, 7: 950-1050 TFLOP/s (7 is gemm_tall.hip since, wherever K is a
+// multiple of 64: 1320-1470 with half weights, 1080-1200 with bf16).  Tried and dropped:
 // 256x256 with four 128x128 wave tiles (750-830), global loads two tiles ahead (no change: L2
 // latency is already hidden), fragment loads software-pipelined against the MFMAs (-5 %),
 // 256x256 with 32-wide K tiles (half the LDS and fewer registers, so that a decode workgroup fits
@@ -500,13 +501,6 @@ static hipError_t launch_bf16(hipStream_t st, int variant, const bf16_t* a, cons
     return hipGetLastError();
 }
 
-// wdt == kF16: the matrix is a half copy of the bf16 weights and goes global -> LDS directly.
-static bool half_weights_ok(int wdt, int adt, int K) { return wdt != kF16 || (adt == kF16 && K % 64 == 0); }
-// the half-weight kernels address both operands with 32-bit byte offsets per lane
-static bool half_offsets_ok(int wdt, long M, long N, long K) {
-    return wdt != kF16 || ((M > N ? M : N) * K * 2 < (1L << 32));
-}
-
 static bool swiglu_shape_ok(int wdt, int adt, int M, int ffn, int K) {
     return (wdt == kBF16 || wdt == kF16) && half_weights_ok(wdt, adt, K) && (adt == kF16 || adt == kBF16) && M > 256 &&
            ffn % 8 == 0 && K % 8 == 0;
@@ -523,7 +517,7 @@ bool gemm_swiglu_supported(int wdt, int adt, int M, int ffn, int K) {
 
 hipError_t launch_gemm_swiglu(hipStream_t st, int wdt, int adt, const void* A, const void* W_gate_up,
                               void* act, int M, int ffn, int K) {
-    if (!swiglu_shape_ok(wdt, adt, M, ffn, K) || !half_offsets_ok(wdt, M, 2L * ffn, K)) return hipErrorInvalidValue;
+    if (!swiglu_shape_ok(wdt, adt, M, ffn, K) || !half_operands_ok(wdt, M, 2L * ffn, K)) return hipErrorInvalidValue;
     if (K % 64 == 0) return launch_gemm_tall_swiglu(st, wdt, adt, A, W_gate_up, act, M, ffn, K);
     constexpr int TM = 256, TN = 256;
     const int N = 2 * ffn;
@@ -544,7 +538,7 @@ hipError_t launch_gemm(hipStream_t st, int wdt, int adt, const void* A, const vo
     if (nsplit < 1 || K <= 0) return hipErrorInvalidValue;
     if (wdt == kF16) {
         // half copy of a bf16 matrix: the tall tiling with both operands global -> LDS directly
-        if (adt != kF16 || K % 64 || (variant != 0 && variant != 7) || !half_offsets_ok(wdt, M, N, K))
+        if (adt != kF16 || K % 64 || (variant != 0 && variant != 7) || !half_operands_ok(wdt, M, N, K))
             return hipErrorInvalidValue;
         return launch_gemm_tall(st, wdt, adt, A, W, C, M, N, K, nsplit);
     }

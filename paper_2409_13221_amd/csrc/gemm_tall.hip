@@ -488,8 +488,10 @@ hipError_t tall_launch(hipStream_t st, int wdt, int adt, const void* A, const vo
 #define RLHF_TALL(AF, CV)                                                                                              \
     k_gemm_tall<AF, CV, EPI><<<grid, 512, 0, st>>>((const bf16_t*)A, (const bf16_t*)W, (float*)C, M, N, K, kchunk, tiles_m, \
                                                    tiles_n, ro, lo)
-    if (adt == kBF16) RLHF_TALL(false, false);
-    else if (wdt == kF16) RLHF_TALL(true, false);
+    if (adt == kBF16) {
+        if constexpr (EPI == kTallAdd) return hipErrorInvalidValue;           // the stage's activations are half
+        else RLHF_TALL(false, false);
+    } else if (wdt == kF16) RLHF_TALL(true, false);
     else RLHF_TALL(true, true);
 #undef RLHF_TALL
     return hipGetLastError();
@@ -522,12 +524,6 @@ hipError_t launch_gemm_tall_swiglu(hipStream_t st, int wdt, int adt, const void*
 
 // ---- tall passes with the consumer in the epilogue
 
-// wdt == kF16: the matrix is a half copy of the bf16 weights; callers bound both operands by 4 GiB
-static bool half_weights_ok(int wdt, int adt, int K) { return wdt != kF16 || (adt == kF16 && K % 64 == 0); }
-static bool half_offsets_ok(int wdt, long M, long N, long K) {
-    return wdt != kF16 || ((M > N ? M : N) * K * 2 < (1L << 32));
-}
-
 static bool rope_shape_ok(int wdt, int adt, int M, int K, int head_dim) {
     return (wdt == kBF16 || wdt == kF16) && half_weights_ok(wdt, adt, K) && (adt == kF16 || adt == kBF16) && M > 256 &&
            K % 64 == 0 && (head_dim == 64 || head_dim == 128);
@@ -546,7 +542,7 @@ hipError_t launch_gemm_rope(hipStream_t st, int wdt, int adt, const void* A, con
     if (!rope_shape_ok(wdt, adt, M, K, ro.head_dim) || !ro.pos || !ro.table || !ro.q || (ro.pool && !ro.kv_dst))
         return hipErrorInvalidValue;
     const int N = (ro.n_q_heads + 2 * ro.n_kv_heads) * ro.head_dim;
-    if (!half_offsets_ok(wdt, M, N, K)) return hipErrorInvalidValue;
+    if (!half_operands_ok(wdt, M, N, K)) return hipErrorInvalidValue;
     return ro.head_dim == 128 ? tall_launch<kTallRope128>(st, wdt, adt, A, Wqkv, nullptr, M, N, K, 1, ro, LseOut{})
                               : tall_launch<kTallRope64>(st, wdt, adt, A, Wqkv, nullptr, M, N, K, 1, ro, LseOut{});
 }
@@ -561,7 +557,7 @@ hipError_t launch_gemm_lse(hipStream_t st, int wdt, int adt, const void* A, cons
                            const LseOut& lo) {
     if (M <= 0) return hipSuccess;
     if (!gemm_lse_supported(wdt, adt, K) || N <= 0 || !lo.tokens || !lo.target_idx || !lo.part_max || !lo.part_sum ||
-        !lo.tgt || lo.n_part != gemm_lse_partials(N) || !half_offsets_ok(wdt, M, N, K))
+        !lo.tgt || lo.n_part != gemm_lse_partials(N) || !half_operands_ok(wdt, M, N, K))
         return hipErrorInvalidValue;
     return tall_launch<kTallLse>(st, wdt, adt, A, W_head, nullptr, M, N, K, 1, RopeOut{}, lo);
 }

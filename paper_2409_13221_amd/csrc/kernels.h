@@ -43,11 +43,16 @@ hipError_t launch_bf16_to_half(hipStream_t st, const void* src, void* dst, size_
 hipError_t launch_gemm(hipStream_t st, int wdt, int adt, const void* A, const void* W, float* C,
                        int M, int N, int K, int nsplit, int variant = 0);
 
+// wdt == kF16: the matrix is a half copy of bf16 weights, for half activations.  The entry points promise such calls for
+// operands below 4 GiB only; k_gemm_tall itself takes a 64-bit base per tile and needs 256 rows of K below 4 GiB.
+inline bool half_weights_ok(int wdt, int adt, int K) { return wdt != kF16 || (adt == kF16 && K % 64 == 0); }
+inline bool half_operands_ok(int wdt, long M, long N, long K) { return wdt != kF16 || (M > N ? M : N) * K * 2 < (1L << 32); }
+
 // The compute-bound kernel behind them (gemm_tall.hip), K a multiple of 64.
 bool gemm_tall_supported(int wdt, int adt, int K);
 hipError_t launch_gemm_tall(hipStream_t st, int wdt, int adt, const void* A, const void* W, float* C, int M, int N, int K,
                             int nsplit);
-// h [M, N] += A W^T, N a multiple of 4
+// h [M, N] += A W^T, N a multiple of 4, half activations
 hipError_t launch_gemm_tall_add(hipStream_t st, int wdt, int adt, const void* A, const void* W, float* h, int M, int N, int K);
 hipError_t launch_gemm_tall_swiglu(hipStream_t st, int wdt, int adt, const void* A, const void* W, void* act, int M, int ffn,
                                    int K);

@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 _GPT2S = CONFIGS["gpt2s"]
 _MODEL = replace(_GPT2S.model, n_layers=2, d_model=256, n_q_heads=4, n_kv_heads=4, head_dim=64, ffn=448, vocab=515)
 _WIDE = replace(_MODEL, d_model=1088)
+_MANY_COLUMNS = replace(_MODEL, ffn=9664, vocab=19300)        # two weight blocks a workgroup in gate||up and head
 _CH = 37
 
 
@@ -42,7 +43,7 @@ _JUMPS = {"outlier": (_outlier, {}), "empty_rows": (_empty_rows, {"rms_eps": 1e-
 
 
 # (the cancellation is exact for 256 channels and half values only)
-@pytest.mark.parametrize("model,n,jump", [(_MODEL, n, j) for n in (3, 16, 20, 40) for j in _JUMPS]
+@pytest.mark.parametrize("model,n,jump", [(m, n, j) for m, n in ((_MODEL, 3), (_MODEL, 16), (_MODEL, 20), (_MODEL, 40), (_MANY_COLUMNS, 6)) for j in _JUMPS]
                          + [(m, n, j) for m, n in ((_WIDE, 5), (_WIDE, 20), (replace(_MODEL, dtype="fp32"), 9))
                             for j in ("outlier", "empty_rows")])
 def test_stream_that_jumps(model, n, jump):
