@@ -100,11 +100,11 @@ typedef struct rlhf_engine_cfg {
                                       copy of every matrix (library-owned device memory, as many
                                       bytes again as the bf16 weights; RLHF_ENOMEM if they do not
                                       fit beside the KV pool), which the prefill / scoring passes
-                                      and decode steps of more than 32 rows read instead: the weights
-                                      then go from memory straight into LDS with no conversion in the
-                                      loop.  Results are bit-identical either way (the on-the-fly
-                                      conversion yields the same half values, and the sums are taken
-                                      in the same order).  0: no copies                          */
+                                      and decode steps beyond 32 to 64 rows (by width) read instead: the
+                                      weights then go from memory straight into LDS with no conversion
+                                      in the loop.  Results are bit-identical either way (the on-the-fly
+                                      conversion yields the same half values, and which kernel runs
+                                      does not depend on the copies).  0: no copies              */
 } rlhf_engine_cfg;
 
 /* One role's tensors (device pointers, element type per rlhf_model_cfg.dtype except the

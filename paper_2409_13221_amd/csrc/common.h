@@ -37,15 +37,6 @@ template <> __device__ __forceinline__ f16_t from_f32<f16_t>(float x) { return (
 template <> __device__ __forceinline__ float from_f32<float>(float x) { return x; }
 template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float x) { return f32_to_bf16(x); }
 
-// a * b in T.  Half: rounded once, by the instruction that the compiler picks for some such expressions and not for
-// others, so that kernels which have to agree on every bit do.
-template <typename T> __device__ __forceinline__ T mul_to(float a, float b) { return from_f32<T>(a * b); }
-template <> __device__ __forceinline__ f16_t mul_to<f16_t>(float a, float b) {
-    uint32_t r;
-    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(r) : "v"(a), "v"(b));
-    return __builtin_bit_cast(f16_t, (uint16_t)r);
-}
-
 // 8 consecutive elements of T as floats (16-byte load for bf16, two for float).
 template <typename T> __device__ __forceinline__ void load8(const T* p, float (&o)[8]);
 template <> __device__ __forceinline__ void load8<bf16_t>(const bf16_t* p, float (&o)[8]) {

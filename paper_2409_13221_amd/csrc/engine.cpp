@@ -396,15 +396,15 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
         HIPCK(c, launch_embed(st, dt, c->d_tokens, pm.tok_idx, w.embed, ws.h, rows, d, m.vocab));
     *n_ssq = 1;
     int ns = 0;
-    // the weights of layer l: the half copy where the kernel of this row count gains by it
-    const bool half = !resid && rows >= kRowsHalfFrom;
+    // k_gemm_rows, and the half copy of layer l's weights where there is one; or k_gemm_stream and the bf16 weights
+    const bool many = takes_gemm_rows(rows, d);
     auto project = [&](int md, const void* A, const void* w_bf16, const void* w_half, int l, int N, int K, const RowsEpi& ep,
                        int nsplit = 1) {
-        const bool hw = half && w_half;
+        const bool hw = many && w_half;
         const void* W = layer_ptr(hw ? w_half : w_bf16, l, N, K, es);
         const double bytes = ((double)N * K + (double)rows * K) * es + (double)rows * N * (md == 0 ? 4 : es);
         return profiled(c, st, gcls, bytes, 2.0 * rows * N * K,
-                        [&] { return launch_gemm_stream(st, hw ? kF16 : dt, adt, md, A, W, ws.part, rows, N, K, ep, nsplit); });
+                        [&] { return launch_gemm_stream(st, hw ? kF16 : dt, adt, md, A, W, ws.part, rows, N, K, ep, nsplit, many); });
     };
     // O and down projections: finish the residual stream, or leave planes and let RMSNorm do it
     auto into_stream = [&](const void* A, const ActLayout& la, const void* w_bf16, const void* w_half, int l, int K,
@@ -417,7 +417,7 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
             HIPCK(c, project(3, A, w_bf16, w_half, l, d, K, ep));
             *n_ssq = d / 16;
         } else {
-            ns = gemm_stream_nsplit(rows, d, K, cap);
+            ns = many ? gemm_rows_nsplit(d, K, cap) : gemm_stream_nsplit(rows, d, K, cap);
             HIPCK(c, project(0, A, w_bf16, w_half, l, d, K, ep, ns));
         }
         return RLHF_OK;
@@ -1185,7 +1185,7 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
         RowsEpi ep;
         const int adt = act_type(c, false);
         if (adt == kF16) ep.a = ActLayout{8, 8 * R};
-        const bool hw = R >= kRowsHalfFrom && c->roles[RLHF_ACTOR].h16.head && !stream_resid(R, d);
+        const bool many = takes_gemm_rows(R, d), hw = many && c->roles[RLHF_ACTOR].h16.head;
         if (R <= kStreamResidRows)
             ep.nrm = stream_norm(c, ws, w.g_final, n_ssq, ws.scale, nullptr);
         else
@@ -1194,7 +1194,7 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
         const double bytes = ((double)V * d + (double)R * d) * c->esz + (double)R * V * 4;
         HIPCK(c, profiled(c, c->sd, kGemmDecode, bytes, 2.0 * R * V * d, [&] {
             return launch_gemm_stream(c->sd, hw ? kF16 : c->dtype, adt, 0, ws.xn, hw ? c->roles[RLHF_ACTOR].h16.head : w.head, ws.part, R,
-                                      V, d, ep);
+                                      V, d, ep, 1, many);
         }));
     } else {
         int pns;

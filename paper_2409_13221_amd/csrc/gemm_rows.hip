@@ -55,9 +55,6 @@ template <int MODE> __device__ __forceinline__ int rows_wrow(const RowsEpi& ep, 
 }
 
 // A: half activations; W: bf16 (CVT, converted after the LDS read) or its half copy.  Modes as in launch_gemm_stream.
-// Up to 64 rows (four compute waves) this kernel runs where there is a half copy and k_gemm_stream where there is
-// none, and both give the same bits: K is summed in the four shares that waves of k_gemm_stream take, each from zero,
-// then the shares in order.  (32 registers and one uniform branch a step; the times are those of one running sum.)
 template <int MBW, int CW, int NB, int D, int MODE, bool CVT>
 __global__ __launch_bounds__((CW + kLoaders) * 64) void k_gemm_rows(const f16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                                                     float* __restrict__ C, int M, int N, int K, int kchunk,
@@ -65,9 +62,7 @@ __global__ __launch_bounds__((CW + kLoaders) * 64) void k_gemm_rows(const f16_t*
 #if defined(__HIP_DEVICE_COMPILE__)                        // buffer resources exist in the device pass only
     constexpr int LPW = NB * 2 / kLoaders;                 // loads (8 rows x 128 bytes) per loader and step
     constexpr int kSlot = NB * 2048;
-    constexpr bool SHARES = CW == 4;
-    // as many as registers allow (with shares and NB = 4: 128, two workgroups a compute unit)
-    constexpr int DA = MBW == 1 ? (SHARES && NB == 4 ? 5 : 8) : NB <= 4 ? 5 : 3;
+    constexpr int DA = MBW == 1 ? 8 : NB <= 4 ? 5 : 3;      // as many as registers allow
     static_assert(NB % 2 == 0 && LPW >= 1 && (D - 2) * LPW < 64, "blocks in pairs, whole loads per loader, six bits of vmcnt");
     __shared__ __attribute__((aligned(16))) uint8_t ring[D * kSlot];
     const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -125,25 +120,11 @@ __global__ __launch_bounds__((CW + kLoaders) * 64) void k_gemm_rows(const f16_t*
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    f32x4_t acc[NB][MBW], tot[SHARES ? NB : 1][MBW];
+    f32x4_t acc[NB][MBW];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int mb = 0; mb < MBW; ++mb) acc[nb][mb] = tot[SHARES ? nb : 0][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    const int share = SHARES ? ((K >> 6) + 4 * (int)gridDim.y - 1) / (4 * (int)gridDim.y) : 0;
-    int left = share;                                      // steps of this share to come
-    auto end_share = [&] {
-        if constexpr (SHARES) {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int mb = 0; mb < MBW; ++mb) {
-                    tot[nb][mb] += acc[nb][mb];
-                    acc[nb][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                }
-            left = share;
-        }
-    };
+        for (int mb = 0; mb < MBW; ++mb) acc[nb][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int j = 0; j < DA; ++j) fetch(min(j, n - 1), j);
     // fragment reads: row fr of a block, chunk s * 4 + fq, in groups of GS blocks, one group ahead of its use
@@ -184,7 +165,6 @@ __global__ __launch_bounds__((CW + kLoaders) * 64) void k_gemm_rows(const f16_t*
             }                                                                                                        \
             __builtin_amdgcn_sched_barrier(0);                                                                       \
         }                                                                                                            \
-        if (SHARES && --left == 0) end_share();                                                                      \
     } while (0)
     int k0 = 0;
     for (; k0 + DA <= n; k0 += DA) {
@@ -197,13 +177,6 @@ __global__ __launch_bounds__((CW + kLoaders) * 64) void k_gemm_rows(const f16_t*
 #pragma unroll
     for (int j = 0; j < DA - 1; ++j)
         if (k0 + j < n) RLHF_R_STEP(j);
-    if constexpr (SHARES) {
-        end_share();
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int mb = 0; mb < MBW; ++mb) acc[nb][mb] = tot[nb][mb];
-    }
 #undef RLHF_R_STEP
 #undef RLHF_R_READ
 #undef RLHF_R_BAR
@@ -233,13 +206,13 @@ __global__ __launch_bounds__((CW + kLoaders) * 64) void k_gemm_rows(const f16_t*
 #pragma unroll
             for (int p = 0; p < NB / 2; ++p) {
                 const int c = (blk * (NB / 2) + p) * 16 + fq * 4;
-                f16x4r_t o;
+                float o[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float g = acc[2 * p][mb][e];
-                    o[e] = mul_to<f16_t>(g / (1.f + __expf(-g)), acc[2 * p + 1][mb][e]);
+                    o[e] = g / (1.f + __expf(-g)) * acc[2 * p + 1][mb][e];
                 }
-                if (c < ep.ffn) *reinterpret_cast<f16x4r_t*>(act + act_index(ep.out, m, c)) = o;           // ffn % 16 == 0
+                if (c < ep.ffn) *reinterpret_cast<f16x4r_t*>(act + act_index(ep.out, m, c)) = half4(o);    // ffn % 16 == 0
             }
         }
         if constexpr (MODE == 2) {
@@ -306,8 +279,7 @@ int rows_nb(int N) {
 template <int MBW, int CW, int NB, int D, bool CVT>
 hipError_t rows_launch3(hipStream_t st, int mode, const f16_t* a, const bf16_t* w, float* C, int M, int N, int K, int nsplit,
                         const RowsEpi& ep) {
-    const int parts = CW == 4 ? 4 * nsplit : nsplit, per = ((K >> 6) + parts - 1) / parts;      // up to 64 rows: shares, in steps of 64
-    const int blocks = ((N + 15) / 16 + NB - 1) / NB, kchunk = per * (parts / nsplit) * 64;
+    const int blocks = ((N + 15) / 16 + NB - 1) / NB, kchunk = ((K + nsplit - 1) / nsplit + 63) / 64 * 64;
     if ((long)(nsplit - 1) * kchunk >= K) return hipErrorInvalidValue;        // a split without a K range
     const dim3 grid(blocks, nsplit), threads((CW + kLoaders) * 64);
     switch (mode) {
@@ -331,10 +303,7 @@ hipError_t rows_launch2(hipStream_t st, int mode, int nb, const f16_t* a, const 
 template <bool CVT>
 hipError_t rows_launch1(hipStream_t st, int mode, int nb, const f16_t* a, const bf16_t* w, float* C, int M, int N, int K,
                         int nsplit, const RowsEpi& ep) {
-    if (M <= 64) {
-        if constexpr (CVT) return hipErrorInvalidValue;    // k_gemm_stream
-        else return rows_launch2<1, 4, CVT>(st, mode, nb, a, w, C, M, N, K, nsplit, ep);
-    }
+    if (M <= 64) return rows_launch2<1, 4, CVT>(st, mode, nb, a, w, C, M, N, K, nsplit, ep);
     if (M <= 128) return rows_launch2<1, 8, CVT>(st, mode, nb, a, w, C, M, N, K, nsplit, ep);
     return rows_launch2<2, 8, CVT>(st, mode, nb, a, w, C, M, N, K, nsplit, ep);
 }
@@ -345,7 +314,7 @@ bool gemm_rows_supported(int wdt, int adt, int M, int K) {
     return (wdt == kBF16 || wdt == kF16) && adt == kF16 && M >= 1 && M <= kRowsMaxRows && K > 0 && K % 64 == 0;
 }
 
-// K split of O and down projections beyond 64 rows: four weight blocks per workgroup, workgroups for every compute unit, at
+// K split of O and down projections: four weight blocks per workgroup, workgroups for every compute unit, at
 // least four steps each, eight planes at most.  (7B down, 256 rows: 35 us with four blocks and four planes, 33 with
 // eight and eight, which the norm that reads them pays for; 51 with two and two.)
 constexpr int kPlaneBlocks = 4;

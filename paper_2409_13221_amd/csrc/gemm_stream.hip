@@ -194,7 +194,7 @@ template <int MB, int NB, int WAVES, int MODE, typename TO> struct StreamEpilogu
                 if (oc < ep.ffn) {
                     const float sc = normed ? s_scale[m] : 1.f;
                     const float g = total(lr, m) * sc, u = total(lr + 8, m) * sc;
-                    act[act_index(ep.out, m, oc)] = mul_to<TO>(g / (1.f + __expf(-g)), u);
+                    act[act_index(ep.out, m, oc)] = from_f32<TO>(g / (1.f + __expf(-g)) * u);
                 }
             }
         }
@@ -555,8 +555,9 @@ bool gemm_stream_supported(int wdt, int adt, int M, int K) {
 // (7B gate||up, us: 16 rows 34.5 / 30.5 with one / two; 32 rows 33.8 / 31.8 with two / three; 64 rows
 // 47.1 / 41.2), as long as about one workgroup per compute unit is left (QKV at 64 rows: 32.0 / 23.0 /
 // 25.5 with two / three / four, the last one 192 workgroups).  N = 4096 falls short of that: with more
-// than 16 rows O and down split K instead and leave planes to the norm that follows (64 rows: O 11.0
-// and down 22.8 as four planes of four blocks, 13.5 and 32.0 unsplit with one block).
+// than 16 rows O and down split K instead and leave planes to the norm that follows (32 rows: O 9.6 and down
+// 23.6 as two planes of two blocks, 13.0 and 29.0 unsplit with one block; 64 rows: 11.0 and 22.8 as four planes
+// of four, 13.5 and 32.0).
 //
 // 17..64 rows of a narrow residual stream (stream_resid: d_model <= 1024): the matrices come from the
 // caches and a kernel's time is mostly its start and its chain of loads, so the five kernels of the norm
@@ -565,6 +566,12 @@ bool gemm_stream_supported(int wdt, int adt, int M, int K) {
 // 4.3 gone; O and down as one group of 64 rows 5.1 and 8.0).  Wider streams keep planes and RMSNorm: their
 // time is weight traffic, which groups of 16 rows would repeat.  The head stays with the norm kernel (32000
 // columns: 25 us against 19.6 + 4.3, and more registers).
+// Where the lines lie, us alone, weights cold: one against two blocks, K = 4096, 8 / 16 rows: N = 4096 7.9 and 9.6 / 8.6
+// and 10.9, 12288 17.3 and 19.2 / 20.5 and 20.7, 22016 30.9 and 29.0 / 37.6 and 31.4, 32000 41.0 and 39.6 / 50.8 and
+// 42.6 (it goes in steps: a round is 256 workgroups of 16 or 32 weight rows; between 4096 and 19200 the better one
+// changes from step to step, and at K = 8192 and 8 rows one block stays ahead).  One against two and three blocks,
+// K = 4096: 32 rows N = 3072 11.5, 13.6, 16.3, 6144 20.1, 14.7, 17.0, 12288 28.9, 26.4, 19.3; 64 rows one and three
+// N = 3072 19.1, 23.6, 6144 34.5, 24.0.
 struct StreamShape { int mb, nb, depth; };
 static StreamShape stream_shape(int M, int N, bool planes) {
     if (M <= 16) return N >= 19200 ? StreamShape{1, 2, 4} : StreamShape{1, 1, 4};
@@ -574,26 +581,22 @@ static StreamShape stream_shape(int M, int N, bool planes) {
     if (mb == 2 && N < 48 * 240) return {2, 2, 4};
     return {mb, 3, 2};
 }
+bool takes_gemm_rows(int M, int d) { return M > kStreamMaxRows || (M > 32 && !stream_resid(M, d) && d < 8192); }
 bool stream_resid(int M, int d) { return M <= kStreamResidRows || (M <= kStreamMaxRows && d <= 1024); }
 int gemm_stream_nsplit(int M, int N, int K, int max_split) {
-    if (M > kStreamMaxRows) return gemm_rows_nsplit(N, K, max_split);
     const StreamShape sh = stream_shape(M, N, true);
     const int blocks = (N + 16 * sh.nb - 1) / (16 * sh.nb);
     int ns = (256 + blocks - 1) / blocks;
     ns = ns < (K >> 6) / 8 ? ns : (K >> 6) / 8;            // at least two steps of 64 per wave
     ns = ns < max_split ? ns : max_split;
-    if (ns < 1) ns = 1;
-    while (ns > 1 && (ns - 1) * 4 * (((K >> 6) + 4 * ns - 1) / (4 * ns)) >= K >> 6) --ns;      // every plane gets a K range
-    return ns;
+    return ns < 1 ? 1 : ns;
 }
 
 hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const void* A, const void* W, float* C, int M,
-                              int N, int K, const RowsEpi& ep_in, int nsplit) {
+                              int N, int K, const RowsEpi& ep_in, int nsplit, bool rows) {
     RowsEpi ep = ep_in;
     if (ep.a.row == 0) ep.a = ActLayout{K, 8};             // row-major unless the caller says otherwise
     if (ep.out.row == 0) ep.out = ActLayout{mode == 1 ? ep.ffn : N, 8};
-    // more rows than this kernel holds, or a half copy to read
-    const bool rows = M > kStreamMaxRows || wdt == kF16;
     if (!(rows ? gemm_rows_supported(wdt, adt, M, K) : gemm_stream_supported(wdt, adt, M, K)) || N <= 0 || mode < 0 || mode > 3) return hipErrorInvalidValue;
     if (rows && (mode == 3 || ep.nrm.ssq)) return hipErrorInvalidValue;
     if ((long)8 * K * 2 >= (1L << 31)) return hipErrorInvalidValue;
@@ -605,7 +608,7 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
             N != (ro.n_q_heads + 2 * ro.n_kv_heads) * ro.head_dim)
             return hipErrorInvalidValue;
     }
-    if (ep.nrm.ssq && wdt == kBF16 && (!ep.nrm.h || !ep.nrm.g)) return hipErrorInvalidValue;
+    if (ep.nrm.ssq && wdt == kBF16 && (adt != kF16 || !ep.nrm.h || !ep.nrm.g)) return hipErrorInvalidValue;
     if (ep.nrm.ssq && M > 16 && (ep.nrm.n_ssq > 64 || wdt == kF32 || mode == 0)) return hipErrorInvalidValue;
     if (rows) return mode == 1 && ep.ffn % 16 ? hipErrorInvalidValue : launch_gemm_rows(st, wdt, mode, A, W, C, M, N, K, ep, nsplit);
     if (mode == 3 && (adt == kBF16 || N % 16 || N > 16 * kSsqStride || !ep.res.h || !ep.res.g || !ep.res.x || !ep.res.s || !ep.res.ssq))
@@ -625,7 +628,7 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
     }
     const bf16_t* a = (const bf16_t*)A;
     const bf16_t* w = (const bf16_t*)W;
-    if (adt == kBF16) return stream_launch<1, 1, 4, 4, false, true>(st, mode, (N + 15) / 16, nsplit, a, w, C, M, N, K, ep);
+    if (adt == kBF16) return stream_launch<1, 1, 4, 4, false, false>(st, mode, (N + 15) / 16, nsplit, a, w, C, M, N, K, ep);
     if (mode == 3) return M <= 16 ? stream_resid_launch<4, 4>(st, a, w, M, N, K, ep) : stream_resid_launch<8, 2>(st, a, w, M, N, K, ep);
     if (ep.nrm.ssq && M > 16)
         return M <= 32 ? stream_norm_launch<2>(st, mode, a, w, M, N, K, ep) : stream_norm_launch<4>(st, mode, a, w, M, N, K, ep);
@@ -641,9 +644,10 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
     RLHF_STREAM(2, 3, 2);
     RLHF_STREAM(4, 1, 4);
     RLHF_STREAM(4, 3, 2);
-    RLHF_STREAM(4, 4, 2);
 #undef RLHF_STREAM
-    return hipErrorInvalidValue;
+    if (mode != 0 || sh.mb != 4 || sh.nb != 4) return hipErrorInvalidValue;
+    k_gemm_stream<4, 4, 4, 2, 0, true, false><<<dim3(blocks, nsplit), 256, 0, st>>>(a, w, C, M, N, K, ep);
+    return hipGetLastError();
 }
 
 }  // namespace rlhf

@@ -123,16 +123,19 @@ bool stream_resid(int M, int d);
 // Mode 0 may split K into nsplit planes C [nsplit][M][N]; the split for O and down projections otherwise:
 int gemm_stream_nsplit(int M, int N, int K, int max_split);
 hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const void* A, const void* W, float* C,
-                              int M, int N, int K, const RowsEpi& ep, int nsplit = 1);
-// The same for more rows (gemm_rows.hip; launch_gemm_stream hands such calls over): modes 0..2 without
+                              int M, int N, int K, const RowsEpi& ep, int nsplit = 1, bool rows = false);
+// The same for more rows (gemm_rows.hip; launch_gemm_stream hands over calls with rows set): modes 0..2 without
 // norms, up to kRowsMaxRows rows, half activations, bf16 weights or their half copy (wdt == kF16).
 constexpr int kRowsMaxRows = 256;
 bool gemm_rows_supported(int wdt, int adt, int M, int K);
-int gemm_rows_nsplit(int N, int K, int max_split);          // beyond 64 rows
-// 33..64 rows: the half copy, where there is one, and this kernel, which then gives the bits of k_gemm_stream over the
-// bf16 weights.  (Converting them in every compute wave costs it 5 us of 25-40 there, and up to 32 rows k_gemm_stream
-// is the faster one: QKV 19 against 31.)
-constexpr int kRowsHalfFrom = 33;
+int gemm_rows_nsplit(int N, int K, int max_split);
+// Whether a pass over a residual stream of d columns takes this kernel, with bf16 weights or their half copy alike (the two
+// give the same bits; k_gemm_stream, whose waves share K, gives others).  Beyond 64 rows; from 33 on where the stream is
+// wide (not stream_resid), but not at 8192 columns.  A decode step of 33 / 64 rows, us, this kernel with half copies, with
+// bf16 weights (every compute wave converts them), k_gemm_stream: d = 2048, 12 layers 680, 766, 716 / 800, 874, 864;
+// 4096, 8 layers 970, 1036, 975 / 1130, 1180, 1195; 5120, 5 layers 800, 878, 1060 / 935, 997, 1264; 8192, 2 layers
+// 840, 922, 828 / 905, 930, 914.  Up to 32 rows k_gemm_stream is the faster one (7B QKV 19 against 31).
+bool takes_gemm_rows(int M, int d);
 hipError_t launch_gemm_rows(hipStream_t st, int wdt, int mode, const void* A, const void* W, float* C, int M, int N, int K,
                             const RowsEpi& ep, int nsplit);
 

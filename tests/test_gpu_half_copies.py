@@ -16,9 +16,10 @@ _BASE = replace(_GPT2S.model, n_layers=1, d_model=4096, n_q_heads=32, n_kv_heads
 _NARROW = replace(_BASE, d_model=1088, n_q_heads=8, n_kv_heads=1, ffn=1600)
 # another number of planes behind O and down
 _ODD = replace(_BASE, d_model=5120, n_q_heads=40, n_kv_heads=5, ffn=2112)
+_WIDEST = replace(_BASE, d_model=8192, n_q_heads=16, n_kv_heads=2, vocab=1030)
 
 
-@pytest.mark.parametrize("model,n", [(_BASE, 32), (_BASE, 33), (_BASE, 64), (_BASE, 65), (_NARROW, 40), (_ODD, 50)])
+@pytest.mark.parametrize("model,n", [(_BASE, 32), (_BASE, 33), (_BASE, 64), (_BASE, 65), (_NARROW, 40), (_ODD, 50), (_WIDEST, 36), (_WIDEST, 70)])
 def test_half_copies_do_not_change_decode_results(model, n):
     cfg = _GPT2S.with_(name="half_copies", model=model, n_samples=n, prompt_len=(3, 5), gain_jitter=0.05)
     inp = H.make_inputs(cfg, n=n, max_len=4, weight_device="cuda")
