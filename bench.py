@@ -178,10 +178,11 @@ def micro(args):
     per-kernel timings.  In dispatch order: a 1 GiB device copy (calibrates FETCH_SIZE / WRITE_SIZE);
     the four projections of a scoring pass at M = --micro_rows (half activations, half copies of the
     weights, rotary fused into QKV and SwiGLU into gate||up, as the stage runs them) and the LM head
-    fused with the log-softmax gather at M = 2048; the four projections in the decode regime at
-    M = 8, 32, 64, 128, 256 (the five tilings of a decode step); paged decode attention (32 samples x
-    1024 cached tokens, 32 heads x 128, half).  Each case launches exactly one GEMM / attention /
-    copy kernel per call, 1 + --micro_reps calls."""
+    fused with the log-softmax gather at M = 2048; the four projections of a decode step of M = 8 rows
+    (rotary and SwiGLU fused, no K split, as the stage runs them) and, at M = 32, 64, 128, 256, what
+    rlhf_op_gemm runs (a decode step of such rows has kernels of its own, which have no entry point);
+    paged decode attention (32 samples x 1024 cached tokens, 32 heads x 128, half).  Each case launches
+    exactly one GEMM / attention / copy kernel per call, 1 + --micro_reps calls."""
     import torch
 
     import paper_2409_13221_amd as R
@@ -209,28 +210,31 @@ def micro(args):
     del src, dst
     shapes = [("qkv", 12288, 4096), ("o", 4096, 4096), ("gate_up", 22016, 4096), ("down", 4096, 11008)]
     half_w = bool(args.half_weight_copies)
-    M = args.micro_rows
-    for name, N, K in shapes:
-        A = torch.randn(M, K, device=dev).to(torch.float16)
-        W = (torch.randn(N, K, device=dev) * 0.02).to(torch.bfloat16)
-        Wx = R.rlhf_op_bf16_to_half(W) if half_w else W
-        if name == "gate_up":          # as the stage runs it: SwiGLU in the epilogue
-            act = torch.empty(M, N // 2, device=dev, dtype=torch.float16)
-            timed(f"gemm_{name}_swiglu_M{M}", lambda: R.rlhf_op_gemm_swiglu(A, Wx, act),
-                  (N * K + M * K) * 2.0 + M * (N // 2) * 2.0, 2.0 * M * N * K)
-        elif name == "qkv":            # as the stage runs it: rotary and the q / k / v scatter in the epilogue
-            Hq, hd = 32, 128
-            pos = torch.randint(0, 2048, (M,), device=dev, dtype=torch.int32)
-            ang = torch.arange(2048, device=dev)[:, None] * 10000.0 ** (-2.0 * torch.arange(hd // 2, device=dev) / hd)[None, :]
-            tab = torch.stack([torch.cos(ang), torch.sin(ang)], dim=-1).float().contiguous()
-            q, k, v = (torch.empty(M, Hq * hd, device=dev, dtype=torch.float16) for _ in range(3))
-            timed(f"gemm_{name}_rope_M{M}", lambda: R.rlhf_op_gemm_rope(A, Wx, pos, tab, q, k, v, n_q_heads=Hq,
-                                                                        n_kv_heads=Hq, head_dim=hd, check_indices=False),
-                  (N * K + M * K) * 2.0 + M * N * 2.0, 2.0 * M * N * K)
-        else:
-            C = torch.empty(1, M, N, device=dev)
-            timed(f"gemm_{name}_M{M}", lambda: R.rlhf_op_gemm(A, Wx, C, 1, 0 if half_w else 7),
-                  (N * K + M * K) * 2.0 + M * N * 4.0, 2.0 * M * N * K)
+    ang = torch.arange(2048, device=dev)[:, None] * 10000.0 ** (-2.0 * torch.arange(64, device=dev) / 128)[None, :]
+    tab = torch.stack([torch.cos(ang), torch.sin(ang)], dim=-1).float().contiguous()
+
+    def projections(M, half_w, variant):
+        for name, N, K in shapes:
+            A = torch.randn(M, K, device=dev).to(torch.float16)
+            W = (torch.randn(N, K, device=dev) * 0.02).to(torch.bfloat16)
+            Wx = R.rlhf_op_bf16_to_half(W) if half_w else W
+            if name == "gate_up":          # as the stage runs it: SwiGLU in the epilogue
+                act = torch.empty(M, N // 2, device=dev, dtype=torch.float16)
+                timed(f"gemm_{name}_swiglu_M{M}", lambda: R.rlhf_op_gemm_swiglu(A, Wx, act),
+                      (N * K + M * K) * 2.0 + M * (N // 2) * 2.0, 2.0 * M * N * K)
+            elif name == "qkv":            # as the stage runs it: rotary and the q / k / v scatter in the epilogue
+                Hq, hd = 32, 128
+                pos = torch.randint(0, 2048, (M,), device=dev, dtype=torch.int32)
+                q, k, v = (torch.empty(M, Hq * hd, device=dev, dtype=torch.float16) for _ in range(3))
+                timed(f"gemm_{name}_rope_M{M}", lambda: R.rlhf_op_gemm_rope(A, Wx, pos, tab, q, k, v, n_q_heads=Hq,
+                                                                            n_kv_heads=Hq, head_dim=hd, check_indices=False),
+                      (N * K + M * K) * 2.0 + M * N * 2.0, 2.0 * M * N * K)
+            else:
+                C = torch.empty(1, M, N, device=dev)
+                timed(f"gemm_{name}_M{M}", lambda: R.rlhf_op_gemm(A, Wx, C, 1, variant),
+                      (N * K + M * K) * 2.0 + M * N * 4.0, 2.0 * M * N * K)
+
+    projections(args.micro_rows, half_w, 0 if half_w else 7)
     # LM head of a scoring pass fused with the log-softmax gather
     Mh, V, K = 2048, 32000, 4096
     A = torch.randn(Mh, K, device=dev).to(torch.float16)
@@ -243,7 +247,8 @@ def micro(args):
     timed(f"gemm_lm_head_logprob_M{Mh}", lambda: R.rlhf_op_lm_head_logprob(A, Wx, toks, idx, lp, idx, scratch),
           (V * K + Mh * K) * 2.0 + scratch.numel() * 4.0, 2.0 * Mh * V * K)
     del A, W, Wx
-    for M in (8, 32, 64, 128, 256):
+    projections(8, False, 8)               # variant 8: the few-row kernel
+    for M in (32, 64, 128, 256):
         for name, N, K in shapes:
             A = torch.randn(M, K, device=dev).to(torch.float16)
             W = (torch.randn(N, K, device=dev) * 0.02).to(torch.bfloat16)
@@ -425,7 +430,7 @@ def main():
         bs_curve(cfg, args)
         return
     R, ctx, weights, wl, max_new = build_stage(cfg, args)
-    # the library picks the plan (fused unless a decode step of this model is launch-bound) unless told otherwise
+    # the library picks the plan (fused unless a small model has about one scoring pass of tokens) unless told otherwise
     plan = False if args.sequential else True if args.fused else "auto"
 
     for i in range(args.warmup):
