@@ -257,10 +257,9 @@ template <int MB, int NB, int WAVES, int MODE, typename TO> struct StreamEpilogu
                 }
                 float q = v * v;
 #pragma unroll
-                for (int o = 1; o < R16; o <<= 1) q += __shfl_xor(q, o, kWave);
-                static_assert(MODE != 3 || R16 == 16, "the lanes of a row are 16 neighbours");
+                for (int o = 1; o < 16; o <<= 1) q += __shfl_xor(q, o, kWave);     // 16 columns of a row: 16 neighbouring lanes
                 if (__ballot(over) >> (t & 48) & 0xFFFF) q = -q;
-                if (m < M && r == 0) rz.ssq[(size_t)m * kSsqStride + blk] = q;
+                if (m < M && r % 16 == 0 && nn < N) rz.ssq[(size_t)m * kSsqStride + nn / 16] = q;
             }
         }
     }
@@ -302,6 +301,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
     const int per = (steps + parts - 1) / parts;
     const int s0 = min(((MODE == 0 ? (int)blockIdx.y * WAVES : 0) + w) * per, steps), n_real = min(steps - s0, per);
     const int n = (per + D - 1) / D * D;
+    // Workgroups start at different places of their shares, the ones of an XCD one step apart: in step with each other
+    // they would all ask for the same offset within a row of W at a time, and where the rows lie a multiple of 16 KB
+    // apart, or 2752 k, that keeps part of the memory channels waiting (us, in step / rotated: N = 4096, 13 rows, K = 8192
+    // 14.8 / 13.0, 11008 18.5 / 16.7, 16384 26.8 / 22.4, 22016 40.8 / 35.1; N = 12288, 32 rows, K = 8192 42.9 / 33.0; the
+    // other K between 1024 and 28672 are the same within 2 %)
+    const int rot = n_real > 0 ? (blk >> 3) % n_real : 0;
 
     __amdgpu_buffer_rsrc_t rs[NB][2];
     uint32_t vo[NB][2];
@@ -333,7 +338,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
     frag_t fa[D][2 * MB];
 #define RLHF_ST_ISSUE(STEP, J)                                                                                     \
     do {                                                                                                           \
-        const int st_ = s0 + max(min((STEP), n_real - 1), 0);                                                      \
+        int ix_ = min((STEP), n_real - 1) + rot;                                                                   \
+        ix_ -= ix_ >= n_real ? n_real : 0;                                                                         \
+        const int st_ = s0 + max(ix_, 0);                                                                          \
         const int sc_ = min(st_, steps - 1);                                                                       \
         _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) {                                                        \
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[nb][0], (lds_ptr_t)(ring + ((J) * NB + nb) * 1024), 16,    \
@@ -527,9 +534,9 @@ hipError_t stream_launch(hipStream_t st, int mode, int blocks, int nsplit, const
     return hipGetLastError();
 }
 // mode 3: groups of 16 rows, each against the whole matrix
-template <int WAVES, int D>
+template <int NB, int WAVES, int D>
 hipError_t stream_resid_launch(hipStream_t st, const bf16_t* a, const bf16_t* w, int M, int N, int K, const RowsEpi& ep) {
-    k_gemm_stream<1, 1, WAVES, D, 3, true, false><<<dim3(N / 16, 1, (M + 15) / 16), WAVES * 64, 0, st>>>(a, w, nullptr, M, N, K, ep);
+    k_gemm_stream<1, NB, WAVES, D, 3, true, false><<<dim3((N + 16 * NB - 1) / (16 * NB), 1, (M + 15) / 16), WAVES * 64, 0, st>>>(a, w, nullptr, M, N, K, ep);
     return hipGetLastError();
 }
 // modes 1 and 2 with the norm of 17..64 rows: one weight block per workgroup, eight waves share K
@@ -548,16 +555,23 @@ bool gemm_stream_supported(int wdt, int adt, int M, int K) {
     return wdt == kBF16 && (adt == kF16 || (adt == kBF16 && M <= 16)) && M >= 1 && M <= kStreamMaxRows && K > 0 && K % 64 == 0;
 }
 
-// Shape of a launch: 16-row blocks of activations, of weights per workgroup, ring depth (four waves
-// throughout).  Every workgroup reads all activation rows of its K range, from the L2, and the loads of
-// a compute unit share one queue: time goes with weight bytes times the latency of HBM plus activation
-// bytes times that of the L2 (about 0.4 of it).  So more weight blocks per workgroup help as rows grow
-// (7B gate||up, us: 16 rows 34.5 / 30.5 with one / two; 32 rows 33.8 / 31.8 with two / three; 64 rows
-// 47.1 / 41.2), as long as about one workgroup per compute unit is left (QKV at 64 rows: 32.0 / 23.0 /
-// 25.5 with two / three / four, the last one 192 workgroups).  N = 4096 falls short of that: with more
-// than 16 rows O and down split K instead and leave planes to the norm that follows (32 rows: O 9.6 and down
-// 23.6 as two planes of two blocks, 13.0 and 29.0 unsplit with one block; 64 rows: 11.0 and 22.8 as four planes
-// of four, 13.5 and 32.0).
+// Shape of a launch: 16-row blocks of activations, of weights per workgroup (nb), ring depth (four waves throughout).
+// Every workgroup reads all activation rows of its K range, from the L2, and the loads of a compute unit share one
+// queue.  A compute unit's time goes with the 16 * nb weight rows of its workgroup plus about half the activation
+// rows, which every workgroup reads again, and the launch takes as many rounds of 256 workgroups as it has: the
+// least rounds * (2 nb + activation blocks) is the best shape, or within 4 % of it, for N = 2048 .. 57344 at K =
+// 2048 .. 28672 and 13, 32, 64 rows (us, the former shape, now the one chosen: 32 rows N = 15360, K = 5120 38.4 28.1; N
+// = 27648, K = 5120 60.5 46.7; N = 10240, K = 8192 41.7 30.9; N = 32000, K = 4096 47.8 43.1; 64 rows N = 57344, K = 8192
+// 180.7 151.3, N = 32000, K = 8192 115.1 86.8; 13 rows N = 12288, K = 4096 17.8 17.1, N = 27648, K = 5120 50.1 44.8; N =
+// 10240, K = 8192 32.1 27.8).  Among shapes a tenth apart the one with fewer blocks keeps the chip evenly loaded (13 rows
+// N = 32000, K = 4096 two blocks 40.0, four 40.7, eight 41.2).  Up to 8 rows activations cost next to nothing and any
+// shape that gives every compute unit its share reads at the rate of HBM (1 row, N = 12288 one, two, three blocks 16.3,
+// 18.1, 16.8; N = 22016 28.8, 27.6, 28.7).
+// With more than 16 rows O and down split K and leave planes to the norm that follows where that pays for the planes
+// (32 rows: N = 5120, K = 13824 unsplit 37.0, three planes of four blocks 25.6; N = 4096, K = 4096 12.2, 8.5 as two of two;
+// N = 8192, K = 28672 84.7, 77.9 as two of four).
+// Four steps in flight where that does not add more than an eighth of surplus steps (one or two blocks, us, depth 2
+// and 4: 1 row N = 12288 17.0 and 16.3; K = 1536, six steps a wave, 5.2 and 5.9), else two.
 //
 // 17..64 rows of a narrow residual stream (stream_resid: d_model <= 1024): the matrices come from the
 // caches and a kernel's time is mostly its start and its chain of loads, so the five kernels of the norm
@@ -566,30 +580,37 @@ bool gemm_stream_supported(int wdt, int adt, int M, int K) {
 // 4.3 gone; O and down as one group of 64 rows 5.1 and 8.0).  Wider streams keep planes and RMSNorm: their
 // time is weight traffic, which groups of 16 rows would repeat.  The head stays with the norm kernel (32000
 // columns: 25 us against 19.6 + 4.3, and more registers).
-// Where the lines lie, us alone, weights cold: one against two blocks, K = 4096, 8 / 16 rows: N = 4096 7.9 and 9.6 / 8.6
-// and 10.9, 12288 17.3 and 19.2 / 20.5 and 20.7, 22016 30.9 and 29.0 / 37.6 and 31.4, 32000 41.0 and 39.6 / 50.8 and
-// 42.6 (it goes in steps: a round is 256 workgroups of 16 or 32 weight rows; between 4096 and 19200 the better one
-// changes from step to step, and at K = 8192 and 8 rows one block stays ahead).  One against two and three blocks,
-// K = 4096: 32 rows N = 3072 11.5, 13.6, 16.3, 6144 20.1, 14.7, 17.0, 12288 28.9, 26.4, 19.3; 64 rows one and three
-// N = 3072 19.1, 23.6, 6144 34.5, 24.0.
+constexpr int kStreamMaxBlocks = 8;
+static int stream_rounds(int N, int nb, int ns) { return (((N + 16 * nb - 1) / (16 * nb)) * ns + 255) / 256; }
 struct StreamShape { int mb, nb, depth; };
-static StreamShape stream_shape(int M, int N, bool planes) {
-    if (M <= 16) return N >= 19200 ? StreamShape{1, 2, 4} : StreamShape{1, 1, 4};
-    const int mb = M <= 32 ? 2 : 4;
-    if (N < 4096) return {mb, 1, 4};                       // small matrices: workgroups before traffic
-    if (planes && N < 48 * 240) return mb == 2 ? StreamShape{2, 2, 4} : StreamShape{4, 4, 2};
-    if (mb == 2 && N < 48 * 240) return {2, 2, 4};
-    return {mb, 3, 2};
+static StreamShape stream_shape(int M, int N, int K, int ns) {
+    StreamShape sh{M <= 16 ? 1 : M <= 32 ? 2 : 4, 1, 2};
+    auto cost = [&](int nb) { return stream_rounds(N, nb, ns) * (2 * nb + sh.mb); };
+    if (M <= 8) {
+        sh.nb = N >= 19200 ? 2 : 1;
+    } else {
+        int least = cost(1);
+        for (int nb = 2; nb <= kStreamMaxBlocks; ++nb) least = least < cost(nb) ? least : cost(nb);
+        while (cost(sh.nb) * 10 > least * 11) ++sh.nb;
+    }
+    const int per = ((K >> 6) + 4 * ns - 1) / (4 * ns);    // steps of a wave
+    if ((sh.nb == 1 || (sh.nb == 2 && sh.mb == 1)) && (per <= 4 || (per + 3) / 4 * 4 * 8 <= per * 9)) sh.depth = 4;
+    return sh;
 }
 bool takes_gemm_rows(int M, int d) { return M > kStreamMaxRows || (M > 32 && !stream_resid(M, d) && d < 8192); }
 bool stream_resid(int M, int d) { return M <= kStreamResidRows || (M <= kStreamMaxRows && d <= 1024); }
+// The split with the least time, in steps of a compute unit as above; a plane more costs its write, and its read by
+// the norm (about 1.3 us at 32 rows of 4096).
 int gemm_stream_nsplit(int M, int N, int K, int max_split) {
-    const StreamShape sh = stream_shape(M, N, true);
-    const int blocks = (N + 16 * sh.nb - 1) / (16 * sh.nb);
-    int ns = (256 + blocks - 1) / blocks;
-    ns = ns < (K >> 6) / 8 ? ns : (K >> 6) / 8;            // at least two steps of 64 per wave
-    ns = ns < max_split ? ns : max_split;
-    return ns < 1 ? 1 : ns;
+    const int steps = K >> 6;
+    int best = 1;
+    long least = 0;
+    for (int ns = 1; ns <= 8 && ns <= max_split && (ns == 1 || ns * 8 <= steps); ++ns) {
+        const StreamShape sh = stream_shape(M, N, K, ns);
+        const long c = (long)stream_rounds(N, sh.nb, ns) * (2 * sh.nb + sh.mb) * ((steps + ns - 1) / ns) + (ns - 1) * ((long)M * N >> 11);
+        if (ns == 1 || c < least) { best = ns; least = c; }
+    }
+    return best;
 }
 
 hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const void* A, const void* W, float* C, int M,
@@ -629,25 +650,29 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
     const bf16_t* a = (const bf16_t*)A;
     const bf16_t* w = (const bf16_t*)W;
     if (adt == kBF16) return stream_launch<1, 1, 4, 4, false, false>(st, mode, (N + 15) / 16, nsplit, a, w, C, M, N, K, ep);
-    if (mode == 3) return M <= 16 ? stream_resid_launch<4, 4>(st, a, w, M, N, K, ep) : stream_resid_launch<8, 2>(st, a, w, M, N, K, ep);
+    if (mode == 3) {
+        if (M > 16) return stream_resid_launch<1, 8, 2>(st, a, w, M, N, K, ep);
+        // two weight blocks where that saves a round (13 rows: N = 5120, K = 5120 12.7 us against 14.8, K = 13824 29.9 against 35.5)
+        return stream_rounds(N, 2, 1) * 5 < stream_rounds(N, 1, 1) * 3 ? stream_resid_launch<2, 4, 4>(st, a, w, M, N, K, ep)
+                                                                      : stream_resid_launch<1, 4, 4>(st, a, w, M, N, K, ep);
+    }
     if (ep.nrm.ssq && M > 16)
         return M <= 32 ? stream_norm_launch<2>(st, mode, a, w, M, N, K, ep) : stream_norm_launch<4>(st, mode, a, w, M, N, K, ep);
-    const StreamShape sh = stream_shape(M, N, mode == 0);
+    const StreamShape sh = stream_shape(M, N, K, nsplit);
     const int blocks = (N + 16 * sh.nb - 1) / (16 * sh.nb);
 #define RLHF_STREAM(MB, NB, D)                       \
     if (sh.mb == MB && sh.nb == NB && sh.depth == D) \
         return stream_launch<MB, NB, 4, D, true, MB == 1>(st, mode, blocks, nsplit, a, w, C, M, N, K, ep)
-    RLHF_STREAM(1, 1, 4);
+#define RLHF_STREAM_MB(MB)                                                                                               \
+    RLHF_STREAM(MB, 1, 4); RLHF_STREAM(MB, 1, 2); RLHF_STREAM(MB, 2, 2); RLHF_STREAM(MB, 3, 2); RLHF_STREAM(MB, 4, 2); \
+    RLHF_STREAM(MB, 5, 2); RLHF_STREAM(MB, 6, 2); RLHF_STREAM(MB, 7, 2); RLHF_STREAM(MB, 8, 2)
+    RLHF_STREAM_MB(1);
     RLHF_STREAM(1, 2, 4);
-    RLHF_STREAM(2, 1, 4);
-    RLHF_STREAM(2, 2, 4);
-    RLHF_STREAM(2, 3, 2);
-    RLHF_STREAM(4, 1, 4);
-    RLHF_STREAM(4, 3, 2);
+    RLHF_STREAM_MB(2);
+    RLHF_STREAM_MB(4);
+#undef RLHF_STREAM_MB
 #undef RLHF_STREAM
-    if (mode != 0 || sh.mb != 4 || sh.nb != 4) return hipErrorInvalidValue;
-    k_gemm_stream<4, 4, 4, 2, 0, true, false><<<dim3(blocks, nsplit), 256, 0, st>>>(a, w, C, M, N, K, ep);
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 }  // namespace rlhf

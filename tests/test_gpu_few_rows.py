@@ -38,3 +38,20 @@ def test_decode_batches_read_half_copies(model, n):
     ref = H.oracle_stage(cfg, n=n, max_len=4)
     got = H.run_gpu_stage(cfg, ref, fused=False, R_t=0, chunk_tokens=64, half_weight_copies=True)
     H.compare_stage(cfg, ref, got)
+
+
+# one to eight weight blocks per workgroup (gate||up and head), ragged last workgroups; O and down in three and four planes,
+# in blocks of two (N = 5120) and with a K that four waves do not share evenly
+_BLOCKS7 = replace(_SMALL, n_layers=1, d_model=1088, n_q_heads=3, n_kv_heads=3, ffn=13760, vocab=31999)
+_BLOCKS6 = replace(_BLOCKS7, ffn=10944, vocab=15351)
+_PLANES = replace(_BLOCKS7, d_model=5120, n_q_heads=2, n_kv_heads=2, head_dim=128, ffn=3456, vocab=515)
+_EIGHT_K = replace(_PLANES, d_model=8192, n_q_heads=1, n_kv_heads=1, ffn=6144)
+
+
+@pytest.mark.parametrize("model,n", [(_BLOCKS7, 11), (_BLOCKS7, 29), (_BLOCKS6, 16), (_BLOCKS6, 17), (_PLANES, 1), (_PLANES, 9), (_PLANES, 32),
+                                     (_EIGHT_K, 5), (_EIGHT_K, 33), (replace(_SMALL, vocab=32000), 50)])
+def test_decode_batches_of_several_weight_blocks(model, n):
+    cfg = _GPT2S.with_(name="few_rows_blocks", model=model, n_samples=n, prompt_len=(3, 5), gain_jitter=0.05)
+    ref = H.oracle_stage(cfg, n=n, max_len=3)
+    got = H.run_gpu_stage(cfg, ref, fused=False, R_t=0, chunk_tokens=64)
+    H.compare_stage(cfg, ref, got)
