@@ -9,9 +9,9 @@
 // global -> LDS directly; CW compute waves own 16 * MBW activation rows each, which nobody shares and
 // which therefore go from the L2 straight into matrix-operand registers, DA steps ahead.  One barrier a step.
 //
-// Measured on the 7B shapes, half copies, weights cold, us: 64 rows QKV / O / gate||up / down / head 25.0 / 9.1 /
-// 37.2 / 19.7 / 55 (k_gemm_stream: 24.7 / 10.8 / 40.5 / 22.6 / 60); 128 rows 32.6 / 12.3 / 43.7 / 25.5 / 60
-// (128 x 128 tiles with rotary and SwiGLU kernels behind them: 42 / 18 / 63 / 29); 256 rows 48 / 18 / 58 / 35 / 74
+// Measured on the 7B shapes, half copies, weights cold, us: 64 rows QKV / O / gate||up / down / head 23.9 / 9 / 30.7 / 18.0 / 41
+// (workgroups in step along K: 25.2 / 9 / 37.5 / 18.3 / 58.6; k_gemm_stream 22.6 / 10.6 / 34.6 / 21.8 / 47); 128 rows 32.6 / 12.3 / 43.7 / 25.5 / 60
+// (128 x 128 tiles with rotary and SwiGLU kernels behind them: 42 / 18 / 63 / 29); 256 rows 47 / 18 / 54 / 34 / 70
 // (256 x 256 tiles with K split: 53 / 27 / 70 / 43 / 83).  From 128 rows on it is the activations: about 75 KB
 // per us and compute unit arrive, whatever their prefetch distance (5 or 8 steps) and the ring's depth (6, 10, 16).
 #include "common.h"
@@ -69,6 +69,9 @@ __global__ __launch_bounds__((CW + kLoaders) * 64) void k_gemm_rows(const f16_t*
     const int blk = blockIdx.x;
     const int kbeg = MODE == 0 ? (int)blockIdx.y * kchunk : 0;
     const int n = (MODE == 0 ? min(K, kbeg + kchunk) - kbeg : K) >> 6;
+    // workgroups start at different steps, as in gemm_stream.hip
+    const int rot = (blk >> 3) % n;
+    auto step_at = [&](int i) { return i + rot >= n ? i + rot - n : i + rot; };
 #define RLHF_R_BAR                                                     \
     do {                                                               \
         __builtin_amdgcn_sched_barrier(0);                             \
@@ -93,7 +96,7 @@ __global__ __launch_bounds__((CW + kLoaders) * 64) void k_gemm_rows(const f16_t*
 #pragma unroll
             for (int i = 0; i < LPW; ++i)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[i], (lds_ptr_t)(ring + slot * kSlot + (lw * LPW + i) * 1024), 16, vo[i],
-                                                         step * 128, 0, 2);
+                                                         step_at(step) * 128, 0, 2);
         };
         for (int j = 0; j < D - 1 && j < n; ++j) issue(j, j);
         int slot = D - 1;                                  // of step k + D - 1, which is that of step k - 1
@@ -112,7 +115,8 @@ __global__ __launch_bounds__((CW + kLoaders) * 64) void k_gemm_rows(const f16_t*
     for (int mb = 0; mb < MBW; ++mb) pa[mb] = A + act_index(ep.a, min((w + mb * CW) * 16 + fr, M - 1), kbeg + fq * 8);
     const size_t a_half = (size_t)4 * ep.a.chunk;          // elements from one 32-k half of a step to the next
     f16x8_t fa[DA][MBW][2];
-    auto fetch = [&](int step, int j) {
+    auto fetch = [&](int i, int j) {
+        const int step = step_at(i);
 #pragma unroll
         for (int mb = 0; mb < MBW; ++mb) {                 // rows past the end: the last one again (no branch, the
             fa[j][mb][0] = *reinterpret_cast<const f16x8_t*>(pa[mb] + (size_t)step * 2 * a_half);  // waits stay exact)

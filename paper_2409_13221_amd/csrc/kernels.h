@@ -131,10 +131,10 @@ bool gemm_rows_supported(int wdt, int adt, int M, int K);
 int gemm_rows_nsplit(int N, int K, int max_split);
 // Whether a pass over a residual stream of d columns takes this kernel, with bf16 weights or their half copy alike (the two
 // give the same bits; k_gemm_stream, whose waves share K, gives others).  Beyond 64 rows; from 33 on where the stream is
-// wide (not stream_resid), but not at 8192 columns.  A decode step of 33 / 64 rows, us, this kernel with half copies, with
-// bf16 weights (every compute wave converts them), k_gemm_stream: d = 2048, 12 layers 680, 766, 716 / 800, 874, 864;
-// 4096, 8 layers 970, 1036, 975 / 1130, 1180, 1195; 5120, 5 layers 800, 878, 1060 / 935, 997, 1264; 8192, 2 layers
-// 840, 922, 828 / 905, 930, 914.  Up to 32 rows k_gemm_stream is the faster one (7B QKV 19 against 31).
+// wide (not stream_resid), but not at 8192 columns.  The four projections of a layer, 40 / 64 rows, weights cold, us, this
+// kernel with half copies, with bf16 weights (every compute wave converts them), k_gemm_stream: d = 2048 30, 37, 34 / 33,
+// 38, 39; 4096 75, 91, 82 / 81, 93, 94; 5120 113, 131, 122 / 123, 133, 131; 8192 302, 334, 286 / 315, 339, 310.  Up to 32
+// rows k_gemm_stream is the faster one.
 bool takes_gemm_rows(int M, int d);
 hipError_t launch_gemm_rows(hipStream_t st, int wdt, int mode, const void* A, const void* W, float* C, int M, int N, int K,
                             const RowsEpi& ep, int nsplit);
