@@ -1,7 +1,7 @@
 // Attention kernels.
 //
 // Decode (the memory-bound phase of Section 2.2 / 4.2): one query per active sample against
-// that sample's paged K/V.  A workgroup owns (sample, KV head, split); its four waves take the
+// that sample's paged K/V.  A workgroup owns (sample, KV head, split); its waves (8 or 16) take the
 // pages of the split round-robin.  A page's K tile ([page_tokens][hd], contiguous) is read
 // with 16-byte loads, consecutive lanes on consecutive chunks; a lane holds 8 dims of one
 // token, the q.k dot product is finished with xor-shuffles inside the hd/8-lane group, and
@@ -88,8 +88,9 @@ __device__ __forceinline__ void load_tile(const T* __restrict__ kt, const T* __r
     for (int p = 0; p < PASSES; ++p) {
         const int tok = p * TPP + tsub;
         const int tk = tok < n_valid ? tok : 0;   // clamp: keep the load in bounds, mask below
-        tr.kc[p] = ld_chunk<T>(kt + (size_t)tk * tstride + dc * 8);
-        tr.vc[p] = ld_chunk<T>(vt + (size_t)tk * tstride + dc * 8);
+        const uint32_t off = (uint32_t)tk * (uint32_t)tstride + dc * 8;    // the bases are the same in all lanes
+        tr.kc[p] = ld_chunk<T>(kt + off);
+        tr.vc[p] = ld_chunk<T>(vt + off);
     }
 }
 
@@ -212,7 +213,10 @@ __device__ __forceinline__ void decode_block_finish(const float* s_m, const floa
     }
 }
 
-template <typename T, int HD, int G, int WV>
+// PF: K and V are fetched a tile ahead, two tiles in flight per wave (116 registers instead of 73, half activations,
+// heads of 128).  32 heads of 128, half, contexts 176..560, us, four waves per workgroup and one tile / eight and two: 32
+// rows 37.2 / 36.3, 64 70.4 / 65.7, 128 130.7 / 125.3, 256 248 / 245 (a read at 6.5 TB/s: 29.6, 59.3, 118.6, 237).
+template <typename T, int HD, int G, int WV, bool PF>
 __global__ __launch_bounds__(WV * 64) void k_decode_attn(const T* __restrict__ q,
                                                      const T* __restrict__ pool,
                                                      const int* __restrict__ page_table,
@@ -225,7 +229,7 @@ __global__ __launch_bounds__(WV * 64) void k_decode_attn(const T* __restrict__ q
     __shared__ float s_m[WV * G], s_l[WV * G];
     __shared__ float s_acc[WV * G * HD];
     const int r = blockIdx.x, kh = blockIdx.y, split = blockIdx.z;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int Hq = Hkv * G;
     const int ctx = ctx_len[r];
     const int n_pages = (ctx + kPT - 1) / kPT;
@@ -253,17 +257,37 @@ __global__ __launch_bounds__(WV * 64) void k_decode_attn(const T* __restrict__ q
     const size_t page_elems = (size_t)n_layers * 2 * Hkv * kPT * HD;
     const size_t head_off = ((size_t)layer * 2 * Hkv + kh) * kPT * HD;
     const size_t v_off = (size_t)Hkv * kPT * HD;
-    // A wave walks pages pb + wave, + WV, ...  The page index of the next tile is fetched before
-    // this tile's K and V, so that a tile costs one memory round trip instead of two dependent
-    // ones.  (Fetching K and V a tile ahead as well was measured: 120 registers instead of 73, the
-    // kernel no longer fits beside a scoring workgroup on a compute unit, and the stage is slower.)
+    // A wave walks pages pb + wave, + WV, ...  The index of the page after it is fetched along with a tile, so that a
+    // tile costs one memory round trip instead of two dependent ones.
     int pi = pb + wave;
     int page = pi < pe ? pt[pi] : 0;
-    for (; pi < pe; pi += WV) {
-        const int page_next = pi + WV < pe ? pt[pi + WV] : 0;
+    auto fetch = [&](int i, TileRegs<T, HD>& tr) {
         const T* kt = pool + (size_t)page * page_elems + head_off;
-        attend_tile<T, HD, G>(kt, kt + v_off, (size_t)HD, min(kPT, ctx - pi * kPT), qf, st, lane);
-        page = page_next;
+        load_tile<T, HD>(kt, kt + v_off, (size_t)HD, min(kPT, ctx - i * kPT), lane, tr);
+        page = pt[min(i + WV, pe - 1)];
+    };
+    auto consume = [&](int i, const TileRegs<T, HD>& tr) { consume_tile<T, HD, G>(tr, min(kPT, ctx - i * kPT), qf, st, lane); };
+    if constexpr (PF) {
+        TileRegs<T, HD> tr[2];
+        bool more = pi < pe;
+        if (more) fetch(pi, tr[0]);
+        while (more) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int next = pi + WV;
+                more = next < pe;
+                if (more) fetch(next, tr[u ^ 1]);
+                consume(pi, tr[u]);
+                pi = next;
+                if (!more) break;
+            }
+        }
+    } else {
+        TileRegs<T, HD> tr;
+        for (; pi < pe; pi += WV) {
+            fetch(pi, tr);
+            consume(pi, tr);
+        }
     }
     block_merge<HD, G>(st, lane, wave, s_m, s_l, s_acc);
     decode_block_finish<T, HD, G, WV>(s_m, s_l, s_acc, r, kh, split, nsplit, Hq, out, ol, part_acc, part_ml);
@@ -425,11 +449,10 @@ __global__ void k_attn_merge(const float* __restrict__ part_acc, const float* __
 }
 
 // Waves per workgroup: a workgroup holds one (row, KV head, split), its waves take the pages in turn.
-// With few workgroups the pages of one are spread over 8 or 16 waves, merged in LDS, where more splits
-// would cost a merge kernel (about 4 us).  32 heads of 128, half, us with 4 waves / with this rule, best
-// split each: 1 row at context 500 12.2 / 9.3, 13 rows at 500 21.4 / 20.0, at 2500 89.9 / 83.4; grouped
-// heads (64 over 8), 32 rows at 1100 33.4 / 27.9.  From 512 workgroups on four waves fill the chip.
-static int decode_attn_waves(long blocks, int group) { return blocks >= 512 ? 4 : blocks >= 256 || group > 1 ? 8 : 16; }
+// With few workgroups the pages of one are spread over 16 waves, merged in LDS, where more splits would cost a
+// merge kernel (about 4 us): 32 heads of 128, half, 1 row at context 500 12.2 us with 4 waves, 9.3 with 16; grouped heads
+// (64 over 8), 32 rows at 1100 33.4 / 27.9 with 4 / 8.
+static int decode_attn_waves(long blocks, int group) { return group > 1 ? (blocks >= 512 ? 4 : 8) : blocks >= 256 ? 8 : 16; }
 
 // As many splits as give the chip about sixteen waves per compute unit (twelve of the grouped kernel,
 // which keeps more in flight: 32 rows at 1100 27.9 us unsplit, 30.3 with two), unless that leaves a wave
@@ -444,58 +467,58 @@ int decode_attn_nsplit(int rows, int max_pages, const Dims& dm, int max_split) {
     return ns < 1 ? 1 : (int)ns;
 }
 
+template <typename T, int HD>
+static void decode_attn_run(hipStream_t st, dim3 grid, int wv, const void* q, const void* pool, const int* page_table, int pt_stride,
+                            const int* row_sample, const int* ctx_len, void* out, float* part_acc, float* part_ml, int layer,
+                            int nsplit, const Dims& dm, const ActLayout& ol) {
+    constexpr bool PF = sizeof(T) * HD <= 256;             // float rows of 128 would take all registers
+    if (wv == 16)
+        k_decode_attn<T, HD, 1, 16, PF><<<grid, 1024, 0, st>>>((const T*)q, (const T*)pool, page_table, pt_stride, row_sample, ctx_len, (T*)out,
+                                                               part_acc, part_ml, layer, nsplit, dm.n_layers, dm.n_kv_heads, ol);
+    else
+        k_decode_attn<T, HD, 1, 8, PF><<<grid, 512, 0, st>>>((const T*)q, (const T*)pool, page_table, pt_stride, row_sample, ctx_len, (T*)out,
+                                                             part_acc, part_ml, layer, nsplit, dm.n_layers, dm.n_kv_heads, ol);
+}
+
 hipError_t launch_decode_attn(hipStream_t st, int dtype, const void* q, const void* pool,
                               const int* page_table, int pt_stride, const int* row_sample,
                               const int* ctx_len, void* out, float* part_acc, float* part_ml,
                               int rows, int layer, int nsplit, const Dims& dm, const ActLayout& out_layout) {
     if (rows <= 0) return hipSuccess;
-    if (dm.page_tokens != kPT || nsplit < 1) return hipErrorInvalidValue;
     const int G = dm.n_q_heads / dm.n_kv_heads, hd = dm.head_dim;
+    if (dm.page_tokens != kPT || nsplit < 1 || (hd != 64 && hd != 128)) return hipErrorInvalidValue;
     ActLayout ol = out_layout;
     if (ol.row == 0) ol = ActLayout{dm.n_q_heads * hd, 8};
     const dim3 grid(rows, dm.n_kv_heads, nsplit);
     const int wv = decode_attn_waves((long)rows * dm.n_kv_heads, G);
-#define RLHF_DEC_WV(KERNEL, TT, ...)                                                                             \
-    KERNEL<__VA_ARGS__><<<grid, WV_ * 64, 0, st>>>((const TT*)q, (const TT*)pool, page_table, pt_stride, row_sample, \
-                                                   ctx_len, (TT*)out, part_acc, part_ml, layer, nsplit, dm.n_layers, \
-                                                   dm.n_kv_heads, ol)
-#define RLHF_DEC(TT, HD_, G_)                                                                                    \
-    do {                                                                                                         \
-        if (wv == 16) { constexpr int WV_ = 16; RLHF_DEC_WV(k_decode_attn, TT, TT, HD_, G_, 16); }               \
-        else if (wv == 8) { constexpr int WV_ = 8; RLHF_DEC_WV(k_decode_attn, TT, TT, HD_, G_, 8); }             \
-        else { constexpr int WV_ = 4; RLHF_DEC_WV(k_decode_attn, TT, TT, HD_, G_, 4); }                          \
-    } while (0)
-#define RLHF_MERGE(TT)                                                                                           \
-    do {                                                                                                         \
-        hipError_t e_ = hipGetLastError();                                                                       \
-        if (e_ != hipSuccess || nsplit == 1) return e_;                                                          \
-        k_attn_merge<TT><<<rows * dm.n_q_heads, hd, 0, st>>>(part_acc, part_ml, (TT*)out, ol, dm.n_q_heads, nsplit, hd); \
-        return hipGetLastError();                                                                                \
-    } while (0)
-    if (dtype == kBF16) {
-        if (hd == 128 && G == 1) RLHF_DEC(bf16_t, 128, 1);
-        else if (hd == 128 && G == 8) { constexpr int WV_ = 4; RLHF_DEC_WV(k_decode_attn, bf16_t, bf16_t, 128, 8, 4); }
-        else if (hd == 64 && G == 1) RLHF_DEC(bf16_t, 64, 1);
-        else return hipErrorInvalidValue;
-        RLHF_MERGE(bf16_t);
+    if (G == 1) {
+        auto run = [&](auto f) {
+            f(st, grid, wv, q, pool, page_table, pt_stride, row_sample, ctx_len, out, part_acc, part_ml, layer, nsplit, dm, ol);
+        };
+        if (dtype == kBF16) hd == 128 ? run(decode_attn_run<bf16_t, 128>) : run(decode_attn_run<bf16_t, 64>);
+        else if (dtype == kF16) hd == 128 ? run(decode_attn_run<f16_t, 128>) : run(decode_attn_run<f16_t, 64>);
+        else hd == 128 ? run(decode_attn_run<float, 128>) : run(decode_attn_run<float, 64>);
+    } else if (G == 8 && hd == 128 && dtype == kBF16) {
+        k_decode_attn<bf16_t, 128, 8, 4, false><<<grid, 256, 0, st>>>((const bf16_t*)q, (const bf16_t*)pool, page_table, pt_stride, row_sample,
+                                                                      ctx_len, (bf16_t*)out, part_acc, part_ml, layer, nsplit, dm.n_layers,
+                                                                      dm.n_kv_heads, ol);
+    } else if (G == 8 && hd == 128 && dtype == kF16) {
+        if (wv == 8)
+            k_decode_attn_gqa<128, 8, 8><<<grid, 512, 0, st>>>((const f16_t*)q, (const f16_t*)pool, page_table, pt_stride, row_sample, ctx_len,
+                                                               (f16_t*)out, part_acc, part_ml, layer, nsplit, dm.n_layers, dm.n_kv_heads, ol);
+        else
+            k_decode_attn_gqa<128, 8, 4><<<grid, 256, 0, st>>>((const f16_t*)q, (const f16_t*)pool, page_table, pt_stride, row_sample, ctx_len,
+                                                               (f16_t*)out, part_acc, part_ml, layer, nsplit, dm.n_layers, dm.n_kv_heads, ol);
+    } else {
+        return hipErrorInvalidValue;
     }
-    if (dtype == kF16) {
-        if (hd == 128 && G == 1) RLHF_DEC(f16_t, 128, 1);
-        else if (hd == 128 && G == 8) {
-            if (wv >= 8) { constexpr int WV_ = 8; RLHF_DEC_WV(k_decode_attn_gqa, f16_t, 128, 8, 8); }
-            else { constexpr int WV_ = 4; RLHF_DEC_WV(k_decode_attn_gqa, f16_t, 128, 8, 4); }
-        }
-        else if (hd == 64 && G == 1) RLHF_DEC(f16_t, 64, 1);
-        else return hipErrorInvalidValue;
-        RLHF_MERGE(f16_t);
-    }
-    if (hd == 128 && G == 1) RLHF_DEC(float, 128, 1);
-    else if (hd == 64 && G == 1) RLHF_DEC(float, 64, 1);
-    else return hipErrorInvalidValue;
-    RLHF_MERGE(float);
-#undef RLHF_DEC
-#undef RLHF_DEC_WV
-#undef RLHF_MERGE
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || nsplit == 1) return e;
+    const int heads = rows * dm.n_q_heads;
+    if (dtype == kBF16) k_attn_merge<bf16_t><<<heads, hd, 0, st>>>(part_acc, part_ml, (bf16_t*)out, ol, dm.n_q_heads, nsplit, hd);
+    else if (dtype == kF16) k_attn_merge<f16_t><<<heads, hd, 0, st>>>(part_acc, part_ml, (f16_t*)out, ol, dm.n_q_heads, nsplit, hd);
+    else k_attn_merge<float><<<heads, hd, 0, st>>>(part_acc, part_ml, (float*)out, ol, dm.n_q_heads, nsplit, hd);
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------- prefill / scoring (v1)
