@@ -15,6 +15,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "tile_walk.h"
+#include <algorithm>
 
 namespace rlhf {
 
@@ -428,14 +429,35 @@ bool gemm_is_tall(int M, int N, int K, int nsplit) { return K % 64 == 0 && kCfgs
 
 // bf16 -> IEEE half, element by element (round toward zero; exact in half's normal range, values
 // below 2^-14 land on half's subnormal grid): the same conversion the kernels apply on the fly.
-__global__ void k_bf16_to_half(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, size_t n_pairs) {
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n_pairs; i += (size_t)gridDim.x * 256)
-        dst[i] = bf16x2_to_f16x2(src[i]);
+// Bound by memory: 16 bytes a lane, four loads in flight (N = 22016, K = 4096, read and written: 78 us with 4 bytes a lane,
+// 73.5 this way; a device copy of as much takes 68).
+__global__ __launch_bounds__(256) void k_bf16_to_half(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, size_t n_pairs) {
+    const size_t n4 = n_pairs >> 2, stride = (size_t)gridDim.x * 256, t = (size_t)blockIdx.x * 256 + threadIdx.x;
+    constexpr int U = 4;
+    for (size_t i = t; i < n4; i += U * stride) {
+        uint4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + u * stride < n4) v[u] = reinterpret_cast<const uint4*>(src)[i + u * stride];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + u * stride < n4)
+                reinterpret_cast<uint4*>(dst)[i + u * stride] = make_uint4(bf16x2_to_f16x2(v[u].x), bf16x2_to_f16x2(v[u].y),
+                                                                           bf16x2_to_f16x2(v[u].z), bf16x2_to_f16x2(v[u].w));
+    }
+    if (t < (n_pairs & 3)) dst[n4 * 4 + t] = bf16x2_to_f16x2(src[n4 * 4 + t]);
+}
+__global__ __launch_bounds__(256) void k_bf16_to_half_unaligned(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, size_t n) {
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
+        dst[i] = (uint16_t)bf16x2_to_f16x2(src[i]);
 }
 hipError_t launch_bf16_to_half(hipStream_t st, const void* src, void* dst, size_t n) {
     if (n == 0) return hipSuccess;
     if (n % 2) return hipErrorInvalidValue;
-    k_bf16_to_half<<<4096, 256, 0, st>>>((const uint32_t*)src, (uint32_t*)dst, n / 2);
+    if (((uintptr_t)src | (uintptr_t)dst) & 15)            // a caller's tensor may start anywhere
+        k_bf16_to_half_unaligned<<<4096, 256, 0, st>>>((const uint16_t*)src, (uint16_t*)dst, n);
+    else
+        k_bf16_to_half<<<(unsigned)std::min<size_t>(4096, (n / 8 + 1023) / 1024 + 1), 256, 0, st>>>((const uint32_t*)src, (uint32_t*)dst, n / 2);
     return hipGetLastError();
 }
 
