@@ -6,7 +6,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librlhf.so")
-SOURCES = ["engine.cpp", "gemm.hip", "gemm_stream.hip", "gemm_rows.hip", "gemm_tall.hip", "attention.hip", "elementwise.hip", "ops_api.cpp"]
+SOURCES = ["engine.cpp", "gemm.hip", "gemm_stream.hip", "gemm_rows.hip", "gemm_tall.hip", "gemm_f32.hip", "attention.hip", "elementwise.hip", "ops_api.cpp"]
 # Kernel arguments in scalar registers when a wave starts, as far as 16 of them go (pointers and sizes come first in every
 # kernel): a chain of short kernels saves the first read of each, about 0.1 us of 3 to 6 (gpt2s stage 115.8 -> 113.5 ms).
 FLAGS = ["-O3", "-mllvm", "-amdgpu-kernarg-preload-count=16", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-result",

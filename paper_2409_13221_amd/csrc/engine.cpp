@@ -99,7 +99,8 @@ struct Workspace {
     int logit_rows = 0;
     float* pick_scratch = nullptr;  // per-chunk partial results of the greedy pick
     float* ssq = nullptr;       // few-row passes: partial sums of h^2 of the rows in flight
-    float* scale = nullptr;     // [2][kStreamMaxRows]: scales of the normed rows, ping and pong
+    float* scale = nullptr;     // [2][few]: scales of the normed rows, ping and pong
+    int few = 0;                // rows these two have room for
     void* w16 = nullptr;        // batch passes without half copies: the matrix in use, converted (or NULL)
     float* attn_acc = nullptr;  // decode split-KV partials
     float* attn_ml = nullptr;
@@ -309,8 +310,10 @@ int alloc_workspace(rlhf_ctx* c, Workspace& ws, int rows, bool decode) {
     HIPCK(c, dev_alloc(&ws, (char**)&ws.act, rows * f * es));
     HIPCK(c, dev_alloc(&ws, (char**)&ws.xsel, rows * d * 4));    // float rows for the value / reward head
     HIPCK(c, dev_alloc(&ws, &ws.pick_scratch, pick_scratch_floats(rows) * 4));
-    HIPCK(c, dev_alloc(&ws, &ws.ssq, (size_t)kStreamMaxRows * kSsqStride * 4));
-    HIPCK(c, dev_alloc(&ws, &ws.scale, (size_t)2 * kStreamMaxRows * 4));
+    const size_t few = c->dtype == kF32 ? std::min(rows, kStreamF32Rows) : kStreamMaxRows;
+    HIPCK(c, dev_alloc(&ws, &ws.ssq, few * kSsqStride * 4));
+    HIPCK(c, dev_alloc(&ws, &ws.scale, 2 * few * 4));
+    ws.few = (int)few;
     if (decode) {
         HIPCK(c, dev_alloc(&ws, &ws.attn_acc, ws.attn_slots * m.head_dim * 4));
         HIPCK(c, dev_alloc(&ws, &ws.attn_ml, ws.attn_slots * 2 * 4));
@@ -363,7 +366,7 @@ struct PassMeta {         // device pointers into a MetaRing arena
 // Few rows: every layer runs on the projections of gemm_stream.hip.
 bool stream_pass(const rlhf_ctx* c, int rows) {
     const rlhf_model_cfg& m = c->mc;
-    if (c->dtype == kF32) return rows <= kStreamResidRows && m.d_model % 16 == 0;
+    if (c->dtype == kF32) return rows <= kStreamF32Rows && m.d_model % 16 == 0;
     return c->dtype == kBF16 && rows <= kRowsMaxRows && m.d_model % 64 == 0 && (m.n_q_heads * m.head_dim) % 64 == 0 &&
            m.ffn % 64 == 0;
 }
@@ -395,13 +398,13 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
     const int d = m.d_model, qd = m.n_q_heads * m.head_dim, kvd = m.n_kv_heads * m.head_dim;
     const int qkv_w = qd + 2 * kvd, f = m.ffn, es = c->esz, dt = c->dtype;
     const int gcls = mode == kModeDecode ? kGemmDecode : kGemmBatch;
-    const bool resid = stream_resid(rows, m.d_model);
+    const bool resid = stream_resid(dt, rows, m.d_model);
     const size_t plane = (size_t)rows * d;
     const int cap = (int)std::min<size_t>(16, ws.part_cap / plane);
     const int adt = act_type(c, mode == kModeBatch);
     // row 0: row-major, whatever the width
     const ActLayout packed = adt == kF16 ? ActLayout{8, 8 * rows} : ActLayout{}, attn_layout = mode == kModeDecode ? packed : ActLayout{};
-    float* sc[2] = {ws.scale, ws.scale + kStreamMaxRows};
+    float* sc[2] = {ws.scale, ws.scale + ws.few};
     auto gain_after = [&](int l) { return l + 1 < m.n_layers ? w.g_attn + (size_t)(l + 1) * d : w.g_final; };
     if (resid)
         HIPCK(c, launch_embed_norm(st, dt, c->d_tokens, pm.tok_idx, w.embed, ws.h, m.n_layers > 0 ? w.g_attn : w.g_final,
@@ -411,7 +414,7 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
     *n_ssq = 1;
     int ns = 0;
     // k_gemm_rows, and the half copy of layer l's weights where there is one; or k_gemm_stream and the bf16 weights
-    const bool many = takes_gemm_rows(rows, d);
+    const bool many = dt == kBF16 && takes_gemm_rows(rows, d);
     auto project = [&](int md, const void* A, const void* w_bf16, const void* w_half, int l, int N, int K, const RowsEpi& ep,
                        int nsplit = 1) {
         const bool hw = many && w_half;
@@ -465,8 +468,8 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
                 if (adt == kF16)
                     return launch_flash_attn(st, ws.q, ws.k, ws.v, pm.tile_start, pm.tile_q0, pm.tile_len, ws.attn,
                                              pm.n_tiles, rows, c->dm);
-                return launch_prefill_attn(st, adt, (const float*)ws.q, (const float*)ws.k, (const float*)ws.v,
-                                           pm.row_start, pm.pos, ws.attn, rows, c->dm);
+                return launch_flash_attn_f32(st, (const float*)ws.q, (const float*)ws.k, (const float*)ws.v, pm.tile_start,
+                                             pm.tile_q0, pm.tile_len, (float*)ws.attn, pm.n_tiles, c->dm);
             }));
         }
         int rc = into_stream(ws.attn, attn_layout, w.wo, wh.wo, l, qd, w.g_mlp + (size_t)l * d, sc[1]);
@@ -518,11 +521,25 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         return RLHF_OK;
     };
     const bool can16 = dt == kBF16 && adt == kF16 && d % 64 == 0;
+    // float models: every projection on the kernel of gemm_f32.hip, its consumer in the epilogue
+    const bool f32 = dt == kF32 && gemm_f32_tall_supported(qkv_w, d, 2) && gemm_f32_tall_supported(2 * f, d, 1) &&
+                     gemm_f32_tall_supported(d, qd, 3) && gemm_f32_tall_supported(d, f, 3);
+    auto project_f32 = [&](int mode, const void* A, const void* W, int N, int K, const RowsEpi& ep) {
+        const double bytes = ((double)N * K + (double)rows * K + (double)rows * N) * es;
+        return profiled(c, st, gcls, bytes, 2.0 * rows * N * K,
+                        [&] { return launch_gemm_f32_tall(st, mode, (const float*)A, (const float*)W, nullptr, rows, N, K, ep); });
+    };
     int pns = 0, rc_proj;
     const size_t pstride = (size_t)rows * d;
     // O and down projections: an unsplit tall one finishes the residual stream, the others leave pns planes that
     // RMSNorm adds
     auto into_stream = [&](const void* A, const void* w_bf16, const void* w_half, int l, int K) -> int {
+        if (f32) {
+            RowsEpi ep;
+            ep.res.h = ws.h;
+            HIPCK(c, project_f32(3, A, layer_ptr(w_bf16, l, d, K, es), d, K, ep));
+            return RLHF_OK;
+        }
         pns = nsplit_for(c, ws, rows, d, K);
         const bool tall = gemm_is_tall(rows, d, K, pns);
         const void* W;
@@ -543,24 +560,32 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, pns, pstride, nullptr, w.g_attn + (size_t)l * d,
                                 ws.xn, rows, d, m.rms_eps));
         int ns = 0;
-        if (mode == kModeBatch && gemm_rope_supported(dt, adt, rows, d, c->dm)) {
+        if (f32 || (mode == kModeBatch && gemm_rope_supported(dt, adt, rows, d, c->dm))) {
             // tall pass: rotary, rounding and the q / k / v / pool scatter ride in the GEMM's epilogue
             RopeOut ro;
             ro.pos = pm.pos;
             ro.kv_dst = pm.kv_dst;
             ro.table = c->d_rope;
-            ro.q = ws.q; ro.k = ws.k; ro.v = ws.v;
+            ro.q = ws.q;
+            ro.k = mode == kModeBatch ? ws.k : nullptr;
+            ro.v = mode == kModeBatch ? ws.v : nullptr;
             ro.pool = pm.kv_dst ? c->pool : nullptr;
             ro.layer = l; ro.n_layers = m.n_layers;
             ro.n_q_heads = m.n_q_heads; ro.n_kv_heads = m.n_kv_heads; ro.head_dim = m.head_dim;
             ro.page_tokens = c->ec.page_tokens;
-            const double bytes = ((double)qkv_w * d + (double)rows * d) * es + (double)rows * qkv_w * es;
-            const void* wq;
-            bool hw;
-            rc_proj = weights_for(w.wqkv, wh.wqkv, l, qkv_w, d, can16, &wq, &hw);
-            if (rc_proj) return rc_proj;
-            HIPCK(c, profiled(c, st, gcls, bytes, 2.0 * rows * qkv_w * d,
-                              [&] { return launch_gemm_rope(st, hw ? kF16 : dt, adt, ws.xn, wq, rows, d, ro); }));
+            if (f32) {
+                RowsEpi ep;
+                ep.ro = ro;
+                HIPCK(c, project_f32(2, ws.xn, layer_ptr(w.wqkv, l, qkv_w, d, es), qkv_w, d, ep));
+            } else {
+                const double bytes = ((double)qkv_w * d + (double)rows * d) * es + (double)rows * qkv_w * es;
+                const void* wq;
+                bool hw;
+                rc_proj = weights_for(w.wqkv, wh.wqkv, l, qkv_w, d, can16, &wq, &hw);
+                if (rc_proj) return rc_proj;
+                HIPCK(c, profiled(c, st, gcls, bytes, 2.0 * rows * qkv_w * d,
+                                  [&] { return launch_gemm_rope(st, hw ? kF16 : dt, adt, ws.xn, wq, rows, d, ro); }));
+            }
         } else {
             ns = nsplit_for(c, ws, rows, qkv_w, d);
             const bool hw = wh.wqkv && adt == kF16 && gemm_is_tall(rows, qkv_w, d, ns);
@@ -582,15 +607,20 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
                 if (adt == kF16)
                     return launch_flash_attn(st, ws.q, ws.k, ws.v, pm.tile_start, pm.tile_q0, pm.tile_len, ws.attn,
                                              pm.n_tiles, rows, c->dm);
-                return launch_prefill_attn(st, adt, (const float*)ws.q, (const float*)ws.k, (const float*)ws.v,
-                                           pm.row_start, pm.pos, ws.attn, rows, c->dm);
+                return launch_flash_attn_f32(st, (const float*)ws.q, (const float*)ws.k, (const float*)ws.v, pm.tile_start,
+                                             pm.tile_q0, pm.tile_len, (float*)ws.attn, pm.n_tiles, c->dm);
             }));
         }
         rc_proj = into_stream(ws.attn, w.wo, wh.wo, l, qd);
         if (rc_proj) return rc_proj;
         HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, pns, pstride, nullptr, w.g_mlp + (size_t)l * d, ws.xn, rows, d,
                                 m.rms_eps));
-        if (gemm_swiglu_supported(dt, adt, rows, f, d)) {
+        if (f32) {
+            RowsEpi ep;
+            ep.act = ws.act;
+            ep.ffn = f;
+            HIPCK(c, project_f32(1, ws.xn, layer_ptr(w.w_gate_up, l, 2 * (size_t)f, d, es), 2 * f, d, ep));
+        } else if (gemm_swiglu_supported(dt, adt, rows, f, d)) {
             const void* wgu;
             bool hw;
             rc_proj = weights_for(w.w_gate_up, wh.w_gate_up, l, 2 * (size_t)f, d, can16, &wgu, &hw);
@@ -1217,8 +1247,8 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
         RowsEpi ep;
         const int adt = act_type(c, false);
         if (adt == kF16) ep.a = ActLayout{8, 8 * R};
-        const bool many = takes_gemm_rows(R, d), hw = many && c->roles[RLHF_ACTOR].h16.head;
-        if (R <= kStreamResidRows)
+        const bool many = adt == kF16 && takes_gemm_rows(R, d), hw = many && c->roles[RLHF_ACTOR].h16.head;
+        if (R <= kStreamResidRows || adt == kF32)
             ep.nrm = stream_norm(c, ws, w.g_final, n_ssq, ws.scale, nullptr);
         else
             HIPCK(c, launch_rmsnorm(c->sd, adt, ws.h, ws.part, pns, (size_t)R * d, nullptr, w.g_final, ws.xn, R, d,
@@ -1615,7 +1645,7 @@ bool serial_is_faster(const rlhf_ctx* c) {
     const double qd = (double)m.n_q_heads * m.head_dim, kvd = (double)m.n_kv_heads * m.head_dim;
     const double per_layer = (qd + 2 * kvd) * m.d_model + m.d_model * qd + 3.0 * m.d_model * m.ffn;
     const double stream_us = (m.n_layers * per_layer + (double)m.vocab * m.d_model) * c->esz / 5.0e6;
-    const int launches = stream_resid(std::min(c->N, c->ec.max_active), m.d_model) ? 5 : 7;
+    const int launches = stream_resid(c->dtype, std::min(c->N, c->ec.max_active), m.d_model) ? 5 : 7;
     return stream_us < (launches * m.n_layers + 6) * 4.0;
 }
 }  // namespace

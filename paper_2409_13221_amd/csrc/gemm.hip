@@ -11,7 +11,7 @@
 // Split-K partials are written to separate buffers and summed by the consumer kernel, which
 // keeps the result deterministic (no float atomics).
 //
-// fp32: a plain LDS-tiled kernel for the float configuration (small model; not tuned).
+// fp32 with a K split: a plain LDS-tiled kernel (not tuned; unsplit launches run on gemm_f32.hip).
 #include "common.h"
 #include "kernels.h"
 #include "tile_walk.h"
@@ -577,6 +577,9 @@ hipError_t launch_gemm(hipStream_t st, int wdt, int adt, const void* A, const vo
                            : launch_bf16<false>(st, variant, a, w, C, M, N, K, nsplit);
     }
     if (K % 4 || adt != kF32) return hipErrorInvalidValue;
+    // unsplit: gemm_f32.hip, which stores 16 bytes at a time and has 16 bits of row tiles
+    if (nsplit == 1 && ((uintptr_t)C & 15) == 0 && M <= 65535L * 64)
+        return launch_gemm_f32_tall(st, 0, (const float*)A, (const float*)W, C, M, N, K, RowsEpi{});
     const int tiles_m = (M + 63) / 64, tiles_n = (N + 63) / 64;
     const int kchunk = ((K + nsplit - 1) / nsplit + 15) / 16 * 16;
     dim3 grid(tiles_m * tiles_n, nsplit);

@@ -470,20 +470,46 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
 #endif
 }
 
-// Float models, up to 16 rows: the same split and epilogues on float matrix instructions (16x16x4: products
-// and sums in float).  These matrices fit the caches, so the time is that of one dependent chain: eight
+// Float models: the same split and epilogues on float matrix instructions (16x16x4: products and sums in float), 16
+// rows at a time (blockIdx.y).  These matrices fit the caches, so the time is that of one dependent chain: eight
 // waves share K, a lane takes four consecutive k of its row and of its activation row per 16 k, four such
 // loads ahead.  (8 rows of 256 x 256 .. 1376 weights: 2.5-3 us a launch, where 64 x 64 tiles took 6.9 us and
-// left planes to rotary, SwiGLU and norm kernels of 3 us each.)
-template <int MODE>
+// left planes to rotary, SwiGLU and norm kernels of 3 us each.)  FEW: at most 64 partial sums of squares a row.
+template <int MODE, bool FEW>
 __global__ __launch_bounds__(512) void k_gemm_stream_f32(const float* __restrict__ A, const float* __restrict__ W,
-                                                         float* __restrict__ C, int M, int N, int K, const RowsEpi ep) {
+                                                         float* __restrict__ C, int M, int N, int K, const RowsEpi ep_in) {
     constexpr int WAVES = 8, U = 4, MP = 17;
     __shared__ float red[WAVES * 16 * MP];
     __shared__ float s_scale[16], s_inv[16];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, fr = lane & 15, fq = lane >> 4, blk = blockIdx.x;
+    RowsEpi ep = ep_in;
+    {                                                      // everything that goes by rows moves along
+        const int m0 = blockIdx.y * 16;
+        M = min(M - m0, 16);
+        A += (size_t)m0 * K;
+        if (MODE == 0) C += (size_t)m0 * N;
+        if (MODE == 1) ep.act = (float*)ep.act + (size_t)m0 * ep.ffn;
+        if (MODE == 2) {
+            RopeOut& ro = ep.ro;
+            ro.pos += m0;
+            if (ro.kv_dst) ro.kv_dst += m0;
+            ro.q = (float*)ro.q + (size_t)m0 * ro.n_q_heads * ro.head_dim;
+            if (ro.k) ro.k = (float*)ro.k + (size_t)m0 * ro.n_kv_heads * ro.head_dim;
+            if (ro.v) ro.v = (float*)ro.v + (size_t)m0 * ro.n_kv_heads * ro.head_dim;
+        }
+        if (MODE == 3) {
+            ep.res.h += (size_t)m0 * N;
+            ep.res.x = (float*)ep.res.x + (size_t)m0 * N;
+            ep.res.s += m0;
+            ep.res.ssq += (size_t)m0 * kSsqStride;
+        } else if (ep.nrm.ssq) {
+            ep.nrm.ssq += (size_t)m0 * kSsqStride;
+            ep.nrm.s_in += m0;
+            if (ep.nrm.s_out) ep.nrm.s_out += m0;
+        }
+    }
     const bool normed = MODE != 3 && ep.nrm.ssq != nullptr;
-    StreamNorm<2, false> norm;
+    StreamNorm<2, FEW> norm;
     if (normed) norm.request(ep.nrm, M, w, lane);
     StreamEpilogue<1, 1, WAVES, MODE, float> epi;
     epi.request(ep, M, N, blk, t);
@@ -551,7 +577,7 @@ hipError_t stream_norm_launch(hipStream_t st, int mode, const bf16_t* a, const b
 }  // namespace
 
 bool gemm_stream_supported(int wdt, int adt, int M, int K) {
-    if (wdt == kF32) return adt == kF32 && M >= 1 && M <= kStreamResidRows && K >= 4 && K % 4 == 0;
+    if (wdt == kF32) return adt == kF32 && M >= 1 && M <= kStreamF32Rows && K >= 4 && K % 4 == 0;
     return wdt == kBF16 && (adt == kF16 || (adt == kBF16 && M <= 16)) && M >= 1 && M <= kStreamMaxRows && K > 0 && K % 64 == 0;
 }
 
@@ -597,8 +623,8 @@ static StreamShape stream_shape(int M, int N, int K, int ns) {
     if ((sh.nb == 1 || (sh.nb == 2 && sh.mb == 1)) && (per <= 4 || (per + 3) / 4 * 4 * 8 <= per * 9)) sh.depth = 4;
     return sh;
 }
-bool takes_gemm_rows(int M, int d) { return M > kStreamMaxRows || (M > 32 && !stream_resid(M, d) && d < 8192); }
-bool stream_resid(int M, int d) { return M <= kStreamResidRows || (M <= kStreamMaxRows && d <= 1024); }
+bool takes_gemm_rows(int M, int d) { return M > kStreamMaxRows || (M > 32 && !stream_resid(kBF16, M, d) && d < 8192); }
+bool stream_resid(int wdt, int M, int d) { return wdt == kF32 || M <= kStreamResidRows || (M <= kStreamMaxRows && d <= 1024); }
 // The split with the least time, in steps of a compute unit as above; a plane more costs its write, and its read by
 // the norm (about 1.3 us at 32 rows of 4096).
 int gemm_stream_nsplit(int M, int N, int K, int max_split) {
@@ -630,7 +656,7 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
             return hipErrorInvalidValue;
     }
     if (ep.nrm.ssq && wdt == kBF16 && (adt != kF16 || !ep.nrm.h || !ep.nrm.g)) return hipErrorInvalidValue;
-    if (ep.nrm.ssq && M > 16 && (ep.nrm.n_ssq > 64 || wdt == kF32 || mode == 0)) return hipErrorInvalidValue;
+    if (ep.nrm.ssq && M > 16 && wdt != kF32 && (ep.nrm.n_ssq > 64 || mode == 0)) return hipErrorInvalidValue;
     if (rows) return mode == 1 && ep.ffn % 16 ? hipErrorInvalidValue : launch_gemm_rows(st, wdt, mode, A, W, C, M, N, K, ep, nsplit);
     if (mode == 3 && (adt == kBF16 || N % 16 || N > 16 * kSsqStride || !ep.res.h || !ep.res.g || !ep.res.x || !ep.res.s || !ep.res.ssq))
         return hipErrorInvalidValue;
@@ -638,13 +664,20 @@ hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const 
         if (nsplit != 1 || ep.a.row != K || (mode == 1 && ep.out.row != ep.ffn) || (mode == 3 && ep.out.row != N))
             return hipErrorInvalidValue;                   // row-major only
         const float *af = (const float*)A, *wf = (const float*)W;
-        const int nb = (N + 15) / 16;
+        const dim3 grid((N + 15) / 16, (M + 15) / 16);
+        const bool few = ep.nrm.ssq && ep.nrm.n_ssq <= 64;
+#define RLHF_STREAM_F32(MODE)                                                                          \
+    case MODE:                                                                                         \
+        if (few) k_gemm_stream_f32<MODE, true><<<grid, 512, 0, st>>>(af, wf, C, M, N, K, ep);          \
+        else k_gemm_stream_f32<MODE, false><<<grid, 512, 0, st>>>(af, wf, C, M, N, K, ep);             \
+        break
         switch (mode) {
-            case 0: k_gemm_stream_f32<0><<<nb, 512, 0, st>>>(af, wf, C, M, N, K, ep); break;
-            case 1: k_gemm_stream_f32<1><<<nb, 512, 0, st>>>(af, wf, C, M, N, K, ep); break;
-            case 2: k_gemm_stream_f32<2><<<nb, 512, 0, st>>>(af, wf, C, M, N, K, ep); break;
-            default: k_gemm_stream_f32<3><<<nb, 512, 0, st>>>(af, wf, C, M, N, K, ep); break;
+            RLHF_STREAM_F32(0);
+            RLHF_STREAM_F32(1);
+            RLHF_STREAM_F32(2);
+            default: k_gemm_stream_f32<3, false><<<grid, 512, 0, st>>>(af, wf, C, M, N, K, ep); break;
         }
+#undef RLHF_STREAM_F32
         return hipGetLastError();
     }
     const bf16_t* a = (const bf16_t*)A;

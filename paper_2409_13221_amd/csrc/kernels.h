@@ -86,8 +86,9 @@ hipError_t launch_gemm_rope(hipStream_t st, int wdt, int adt, const void* A, con
 // mode 2: QKV with rotary embedding and the q / k / v / paged-pool scatter (ep.ro as in launch_gemm_rope);
 // mode 3: residual: h += result, and the unscaled input of the next norm (ep.res).
 // Half activations: 1..kStreamMaxRows rows; bf16 activations: 1..16; K a multiple of 64.  Float weights and
-// activations (row-major): 1..16 rows, K a multiple of 4.
+// activations (row-major): 1..kStreamF32Rows rows, K a multiple of 4.
 constexpr int kStreamMaxRows = 64;
+constexpr int kStreamF32Rows = 448;   // prefill of 32-token prompts, 2 layers of d = 256, this kernel / gemm_f32.hip, ms: 64 rows 0.18 0.24, 256 0.20 0.25, 384 0.23 0.24, 480 0.257 0.254
 constexpr int kSsqStride = 512; // floats per row of the partial sums of squares (d_model <= 8192, 16 columns each)
 struct NormIn {                 // modes 0..2: A holds x = h * gain * s_in; result of row m times (1/rms) / s_in[m]
     const float* ssq = nullptr;     // [M, kSsqStride] partial sums of h^2 (n_ssq used, the others zero), or NULL: A is used as it is
@@ -118,8 +119,8 @@ bool gemm_stream_supported(int wdt, int adt, int M, int K);
 constexpr int kStreamResidRows = 16;
 // Whether a pass over a residual stream of d columns runs on mode 3 and NormIn: any up to kStreamResidRows
 // rows; half activations of up to 64 partial sums (n_ssq, a column block of 16 each) at any row count here,
-// but not into mode 0.
-bool stream_resid(int M, int d);
+// but not into mode 0; float ones always.
+bool stream_resid(int wdt, int M, int d);
 // Mode 0 may split K into nsplit planes C [nsplit][M][N]; the split for O and down projections otherwise:
 int gemm_stream_nsplit(int M, int N, int K, int max_split);
 hipError_t launch_gemm_stream(hipStream_t st, int wdt, int adt, int mode, const void* A, const void* W, float* C,
@@ -138,6 +139,11 @@ int gemm_rows_nsplit(int N, int K, int max_split);
 bool takes_gemm_rows(int M, int d);
 hipError_t launch_gemm_rows(hipStream_t st, int wdt, int mode, const void* A, const void* W, float* C, int M, int N, int K,
                             const RowsEpi& ep, int nsplit);
+
+// Many rows of float models (gemm_f32.hip), row-major, modes as in launch_gemm_stream without norms; mode 3: ep.res.h += result.
+bool gemm_f32_tall_supported(int N, int K, int mode);
+hipError_t launch_gemm_f32_tall(hipStream_t st, int mode, const float* A, const float* W, float* C, int M, int N, int K,
+                                const RowsEpi& ep);
 
 // LM head of a scoring pass fused with the log-softmax gather: the logits stay in registers.  Per
 // row m the GEMM leaves n_part = gemm_lse_partials(N) pairs (max, sum of exp(z - max)), one per 128
@@ -248,6 +254,10 @@ constexpr int kFlashTile = 128;
 hipError_t launch_flash_attn(hipStream_t st, const void* q, const void* k, const void* v,
                              const int* tile_start, const int* tile_q0, const int* tile_len, void* out,
                              int n_tiles, int T_total, const Dims& dm);
+
+// The same in float.
+hipError_t launch_flash_attn_f32(hipStream_t st, const float* q, const float* k, const float* v, const int* tile_start,
+                                 const int* tile_q0, const int* tile_len, float* out, int n_tiles, const Dims& dm);
 
 size_t pool_page_elems(const Dims& dm);  // elements of one page over all layers
 

@@ -1,0 +1,35 @@
+"""Float models beyond 16 rows: decode steps and short passes in groups of 16 rows, longer passes on the matrix-instruction
+kernels with their epilogues, packed attention over sequences at the edges of 16 and 128 queries.  Sizes leave remainders
+everywhere: K of 13 and 7.5 chunks of 16, ragged column tiles, a width that is no multiple of 16."""
+from dataclasses import replace
+
+import pytest
+
+from tests import stage_harness as H
+from workload import CONFIGS
+
+pytestmark = pytest.mark.gpu
+
+_TINY = CONFIGS["tiny"]
+_BASE = replace(_TINY.model, n_layers=2, d_model=208, n_q_heads=2, n_kv_heads=2, head_dim=64, ffn=120, vocab=203)
+_HD128 = replace(_BASE, head_dim=128, n_q_heads=3, n_kv_heads=3)
+_UNEVEN = replace(_BASE, d_model=200)
+# more partial sums of squares than one per lane
+_WIDE = replace(_BASE, n_layers=1, d_model=1040)
+
+
+@pytest.mark.parametrize("model,n,prompt", [(_BASE, 17, (3, 5)), (_BASE, 64, (3, 5)), (_BASE, 120, (3, 5)), (_BASE, 200, (3, 5)),
+                                            (_HD128, 33, (3, 5)), (_UNEVEN, 5, (3, 5)), (_UNEVEN, 40, (3, 5)), (_WIDE, 20, (3, 5)),
+                                            (_BASE, 5, (110, 150)), (_HD128, 4, (120, 145)), (_BASE, 3, (15, 33)), (_TINY.model, 4, (127, 129))])
+def test_float_stage_beyond_16_rows(model, n, prompt):
+    cfg = _TINY.with_(name="float_rows", model=model, n_samples=n, prompt_len=prompt, gain_jitter=0.05)
+    ref = H.oracle_stage(cfg, n=n, max_len=4)
+    got = H.run_gpu_stage(cfg, ref, fused=False, R_t=0, chunk_tokens=4096, max_batch_tokens=4096)
+    H.compare_stage(cfg, ref, got)
+
+
+def test_float_decode_steps_beyond_the_few_row_kernel():
+    cfg = _TINY.with_(name="float_many", model=replace(_BASE, n_layers=1), n_samples=460, prompt_len=(2, 3), gain_jitter=0.05)
+    ref = H.oracle_stage(cfg, n=460, max_len=3)
+    got = H.run_gpu_stage(cfg, ref, fused=False, R_t=0, chunk_tokens=4096, max_batch_tokens=4096)
+    H.compare_stage(cfg, ref, got)
