@@ -448,18 +448,27 @@ __global__ void k_attn_merge(const float* __restrict__ part_acc, const float* __
     out[act_index(ol, r, h * HD + e)] = from_f32<T>(at / lt);
 }
 
+// Longest context, in pages, up to which four waves a row and one page in flight are enough where the rows fill the chip
+// (64 rows of 32 heads of 128, contexts between half of it and all, us, four waves / eight with two pages in flight: 1 page 6.3
+// 12.5, 4 11.5 15.3, 8 21.2 21.2, 12 28.0 27.1, 20 47.0 41.1, 32 71.3 65.1; 123 rows of 12 heads of 64: 4 6.3 9.3, 12 12.5 13.0, 24
+// 22.3 20.1).
+constexpr int kShortPages = 12;
+
 // Waves per workgroup: a workgroup holds one (row, KV head, split), its waves take the pages in turn.
 // With few workgroups the pages of one are spread over 16 waves, merged in LDS, where more splits would cost a
 // merge kernel (about 4 us): 32 heads of 128, half, 1 row at context 500 12.2 us with 4 waves, 9.3 with 16; grouped heads
 // (64 over 8), 32 rows at 1100 33.4 / 27.9 with 4 / 8.
-static int decode_attn_waves(long blocks, int group) { return group > 1 ? (blocks >= 512 ? 4 : 8) : blocks >= 256 ? 8 : 16; }
+static int decode_attn_waves(long blocks, int group, int max_pages) {
+    if (group > 1) return blocks >= 512 ? 4 : 8;
+    return blocks >= 512 && max_pages > 0 && max_pages <= kShortPages ? 4 : blocks >= 256 ? 8 : 16;
+}
 
 // As many splits as give the chip about sixteen waves per compute unit (twelve of the grouped kernel,
 // which keeps more in flight: 32 rows at 1100 27.9 us unsplit, 30.3 with two), unless that leaves a wave
 // with fewer than four pages.
 int decode_attn_nsplit(int rows, int max_pages, const Dims& dm, int max_split) {
     const long blocks = (long)rows * dm.n_kv_heads;
-    const int group = dm.n_q_heads / dm.n_kv_heads, wv = decode_attn_waves(blocks, group);
+    const int group = dm.n_q_heads / dm.n_kv_heads, wv = decode_attn_waves(blocks, group, max_pages);
     long ns = (group > 1 ? 3072 : 4096) / (blocks * wv > 0 ? blocks * wv : 1);
     const int by_pages = (max_pages + wv * 4 - 1) / (wv * 4);
     if (ns > by_pages) ns = by_pages;
@@ -475,6 +484,9 @@ static void decode_attn_run(hipStream_t st, dim3 grid, int wv, const void* q, co
     if (wv == 16)
         k_decode_attn<T, HD, 1, 16, PF><<<grid, 1024, 0, st>>>((const T*)q, (const T*)pool, page_table, pt_stride, row_sample, ctx_len, (T*)out,
                                                                part_acc, part_ml, layer, nsplit, dm.n_layers, dm.n_kv_heads, ol);
+    else if (wv == 4)
+        k_decode_attn<T, HD, 1, 4, false><<<grid, 256, 0, st>>>((const T*)q, (const T*)pool, page_table, pt_stride, row_sample, ctx_len, (T*)out,
+                                                                part_acc, part_ml, layer, nsplit, dm.n_layers, dm.n_kv_heads, ol);
     else
         k_decode_attn<T, HD, 1, 8, PF><<<grid, 512, 0, st>>>((const T*)q, (const T*)pool, page_table, pt_stride, row_sample, ctx_len, (T*)out,
                                                              part_acc, part_ml, layer, nsplit, dm.n_layers, dm.n_kv_heads, ol);
@@ -483,14 +495,14 @@ static void decode_attn_run(hipStream_t st, dim3 grid, int wv, const void* q, co
 hipError_t launch_decode_attn(hipStream_t st, int dtype, const void* q, const void* pool,
                               const int* page_table, int pt_stride, const int* row_sample,
                               const int* ctx_len, void* out, float* part_acc, float* part_ml,
-                              int rows, int layer, int nsplit, const Dims& dm, const ActLayout& out_layout) {
+                              int rows, int layer, int nsplit, const Dims& dm, const ActLayout& out_layout, int max_pages) {
     if (rows <= 0) return hipSuccess;
     const int G = dm.n_q_heads / dm.n_kv_heads, hd = dm.head_dim;
     if (dm.page_tokens != kPT || nsplit < 1 || (hd != 64 && hd != 128)) return hipErrorInvalidValue;
     ActLayout ol = out_layout;
     if (ol.row == 0) ol = ActLayout{dm.n_q_heads * hd, 8};
     const dim3 grid(rows, dm.n_kv_heads, nsplit);
-    const int wv = decode_attn_waves((long)rows * dm.n_kv_heads, G);
+    const int wv = decode_attn_waves((long)rows * dm.n_kv_heads, G, max_pages);
     if (G == 1) {
         auto run = [&](auto f) {
             f(st, grid, wv, q, pool, page_table, pt_stride, row_sample, ctx_len, out, part_acc, part_ml, layer, nsplit, dm, ol);

@@ -355,6 +355,7 @@ struct PassMeta {         // device pointers into a MetaRing arena
     const int* kv_dst = nullptr;       // NULL: no pool writes
     const int* row_sample = nullptr;   // decode
     const int* ctx_len = nullptr;      // decode
+    int max_pages = 0;                 // decode: of the longest context
     const int* row_start = nullptr;    // batch (float models)
     const int* tile_start = nullptr;   // batch (bf16 models): query tiles of the MFMA attention
     const int* tile_q0 = nullptr;
@@ -461,7 +462,7 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
             HIPCK(c, profiled(c, st, kAttnDecode, pm.attn_bytes, pm.attn_flops, [&] {
                 return launch_decode_attn(st, adt, ws.q, c->pool, c->d_page_table, c->max_pages, pm.row_sample,
                                           pm.ctx_len, ws.attn, ws.attn_acc, ws.attn_ml, rows, l, attn_nsplit, c->dm,
-                                          attn_layout);
+                                          attn_layout, pm.max_pages);
             }));
         } else {
             HIPCK(c, profiled(c, st, kAttnBatch, pm.attn_bytes, pm.attn_flops, [&] {
@@ -600,7 +601,7 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
             HIPCK(c, profiled(c, st, kAttnDecode, pm.attn_bytes, pm.attn_flops, [&] {
                 return launch_decode_attn(st, adt, ws.q, c->pool, c->d_page_table, c->max_pages, pm.row_sample,
                                           pm.ctx_len, ws.attn, ws.attn_acc, ws.attn_ml, rows, l, attn_nsplit,
-                                          c->dm);
+                                          c->dm, ActLayout{}, pm.max_pages);
             }));
         } else {
             HIPCK(c, profiled(c, st, kAttnBatch, pm.attn_bytes, pm.attn_flops, [&] {
@@ -1226,6 +1227,7 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
     pm.kv_dst = dmeta + 2 * R;
     pm.row_sample = dmeta + 3 * R;
     pm.ctx_len = dmeta + 4 * R;
+    pm.max_pages = ceil_div(max_ctx_len, pt);
     {
         const double kvd_ = (double)c->mc.n_kv_heads * c->mc.head_dim, qd_ = (double)c->mc.n_q_heads * c->mc.head_dim;
         const double keys = (double)(kv_tokens - R);           // sum of visible keys over rows
@@ -1235,7 +1237,7 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
     // split long contexts so that a handful of samples still fills the chip
     Workspace& ws = c->ws_dec;
     const int max_split = (int)std::min<size_t>(32, ws.attn_slots / ((size_t)R * c->mc.n_q_heads));
-    const int asplit = decode_attn_nsplit(R, ceil_div(max_ctx_len, pt), c->dm, std::max(1, max_split));
+    const int asplit = decode_attn_nsplit(R, pm.max_pages, c->dm, std::max(1, max_split));
 
     const rlhf_weights& w = c->roles[RLHF_ACTOR].w;
     const int d = c->mc.d_model, V = c->mc.vocab;

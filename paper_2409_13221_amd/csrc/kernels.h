@@ -232,11 +232,12 @@ hipError_t launch_gae(hipStream_t st, const float* lp_actor, const float* lp_ref
 // Decode: one query row per active sample against its paged K/V.  q [rows, Hq*hd]; out the same.
 // row_sample[r] selects the page-table row; ctx_len[r] keys are visible.  part_* hold split
 // partials when nsplit > 1 (sizes rows*Hq*nsplit*(hd or 1)).
-// out_layout: row-major by default.
+// out_layout: row-major by default.  max_pages: pages of the longest context, 0 where the caller does not know.
 hipError_t launch_decode_attn(hipStream_t st, int dtype, const void* q, const void* pool,
                               const int* page_table, int pt_stride, const int* row_sample,
                               const int* ctx_len, void* out, float* part_acc, float* part_ml,
-                              int rows, int layer, int nsplit, const Dims& dm, const ActLayout& out_layout = ActLayout{});
+                              int rows, int layer, int nsplit, const Dims& dm, const ActLayout& out_layout = ActLayout{},
+                              int max_pages = 0);
 // Splits of the contexts for a decode step of `rows` rows whose longest context has max_pages pages.
 int decode_attn_nsplit(int rows, int max_pages, const Dims& dm, int max_split);
 // Prefill / scoring: packed varlen causal attention over contiguous float q [T,Hq*hd], k, v
