@@ -305,8 +305,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_gemm_stream(const bf16_t* __rest
     // they would all ask for the same offset within a row of W at a time, and where the rows lie a multiple of 16 KB
     // apart, or 2752 k, that keeps part of the memory channels waiting (us, in step / rotated: N = 4096, 13 rows, K = 8192
     // 14.8 / 13.0, 11008 18.5 / 16.7, 16384 26.8 / 22.4, 22016 40.8 / 35.1; N = 12288, 32 rows, K = 8192 42.9 / 33.0; the
-    // other K between 1024 and 28672 are the same within 2 %)
-    const int rot = n_real > 0 ? (blk >> 3) % n_real : 0;
+    // other K between 1024 and 28672 are the same within 2 %; but for the LM head, N = 32000, K = 4096, 1 row 38.6 / 40.8: one plane
+    // of mode 0 is rotated for the first reason only)
+    const int rot = n_real > 0 && (MODE != 0 || gridDim.y > 1 || K % 8192 == 0) ? (blk >> 3) % n_real : 0;
 
     __amdgpu_buffer_rsrc_t rs[NB][2];
     uint32_t vo[NB][2];
