@@ -11,6 +11,7 @@
 // working on the present one, two in flight, ran at 71 and 82.
 #include "common.h"
 #include "kernels.h"
+#include <algorithm>
 
 namespace rlhf {
 
@@ -280,6 +281,28 @@ __global__ __launch_bounds__(256) void k_flash_attn_f32(const float* __restrict_
                 make_float4(o[x * 4][e] * inv, o[x * 4 + 1][e] * inv, o[x * 4 + 2][e] * inv, o[x * 4 + 3][e] * inv);
 }
 
+// Rows per wave (16 * mbw) with the least time.  A workgroup's chunk of 16 k takes its matrix instructions, 512 * mbw cycles, or
+// its four waves' loads, 66 cycles each (mbw + 4 of them a wave), whichever is more, and workgroups share a compute unit's
+// time: rounds of 256 of them.  More rows a wave need fewer loads a product but fill the chip later.  us, 16 / 32 / 64
+// rows a wave: N = K = 4096 64 rows 141 / 120 / 234, 512 rows 281 / 174 / 240, 1024 rows 560 / 344 / 242, 2048 rows 1115 / 688 / 567;
+// N = 22016, K = 4096 64 rows 302 / 246 / 238; N = K = 768 1024 rows 29 / 34 / 49.  (By the number of workgroups alone, from 512
+// of them on, the choice was up to 2.3 times the best one, and up to 1.22 times the kernel of gemm.hip.)  A second round
+// of 64 rows takes a sixth more than the first.  The choice is within 3 % of the best one from 64 rows on (N = 256 .. 32000, K =
+// 256 .. 11008, up to 4096 rows), and below 0.94 times the kernel of gemm.hip.
+struct F32Shape { int mbw; double us; };
+static F32Shape f32_shape(int M, int N, int K) {
+    F32Shape best{1, 0.};
+    for (int b = 1; b <= 4; b *= 2) {
+        const int waves = std::min(4, (M + 16 * b - 1) / (16 * b));
+        const long rounds = ((long)((N + 63) / 64) * ((M + 64 * b - 1) / (64 * b)) + 255) / 256;
+        const double chunk = b == 4 && rounds > 1 ? 37. : std::max(8 * b, waves * (b + 4));       // in 64 cycles
+        const double us = 3. + (K + 15) / 16 * 0.0272 * (double)rounds * chunk;
+        if (b == 1 || us < 0.97 * best.us) best = F32Shape{b, us};
+    }
+    return best;
+}
+double gemm_f32_tall_us(int M, int N, int K) { return f32_shape(M, N, K).us; }
+
 bool gemm_f32_tall_supported(int N, int K, int mode) { return K >= 4 && K % 4 == 0 && (mode == 0 || N % 8 == 0); }
 
 hipError_t launch_gemm_f32_tall(hipStream_t st, int mode, const float* A, const float* W, float* C, int M, int N, int K,
@@ -294,8 +317,7 @@ hipError_t launch_gemm_f32_tall(hipStream_t st, int mode, const float* A, const 
             return hipErrorInvalidValue;
     }
     const int cols = mode == 1 ? (ep.ffn + 31) / 32 : (N + 63) / 64;
-    // 32 rows a wave as soon as that leaves four workgroups for every compute unit
-    const int mbw = (long)cols * ((M + 255) / 256) >= 512 ? 4 : (long)cols * ((M + 127) / 128) >= 512 ? 2 : 1;
+    const int mbw = f32_shape(M, N, K).mbw;
     const dim3 grid(cols, (M + 64 * mbw - 1) / (64 * mbw));
 #define RLHF_F32(MODE)                                                                                    \
     case MODE:                                                                                            \

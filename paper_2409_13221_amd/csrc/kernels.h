@@ -142,6 +142,7 @@ hipError_t launch_gemm_rows(hipStream_t st, int wdt, int mode, const void* A, co
 
 // Many rows of float models (gemm_f32.hip), row-major, modes as in launch_gemm_stream without norms; mode 3: ep.res.h += result.
 bool gemm_f32_tall_supported(int N, int K, int mode);
+double gemm_f32_tall_us(int M, int N, int K);      // estimated time of a launch
 hipError_t launch_gemm_f32_tall(hipStream_t st, int mode, const float* A, const float* W, float* C, int M, int N, int K,
                                 const RowsEpi& ep);
 

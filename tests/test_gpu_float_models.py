@@ -3,8 +3,11 @@ kernels with their epilogues, packed attention over sequences at the edges of 16
 everywhere: K of 13 and 7.5 chunks of 16, ragged column tiles, a width that is no multiple of 16."""
 from dataclasses import replace
 
+import numpy as np
 import pytest
+import torch
 
+import paper_2409_13221_amd as R
 from tests import stage_harness as H
 from workload import CONFIGS
 
@@ -33,3 +36,16 @@ def test_float_decode_steps_beyond_the_few_row_kernel():
     ref = H.oracle_stage(cfg, n=460, max_len=3)
     got = H.run_gpu_stage(cfg, ref, fused=False, R_t=0, chunk_tokens=4096, max_batch_tokens=4096)
     H.compare_stage(cfg, ref, got)
+
+
+# 16, 32 and 64 rows a wave, one round of workgroups and more, with ragged rows, columns and chunks of 16 k
+@pytest.mark.parametrize("M,N,K", [(1, 65, 4), (63, 1003, 36), (100, 9001, 36), (129, 8999, 20), (600, 4100, 36), (513, 9002, 20), (2049, 515, 260)])
+def test_unsplit_float_gemm_at_every_tile_height(M, N, K):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    A, W = torch.randn(M, K, device="cuda", generator=g), torch.randn(N, K, device="cuda", generator=g)
+    out = torch.full((1, M, N), float("nan"), device="cuda")
+    R.rlhf_op_gemm(A, W, out, 1)
+    want = (A.double() @ W.double().T).cpu().numpy()
+    # K products of size 1 summed in float: sqrt(K) roundings of terms up to sqrt(K) in size, four times over
+    np.testing.assert_allclose(out[0].cpu().numpy(), want, rtol=0, atol=4 * 2.0 ** -23 * K + 1e-5)
