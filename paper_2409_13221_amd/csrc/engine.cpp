@@ -367,7 +367,10 @@ struct PassMeta {         // device pointers into a MetaRing arena
 // Few rows: every layer runs on the projections of gemm_stream.hip.
 bool stream_pass(const rlhf_ctx* c, int rows) {
     const rlhf_model_cfg& m = c->mc;
-    if (c->dtype == kF32) return rows <= kStreamF32Rows && m.d_model % 16 == 0;
+    if (c->dtype == kF32) {
+        const double d = m.d_model, qd = (double)m.n_q_heads * m.head_dim, kvd = (double)m.n_kv_heads * m.head_dim;
+        return m.d_model % 16 == 0 && stream_f32_pays(rows, ((2 * qd + 2 * kvd) * d + 3 * d * m.ffn) * 4);
+    }
     return c->dtype == kBF16 && rows <= kRowsMaxRows && m.d_model % 64 == 0 && (m.n_q_heads * m.head_dim) % 64 == 0 &&
            m.ffn % 64 == 0;
 }
@@ -522,9 +525,8 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         return RLHF_OK;
     };
     const bool can16 = dt == kBF16 && adt == kF16 && d % 64 == 0;
-    // float models: every projection on the kernel of gemm_f32.hip, its consumer in the epilogue
-    const bool f32 = dt == kF32 && gemm_f32_tall_supported(qkv_w, d, 2) && gemm_f32_tall_supported(2 * f, d, 1) &&
-                     gemm_f32_tall_supported(d, qd, 3) && gemm_f32_tall_supported(d, f, 3);
+    // float models: a projection that is not split runs on the kernel of gemm_f32.hip, its consumer in the epilogue
+    auto whole_f32 = [&](int N, int K) { return dt == kF32 && nsplit_for(c, ws, rows, N, K) == 1; };
     auto project_f32 = [&](int mode, const void* A, const void* W, int N, int K, const RowsEpi& ep) {
         const double bytes = ((double)N * K + (double)rows * K + (double)rows * N) * es;
         return profiled(c, st, gcls, bytes, 2.0 * rows * N * K,
@@ -535,7 +537,8 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
     // O and down projections: an unsplit tall one finishes the residual stream, the others leave pns planes that
     // RMSNorm adds
     auto into_stream = [&](const void* A, const void* w_bf16, const void* w_half, int l, int K) -> int {
-        if (f32) {
+        if (whole_f32(d, K)) {
+            pns = 0;
             RowsEpi ep;
             ep.res.h = ws.h;
             HIPCK(c, project_f32(3, A, layer_ptr(w_bf16, l, d, K, es), d, K, ep));
@@ -561,6 +564,7 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, pns, pstride, nullptr, w.g_attn + (size_t)l * d,
                                 ws.xn, rows, d, m.rms_eps));
         int ns = 0;
+        const bool f32 = whole_f32(qkv_w, d);
         if (f32 || (mode == kModeBatch && gemm_rope_supported(dt, adt, rows, d, c->dm))) {
             // tall pass: rotary, rounding and the q / k / v / pool scatter ride in the GEMM's epilogue
             RopeOut ro;
@@ -616,7 +620,7 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         if (rc_proj) return rc_proj;
         HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, pns, pstride, nullptr, w.g_mlp + (size_t)l * d, ws.xn, rows, d,
                                 m.rms_eps));
-        if (f32) {
+        if (whole_f32(2 * f, d)) {
             RowsEpi ep;
             ep.act = ws.act;
             ep.ffn = f;
@@ -1003,7 +1007,7 @@ int lm_head_chunks(rlhf_ctx* c, hipStream_t st, Workspace& ws, const rlhf_weight
     for (int r0 = 0; r0 < hp.n_sel; r0 += ws.logit_rows) {
         const int nr = std::min(ws.logit_rows, hp.n_sel - r0);
         const char* x = (const char*)ws.xsel + (size_t)r0 * d * c->esz;
-        if (gemm_stream_supported(c->dtype, act_type(c, true), nr, d)) {
+        if (gemm_stream_supported(c->dtype, act_type(c, true), nr, d) && (c->dtype != kF32 || stream_f32_pays(nr, (double)V * d * 4))) {
             const double bytes = ((double)V * d + (double)nr * d) * c->esz + (double)nr * V * 4;
             HIPCK(c, profiled(c, st, kGemmBatch, bytes, 2.0 * nr * V * d, [&] {
                 return launch_gemm_stream(st, c->dtype, act_type(c, true), 0, x, w.head, ws.logits, nr, V, d, RowsEpi{});
@@ -1250,16 +1254,22 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
         const int adt = act_type(c, false);
         if (adt == kF16) ep.a = ActLayout{8, 8 * R};
         const bool many = adt == kF16 && takes_gemm_rows(R, d), hw = many && c->roles[RLHF_ACTOR].h16.head;
-        if (R <= kStreamResidRows || adt == kF32)
+        const bool head_stream = adt != kF32 || stream_f32_pays(R, (double)V * d * 4);
+        if (R <= kStreamResidRows || (adt == kF32 && head_stream))
             ep.nrm = stream_norm(c, ws, w.g_final, n_ssq, ws.scale, nullptr);
         else
             HIPCK(c, launch_rmsnorm(c->sd, adt, ws.h, ws.part, pns, (size_t)R * d, nullptr, w.g_final, ws.xn, R, d,
                                     c->mc.rms_eps, ep.a));
-        const double bytes = ((double)V * d + (double)R * d) * c->esz + (double)R * V * 4;
-        HIPCK(c, profiled(c, c->sd, kGemmDecode, bytes, 2.0 * R * V * d, [&] {
-            return launch_gemm_stream(c->sd, hw ? kF16 : c->dtype, adt, 0, ws.xn, hw ? c->roles[RLHF_ACTOR].h16.head : w.head, ws.part, R,
-                                      V, d, ep, 1, many);
-        }));
+        if (head_stream) {
+            const double bytes = ((double)V * d + (double)R * d) * c->esz + (double)R * V * 4;
+            HIPCK(c, profiled(c, c->sd, kGemmDecode, bytes, 2.0 * R * V * d, [&] {
+                return launch_gemm_stream(c->sd, hw ? kF16 : c->dtype, adt, 0, ws.xn, hw ? c->roles[RLHF_ACTOR].h16.head : w.head, ws.part, R,
+                                          V, d, ep, 1, many);
+            }));
+        } else {
+            ns = nsplit_for(c, ws, R, V, d);
+            HIPCK(c, gemm_profiled(c, c->sd, kGemmDecode, adt, ws.xn, w.head, ws.part, R, V, d, ns));
+        }
     } else {
         int pns;
         size_t pstride;
@@ -1647,7 +1657,8 @@ bool serial_is_faster(const rlhf_ctx* c) {
     const double qd = (double)m.n_q_heads * m.head_dim, kvd = (double)m.n_kv_heads * m.head_dim;
     const double per_layer = (qd + 2 * kvd) * m.d_model + m.d_model * qd + 3.0 * m.d_model * m.ffn;
     const double stream_us = (m.n_layers * per_layer + (double)m.vocab * m.d_model) * c->esz / 5.0e6;
-    const int launches = stream_resid(c->dtype, std::min(c->N, c->ec.max_active), m.d_model) ? 5 : 7;
+    const int rows = std::min(c->N, c->ec.max_active);
+    const int launches = stream_resid(c->dtype, rows, m.d_model) && (c->dtype != kF32 || stream_pass(c, rows)) ? 5 : 7;
     return stream_us < (launches * m.n_layers + 6) * 4.0;
 }
 }  // namespace

@@ -487,6 +487,15 @@ int gemm_choose_nsplit(int wdt, int M, int N, int K, int max_split) {
         if ((long)(ns - 1) * kchunk < K) break;
         --ns;
     }
+    // Float planes against the unsplit kernel of gemm_f32.hip, which also finishes rotary, SwiGLU or the residual stream.  Planes:
+    // 0.065 us a k of a split, more from about 512 workgroups on, and a plane is written and read.  us, unsplit / planes with
+    // their reading: N = K = 1024 64 rows 31 / 7, 512 rows 37 / 22; N = 11008, K = 2048 256 rows 122 / 176, 64 rows 62 / 54;
+    // N = K = 4096 512 rows 174 / 238, 256 rows 142 / 133; N = 4096, K = 256 448 rows 15 / 24.
+    if (wdt == kF32 && ns > 1) {
+        const double planes_us = 3. + (double)((K + ns - 1) / ns) * std::max(0.065, 0.01 + 1.02e-4 * (double)tiles * ns) +
+                                 8. * M * N * ns / 5e6;
+        if (gemm_f32_tall_us(M, N, K) < planes_us) ns = 1;
+    }
     return ns;
 }
 

@@ -582,6 +582,15 @@ bool gemm_stream_supported(int wdt, int adt, int M, int K) {
     return wdt == kBF16 && (adt == kF16 || (adt == kBF16 && M <= 16)) && M >= 1 && M <= kStreamMaxRows && K > 0 && K % 64 == 0;
 }
 
+// Every group of 16 rows reads the whole matrix again, mostly out of the caches, and beyond two groups that pays as long as
+// the groups together read less than about 256 MB a layer.  Prefill, us a layer, groups of 16 / the kernels of gemm.hip and
+// gemm_f32.hip: d = 256 (3.2 MB a layer) 64 rows 55 / 76, 448 rows 90 / 94; 512 (13 MB) 128 rows 67 / 93, 256 93 / 107, 448 134 / 133;
+// 768 (28 MB) 96 rows 105 / 110, 192 148 / 125; 1024 (50 MB) 64 rows 92 / 107, 128 135 / 130; 1536 (113 MB) 32 rows 117 / 139, 48
+// 151 / 145; 2048 (201 MB) 32 rows 172 / 204, 64 265 / 222, 448 1290 / 766; 4096 (809 MB) 32 rows 556 / 588, 64 934 / 633.
+bool stream_f32_pays(int M, double bytes) {
+    return M <= 32 || (M <= kStreamF32Rows && (M + 15) / 16 * bytes <= 256e6);
+}
+
 // Shape of a launch: 16-row blocks of activations, of weights per workgroup (nb), ring depth (four waves throughout).
 // Every workgroup reads all activation rows of its K range, from the L2, and the loads of a compute unit share one
 // queue.  A compute unit's time goes with the 16 * nb weight rows of its workgroup plus about half the activation

@@ -88,7 +88,7 @@ hipError_t launch_gemm_rope(hipStream_t st, int wdt, int adt, const void* A, con
 // Half activations: 1..kStreamMaxRows rows; bf16 activations: 1..16; K a multiple of 64.  Float weights and
 // activations (row-major): 1..kStreamF32Rows rows, K a multiple of 4.
 constexpr int kStreamMaxRows = 64;
-constexpr int kStreamF32Rows = 448;   // prefill of 32-token prompts, 2 layers of d = 256, this kernel / gemm_f32.hip, ms: 64 rows 0.18 0.24, 256 0.20 0.25, 384 0.23 0.24, 480 0.257 0.254
+constexpr int kStreamF32Rows = 448;   // beyond, other kernels are level or ahead at every width (stream_f32_pays)
 constexpr int kSsqStride = 512; // floats per row of the partial sums of squares (d_model <= 8192, 16 columns each)
 struct NormIn {                 // modes 0..2: A holds x = h * gain * s_in; result of row m times (1/rms) / s_in[m]
     const float* ssq = nullptr;     // [M, kSsqStride] partial sums of h^2 (n_ssq used, the others zero), or NULL: A is used as it is
@@ -116,6 +116,8 @@ struct RowsEpi {
     ResidOut res;
 };
 bool gemm_stream_supported(int wdt, int adt, int M, int K);
+// Whether float weights of `bytes` (a layer, or the LM head) are best read once per 16 rows: see gemm_stream.hip.
+bool stream_f32_pays(int M, double bytes);
 constexpr int kStreamResidRows = 16;
 // Whether a pass over a residual stream of d columns runs on mode 3 and NormIn: any up to kStreamResidRows
 // rows; half activations of up to 64 partial sums (n_ssq, a column block of 16 each) at any row count here,

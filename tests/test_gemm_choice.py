@@ -27,3 +27,15 @@ def test_every_split_has_a_k_range(max_split):
                 ns = R.rlhf_op_gemm_nsplit(R.RLHF_BF16, M, N, K, max_split)
                 assert 1 <= ns <= max_split
                 assert (ns - 1) * (-(-(-(-K // ns)) // 64) * 64) < K
+
+
+@pytest.mark.parametrize("M,N,K,nsplit", [
+    (64, 1024, 1024, 16),     # planes 7, unsplit 31
+    (512, 1024, 1024, 8),     # planes 22, unsplit 37
+    (512, 4096, 4096, 1),     # planes 238 with their reading, unsplit 174
+    (256, 4096, 4096, 4),     # planes 133, unsplit 142
+    (256, 11008, 2048, 1),    # planes 176, unsplit 122
+    (460, 4096, 256, 1),      # planes 24, unsplit 15
+])
+def test_split_of_float_models(M, N, K, nsplit):
+    assert R.rlhf_op_gemm_nsplit(R.RLHF_FP32, M, N, K, 16) == nsplit

@@ -31,6 +31,20 @@ def test_float_stage_beyond_16_rows(model, n, prompt):
     H.compare_stage(cfg, ref, got)
 
 
+# layers of 60 MB, which groups of 16 rows would read five times and more: planes and unsplit projections instead; and an
+# LM head of 27 MB beside small layers, which leaves the groups before the layers do
+_HEAVY = replace(_BASE, n_layers=1, d_model=1040, n_q_heads=8, n_kv_heads=8, ffn=4096)
+_HEAD = replace(_BASE, n_layers=1, vocab=32001)
+
+
+@pytest.mark.parametrize("model,n,prompt", [(_HEAVY, 33, (2, 3)), (_HEAVY, 80, (2, 3)), (_HEAVY, 6, (60, 90)), (_HEAD, 150, (2, 3))])
+def test_float_weights_too_large_to_read_again(model, n, prompt):
+    cfg = _TINY.with_(name="float_heavy", model=model, n_samples=n, prompt_len=prompt, gain_jitter=0.05)
+    ref = H.oracle_stage(cfg, n=n, max_len=3)
+    got = H.run_gpu_stage(cfg, ref, fused=False, R_t=0, chunk_tokens=4096, max_batch_tokens=4096)
+    H.compare_stage(cfg, ref, got)
+
+
 def test_float_decode_steps_beyond_the_few_row_kernel():
     cfg = _TINY.with_(name="float_many", model=replace(_BASE, n_layers=1), n_samples=460, prompt_len=(2, 3), gain_jitter=0.05)
     ref = H.oracle_stage(cfg, n=460, max_len=3)
