@@ -104,9 +104,7 @@ typedef struct rlhf_engine_cfg {
                                       weights then go from memory straight into LDS with no conversion
                                       in the loop.  Results are bit-identical either way (the on-the-fly
                                       conversion yields the same half values, and which kernel runs
-                                      does not depend on the copies).  0: no copies; contexts of 3072 batch
-                                      tokens and more then hold room for one converted matrix (the largest)
-                                      per pass stream, where there is any            */
+                                      does not depend on the copies).  0: no copies              */
 } rlhf_engine_cfg;
 
 /* One role's tensors (device pointers, element type per rlhf_model_cfg.dtype except the

@@ -101,18 +101,20 @@ struct Workspace {
     float* ssq = nullptr;       // few-row passes: partial sums of h^2 of the rows in flight
     float* scale = nullptr;     // [2][few]: scales of the normed rows, ping and pong
     int few = 0;                // rows these two have room for
-    void* w16 = nullptr;        // batch passes without half copies: the matrix in use, converted (or NULL)
     float* attn_acc = nullptr;  // decode split-KV partials
     float* attn_ml = nullptr;
     size_t attn_slots = 0;
     std::vector<void*> owned;
 };
 
-// Rows from which a batch pass without half copies of the weights converts each matrix into a workspace before its
-// projection: the tall kernel runs at 1.4 PFLOP/s on half weights, at 1.15 where it converts them itself, once per
-// tile; a conversion reads and writes the matrix once (7B gate||up 73 us beside 1250).  Prefill of 1100, 2048, 3072, 4096,
-// 6144, 8192 rows, converting in the kernel / before it: 7B widths, 4 layers, ms, 2.45 3.99 5.60 6.54 10.3 12.5 / 2.70
-// 3.94 5.37 6.22 9.4 11.3; 70B widths, 1 layer 2.40 3.43 4.96 6.37 9.4 12.4 / 2.70 3.54 4.89 6.10 8.6 11.1.
+// Rows from which a batch pass without half copies of the weights converts each matrix before its projection, into the part
+// of the workspace that is there for planes and that this projection leaves free (gate||up of d_model beyond 6144 fits
+// where a pass may have d_model / 2 rows): the tall kernel runs at 1.4 PFLOP/s on half weights, at 1.15 where it converts
+// them itself, once per tile; a conversion reads and writes the matrix once (7B gate||up 73 us beside 1250).  Prefill of
+// 1100, 2048, 3072, 4096, 6144, 8192 rows, converting in the kernel / before it: 7B widths, 4 layers, ms, 2.45 3.99 5.60
+// 6.54 10.3 12.5 / 2.70 3.94 5.37 6.22 9.4 11.3; 70B widths, 1 layer 2.40 3.43 4.96 6.37 9.4 12.4 / 2.70 3.54 4.89 6.10 8.6
+// 11.1.  Narrow layers gain less and lose nothing: 3072 and 8192 rows, d = 512, 8 layers 1.00 1.55 / 1.00 1.51, d = 768, 12 layers
+// 1.85 3.38 / 1.83 3.30, d = 1536, 6 layers 2.12 3.96 / 2.03 3.70.
 constexpr int kConvertRows = 3072;
 
 // Optional per-kernel-class timing: every `every`-th launch of a class is bracketed by two
@@ -321,12 +323,6 @@ int alloc_workspace(rlhf_ctx* c, Workspace& ws, int rows, bool decode) {
         HIPCK(c, dev_alloc(&ws, (char**)&ws.k, rows * kvd * es));
         HIPCK(c, dev_alloc(&ws, (char**)&ws.v, rows * kvd * es));
         HIPCK(c, dev_alloc(&ws, &ws.logits, (size_t)ws.logit_rows * V * 4));
-        const size_t largest = std::max({qkv_w * d, qd * d, 2 * f * d}) * 2;
-        if (c->dtype == kBF16 && !c->ec.half_weight_copies && rows >= kConvertRows &&
-            dev_alloc(&ws, (char**)&ws.w16, largest) != hipSuccess) {
-            (void)hipGetLastError();             // without it the passes read the bf16 weights
-            ws.w16 = nullptr;
-        }
     }
     return RLHF_OK;
 }
@@ -514,13 +510,19 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         return forward_layers_stream(c, st, ws, rw, rows, pm, mode, 1, pend_ns, &n_ssq);
     }
     HIPCK(c, launch_embed(st, dt, c->d_tokens, pm.tok_idx, w.embed, ws.h, rows, d, m.vocab));
-    // Weights of layer l for a projection: bf16, or where the tall kernel takes it their half copy, if need be made now
-    auto weights_for = [&](const void* w_bf16, const void* w_half, int l, size_t N, size_t K, bool tall, const void** W, bool* half) -> int {
+    // Weights of layer l for a projection that leaves `planes` planes: bf16, or where the tall kernel takes it their half
+    // copy, if need be made now (behind the planes; earlier ones have been read by then)
+    auto weights_for = [&](const void* w_bf16, const void* w_half, int l, size_t N, size_t K, bool tall, int planes, const void** W,
+                           bool* half) -> int {
         *half = w_half && tall;
         *W = layer_ptr(*half ? w_half : w_bf16, l, N, K, es);
-        if (*half || !tall || !ws.w16 || rows < kConvertRows || !half_operands_ok(kF16, rows, (long)N, (long)K)) return RLHF_OK;
-        HIPCK(c, launch_bf16_to_half(st, *W, ws.w16, N * K));
-        *W = ws.w16;
+        const size_t off = ((size_t)planes * rows * N + 63) / 64 * 64;
+        if (*half || !tall || dt != kBF16 || c->ec.half_weight_copies || rows < kConvertRows || !half_operands_ok(kF16, rows, (long)N, (long)K) ||
+            off + (N * K + 1) / 2 > ws.part_cap)
+            return RLHF_OK;
+        void* w16 = ws.part + off;
+        HIPCK(c, launch_bf16_to_half(st, *W, w16, N * K));
+        *W = w16;
         *half = true;
         return RLHF_OK;
     };
@@ -548,10 +550,11 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         const bool tall = gemm_is_tall(rows, d, K, pns);
         const void* W;
         bool hw;
-        int rc = weights_for(w_bf16, w_half, l, d, K, tall && adt == kF16, &W, &hw);
+        const bool whole = tall && rows > 256 && pns == 1 && dt == kBF16 && d % 4 == 0;
+        if (whole) pns = 0;
+        int rc = weights_for(w_bf16, w_half, l, d, K, tall && adt == kF16, pns, &W, &hw);
         if (rc) return rc;
-        if (tall && rows > 256 && pns == 1 && dt == kBF16 && d % 4 == 0) {
-            pns = 0;
+        if (whole) {
             const double bytes = ((double)d * K + (double)rows * K) * es + (double)rows * d * 8;
             HIPCK(c, profiled(c, st, gcls, bytes, 2.0 * rows * d * K,
                               [&] { return launch_gemm_tall_add(st, hw ? kF16 : dt, adt, A, W, ws.h, rows, d, K); }));
@@ -586,7 +589,7 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
                 const double bytes = ((double)qkv_w * d + (double)rows * d) * es + (double)rows * qkv_w * es;
                 const void* wq;
                 bool hw;
-                rc_proj = weights_for(w.wqkv, wh.wqkv, l, qkv_w, d, can16, &wq, &hw);
+                rc_proj = weights_for(w.wqkv, wh.wqkv, l, qkv_w, d, can16, 0, &wq, &hw);
                 if (rc_proj) return rc_proj;
                 HIPCK(c, profiled(c, st, gcls, bytes, 2.0 * rows * qkv_w * d,
                                   [&] { return launch_gemm_rope(st, hw ? kF16 : dt, adt, ws.xn, wq, rows, d, ro); }));
@@ -628,7 +631,7 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         } else if (gemm_swiglu_supported(dt, adt, rows, f, d)) {
             const void* wgu;
             bool hw;
-            rc_proj = weights_for(w.w_gate_up, wh.w_gate_up, l, 2 * (size_t)f, d, can16, &wgu, &hw);
+            rc_proj = weights_for(w.w_gate_up, wh.w_gate_up, l, 2 * (size_t)f, d, can16, 0, &wgu, &hw);
             if (rc_proj) return rc_proj;
             const double bytes = (2.0 * f * d + (double)rows * d) * es + (double)rows * f * es;
             HIPCK(c, profiled(c, st, gcls, bytes, 4.0 * rows * f * d,

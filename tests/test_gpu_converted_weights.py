@@ -28,6 +28,19 @@ def test_converted_weights_do_not_change_results(model, n, prompt):
         np.testing.assert_array_equal(a[k], b[k], err_msg=k)
 
 
+def test_conversions_hold_no_memory_of_their_own():
+    def taken(half):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        ctx = R.rlhf_create(R.rlhf_model_cfg(1, 4096, 32, 32, 128, 11008, 515, R.RLHF_BF16, 1e-5, 10000.0),
+                            R.rlhf_engine_cfg(16, 1 << 24, 4, 64, 4, 3072, 2, 0, 0, 0, None, None, half))
+        used = before - torch.cuda.mem_get_info()[0]
+        R.rlhf_destroy(ctx)
+        return used
+    taken(1)
+    assert abs(taken(0) - taken(1)) <= 16 << 20            # a converted gate || up matrix would be 180 MB
+
+
 @pytest.mark.parametrize("n", [2, 6, 8, 14, 4096, 4096 * 1024 + 6])
 @pytest.mark.parametrize("offset", [0, 2, 8])
 def test_conversion_at_any_length_and_alignment(n, offset):
