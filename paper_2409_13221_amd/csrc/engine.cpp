@@ -510,21 +510,20 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         return forward_layers_stream(c, st, ws, rw, rows, pm, mode, 1, pend_ns, &n_ssq);
     }
     HIPCK(c, launch_embed(st, dt, c->d_tokens, pm.tok_idx, w.embed, ws.h, rows, d, m.vocab));
-    // Weights of layer l for a projection that leaves `planes` planes: bf16, or where the tall kernel takes it their half
-    // copy, if need be made now (behind the planes; earlier ones have been read by then)
-    auto weights_for = [&](const void* w_bf16, const void* w_half, int l, size_t N, size_t K, bool tall, int planes, const void** W,
-                           bool* half) -> int {
-        *half = w_half && tall;
-        *W = layer_ptr(*half ? w_half : w_bf16, l, N, K, es);
+    // A projection of layer l that leaves `planes` planes: run(W, half) on the bf16 weights, or where the tall kernel takes it
+    // on their half copy, if need be made now (behind the planes; earlier ones have been read by then)
+    auto project_bf16 = [&](const void* w_bf16, const void* w_half, int l, size_t N, size_t K, bool tall, int planes, double bytes,
+                            auto run) {
+        const bool copy = w_half && tall;
+        const void* W = layer_ptr(copy ? w_half : w_bf16, l, N, K, es);
         const size_t off = ((size_t)planes * rows * N + 63) / 64 * 64;
-        if (*half || !tall || dt != kBF16 || c->ec.half_weight_copies || rows < kConvertRows || !half_operands_ok(kF16, rows, (long)N, (long)K) ||
-            off + (N * K + 1) / 2 > ws.part_cap)
-            return RLHF_OK;
-        void* w16 = ws.part + off;
-        HIPCK(c, launch_bf16_to_half(st, *W, w16, N * K));
-        *W = w16;
-        *half = true;
-        return RLHF_OK;
+        const bool convert = !copy && tall && dt == kBF16 && !c->ec.half_weight_copies && rows >= kConvertRows &&
+                             half_operands_ok(kF16, rows, (long)N, (long)K) && off + (N * K + 1) / 2 <= ws.part_cap;
+        return profiled(c, st, gcls, bytes, 2.0 * rows * N * K, [&] {
+            if (!convert) return run(W, copy);
+            const hipError_t e = launch_bf16_to_half(st, W, ws.part + off, N * K);
+            return e == hipSuccess ? run((const void*)(ws.part + off), true) : e;
+        });
     };
     const bool can16 = dt == kBF16 && adt == kF16 && d % 64 == 0;
     // float models: a projection that is not split runs on the kernel of gemm_f32.hip, its consumer in the epilogue
@@ -534,7 +533,7 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         return profiled(c, st, gcls, bytes, 2.0 * rows * N * K,
                         [&] { return launch_gemm_f32_tall(st, mode, (const float*)A, (const float*)W, nullptr, rows, N, K, ep); });
     };
-    int pns = 0, rc_proj;
+    int pns = 0;
     const size_t pstride = (size_t)rows * d;
     // O and down projections: an unsplit tall one finishes the residual stream, the others leave pns planes that
     // RMSNorm adds
@@ -548,19 +547,13 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
         }
         pns = nsplit_for(c, ws, rows, d, K);
         const bool tall = gemm_is_tall(rows, d, K, pns);
-        const void* W;
-        bool hw;
         const bool whole = tall && rows > 256 && pns == 1 && dt == kBF16 && d % 4 == 0;
         if (whole) pns = 0;
-        int rc = weights_for(w_bf16, w_half, l, d, K, tall && adt == kF16, pns, &W, &hw);
-        if (rc) return rc;
-        if (whole) {
-            const double bytes = ((double)d * K + (double)rows * K) * es + (double)rows * d * 8;
-            HIPCK(c, profiled(c, st, gcls, bytes, 2.0 * rows * d * K,
-                              [&] { return launch_gemm_tall_add(st, hw ? kF16 : dt, adt, A, W, ws.h, rows, d, K); }));
-        } else {
-            HIPCK(c, gemm_profiled(c, st, gcls, adt, A, W, ws.part, rows, d, K, pns, hw));
-        }
+        const double bytes = ((double)d * K + (double)rows * K) * es + (double)rows * d * (whole ? 8 : 4);
+        HIPCK(c, project_bf16(w_bf16, w_half, l, d, K, tall && adt == kF16, pns, bytes, [&](const void* W, bool half) {
+            return whole ? launch_gemm_tall_add(st, half ? kF16 : dt, adt, A, W, ws.h, rows, d, K)
+                         : launch_gemm(st, half ? kF16 : dt, adt, A, W, ws.part, rows, d, K, pns);
+        }));
         return RLHF_OK;
     };
     for (int l = 0; l < m.n_layers; ++l) {
@@ -587,12 +580,9 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
                 HIPCK(c, project_f32(2, ws.xn, layer_ptr(w.wqkv, l, qkv_w, d, es), qkv_w, d, ep));
             } else {
                 const double bytes = ((double)qkv_w * d + (double)rows * d) * es + (double)rows * qkv_w * es;
-                const void* wq;
-                bool hw;
-                rc_proj = weights_for(w.wqkv, wh.wqkv, l, qkv_w, d, can16, 0, &wq, &hw);
-                if (rc_proj) return rc_proj;
-                HIPCK(c, profiled(c, st, gcls, bytes, 2.0 * rows * qkv_w * d,
-                                  [&] { return launch_gemm_rope(st, hw ? kF16 : dt, adt, ws.xn, wq, rows, d, ro); }));
+                HIPCK(c, project_bf16(w.wqkv, wh.wqkv, l, qkv_w, d, can16, 0, bytes, [&](const void* W, bool half) {
+                    return launch_gemm_rope(st, half ? kF16 : dt, adt, ws.xn, W, rows, d, ro);
+                }));
             }
         } else {
             ns = nsplit_for(c, ws, rows, qkv_w, d);
@@ -619,8 +609,8 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
                                              pm.tile_q0, pm.tile_len, (float*)ws.attn, pm.n_tiles, c->dm);
             }));
         }
-        rc_proj = into_stream(ws.attn, w.wo, wh.wo, l, qd);
-        if (rc_proj) return rc_proj;
+        int rc = into_stream(ws.attn, w.wo, wh.wo, l, qd);
+        if (rc) return rc;
         HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, pns, pstride, nullptr, w.g_mlp + (size_t)l * d, ws.xn, rows, d,
                                 m.rms_eps));
         if (whole_f32(2 * f, d)) {
@@ -629,13 +619,10 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
             ep.ffn = f;
             HIPCK(c, project_f32(1, ws.xn, layer_ptr(w.w_gate_up, l, 2 * (size_t)f, d, es), 2 * f, d, ep));
         } else if (gemm_swiglu_supported(dt, adt, rows, f, d)) {
-            const void* wgu;
-            bool hw;
-            rc_proj = weights_for(w.w_gate_up, wh.w_gate_up, l, 2 * (size_t)f, d, can16, 0, &wgu, &hw);
-            if (rc_proj) return rc_proj;
             const double bytes = (2.0 * f * d + (double)rows * d) * es + (double)rows * f * es;
-            HIPCK(c, profiled(c, st, gcls, bytes, 4.0 * rows * f * d,
-                              [&] { return launch_gemm_swiglu(st, hw ? kF16 : dt, adt, ws.xn, wgu, ws.act, rows, f, d); }));
+            HIPCK(c, project_bf16(w.w_gate_up, wh.w_gate_up, l, 2 * (size_t)f, d, can16, 0, bytes, [&](const void* W, bool half) {
+                return launch_gemm_swiglu(st, half ? kF16 : dt, adt, ws.xn, W, ws.act, rows, f, d);
+            }));
         } else {
             ns = nsplit_for(c, ws, rows, 2 * f, d);
             const bool hw = wh.w_gate_up && adt == kF16 && gemm_is_tall(rows, 2 * f, d, ns);
@@ -643,8 +630,8 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
                                    ws.part, rows, 2 * f, d, ns, hw));
             HIPCK(c, launch_swiglu(st, adt, ws.part, ns, (size_t)rows * 2 * f, ws.act, rows, f));
         }
-        rc_proj = into_stream(ws.act, w.w_down, wh.w_down, l, f);
-        if (rc_proj) return rc_proj;
+        rc = into_stream(ws.act, w.w_down, wh.w_down, l, f);
+        if (rc) return rc;
     }
     *pend_ns = pns;
     *pend_stride = pstride;
