@@ -1,7 +1,7 @@
 // Attention kernels.
 //
 // Decode (the memory-bound phase of Section 2.2 / 4.2): one query per active sample against
-// that sample's paged K/V.  A workgroup owns (sample, KV head, split); its waves (8 or 16) take the
+// that sample's paged K/V.  A workgroup owns (sample, KV head, split); its waves (4, 8 or 16) take the
 // pages of the split round-robin.  A page's K tile ([page_tokens][hd], contiguous) is read
 // with 16-byte loads, consecutive lanes on consecutive chunks; a lane holds 8 dims of one
 // token, the q.k dot product is finished with xor-shuffles inside the hd/8-lane group, and
@@ -215,7 +215,8 @@ __device__ __forceinline__ void decode_block_finish(const float* s_m, const floa
 
 // PF: K and V are fetched a tile ahead, two tiles in flight per wave (116 registers instead of 73, half activations,
 // heads of 128).  32 heads of 128, half, contexts 176..560, us, four waves per workgroup and one tile / eight and two: 32
-// rows 37.2 / 36.3, 64 70.4 / 65.7, 128 130.7 / 125.3, 256 248 / 245 (a read at 6.5 TB/s: 29.6, 59.3, 118.6, 237).
+// rows 37.2 / 36.3, 64 70.4 / 65.7, 128 130.7 / 125.3, 256 248 / 245 (a read at 6.5 TB/s: 29.6, 59.3, 118.6, 237).  Beside
+// scoring too: 7B mixture of 64 samples, fused, 1.4 % less for the whole stage.
 template <typename T, int HD, int G, int WV, bool PF>
 __global__ __launch_bounds__(WV * 64) void k_decode_attn(const T* __restrict__ q,
                                                      const T* __restrict__ pool,
@@ -451,7 +452,8 @@ __global__ void k_attn_merge(const float* __restrict__ part_acc, const float* __
 // Longest context, in pages, up to which four waves a row and one page in flight are enough where the rows fill the chip
 // (64 rows of 32 heads of 128, contexts between half of it and all, us, four waves / eight with two pages in flight: 1 page 6.3
 // 12.5, 4 11.5 15.3, 8 21.2 21.2, 12 28.0 27.1, 20 47.0 41.1, 32 71.3 65.1; 123 rows of 12 heads of 64: 4 6.3 9.3, 12 12.5 13.0, 24
-// 22.3 20.1).
+// 22.3 20.1).  Where the caller does not know the contexts four waves stay (kernel-level call, 64 rows of 32 heads, all contexts
+// alike, 1, 4, 12, 32 pages 8.1 11.9 32.8 84.9 / 11.0 15.7 32.3 83.9: there is more to lose than to gain).
 constexpr int kShortPages = 12;
 
 // Waves per workgroup: a workgroup holds one (row, KV head, split), its waves take the pages in turn.
@@ -460,7 +462,7 @@ constexpr int kShortPages = 12;
 // (64 over 8), 32 rows at 1100 33.4 / 27.9 with 4 / 8.
 static int decode_attn_waves(long blocks, int group, int max_pages) {
     if (group > 1) return blocks >= 512 ? 4 : 8;
-    return blocks >= 512 && max_pages > 0 && max_pages <= kShortPages ? 4 : blocks >= 256 ? 8 : 16;
+    return blocks >= 512 && max_pages <= kShortPages ? 4 : blocks >= 256 ? 8 : 16;
 }
 
 // As many splits as give the chip about sixteen waves per compute unit (twelve of the grouped kernel,
