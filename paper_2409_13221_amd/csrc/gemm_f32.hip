@@ -12,6 +12,7 @@
 #include "common.h"
 #include "kernels.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace rlhf {
 
@@ -222,9 +223,9 @@ __global__ __launch_bounds__(256) void k_flash_attn_f32(const float* __restrict_
     f32x4_t o[VC * 4];
 #pragma unroll
     for (int b = 0; b < VC * 4; ++b) o[b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    float m = -INFINITY, l = 0.f;
-    fetch_k(0);
-    for (int kt = 0; kt < n_kt; ++kt) {
+    float m = -INFINITY, l = 0.f, p[4];
+    bool redo = false;
+    auto attend = [&](int kt, auto last) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float* src = vb + (size_t)min(kt * 16 + fq * 4 + i, L - 1) * kstride;
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(256) void k_flash_attn_f32(const float* __restrict_
         const float m_new = fmaxf(m, mx);                  // finite: every query sees key 0
         const float alpha = __expf(m - m_new);             // exp(-inf) = 0 on the first tile
         m = m_new;
-        float p[4], ls = 0.f;
+        float ls = 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             p[e] = __expf(s[e] - m_new);
@@ -260,6 +261,15 @@ __global__ __launch_bounds__(256) void k_flash_attn_f32(const float* __restrict_
         l = l * alpha + ls;                                // this lane's keys; the lanes of a query meet at the end
 #pragma unroll
         for (int b = 0; b < VC * 4; ++b) o[b] *= alpha;
+        if constexpr (decltype(last)::value) {             // the tile with keys that some queries do not see
+            bool bad = false;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int x = 0; x < VC; ++x) bad |= !isfinite(vf[i][x].x + vf[i][x].y + vf[i][x].z + vf[i][x].w);
+            redo = __any(bad);
+            if (redo) return;                              // 0 * inf would reach them
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -267,6 +277,27 @@ __global__ __launch_bounds__(256) void k_flash_attn_f32(const float* __restrict_
 #pragma unroll
                 for (int b = 0; b < 4; ++b)
                     o[x * 4 + b] = __builtin_amdgcn_mfma_f32_16x16x4f32((&vf[i][x].x)[b], p[i], o[x * 4 + b], 0, 0, 0);
+    };
+    fetch_k(0);
+    for (int kt = 0; kt < n_kt - 1; ++kt) attend(kt, std::false_type{});
+    attend(n_kt - 1, std::true_type{});
+    if (__builtin_expect(redo, 0)) {                       // the last tile key by key, for the queries that see it
+#pragma unroll 1
+        for (int j = 0; j < 16; ++j) {
+            const int key = (n_kt - 1) * 16 + j;
+            const float pe = (j & 3) == 0 ? p[0] : (j & 3) == 1 ? p[1] : (j & 3) == 2 ? p[2] : p[3];
+            const float pj = __shfl(pe, (j >> 2) * 16 + fr, kWave);
+            const float* src = vb + (fq * 16 - fr * 4) + (size_t)min(key, L - 1) * kstride;
+            if (key > qrow) continue;
+#pragma unroll
+            for (int x = 0; x < VC; ++x)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float4 w = *reinterpret_cast<const float4*>(src + x * 64 + e * 4);
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) o[x * 4 + b][e] += pj * (&w.x)[b];
+                }
+        }
     }
     l += __shfl_xor(l, 16, kWave);
     l += __shfl_xor(l, 32, kWave);

@@ -63,3 +63,25 @@ def test_unsplit_float_gemm_at_every_tile_height(M, N, K):
     want = (A.double() @ W.double().T).cpu().numpy()
     # K products of size 1 summed in float: sqrt(K) roundings of terms up to sqrt(K) in size, four times over
     np.testing.assert_allclose(out[0].cpu().numpy(), want, rtol=0, atol=4 * 2.0 ** -23 * K + 1e-5)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_last_token_without_finite_values_stays_invisible(head_dim, value):
+    """No position sees the last response token, the end of the sample, so the other tokens' scores do not depend on what
+    its row of the embedding holds."""
+    model = replace(_BASE, head_dim=head_dim)
+    cfg = _TINY.with_(name="float_last", model=model, n_samples=9, prompt_len=(9, 40), gain_jitter=0.05)
+    inp = H.make_inputs(cfg, n=9, max_len=7)
+    last = cfg.eos_id
+    inp["prompt_tokens"] = np.where(inp["prompt_tokens"] == last, 3, inp["prompt_tokens"]).astype(np.int32)
+    rng = np.random.default_rng(1)
+    inp["forced"] = [np.concatenate([rng.integers(3, model.vocab, n - 1), [last]]).astype(np.int32) for n in inp["out_len"]]
+    ref = H.run_gpu_stage(cfg, inp, fused=False, R_t=0, chunk_tokens=4096, role_mask=0b0110, max_batch_tokens=4096)
+    for role in (1, 2):
+        inp["weights"][role]["embed"][last] = value
+    got = H.run_gpu_stage(cfg, inp, fused=False, R_t=0, chunk_tokens=4096, role_mask=0b0110, max_batch_tokens=4096)
+    for k in ("tokens", "lp_actor"):
+        np.testing.assert_array_equal(got[k], ref[k], err_msg=k)
+    for k in ("lp_ref", "values"):                         # up to 16 keys added in another order: a few times 2^-24 of sizes up to ~6
+        np.testing.assert_allclose(got[k], ref[k], rtol=0, atol=5e-6, err_msg=k)
