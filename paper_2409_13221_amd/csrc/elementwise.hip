@@ -454,11 +454,12 @@ __global__ __launch_bounds__(64) void k_pick_stage2(const float* __restrict__ lo
 }
 
 // The same in one kernel, for one plane of up to 32 * 1024 columns: a block of 1024 threads per row, up to 32 logits a
-// thread, all requested at once and kept for the second pass (32000 columns, us, two
-// kernels / one: 1 row 9.7 8.8, 64 rows 11.5 9.7, 256 rows 25.5 13.0; 1 row of 4096 6.6 4.9).
-constexpr int kPickRowIter = 32, kPickRowThreads = 1024;
-template <int IT>
-__global__ __launch_bounds__(kPickRowThreads) void k_pick_row(const float* __restrict__ logits, int vocab,
+// thread, all requested at once and kept for the second pass (32000 columns, us, two kernels / one: 1 row 9.7 8.8, 64 rows
+// 11.5 9.7, 256 rows 25.5 13.0).  512 threads up to 4096 columns, fewer waves to start and to merge (two kernels / 1024 threads /
+// 512: 8 rows of 4096 6.3 4.6 3.9, 448 rows 21.3 6.2 4.6).
+constexpr int kPickRowMax = 32 * 1024;
+template <int IT, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_pick_row(const float* __restrict__ logits, int vocab,
                                                               const int* __restrict__ forced, int* __restrict__ tokens,
                                                               const int* __restrict__ tok_dst, float* __restrict__ lp,
                                                               const int* __restrict__ lp_dst, int* __restrict__ picked,
@@ -469,12 +470,12 @@ __global__ __launch_bounds__(kPickRowThreads) void k_pick_row(const float* __res
     const float* row = logits + (size_t)r * vocab;
     float z[IT];
 #pragma unroll
-    for (int i = 0; i < IT; ++i) z[i] = row[min(t + i * kPickRowThreads, vocab - 1)];
+    for (int i = 0; i < IT; ++i) z[i] = row[min(t + i * THREADS, vocab - 1)];
     float best = -INFINITY;
     int arg = 0x7FFFFFFF;
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
-        const int n = t + i * kPickRowThreads;
+        const int n = t + i * THREADS;
         if (n < vocab && z[i] > best) { best = z[i]; arg = n; }    // ascending: the first maximum is kept
     }
 #pragma unroll
@@ -487,12 +488,12 @@ __global__ __launch_bounds__(kPickRowThreads) void k_pick_row(const float* __res
     __syncthreads();
     best = s_val[0]; arg = s_idx[0];
 #pragma unroll
-    for (int w = 1; w < kPickRowThreads / 64; ++w)
+    for (int w = 1; w < THREADS / 64; ++w)
         if (s_val[w] > best || (s_val[w] == best && s_idx[w] < arg)) { best = s_val[w]; arg = s_idx[w]; }
     float se = 0.f;
 #pragma unroll
     for (int i = 0; i < IT; ++i)
-        if (t + i * kPickRowThreads < vocab) se += expf(z[i] - best);
+        if (t + i * THREADS < vocab) se += expf(z[i] - best);
     const float tot = block_sum(se, s_red);
     if (t == 0) pick_finish(row, 1, 0, vocab, best, arg, tot, r, forced, tokens, tok_dst, lp, lp_dst, picked, nonfinite);
 }
@@ -501,12 +502,11 @@ hipError_t launch_pick(hipStream_t st, const float* logits, int nsplit, size_t s
                        int vocab, const int* forced, int* tokens, const int* tok_dst, float* lp,
                        const int* lp_dst, int* picked, float* scratch, int* nonfinite) {
     if (rows <= 0) return hipSuccess;
-    if (nsplit == 1 && vocab <= kPickRowIter * kPickRowThreads) {
-        const int it = (vocab + kPickRowThreads - 1) / kPickRowThreads;
-#define RLHF_PICK(IT) k_pick_row<IT><<<rows, kPickRowThreads, 0, st>>>(logits, vocab, forced, tokens, tok_dst, lp, lp_dst, picked, nonfinite)
-        if (it <= 4) RLHF_PICK(4);
-        else if (it <= 16) RLHF_PICK(16);
-        else RLHF_PICK(32);
+    if (nsplit == 1 && vocab <= kPickRowMax) {
+#define RLHF_PICK(IT, THREADS) k_pick_row<IT, THREADS><<<rows, THREADS, 0, st>>>(logits, vocab, forced, tokens, tok_dst, lp, lp_dst, picked, nonfinite)
+        if (vocab <= 4096) RLHF_PICK(8, 512);
+        else if (vocab <= 16384) RLHF_PICK(16, 1024);
+        else RLHF_PICK(32, 1024);
 #undef RLHF_PICK
         return hipGetLastError();
     }
