@@ -352,8 +352,7 @@ struct PassMeta {         // device pointers into a MetaRing arena
     const int* row_sample = nullptr;   // decode
     const int* ctx_len = nullptr;      // decode
     int max_pages = 0;                 // decode: of the longest context
-    const int* row_start = nullptr;    // batch (float models)
-    const int* tile_start = nullptr;   // batch (bf16 models): query tiles of the MFMA attention
+    const int* tile_start = nullptr;   // batch: query tiles of the packed attention
     const int* tile_q0 = nullptr;
     const int* tile_len = nullptr;
     int n_tiles = 0;
@@ -783,9 +782,9 @@ static int create_impl(rlhf_ctx* c) {
     if ((rc = alloc_workspace(c, c->ws_score, e.max_batch_tokens, false))) return rc;
     HIPCK(c, c->meta_dec.init((size_t)e.max_active * 10 + (size_t)e.max_active * 2 + 64));
     // prefill metadata also carries the page-table updates of the admitted prompts
-    HIPCK(c, c->meta_pre.init((size_t)e.max_batch_tokens * 9 + (size_t)e.max_samples * 12 +
+    HIPCK(c, c->meta_pre.init((size_t)e.max_batch_tokens * 8 + (size_t)e.max_samples * 12 +
                               2 * ((size_t)e.max_batch_tokens / e.page_tokens + e.max_samples) + 64));
-    HIPCK(c, c->meta_score.init((size_t)e.max_batch_tokens * 9 + (size_t)e.max_samples * 8 + 64));
+    HIPCK(c, c->meta_score.init((size_t)e.max_batch_tokens * 8 + (size_t)e.max_samples * 8 + 64));
     return RLHF_OK;
 }
 
@@ -1093,12 +1092,11 @@ int prefill_group(rlhf_ctx* c, const std::vector<int>& group, int T) {
     const int mc = c->ec.max_ctx, pt = c->ec.page_tokens, n = (int)group.size();
     int* hm;
     HIPCK(c, c->meta_pre.begin(&hm));
-    // layout: tok_idx[T] pos[T] row_start[T] kv_dst[T] | sel[n] forced[n] tok_dst[n] lp_dst[n] | upd_idx[U] upd_val[U]
+    // layout: tok_idx[T] pos[T] kv_dst[T] | sel[n] forced[n] tok_dst[n] lp_dst[n] | upd_idx[U] upd_val[U]
     int* tok_idx = hm;
     int* pos = hm + T;
-    int* row_start = hm + 2 * T;
-    int* kv_dst = hm + 3 * T;
-    int* sel = hm + 4 * T;
+    int* kv_dst = hm + 2 * T;
+    int* sel = hm + 3 * T;
     int* forced = sel + n;
     int* tok_dst = forced + n;
     int* lp_dst = tok_dst + n;
@@ -1108,7 +1106,7 @@ int prefill_group(rlhf_ctx* c, const std::vector<int>& group, int T) {
     for (int gi = 0; gi < n; ++gi) {
         const int i = group[gi];
         Sample& s = c->smp[i];
-        const int start = row, rows_i = prefill_rows(s);
+        const int rows_i = prefill_rows(s);
         lens.push_back(rows_i);
         for (int p = 0; p < rows_i; ++p, ++row) {
             if (p % pt == 0) {
@@ -1118,7 +1116,6 @@ int prefill_group(rlhf_ctx* c, const std::vector<int>& group, int T) {
             }
             tok_idx[row] = i * mc + p;
             pos[row] = p;
-            row_start[row] = start;
             kv_dst[row] = s.pages[p / pt] * pt + p % pt;
         }
         s.ctx = rows_i;
@@ -1136,19 +1133,18 @@ int prefill_group(rlhf_ctx* c, const std::vector<int>& group, int T) {
     std::copy(upd_idx.begin(), upd_idx.end(), upd);
     std::copy(upd_val.begin(), upd_val.end(), upd + U);
     const int n_tiles = count_tiles(lens);
-    const size_t tiles_off = (size_t)4 * T + 4 * n + 2 * U;
+    const size_t tiles_off = (size_t)3 * T + 4 * n + 2 * U;
     const size_t n_ints = tiles_off + 3 * (size_t)n_tiles;
     if (n_ints > c->meta_pre.cap) return c->fail(RLHF_EINVAL, "internal: prefill metadata overflow");
     fill_tiles(lens, hm + tiles_off);
     HIPCK(c, c->meta_pre.commit(c->sd, n_ints));
     const int* dm_ = c->meta_pre.dev;
-    HIPCK(c, launch_scatter_int(c->sd, c->d_page_table, dm_ + 4 * T + 4 * n, dm_ + 4 * T + 4 * n + U, U));
+    HIPCK(c, launch_scatter_int(c->sd, c->d_page_table, dm_ + 3 * T + 4 * n, dm_ + 3 * T + 4 * n + U, U));
 
     PassMeta pm;
     pm.tok_idx = dm_;
     pm.pos = dm_ + T;
-    pm.row_start = dm_ + 2 * T;
-    pm.kv_dst = dm_ + 3 * T;
+    pm.kv_dst = dm_ + 2 * T;
     pm.tile_start = dm_ + tiles_off;
     pm.tile_q0 = dm_ + tiles_off + n_tiles;
     pm.tile_len = dm_ + tiles_off + 2 * n_tiles;
@@ -1161,13 +1157,13 @@ int prefill_group(rlhf_ctx* c, const std::vector<int>& group, int T) {
     int rc = forward_layers(c, c->sd, ws, c->roles[RLHF_ACTOR], T, pm, kModeBatch, 1, &pns, &pstride);
     if (rc) return rc;
     if (n_sel > 0) {
-        HIPCK(c, launch_rmsnorm(c->sd, act_type(c, true), ws.h, ws.part, pns, pstride, dm_ + 4 * T, w.g_final, ws.xsel,
+        HIPCK(c, launch_rmsnorm(c->sd, act_type(c, true), ws.h, ws.part, pns, pstride, dm_ + 3 * T, w.g_final, ws.xsel,
                                 n_sel, c->mc.d_model, c->mc.rms_eps));
         HeadPlan hp;
         hp.n_sel = n_sel;
-        hp.forced = dm_ + 4 * T + n;
-        hp.tok_dst = dm_ + 4 * T + 2 * n;
-        hp.lp_dst = dm_ + 4 * T + 3 * n;
+        hp.forced = dm_ + 3 * T + n;
+        hp.tok_dst = dm_ + 3 * T + 2 * n;
+        hp.lp_dst = dm_ + 3 * T + 3 * n;
         rc = lm_head_chunks(c, c->sd, ws, w, hp, true);
         if (rc) return rc;
     }
@@ -1462,17 +1458,16 @@ int score_pass(rlhf_ctx* c, hipStream_t st, MetaRing& meta, Workspace& ws, const
     HIPCK(c, meta.begin(&hm));
     int n_sel = 0;
     for (int k = 0; k < n; ++k) n_sel += role == RLHF_REWARD ? 1 : c->smp[ids[k]].gen_len;
-    // layout: tok_idx[T] pos[T] row_start[T] | sel[n_sel] target_idx[n_sel] out_dst[n_sel]
+    // layout: tok_idx[T] pos[T] | sel[n_sel] target_idx[n_sel] out_dst[n_sel]
     int* tok_idx = hm;
     int* pos = hm + T;
-    int* row_start = hm + 2 * T;
-    int* sel = hm + 3 * T;
+    int* sel = hm + 2 * T;
     int* target = sel + n_sel;
     int* out_dst = target + n_sel;
     std::vector<int> lens;
     for (int k = 0; k < n; ++k) lens.push_back(c->smp[ids[k]].P + c->smp[ids[k]].gen_len);
     const int n_tiles = count_tiles(lens);
-    const size_t tiles_off = (size_t)3 * T + 3 * n_sel;
+    const size_t tiles_off = (size_t)2 * T + 3 * n_sel;
     if (tiles_off + 3 * (size_t)n_tiles > meta.cap) return c->fail(RLHF_EINVAL, "internal: scoring metadata overflow");
     fill_tiles(lens, hm + tiles_off);
     int row = 0, si = 0;
@@ -1483,7 +1478,6 @@ int score_pass(rlhf_ctx* c, hipStream_t st, MetaRing& meta, Workspace& ws, const
         for (int p = 0; p < Ti; ++p, ++row) {
             tok_idx[row] = i * mc + p;
             pos[row] = p;
-            row_start[row] = start;
         }
         if (role == RLHF_REWARD) {
             sel[si] = start + Ti - 1;
@@ -1503,7 +1497,6 @@ int score_pass(rlhf_ctx* c, hipStream_t st, MetaRing& meta, Workspace& ws, const
     PassMeta pm;
     pm.tok_idx = dmeta;
     pm.pos = dmeta + T;
-    pm.row_start = dmeta + 2 * T;
     pm.tile_start = dmeta + tiles_off;
     pm.tile_q0 = dmeta + tiles_off + n_tiles;
     pm.tile_len = dmeta + tiles_off + 2 * n_tiles;
@@ -1520,19 +1513,19 @@ int score_pass(rlhf_ctx* c, hipStream_t st, MetaRing& meta, Workspace& ws, const
     // in front of a single dot product); the LM head's GEMM takes the activation type.
     const bool scalar_head = role == RLHF_CRITIC || role == RLHF_REWARD;
     const int adt = scalar_head ? kF32 : act_type(c, true);
-    HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, pns, pstride, dmeta + 3 * T, w.g_final, ws.xsel, n_sel, d,
+    HIPCK(c, launch_rmsnorm(st, adt, ws.h, ws.part, pns, pstride, dmeta + 2 * T, w.g_final, ws.xsel, n_sel, d,
                             c->mc.rms_eps));
     if (role == RLHF_CRITIC)
-        HIPCK(c, launch_head_dot(st, adt, c->dtype, ws.xsel, w.head, n_sel, d, c->d_values, dmeta + 3 * T + 2 * n_sel,
+        HIPCK(c, launch_head_dot(st, adt, c->dtype, ws.xsel, w.head, n_sel, d, c->d_values, dmeta + 2 * T + 2 * n_sel,
                                  c->d_nonfinite));
     else if (role == RLHF_REWARD)
-        HIPCK(c, launch_head_dot(st, adt, c->dtype, ws.xsel, w.head, n_sel, d, c->d_reward, dmeta + 3 * T + 2 * n_sel,
+        HIPCK(c, launch_head_dot(st, adt, c->dtype, ws.xsel, w.head, n_sel, d, c->d_reward, dmeta + 2 * T + 2 * n_sel,
                                  c->d_nonfinite));
     else {
         HeadPlan hp;
         hp.n_sel = n_sel;
-        hp.target_idx = dmeta + 3 * T + n_sel;
-        hp.out_dst = dmeta + 3 * T + 2 * n_sel;
+        hp.target_idx = dmeta + 2 * T + n_sel;
+        hp.out_dst = dmeta + 2 * T + 2 * n_sel;
         hp.out = role == RLHF_REF ? c->d_lp_ref : c->d_lp_rescored;
         rc = gemm_lse_supported(c->dtype, adt, d) ? lm_head_logprob_fused(c, st, ws, c->roles[role], hp)
                                                   : lm_head_chunks(c, st, ws, w, hp, false);
