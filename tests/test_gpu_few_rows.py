@@ -4,10 +4,11 @@ wide enough for several weight blocks per workgroup and for K splits.  The oracl
 values and rewards are held to the tolerances of the other stage tests."""
 from dataclasses import replace
 
+import numpy as np
 import pytest
 
 from tests import stage_harness as H
-from workload import CONFIGS
+from workload import CONFIGS, make_weights, make_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -40,7 +41,7 @@ def test_decode_batches_read_half_copies(model, n):
     H.compare_stage(cfg, ref, got)
 
 
-# one to eight weight blocks per workgroup (gate||up and head), ragged last workgroups; O and down in three and four planes,
+# one to eight weight blocks per workgroup (gate||up and head, up to 32 rows), ragged last workgroups; O and down in three and four planes,
 # in blocks of two (N = 5120) and with a K that four waves do not share evenly
 _BLOCKS7 = replace(_SMALL, n_layers=1, d_model=1088, n_q_heads=3, n_kv_heads=3, ffn=13760, vocab=31999)
 _BLOCKS6 = replace(_BLOCKS7, ffn=10944, vocab=15351)
@@ -55,3 +56,23 @@ def test_decode_batches_of_several_weight_blocks(model, n):
     ref = H.oracle_stage(cfg, n=n, max_len=3)
     got = H.run_gpu_stage(cfg, ref, fused=False, R_t=0, chunk_tokens=64)
     H.compare_stage(cfg, ref, got)
+
+
+# The shapes of real widths that the models above do not have: three to five weight blocks in rotary and planes, and seven
+# (gate||up) and three (QKV) with 33 rows of 8192 columns.  A layer of such a width is too much for the oracle at these
+# row counts, so decode steps are held to the Actor's own re-scoring pass, which runs on the kernels for many rows.
+_7B, _13B, _70B = (CONFIGS[k].model for k in ("7b", "13b", "70b_slice"))
+_2048 = replace(_7B, d_model=2048, n_q_heads=16, n_kv_heads=16, ffn=5504)
+
+
+@pytest.mark.parametrize("model,n", [(_2048, 17), (_7B, 9), (_7B, 17), (_13B, 9), (_13B, 17), (_70B, 9), (_70B, 33), (_70B, 64)])
+def test_decode_steps_of_real_widths_agree_with_scoring(model, n):
+    cfg = _GPT2S.with_(name="real_width", model=replace(model, n_layers=1, vocab=4100), n_samples=n, prompt_len=(40, 44), gain_jitter=0.05)
+    wl = make_workload(cfg, n)
+    inp = {"prompt_tokens": wl["prompt_tokens"], "prompt_offsets": wl["prompt_offsets"], "n_layers": None,
+           "out_len": np.minimum(wl["out_len"], 5).astype(np.int32), "weights": [make_weights(cfg, 0, device="cuda")]}
+    got = H.run_gpu_stage(cfg, inp, fused=False, R_t=0, chunk_tokens=8192, role_mask=1, max_batch_tokens=8192)
+    d = np.abs(got["lp_actor"].astype(np.float64) - got["lp_actor_rescored"])
+    assert int(got["stats"].n_steps) >= 4 and float(np.abs(got["lp_actor"]).max()) > 5
+    # the oracle's tolerance for log-probs on half activations; a wrong column or row is off by its own size (~8)
+    assert float(d.max()) < H.LP_TOL["bf16"], d.max()
