@@ -15,6 +15,7 @@
 #include <cstring>
 #include <deque>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "kernels.h"
@@ -359,15 +360,35 @@ struct PassMeta {         // device pointers into a MetaRing arena
     double attn_bytes = 0, attn_flops = 0;   // algorithmic, per layer (for the profiler)
 };
 
-// Few rows: every layer runs on the projections of gemm_stream.hip.
+// Few rows: every layer runs on the projections of gemm_stream.hip.  Float ones in groups of 16 rows, each of which reads the
+// whole matrix again: up to 32 rows, beyond that as long as the four projections together are estimated no slower than on
+// the kernels of gemm.hip and gemm_f32.hip.  Prefill, us a layer, groups / those (/ all in vector code with norm, rotary and
+// SwiGLU kernels): d = 256, ffn = 688 192 rows 45 / 58 / 65, 448 69 / 63 / 92; ffn = 4096 48 rows 54 / 59 / 66, 96 69 / 65 / 74, 192
+// 92 / 70 / 84; ffn = 11008 24 rows 86 / 89 / 96, 96 128 / 102 / 112; d = 256 with 32 heads 96 rows 62 / 64 / 75, 320 124 / 85 / 116; 512
+// 192 rows 69 / 79 / 93, 320 92 / 88 / 123; 1024 96 rows 104 / 105 / 107; 2048 32 rows 172 / 204, 64 265 / 222; 4096 32 rows 556 / 588,
+// 64 934 / 633.
 bool stream_pass(const rlhf_ctx* c, int rows) {
     const rlhf_model_cfg& m = c->mc;
     if (c->dtype == kF32) {
-        const double d = m.d_model, qd = (double)m.n_q_heads * m.head_dim, kvd = (double)m.n_kv_heads * m.head_dim;
-        return m.d_model % 16 == 0 && stream_f32_pays(rows, ((2 * qd + 2 * kvd) * d + 3 * d * m.ffn) * 4);
+        if (m.d_model % 16 || rows > kStreamF32Rows) return false;
+        if (rows <= 32) return true;
+        const int d = m.d_model, qd = m.n_q_heads * m.head_dim, qkv_w = qd + 2 * m.n_kv_heads * m.head_dim;
+        double us = 0;
+        for (auto [N, K] : {std::pair{qkv_w, d}, std::pair{d, qd}, std::pair{2 * m.ffn, d}, std::pair{d, m.ffn}})
+            us += stream_f32_us(rows, N, K) - gemm_f32_us(rows, N, K);
+        return us <= 0;
     }
     return c->dtype == kBF16 && rows <= kRowsMaxRows && m.d_model % 64 == 0 && (m.n_q_heads * m.head_dim) % 64 == 0 &&
            m.ffn % 64 == 0;
+}
+
+// The LM head of a float model, by its own times; where the groups can take the final norm along, the others need an RMSNorm
+// kernel.  us, groups / unsplit (/ vector code): 4096 columns of K = 256 48 rows 7.7 / 8.4, 64 9.5 / 9.4, 200 26 / 11 / 17, 448 53 / 14 / 20;
+// 32000 of K = 256 17 rows 28 / 12 / 19, 64 59 / 19 / 21; 515 of K = 256 448 rows 9.7 / 11.3; 4096 of K = 1024 128 rows 31 / 36,
+// 200 47 / 37; 32000 of K = 768 32 rows 58 / 32 / 53.
+bool head_in_groups(int rows, int vocab, int d, bool norm) {
+    if (rows <= 16 || rows > kStreamF32Rows) return rows <= 16;
+    return stream_f32_us(rows, vocab, d) <= (norm ? gemm_f32_us(rows, vocab, d) + 4. : gemm_f32_tall_us(rows, vocab, d));
 }
 
 // Norm input of a few-row projection over the residual stream: how ws.xn was scaled, the sums of squares
@@ -996,7 +1017,7 @@ int lm_head_chunks(rlhf_ctx* c, hipStream_t st, Workspace& ws, const rlhf_weight
     for (int r0 = 0; r0 < hp.n_sel; r0 += ws.logit_rows) {
         const int nr = std::min(ws.logit_rows, hp.n_sel - r0);
         const char* x = (const char*)ws.xsel + (size_t)r0 * d * c->esz;
-        if (gemm_stream_supported(c->dtype, act_type(c, true), nr, d) && (c->dtype != kF32 || stream_f32_pays(nr, (double)V * d * 4))) {
+        if (gemm_stream_supported(c->dtype, act_type(c, true), nr, d) && (c->dtype != kF32 || head_in_groups(nr, V, d, false))) {
             const double bytes = ((double)V * d + (double)nr * d) * c->esz + (double)nr * V * 4;
             HIPCK(c, profiled(c, st, kGemmBatch, bytes, 2.0 * nr * V * d, [&] {
                 return launch_gemm_stream(st, c->dtype, act_type(c, true), 0, x, w.head, ws.logits, nr, V, d, RowsEpi{});
@@ -1240,7 +1261,7 @@ int decode_rows(rlhf_ctx* c, const std::vector<int>& rows_ids) {
         const int adt = act_type(c, false);
         if (adt == kF16) ep.a = ActLayout{8, 8 * R};
         const bool many = adt == kF16 && takes_gemm_rows(R, d), hw = many && c->roles[RLHF_ACTOR].h16.head;
-        const bool head_stream = adt != kF32 || stream_f32_pays(R, (double)V * d * 4);
+        const bool head_stream = adt != kF32 || head_in_groups(R, V, d, true);
         if (R <= kStreamResidRows || (adt == kF32 && head_stream))
             ep.nrm = stream_norm(c, ws, w.g_final, n_ssq, ws.scale, nullptr);
         else

@@ -461,6 +461,15 @@ hipError_t launch_bf16_to_half(hipStream_t st, const void* src, void* dst, size_
     return hipGetLastError();
 }
 
+// Float planes against the unsplit kernel of gemm_f32.hip, which also finishes rotary, SwiGLU or the residual stream.  Planes:
+// 0.065 us a k of a split, more from about 512 workgroups on, and a plane is written and read.  us, unsplit / planes with
+// their reading: N = K = 1024 64 rows 31 / 7, 512 rows 37 / 22; N = 11008, K = 2048 256 rows 122 / 176, 64 rows 62 / 54;
+// N = K = 4096 512 rows 174 / 238, 256 rows 142 / 133; N = 4096, K = 256 448 rows 15 / 24.
+static double f32_planes_us(int M, int N, int K, int ns) {
+    const double wgs = (double)((M + 63) / 64) * ((N + 63) / 64) * ns;
+    return 3. + (double)((K + ns - 1) / ns) * std::max(0.065, 0.01 + 1.02e-4 * wgs) + 8. * M * N * ns / 5e6;
+}
+
 int gemm_choose_nsplit(int wdt, int M, int N, int K, int max_split) {
     int tm, tn, kgran;
     if (wdt == kBF16) {
@@ -487,16 +496,13 @@ int gemm_choose_nsplit(int wdt, int M, int N, int K, int max_split) {
         if ((long)(ns - 1) * kchunk < K) break;
         --ns;
     }
-    // Float planes against the unsplit kernel of gemm_f32.hip, which also finishes rotary, SwiGLU or the residual stream.  Planes:
-    // 0.065 us a k of a split, more from about 512 workgroups on, and a plane is written and read.  us, unsplit / planes with
-    // their reading: N = K = 1024 64 rows 31 / 7, 512 rows 37 / 22; N = 11008, K = 2048 256 rows 122 / 176, 64 rows 62 / 54;
-    // N = K = 4096 512 rows 174 / 238, 256 rows 142 / 133; N = 4096, K = 256 448 rows 15 / 24.
-    if (wdt == kF32 && ns > 1) {
-        const double planes_us = 3. + (double)((K + ns - 1) / ns) * std::max(0.065, 0.01 + 1.02e-4 * (double)tiles * ns) +
-                                 8. * M * N * ns / 5e6;
-        if (gemm_f32_tall_us(M, N, K) < planes_us) ns = 1;
-    }
+    if (wdt == kF32 && ns > 1 && gemm_f32_tall_us(M, N, K) < f32_planes_us(M, N, K, ns)) ns = 1;
     return ns;
+}
+
+double gemm_f32_us(int M, int N, int K) {
+    const int ns = gemm_choose_nsplit(kF32, M, N, K, 16);
+    return ns > 1 ? f32_planes_us(M, N, K, ns) : gemm_f32_tall_us(M, N, K);
 }
 
 template <bool AF16>

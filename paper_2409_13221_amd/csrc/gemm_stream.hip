@@ -26,6 +26,7 @@
 // stream that RMSNorm as a kernel can take is taken here, and ordinary rows pay one test.
 #include "common.h"
 #include "kernels.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace rlhf {
@@ -583,13 +584,13 @@ bool gemm_stream_supported(int wdt, int adt, int M, int K) {
     return wdt == kBF16 && (adt == kF16 || (adt == kBF16 && M <= 16)) && M >= 1 && M <= kStreamMaxRows && K > 0 && K % 64 == 0;
 }
 
-// Every group of 16 rows reads the whole matrix again, mostly out of the caches, and beyond two groups that pays as long as
-// the groups together read less than about 256 MB a layer.  Prefill, us a layer, groups of 16 / the kernels of gemm.hip and
-// gemm_f32.hip: d = 256 (3.2 MB a layer) 64 rows 55 / 76, 448 rows 90 / 94; 512 (13 MB) 128 rows 67 / 93, 256 93 / 107, 448 134 / 133;
-// 768 (28 MB) 96 rows 105 / 110, 192 148 / 125; 1024 (50 MB) 64 rows 92 / 107, 128 135 / 130; 1536 (113 MB) 32 rows 117 / 139, 48
-// 151 / 145; 2048 (201 MB) 32 rows 172 / 204, 64 265 / 222, 448 1290 / 766; 4096 (809 MB) 32 rows 556 / 588, 64 934 / 633.
-bool stream_f32_pays(int M, double bytes) {
-    return M <= 32 || (M <= kStreamF32Rows && (M + 15) / 16 * bytes <= 256e6);
+// Every workgroup of 16 columns and 16 rows takes 0.0069 us of the chip per 512 k, and the launch at least a round trip of about
+// 1.7 us for each 512 k of a wave's chain.  us, estimate / measured: N = 4096, K = 256 48 rows 8.3 / 7.7, 200 rows 26 / 26, 448 52 /
+// 53; N = 32000, K = 768 32 rows 58 / 58, 448 776 / 767; N = 4096, K = 1024 33 rows 13.6 / 11.9, 300 70 / 68; N = 515, K = 256 448
+// rows 9.4 / 9.7.
+double stream_f32_us(int M, int N, int K) {
+    const double its = (K + 511) / 512;
+    return std::max(3. + 0.0069 * ((N + 15) / 16) * ((M + 15) / 16) * its, 2. + 1.7 * its);
 }
 
 // Shape of a launch: 16-row blocks of activations, of weights per workgroup (nb), ring depth (four waves throughout).

@@ -88,7 +88,7 @@ hipError_t launch_gemm_rope(hipStream_t st, int wdt, int adt, const void* A, con
 // Half activations: 1..kStreamMaxRows rows; bf16 activations: 1..16; K a multiple of 64.  Float weights and
 // activations (row-major): 1..kStreamF32Rows rows, K a multiple of 4.
 constexpr int kStreamMaxRows = 64;
-constexpr int kStreamF32Rows = 448;   // beyond, other kernels are level or ahead at every width (stream_f32_pays)
+constexpr int kStreamF32Rows = 448;   // beyond, other kernels are level or ahead at nearly every width
 constexpr int kSsqStride = 512; // floats per row of the partial sums of squares (d_model <= 8192, 16 columns each)
 struct NormIn {                 // modes 0..2: A holds x = h * gain * s_in; result of row m times (1/rms) / s_in[m]
     const float* ssq = nullptr;     // [M, kSsqStride] partial sums of h^2 (n_ssq used, the others zero), or NULL: A is used as it is
@@ -116,8 +116,8 @@ struct RowsEpi {
     ResidOut res;
 };
 bool gemm_stream_supported(int wdt, int adt, int M, int K);
-// Whether float weights of `bytes` (a layer, or the LM head) are best read once per 16 rows: see gemm_stream.hip.
-bool stream_f32_pays(int M, double bytes);
+// Estimated time of a float launch, which reads the matrix once per 16 rows.
+double stream_f32_us(int M, int N, int K);
 constexpr int kStreamResidRows = 16;
 // Whether a pass over a residual stream of d columns runs on mode 3 and NormIn: any up to kStreamResidRows
 // rows; half activations of up to 64 partial sums (n_ssq, a column block of 16 each) at any row count here,
@@ -145,6 +145,7 @@ hipError_t launch_gemm_rows(hipStream_t st, int wdt, int mode, const void* A, co
 // Many rows of float models (gemm_f32.hip), row-major, modes as in launch_gemm_stream without norms; mode 3: ep.res.h += result.
 bool gemm_f32_tall_supported(int N, int K, int mode);
 double gemm_f32_tall_us(int M, int N, int K);      // estimated time of a launch
+double gemm_f32_us(int M, int N, int K);           // the same, or that of planes and their reading where gemm_choose_nsplit splits K
 hipError_t launch_gemm_f32_tall(hipStream_t st, int mode, const float* A, const float* W, float* C, int M, int N, int K,
                                 const RowsEpi& ep);
 

@@ -85,3 +85,36 @@ def test_last_token_without_finite_values_stays_invisible(head_dim, value):
         np.testing.assert_array_equal(got[k], ref[k], err_msg=k)
     for k in ("lp_ref", "values"):                         # up to 16 keys added in another order: a few times 2^-24 of sizes up to ~6
         np.testing.assert_allclose(got[k], ref[k], rtol=0, atol=5e-6, err_msg=k)
+
+
+def _admission_ms(model, n, prompt):
+    """Projections of a pass that admits n samples, in ms, the least of ten."""
+    cfg = _TINY.with_(name="float_admission", model=model, n_samples=n, prompt_len=(prompt, prompt))
+    inp = H.make_inputs(cfg, n=n, max_len=1, weight_device="cuda")
+    ms = []
+    with H.GpuStage(cfg, inp, max_batch_tokens=512) as st:
+        for _ in range(12):
+            st.submit()
+            R.rlhf_profile_begin(st.ctx, 1)
+            R.rlhf_generate_step(st.ctx)
+            p = R.rlhf_profile_end(st.ctx)["gemm_batch"]
+            assert p["sampled"] == p["launches"] and p["dropped"] == 0
+            ms.append(p["sampled_ms"])
+    return min(ms[2:])
+
+
+def test_wide_lm_head_is_not_read_again_for_every_16_rows():
+    """Admission of 64 samples over one narrow layer: what 32000 columns of the head add to 512.  64 x 32000 x 256 takes 19 us
+    unsplit (21 on the vector kernel), 59 in four groups of rows."""
+    ms = [_admission_ms(replace(_TINY.model, n_layers=1, vocab=v), 64, 2) for v in (512, 32000)]
+    print("projections, ms, 512 and 32000 columns:", ms)
+    assert ms[1] - ms[0] < 0.035
+
+
+@pytest.mark.parametrize("ffn,heads", [(11008, 4), (688, 48)])
+def test_fewer_float_rows_take_no_longer(ffn, heads):
+    """Narrow streams beside wide projections: 96 rows in groups of 16 would take longer than 128 rows on the other kernels."""
+    model = replace(_TINY.model, n_layers=4, n_q_heads=heads, n_kv_heads=heads, ffn=ffn, vocab=512)
+    ms = [_admission_ms(model, n, 8) for n in (12, 14, 16, 24)]
+    print("projections of 4 layers, ms, 96, 112, 128, 192 rows:", ms)
+    assert all(a < 1.08 * b for a, b in zip(ms, ms[1:]))
