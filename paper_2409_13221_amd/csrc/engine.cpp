@@ -356,7 +356,7 @@ struct PassMeta {         // device pointers into a MetaRing arena
     const int* tile_start = nullptr;   // batch: query tiles of the packed attention
     const int* tile_q0 = nullptr;
     const int* tile_len = nullptr;
-    int n_tiles = 0;
+    int n_tiles = 0, longest = 0;      // tiles; rows of the longest sequence
     double attn_bytes = 0, attn_flops = 0;   // algorithmic, per layer (for the profiler)
 };
 
@@ -489,7 +489,7 @@ int forward_layers_stream(rlhf_ctx* c, hipStream_t st, Workspace& ws, const Role
                     return launch_flash_attn(st, ws.q, ws.k, ws.v, pm.tile_start, pm.tile_q0, pm.tile_len, ws.attn,
                                              pm.n_tiles, rows, c->dm);
                 return launch_flash_attn_f32(st, (const float*)ws.q, (const float*)ws.k, (const float*)ws.v, pm.tile_start,
-                                             pm.tile_q0, pm.tile_len, (float*)ws.attn, pm.n_tiles, c->dm);
+                                             pm.tile_q0, pm.tile_len, (float*)ws.attn, pm.n_tiles, pm.longest, c->dm);
             }));
         }
         int rc = into_stream(ws.attn, attn_layout, w.wo, wh.wo, l, qd, w.g_mlp + (size_t)l * d, sc[1]);
@@ -626,7 +626,7 @@ int forward_layers(rlhf_ctx* c, hipStream_t st, Workspace& ws, const RoleWeights
                     return launch_flash_attn(st, ws.q, ws.k, ws.v, pm.tile_start, pm.tile_q0, pm.tile_len, ws.attn,
                                              pm.n_tiles, rows, c->dm);
                 return launch_flash_attn_f32(st, (const float*)ws.q, (const float*)ws.k, (const float*)ws.v, pm.tile_start,
-                                             pm.tile_q0, pm.tile_len, (float*)ws.attn, pm.n_tiles, c->dm);
+                                             pm.tile_q0, pm.tile_len, (float*)ws.attn, pm.n_tiles, pm.longest, c->dm);
             }));
         }
         int rc = into_stream(ws.attn, w.wo, wh.wo, l, qd);
@@ -1170,6 +1170,7 @@ int prefill_group(rlhf_ctx* c, const std::vector<int>& group, int T) {
     pm.tile_q0 = dm_ + tiles_off + n_tiles;
     pm.tile_len = dm_ + tiles_off + 2 * n_tiles;
     pm.n_tiles = n_tiles;
+    pm.longest = *std::max_element(lens.begin(), lens.end());
     batch_attn_cost(c, lens, T, &pm);
     const rlhf_weights& w = c->roles[RLHF_ACTOR].w;
     Workspace& ws = c->ws_pre;
@@ -1522,6 +1523,7 @@ int score_pass(rlhf_ctx* c, hipStream_t st, MetaRing& meta, Workspace& ws, const
     pm.tile_q0 = dmeta + tiles_off + n_tiles;
     pm.tile_len = dmeta + tiles_off + 2 * n_tiles;
     pm.n_tiles = n_tiles;
+    pm.longest = *std::max_element(lens.begin(), lens.end());
     batch_attn_cost(c, lens, T, &pm);
     const rlhf_weights& w = c->roles[role].w;
     int pns;

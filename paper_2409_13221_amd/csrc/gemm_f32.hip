@@ -192,15 +192,21 @@ __global__ __launch_bounds__(256) void k_gemm_f32_tall(const float* __restrict__
 // block b taken as 4 * row + b its left one is four rows of V read 16 bytes a lane.  K and V come from the caches (the waves
 // of a workgroup read the same ones), V requested before the first product, the next K before the second; no LDS and no
 // barriers, so waves past the end of their sequence just end.
-template <int HD>
+// SPLIT: the four waves of a workgroup own the same 16 queries and every fourth tile of keys, and meet in LDS.  With few
+// tiles the time is that of the longest sequence's chain, 0.85 us for 16 keys (1.4 with heads of 128).  us, a wave per 16 queries / SPLIT / a
+// workgroup per query (k_prefill_attn): one sequence, 4 heads of 64, 64 tokens 8 / 6 / 6, 300 20 / 10 / 11, 1200 63 / 28 / 74, 4800 357 /
+// 195 / 961; 8 heads of 128 300 tokens 31 / 14 / 37, 1200 104 / 68 / 340.  Where every SIMD has work the shares cost more than they
+// save: tiles times heads, 128 of 64 tokens 9 / 8, 180 of 64 9 / 9 (64; heads of 128 192 13 / 18), 192 of 300 24 / 21 (128: 41 / 40), 320 of
+// 600 69 / 55 (128: 113 / 115), 360 of 100 21 / 27, 640 of 1200 181 / 209.
+template <int HD, bool SPLIT>
 __global__ __launch_bounds__(256) void k_flash_attn_f32(const float* __restrict__ q, const float* __restrict__ k,
                                                         const float* __restrict__ v, const int* __restrict__ tile_start,
                                                         const int* __restrict__ tile_q0, const int* __restrict__ tile_len,
                                                         float* __restrict__ out, int Hq, int Hkv) {
-    constexpr int KC = HD / 16, VC = HD / 64;
+    constexpr int KC = HD / 16, VC = HD / 64, STEP = SPLIT ? 4 : 1;
     const int tile = blockIdx.x, h = blockIdx.y, kh = h / (Hq / Hkv);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), fr = lane & 15, fq = lane >> 4;
-    const int s0 = tile_start[tile], L = tile_len[tile], q0 = tile_q0[tile] + (blockIdx.z * 4 + wave) * 16;
+    const int s0 = tile_start[tile], L = tile_len[tile], q0 = tile_q0[tile] + (SPLIT ? (int)blockIdx.z : (int)blockIdx.z * 4 + wave) * 16;
     if (q0 >= L) return;
     const int qrow = q0 + fr;
     const size_t qstride = (size_t)Hq * HD, kstride = (size_t)Hkv * HD;
@@ -239,7 +245,7 @@ __global__ __launch_bounds__(256) void k_flash_attn_f32(const float* __restrict_
 #pragma unroll
             for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32((&kf[c].x)[e], (&qf[c].x)[e], s, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        fetch_k(min(kt + 1, n_kt - 1));
+        fetch_k(min(kt + STEP, n_kt - 1));
         __builtin_amdgcn_sched_barrier(0);
         float mx = -INFINITY;
 #pragma unroll
@@ -249,7 +255,7 @@ __global__ __launch_bounds__(256) void k_flash_attn_f32(const float* __restrict_
         }
         mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
         mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-        const float m_new = fmaxf(m, mx);                  // finite: every query sees key 0
+        const float m_new = fmaxf(m, mx);                  // finite: every query sees the first key of every tile
         const float alpha = __expf(m - m_new);             // exp(-inf) = 0 on the first tile
         m = m_new;
         float ls = 0.f;
@@ -278,9 +284,10 @@ __global__ __launch_bounds__(256) void k_flash_attn_f32(const float* __restrict_
                 for (int b = 0; b < 4; ++b)
                     o[x * 4 + b] = __builtin_amdgcn_mfma_f32_16x16x4f32((&vf[i][x].x)[b], p[i], o[x * 4 + b], 0, 0, 0);
     };
-    fetch_k(0);
-    for (int kt = 0; kt < n_kt - 1; ++kt) attend(kt, std::false_type{});
-    attend(n_kt - 1, std::true_type{});
+    const int kt0 = SPLIT ? wave : 0;
+    fetch_k(min(kt0, n_kt - 1));
+    for (int kt = kt0; kt < n_kt - 1; kt += STEP) attend(kt, std::false_type{});
+    if (!SPLIT || (n_kt - 1) % STEP == wave) attend(n_kt - 1, std::true_type{});
     if (__builtin_expect(redo, 0)) {                       // the last tile key by key, for the queries that see it
 #pragma unroll 1
         for (int j = 0; j < 16; ++j) {
@@ -301,6 +308,37 @@ __global__ __launch_bounds__(256) void k_flash_attn_f32(const float* __restrict_
     }
     l += __shfl_xor(l, 16, kWave);
     l += __shfl_xor(l, 32, kWave);
+    if constexpr (SPLIT) {                                 // the waves' shares of the keys meet (none: m = -inf, l = 0)
+        __shared__ float s_m[4][16], s_l[4][16];
+        __shared__ __align__(16) float s_o[4][16][HD + 4];
+        if (fq == 0) { s_m[wave][fr] = m; s_l[wave][fr] = l; }
+        __syncthreads();
+        const float w = __expf(m - fmaxf(fmaxf(s_m[0][fr], s_m[1][fr]), fmaxf(s_m[2][fr], s_m[3][fr])));
+#pragma unroll
+        for (int x = 0; x < VC; ++x)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                *reinterpret_cast<float4*>(&s_o[wave][fr][x * 64 + (fq * 4 + e) * 4]) =
+                    make_float4(o[x * 4][e] * w, o[x * 4 + 1][e] * w, o[x * 4 + 2][e] * w, o[x * 4 + 3][e] * w);
+        __syncthreads();
+        for (int i = threadIdx.x; i < 16 * (HD / 4); i += 256) {
+            const int r = i / (HD / 4), c = i % (HD / 4) * 4;
+            if (q0 + r >= L) continue;
+            const float mr = fmaxf(fmaxf(s_m[0][r], s_m[1][r]), fmaxf(s_m[2][r], s_m[3][r]));
+            float lt = 0.f;
+            float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int k4 = 0; k4 < 4; ++k4) {
+                lt += s_l[k4][r] * __expf(s_m[k4][r] - mr);
+                const float4 b = *reinterpret_cast<const float4*>(&s_o[k4][r][c]);
+                a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+            }
+            const float inv = 1.f / lt;
+            *reinterpret_cast<float4*>(out + (size_t)(s0 + q0 + r) * qstride + (size_t)h * HD + c) =
+                make_float4(a.x * inv, a.y * inv, a.z * inv, a.w * inv);
+        }
+        return;
+    }
     if (qrow >= L) return;
     const float inv = 1.f / l;
     float* dst = out + (size_t)(s0 + qrow) * qstride + (size_t)h * HD;
@@ -362,15 +400,16 @@ hipError_t launch_gemm_f32_tall(hipStream_t st, int mode, const float* A, const 
 }
 
 hipError_t launch_flash_attn_f32(hipStream_t st, const float* q, const float* k, const float* v, const int* tile_start,
-                                 const int* tile_q0, const int* tile_len, float* out, int n_tiles, const Dims& dm) {
+                                 const int* tile_q0, const int* tile_len, float* out, int n_tiles, int longest, const Dims& dm) {
     if (n_tiles <= 0) return hipSuccess;
-    const dim3 grid(n_tiles, dm.n_q_heads, kFlashTile / 64);   // four waves of 16 queries a workgroup
-    if (dm.head_dim == 64)
-        k_flash_attn_f32<64><<<grid, 256, 0, st>>>(q, k, v, tile_start, tile_q0, tile_len, out, dm.n_q_heads, dm.n_kv_heads);
-    else if (dm.head_dim == 128)
-        k_flash_attn_f32<128><<<grid, 256, 0, st>>>(q, k, v, tile_start, tile_q0, tile_len, out, dm.n_q_heads, dm.n_kv_heads);
-    else
-        return hipErrorInvalidValue;
+    const bool split = (long)n_tiles * dm.n_q_heads <= std::min(384, longest / 2 + 32);
+    const dim3 grid(n_tiles, dm.n_q_heads, split ? kFlashTile / 16 : kFlashTile / 64);
+#define RLHF_FLASH_F32(HD, SPLIT) \
+    k_flash_attn_f32<HD, SPLIT><<<grid, 256, 0, st>>>(q, k, v, tile_start, tile_q0, tile_len, out, dm.n_q_heads, dm.n_kv_heads)
+    if (dm.head_dim == 64) { if (split) RLHF_FLASH_F32(64, true); else RLHF_FLASH_F32(64, false); }
+    else if (dm.head_dim == 128) { if (split) RLHF_FLASH_F32(128, true); else RLHF_FLASH_F32(128, false); }
+    else return hipErrorInvalidValue;
+#undef RLHF_FLASH_F32
     return hipGetLastError();
 }
 

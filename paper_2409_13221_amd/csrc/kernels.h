@@ -260,9 +260,9 @@ hipError_t launch_flash_attn(hipStream_t st, const void* q, const void* k, const
                              const int* tile_start, const int* tile_q0, const int* tile_len, void* out,
                              int n_tiles, int T_total, const Dims& dm);
 
-// The same in float.
+// The same in float; longest: rows of the longest sequence.
 hipError_t launch_flash_attn_f32(hipStream_t st, const float* q, const float* k, const float* v, const int* tile_start,
-                                 const int* tile_q0, const int* tile_len, float* out, int n_tiles, const Dims& dm);
+                                 const int* tile_q0, const int* tile_len, float* out, int n_tiles, int longest, const Dims& dm);
 
 size_t pool_page_elems(const Dims& dm);  // elements of one page over all layers
 

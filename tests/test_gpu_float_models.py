@@ -23,7 +23,8 @@ _WIDE = replace(_BASE, n_layers=1, d_model=1040)
 
 @pytest.mark.parametrize("model,n,prompt", [(_BASE, 17, (3, 5)), (_BASE, 64, (3, 5)), (_BASE, 120, (3, 5)), (_BASE, 200, (3, 5)),
                                             (_HD128, 33, (3, 5)), (_UNEVEN, 5, (3, 5)), (_UNEVEN, 40, (3, 5)), (_WIDE, 20, (3, 5)),
-                                            (_BASE, 5, (110, 150)), (_HD128, 4, (120, 145)), (_BASE, 3, (15, 33)), (_TINY.model, 4, (127, 129))])
+                                            (_BASE, 5, (110, 150)), (_HD128, 4, (120, 145)), (_BASE, 3, (15, 33)), (_TINY.model, 4, (127, 129)),
+                                            (_BASE, 54, (110, 150)), (_HD128, 30, (60, 145)), (_HD128, 2, (47, 50))])
 def test_float_stage_beyond_16_rows(model, n, prompt):
     cfg = _TINY.with_(name="float_rows", model=model, n_samples=n, prompt_len=prompt, gain_jitter=0.05)
     ref = H.oracle_stage(cfg, n=n, max_len=4)
@@ -67,16 +68,17 @@ def test_unsplit_float_gemm_at_every_tile_height(M, N, K):
 
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
-def test_last_token_without_finite_values_stays_invisible(head_dim, value):
+@pytest.mark.parametrize("n", [9, 70])                     # keys shared by the waves of a workgroup, and not
+def test_last_token_without_finite_values_stays_invisible(head_dim, value, n):
     """No position sees the last response token, the end of the sample, so the other tokens' scores do not depend on what
     its row of the embedding holds."""
     model = replace(_BASE, head_dim=head_dim)
-    cfg = _TINY.with_(name="float_last", model=model, n_samples=9, prompt_len=(9, 40), gain_jitter=0.05)
-    inp = H.make_inputs(cfg, n=9, max_len=7)
+    cfg = _TINY.with_(name="float_last", model=model, n_samples=n, prompt_len=(9, 40), gain_jitter=0.05)
+    inp = H.make_inputs(cfg, n=n, max_len=7)
     last = cfg.eos_id
     inp["prompt_tokens"] = np.where(inp["prompt_tokens"] == last, 3, inp["prompt_tokens"]).astype(np.int32)
     rng = np.random.default_rng(1)
-    inp["forced"] = [np.concatenate([rng.integers(3, model.vocab, n - 1), [last]]).astype(np.int32) for n in inp["out_len"]]
+    inp["forced"] = [np.concatenate([rng.integers(3, model.vocab, k - 1), [last]]).astype(np.int32) for k in inp["out_len"]]
     ref = H.run_gpu_stage(cfg, inp, fused=False, R_t=0, chunk_tokens=4096, role_mask=0b0110, max_batch_tokens=4096)
     for role in (1, 2):
         inp["weights"][role]["embed"][last] = value
@@ -87,17 +89,17 @@ def test_last_token_without_finite_values_stays_invisible(head_dim, value):
         np.testing.assert_allclose(got[k], ref[k], rtol=0, atol=5e-6, err_msg=k)
 
 
-def _admission_ms(model, n, prompt):
-    """Projections of a pass that admits n samples, in ms, the least of ten."""
+def _admission_ms(model, n, prompt, kind="gemm_batch"):
+    """Projections (or attention) of a pass that admits n samples, in ms, the least of ten."""
     cfg = _TINY.with_(name="float_admission", model=model, n_samples=n, prompt_len=(prompt, prompt))
     inp = H.make_inputs(cfg, n=n, max_len=1, weight_device="cuda")
     ms = []
-    with H.GpuStage(cfg, inp, max_batch_tokens=512) as st:
+    with H.GpuStage(cfg, inp, max_batch_tokens=640) as st:
         for _ in range(12):
             st.submit()
             R.rlhf_profile_begin(st.ctx, 1)
             R.rlhf_generate_step(st.ctx)
-            p = R.rlhf_profile_end(st.ctx)["gemm_batch"]
+            p = R.rlhf_profile_end(st.ctx)[kind]
             assert p["sampled"] == p["launches"] and p["dropped"] == 0
             ms.append(p["sampled_ms"])
     return min(ms[2:])
@@ -118,3 +120,11 @@ def test_fewer_float_rows_take_no_longer(ffn, heads):
     ms = [_admission_ms(model, n, 8) for n in (12, 14, 16, 24)]
     print("projections of 4 layers, ms, 96, 112, 128, 192 rows:", ms)
     assert all(a < 1.08 * b for a, b in zip(ms, ms[1:]))
+
+
+def test_one_long_sequence_of_few_heads_is_spread():
+    """600 tokens, 2 heads, four layers of attention: 14 us each with the keys shared by the waves of a workgroup (a workgroup per
+    query 15), 35 where a wave walks all of them."""
+    ms = _admission_ms(replace(_TINY.model, n_layers=4, n_q_heads=2, n_kv_heads=2, vocab=512), 1, 600, "attn_batch")
+    print("attention of 4 layers, ms:", ms)
+    assert ms < 4 * 0.024
