@@ -12,9 +12,9 @@
 // With eight query heads per KV head (half precision) the decode kernel is an MFMA one, see
 // k_decode_attn_gqa.
 //
-// Prefill / scoring of float models uses the same inner loop over 16-token tiles of contiguous
-// K/V (one workgroup per query row and KV head); bf16 models use the MFMA kernel at the end of
-// this file.
+// Prefill / scoring of bf16 models uses the MFMA kernel at the end of this file, float models that of
+// gemm_f32.hip.  k_prefill_attn, behind the kernel-level entry point, has the same inner loop as the
+// decode kernel over 16-token tiles of contiguous K/V (one workgroup per query row and KV head).
 #include "common.h"
 #include "kernels.h"
 
@@ -287,6 +287,10 @@ __global__ __launch_bounds__(WV * 64) void k_decode_attn(const T* __restrict__ q
         TileRegs<T, HD> tr;
         for (; pi < pe; pi += WV) {
             fetch(pi, tr);
+            // The whole tile is requested before any of it is used: left to itself the compiler keeps 59 and 63 registers instead of
+            // 78 and 105 and waits for K before it asks for V (24 rows of 8 float heads of 128, contexts 1500..2500 91 us, 71 this
+            // way; 16 rows of 32 half heads, 64 tokens 9.5 and 8.4).
+            __builtin_amdgcn_sched_barrier(0);
             consume(pi, tr);
         }
     }
@@ -450,9 +454,9 @@ __global__ void k_attn_merge(const float* __restrict__ part_acc, const float* __
 }
 
 // Longest context, in pages, up to which four waves a row and one page in flight are enough where the rows fill the chip
-// (64 rows of 32 heads of 128, contexts between half of it and all, us, four waves / eight with two pages in flight: 1 page 6.3
-// 12.5, 4 11.5 15.3, 8 21.2 21.2, 12 28.0 27.1, 20 47.0 41.1, 32 71.3 65.1; 123 rows of 12 heads of 64: 4 6.3 9.3, 12 12.5 13.0, 24
-// 22.3 20.1).  Where the caller does not know the contexts four waves stay (kernel-level call, 64 rows of 32 heads, all contexts
+// (64 rows of 32 heads of 128, contexts between half of it and all, us, four waves / eight with two pages in flight: 6 pages 19.1
+// 21.3, 10 26.2 27.7, 14 34.6 34.6, 18 42.2 40.7, 32 70.2 66.9; 16 rows 10 10.4 10.4, 14 12.3 12.7, 18 16.7 14.2; 128 rows of 12 heads of 64 6
+// 10.7 12.9, 10 13.5 14.9, 14 17.5 17.6, 32 32.2 30.1).  Where the caller does not know the contexts four waves stay (kernel-level call, 64 rows of 32 heads, all contexts
 // alike, 1, 4, 12, 32 pages 8.1 11.9 32.8 84.9 / 11.0 15.7 32.3 83.9: there is more to lose than to gain).
 constexpr int kShortPages = 12;
 

@@ -54,3 +54,28 @@ def test_steps_across_the_longest_short_context():
     ref = H.oracle_stage(cfg, n=128, max_len=6)
     got = H.run_gpu_stage(cfg, ref, fused=False, R_t=0, chunk_tokens=4096, max_batch_tokens=4096)
     H.compare_stage(cfg, ref, got)
+
+
+def test_float_heads_of_128_read_at_the_rate_of_heads_of_64():
+    """The same 400 MB of K and V a layer: 8 float heads of 128, one page in flight, and 16 of 64, two.  71 and 73 us; 90 where a
+    page's V is asked for only when its K has arrived."""
+    base = CONFIGS["tiny"]
+    us = []
+    for heads, hd in ((8, 128), (16, 64)):
+        cfg = base.with_(name="float_heads", n_samples=24, prompt_len=(1500, 2500),
+                         model=replace(base.model, n_layers=2, d_model=256, n_q_heads=heads, n_kv_heads=heads, head_dim=hd, ffn=64, vocab=203))
+        inp = H.make_inputs(cfg, n=24, max_len=24, weight_device="cuda")
+        inp["out_len"][:] = 24
+        best = []
+        with H.GpuStage(cfg, inp, max_batch_tokens=8192) as st:
+            st.submit()
+            R.rlhf_generate_step(st.ctx)
+            for _ in range(5):
+                R.rlhf_profile_begin(st.ctx, 1)
+                for _ in range(4):
+                    R.rlhf_generate_step(st.ctx)
+                p = R.rlhf_profile_end(st.ctx)["attn_decode"]
+                best.append(p["sampled_ms"] / p["sampled"] * 1e3)
+        us.append(min(best))
+    print("attention, us, heads of 128 and of 64:", us)
+    assert us[0] < 1.12 * us[1]
