@@ -539,7 +539,7 @@ hipError_t launch_decode_attn(hipStream_t st, int dtype, const void* q, const vo
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------- prefill / scoring (v1)
+// ------------------------------------------------------------- prefill / scoring, kernel-level entry point
 template <typename TO, int HD, int G>
 __global__ __launch_bounds__(256) void k_prefill_attn(const float* __restrict__ q,
                                                       const float* __restrict__ k,

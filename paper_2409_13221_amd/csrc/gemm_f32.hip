@@ -6,9 +6,9 @@
 // wave owns 16 * MBW activation rows and 64 weight rows, and a chunk of 16 k is (MBW + 4) loads of 16 bytes a lane for
 // 16 * MBW matrix instructions of 32 cycles; two to four chunks are in flight.  The four waves of a workgroup lie below each
 // other and read the same weight rows out of the L1.
-// M = 8192, K = 256, us and TFLOP/s: N = 1376 69, 83; N = 4096 167, 103; N = 256 20, 54 (a register-only loop of these
+// M = 8192, K = 256, us and TFLOP/s: N = 1376 65, 88; N = 4096 166, 104; N = 256 15, 73 (a register-only loop of these
 // instructions 154, in long runs 123; 64 x 64 tiles of vector code in gemm.hip about 25).  Asking for the next chunk before
-// working on the present one, two in flight, ran at 71 and 82.
+// working on the present one, two in flight, ran at 71 and 82 where this order ran at 83 and 103.
 #include "common.h"
 #include "kernels.h"
 #include <algorithm>
